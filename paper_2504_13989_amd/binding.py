@@ -1,8 +1,10 @@
-"""ctypes binding of librotq.so: argument marshalling only.
+"""Binding of librotq.so: argument marshalling only.
 
 Every step of the path runs in the HIP kernels behind the C ABI (include/rotq.h); PyTorch
-is used for device memory and streams.  There is no CPU fallback: if the library has not
-been built, loading raises.
+is used for device memory and streams.  The calls on tensors go through the native module
+_pyrotq (csrc/pyrotq.cpp), which reads the tensors, allocates the results and takes the current
+stream without a trip through Python; handles and host-side helpers use ctypes.  There is no CPU
+fallback: if the library has not been built, loading raises.
 """
 from __future__ import annotations
 
@@ -12,6 +14,7 @@ from typing import Optional, Sequence
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "librotq.so")
+NATIVE_PATH = os.path.join(HERE, "_pyrotq.so")
 
 RQ_OK, RQ_ERR_ARG, RQ_ERR_NO_ORDER, RQ_ERR_HIP, RQ_ERR_NOMEM, RQ_ERR_TOO_LARGE = 0, -1, -2, -3, -4, -5
 RQ_NOALLOC_SCRATCH_BYTES = 4 << 20
@@ -19,6 +22,7 @@ RQ_BF16, RQ_F32, RQ_F16 = 0, 1, 2
 RQ_MAX_CLIPS = 64
 
 _lib = None
+_nat = None
 
 
 class RotqError(RuntimeError):
@@ -77,6 +81,20 @@ def lib() -> C.CDLL:
     return L
 
 
+def _native():
+    """The native module behind the calls on tensors; raises if it has not been built (no fallback)."""
+    global _nat
+    import torch  # noqa: F401  (the module uses its libraries)
+    lib()                      # before _pyrotq, which links against it: a missing librotq.so is reported as such
+    if not os.path.exists(NATIVE_PATH):
+        raise RuntimeError(
+            f"{NATIVE_PATH} is missing: build it with `python -m paper_2504_13989_amd.build`; there is no fallback path")
+    from . import _pyrotq
+    _pyrotq.set_error(RotqError)
+    _nat = _pyrotq
+    return _nat
+
+
 def _check(code: int, where: str) -> None:
     if code != RQ_OK:
         raise RotqError(code, where)
@@ -89,6 +107,7 @@ class Hadamard:
         h = C.c_void_p()
         _check(lib().rq_hadamard_build(int(n), C.byref(h)), f"rq_hadamard_build({n})")
         self._h = h
+        self._p = h.value                  # the pointer as a number, for the native module; 0 once closed
         v = [C.c_int() for _ in range(5)]
         _check(lib().rq_hadamard_info(h, *[C.byref(x) for x in v]), "rq_hadamard_info")
         self.n, self.p, self.kind, self.q, self.log2m = (x.value for x in v)
@@ -97,6 +116,7 @@ class Hadamard:
         if getattr(self, "_h", None):
             lib().rq_hadamard_free(self._h)
             self._h = None
+            self._p = 0
 
     def __del__(self):
         try:
@@ -160,20 +180,7 @@ def _stream_ptr(stream):
 def rotate_quantize(h: Hadamard, x, bits: int, clip: float, codes=None, scales=None, stream=None):
     """rq_rotate_quantize on a CUDA tensor x [..., d]; returns (codes uint8 [rows, n*bits/8],
     scales float32 [rows]).  Output tensors are allocated with torch unless given."""
-    import torch
-    if not x.is_cuda:
-        raise ValueError("x must be a device tensor")
-    x2, rows, d, ld = _rows_view(x)
-    nbytes = h.n * bits // 8
-    if codes is None:
-        codes = torch.empty((rows, nbytes), dtype=torch.uint8, device=x.device)
-    if scales is None:
-        scales = torch.empty((rows,), dtype=torch.float32, device=x.device)
-    rc = lib().rq_rotate_quantize(h._h, C.c_void_p(x2.data_ptr()), _dtype_code(x2), rows, d, ld,
-                                  int(bits), C.c_float(clip), C.c_void_p(codes.data_ptr()),
-                                  C.c_void_p(scales.data_ptr()), _stream_ptr(stream))
-    _check(rc, "rq_rotate_quantize")
-    return codes, scales
+    return (_nat or _native()).rotate_quantize(h._p, x, bits, clip, codes, scales, stream)
 
 
 GROUP = 128
@@ -183,63 +190,19 @@ def rotate_quantize_asym(h: Hadamard, x, bits: int, clip: float, codes=None, sca
                          stream=None):
     """rq_rotate_quantize_asym on a CUDA tensor x [..., d]; returns (codes uint8 [rows, n*bits/8],
     scales float32 [rows, n/128], mins float32 [rows, n/128])."""
-    import torch
-    if not x.is_cuda:
-        raise ValueError("x must be a device tensor")
-    x2, rows, d, ld = _rows_view(x)
-    groups = max(h.n // GROUP, 1)
-    if codes is None:
-        codes = torch.empty((rows, h.n * bits // 8), dtype=torch.uint8, device=x.device)
-    if scales is None:
-        scales = torch.empty((rows, groups), dtype=torch.float32, device=x.device)
-    if mins is None:
-        mins = torch.empty((rows, groups), dtype=torch.float32, device=x.device)
-    rc = lib().rq_rotate_quantize_asym(h._h, C.c_void_p(x2.data_ptr()), _dtype_code(x2), rows, d, ld,
-                                       int(bits), C.c_float(clip), C.c_void_p(codes.data_ptr()),
-                                       C.c_void_p(scales.data_ptr()), C.c_void_p(mins.data_ptr()),
-                                       _stream_ptr(stream))
-    _check(rc, "rq_rotate_quantize_asym")
-    return codes, scales, mins
+    return (_nat or _native()).rotate_quantize_asym(h._p, x, bits, clip, codes, scales, mins, stream)
 
 
 def quantize(x, bits: int, clip: float, codes=None, scales=None, stream=None):
     """rq_quantize (no rotation) on a CUDA tensor x [..., d]; returns (codes uint8 [rows, d*bits/8],
     scales float32 [rows])."""
-    import torch
-    if not x.is_cuda:
-        raise ValueError("x must be a device tensor")
-    x2, rows, d, ld = _rows_view(x)
-    if codes is None:
-        codes = torch.empty((rows, d * bits // 8), dtype=torch.uint8, device=x.device)
-    if scales is None:
-        scales = torch.empty((rows,), dtype=torch.float32, device=x.device)
-    rc = lib().rq_quantize(C.c_void_p(x2.data_ptr()), _dtype_code(x2), rows, d, ld, int(bits),
-                           C.c_float(clip), C.c_void_p(codes.data_ptr()),
-                           C.c_void_p(scales.data_ptr()), _stream_ptr(stream))
-    _check(rc, "rq_quantize")
-    return codes, scales
+    return (_nat or _native()).quantize(x, bits, clip, codes, scales, stream)
 
 
 def quantize_asym(x, bits: int, clip: float, codes=None, scales=None, mins=None, stream=None):
     """rq_quantize_asym (no rotation, asymmetric groups of 128) on a CUDA tensor x [..., d]; returns
     (codes uint8 [rows, d*bits/8], scales float32 [rows, d/128], mins float32 [rows, d/128])."""
-    import torch
-    if not x.is_cuda:
-        raise ValueError("x must be a device tensor")
-    x2, rows, d, ld = _rows_view(x)
-    groups = max(d // GROUP, 1)
-    if codes is None:
-        codes = torch.empty((rows, d * bits // 8), dtype=torch.uint8, device=x.device)
-    if scales is None:
-        scales = torch.empty((rows, groups), dtype=torch.float32, device=x.device)
-    if mins is None:
-        mins = torch.empty((rows, groups), dtype=torch.float32, device=x.device)
-    rc = lib().rq_quantize_asym(C.c_void_p(x2.data_ptr()), _dtype_code(x2), rows, d, ld, int(bits),
-                                C.c_float(clip), C.c_void_p(codes.data_ptr()),
-                                C.c_void_p(scales.data_ptr()), C.c_void_p(mins.data_ptr()),
-                                _stream_ptr(stream))
-    _check(rc, "rq_quantize_asym")
-    return codes, scales, mins
+    return (_nat or _native()).quantize_asym(x, bits, clip, codes, scales, mins, stream)
 
 
 def stream_reference(x, bits: int, codes=None, scales=None, stream=None):
@@ -260,72 +223,25 @@ def stream_reference(x, bits: int, codes=None, scales=None, stream=None):
     return codes, scales
 
 
-def _out_code(torch, dtype):
-    if dtype == torch.float32:
-        return RQ_F32
-    if dtype == torch.bfloat16:
-        return RQ_BF16
-    if dtype == torch.float16:
-        return RQ_F16
-    raise ValueError("output dtype must be float32, bfloat16 or float16")
-
-
 def rotate(h: Hadamard, x, transpose: bool = False, d_out: Optional[int] = None, out_dtype=None,
            out=None, stream=None):
     """rq_rotate on a CUDA tensor x [..., d]: (H_n pad(x) / sqrt(n))[:, :d_out] per row (H_n^T with
     transpose), as float32 (default) or bfloat16.  Applied to the rows of a weight stored
     [out_features, in_features] it is the offline input-side fusion of section 4.2."""
-    import torch
-    if not x.is_cuda:
-        raise ValueError("x must be a device tensor")
-    x2, rows, d, ld = _rows_view(x)
-    d_out = h.n if d_out is None else int(d_out)
-    if out is None:
-        out = torch.empty((rows, d_out), dtype=out_dtype or torch.float32, device=x.device)
-    rc = lib().rq_rotate(h._h, C.c_void_p(x2.data_ptr()), _dtype_code(x2), rows, d, ld,
-                         1 if transpose else 0, C.c_void_p(out.data_ptr()), _out_code(torch, out.dtype),
-                         d_out, out.stride(0) if rows > 1 else max(d_out, out.stride(0)),
-                         _stream_ptr(stream))
-    _check(rc, "rq_rotate")
-    return out
+    return (_nat or _native()).rotate(h._p, x, transpose, d_out, out_dtype, out, stream)
 
 
 def dequantize_rotate(h: Hadamard, codes, scales, bits: int, mins=None, transpose: bool = True,
                       d_out: Optional[int] = None, out_dtype=None, out=None, stream=None):
     """rq_dequantize_rotate: packed codes (+ scales, + mins for the asymmetric variant) back to
     rows in the original basis, (H_n^T y^ / sqrt(n))[:, :d_out]."""
-    import torch
-    rows = codes.shape[0]
-    d_out = h.n if d_out is None else int(d_out)
-    if out is None:
-        out = torch.empty((rows, d_out), dtype=out_dtype or torch.float32, device=codes.device)
-    rc = lib().rq_dequantize_rotate(h._h, C.c_void_p(codes.data_ptr()), C.c_void_p(scales.data_ptr()),
-                                    C.c_void_p(mins.data_ptr()) if mins is not None else None, rows,
-                                    int(bits), 1 if transpose else 0, C.c_void_p(out.data_ptr()),
-                                    _out_code(torch, out.dtype), d_out,
-                                    out.stride(0) if rows > 1 else max(d_out, out.stride(0)),
-                                    _stream_ptr(stream))
-    _check(rc, "rq_dequantize_rotate")
-    return out
+    return (_nat or _native()).dequantize_rotate(h._p, codes, scales, bits, mins, transpose, d_out, out_dtype, out, stream)
 
 
 def dequantize(h: Hadamard, codes, scales, bits: int, mins=None, out=None, stream=None):
     """rq_dequantize (rq_dequantize_asym when mins is given): packed codes and scales to float32
     values [rows, n] in the rotated domain."""
-    import torch
-    rows = codes.shape[0]
-    if out is None:
-        out = torch.empty((rows, h.n), dtype=torch.float32, device=codes.device)
-    if mins is None:
-        rc = lib().rq_dequantize(h._h, C.c_void_p(codes.data_ptr()), C.c_void_p(scales.data_ptr()), rows,
-                                 int(bits), C.c_void_p(out.data_ptr()), _stream_ptr(stream))
-        _check(rc, "rq_dequantize")
-    else:
-        rc = lib().rq_dequantize_asym(h._h, C.c_void_p(codes.data_ptr()), C.c_void_p(scales.data_ptr()),
-                                      C.c_void_p(mins.data_ptr()), rows, int(bits),
-                                      C.c_void_p(out.data_ptr()), _stream_ptr(stream))
-        _check(rc, "rq_dequantize_asym")
-    return out
+    return (_nat or _native()).dequantize(h._p, codes, scales, bits, mins, out, stream)
 
 
 def expand_limit(n: int, bits: int, bits_reduced: int) -> int:
@@ -343,36 +259,14 @@ def quant_error(h: Hadamard, x, bits: int, clips: Sequence[float], mse=None, wor
                 stream=None, asym: bool = False):
     """rq_quant_error (rq_quant_error_asym with asym=True) on a CUDA tensor x [..., d]; returns mse
     float32 [len(clips)] (device)."""
-    import torch
-    if not x.is_cuda:
-        raise ValueError("x must be a device tensor")
-    x2, rows, d, ld = _rows_view(x)
-    k = len(clips)
-    arr = (C.c_float * k)(*[float(c) for c in clips])
-    if mse is None:
-        mse = torch.empty((k,), dtype=torch.float32, device=x.device)
-    need = quant_error_workspace(rows, k)
-    if workspace is None:
-        workspace = torch.empty((max(need, 8) + 7) // 8, dtype=torch.float64, device=x.device)
-    ws_bytes = workspace.numel() * workspace.element_size()
-    fn = lib().rq_quant_error_asym if asym else lib().rq_quant_error
-    rc = fn(h._h, C.c_void_p(x2.data_ptr()), _dtype_code(x2), rows, d, ld, int(bits), arr, k,
-            C.c_void_p(mse.data_ptr()), C.c_void_p(workspace.data_ptr()), ws_bytes, _stream_ptr(stream))
-    _check(rc, "rq_quant_error_asym" if asym else "rq_quant_error")
-    return mse
+    return (_nat or _native()).quant_error(h._p, x, bits, clips, mse, workspace, stream, asym)
 
 
 def quant_error_noalloc(h: Hadamard, x, bits: int, clips: Sequence[float], mse, stream=None):
     """rq_quant_error_noalloc on a CUDA tensor x [..., d]: rq_quant_error with the library's static
     scratch array in place of a workspace.  `mse` (float32 [len(clips)], device) is the caller's: the
     call itself allocates nothing."""
-    x2, rows, d, ld = _rows_view(x)
-    k = len(clips)
-    arr = (C.c_float * k)(*[float(c) for c in clips])
-    rc = lib().rq_quant_error_noalloc(h._h, C.c_void_p(x2.data_ptr()), _dtype_code(x2), rows, d, ld, int(bits),
-                                      arr, k, C.c_void_p(mse.data_ptr()), _stream_ptr(stream))
-    _check(rc, "rq_quant_error_noalloc")
-    return mse
+    return (_nat or _native()).quant_error_noalloc(h._p, x, bits, clips, mse, stream)
 
 
 def gbs_search(h: Hadamard, x, bits: int, eps: float, max_evals: int = 64, workspace=None, stream=None,
@@ -380,19 +274,4 @@ def gbs_search(h: Hadamard, x, bits: int, eps: float, max_evals: int = 64, works
     """rq_gbs_search (rq_gbs_search_asym with asym=True) on a CUDA tensor x [..., d]; returns
     (clip, mse, trace) with trace a list of (probe, objective) pairs in the algorithm's order.
     Synchronises the stream once per batch of probes."""
-    import torch
-    if not x.is_cuda:
-        raise ValueError("x must be a device tensor")
-    x2, rows, d, ld = _rows_view(x)
-    need = int(lib().rq_gbs_workspace(rows))
-    if workspace is None:
-        workspace = torch.empty((need + 7) // 8, dtype=torch.float64, device=x.device)
-    clip, mse, n = C.c_float(), C.c_float(), C.c_int()
-    tc, tm = (C.c_float * max_evals)(), (C.c_float * max_evals)()
-    fn = lib().rq_gbs_search_asym if asym else lib().rq_gbs_search
-    rc = fn(h._h, C.c_void_p(x2.data_ptr()), _dtype_code(x2), rows, d, ld, int(bits),
-            C.c_float(eps), int(max_evals), C.c_void_p(workspace.data_ptr()),
-            workspace.numel() * workspace.element_size(), _stream_ptr(stream),
-            C.byref(clip), C.byref(mse), tc, tm, C.byref(n))
-    _check(rc, "rq_gbs_search_asym" if asym else "rq_gbs_search")
-    return clip.value, mse.value, [(tc[i], tm[i]) for i in range(n.value)]
+    return (_nat or _native()).gbs_search(h._p, x, bits, eps, max_evals, workspace, stream, asym)

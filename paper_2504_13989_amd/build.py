@@ -1,4 +1,4 @@
-"""Build librotq.so (HIP kernels + C ABI) in-tree for gfx950 with hipcc."""
+"""Build librotq.so (HIP kernels + C ABI) for gfx950 and _pyrotq.so (its Python side) in-tree with hipcc."""
 from __future__ import annotations
 
 import os
@@ -10,6 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "librotq.so")
+NATIVE_PATH = os.path.join(HERE, "_pyrotq.so")
 
 SOURCES = ["hadamard.cpp", "rotq_api.cpp", "kernels_generic.hip", "kernels_wave.hip", "kernels_wgblock.hip", "kernels_dense.hip", "kernels_ref.hip", "kernels_waveblock2.hip", "kernels_rotate.hip", "kernels_plainasym.hip", "kernels_dequant.hip", "noalloc.hip"]
 
@@ -41,19 +42,40 @@ def _run(cmd, verbose):
         print(res.stderr)
 
 
+def _native_compile(hipcc: str, obj: str):
+    """Command that compiles the Python side (host code only) against the installed torch."""
+    import sysconfig
+    from torch.utils import cpp_extension
+    inc = [f"-I{d}" for d in (*cpp_extension.include_paths("cuda"), sysconfig.get_paths()["include"])]
+    return [hipcc, "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-DUSE_ROCM", *inc, "-Wno-unused-command-line-argument",
+            "-c", "-x", "hip", "--cuda-host-only", os.path.join(CSRC, "pyrotq.cpp"), "-o", obj]
+
+
+def _native_link(hipcc: str, obj: str, out: str):
+    from torch.utils import cpp_extension
+    dirs = [f"-L{d}" for d in cpp_extension.library_paths("cuda")]
+    return [hipcc, "-shared", "-fPIC", obj, "-o", out, f"-L{HERE}", "-l:librotq.so", *dirs, "-ltorch_python", "-ltorch",
+            "-ltorch_cpu", "-ltorch_hip", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+
+
 def build_library(verbose: bool = False, extra_flags=()) -> str:
-    """Compile every source to an object (a few at a time), then link the shared library."""
+    """Compile every source to an object (a few at a time), then link the library and the Python side."""
     hipcc = hipcc_path()
     compile_flags = [f for f in FLAGS if f != "-shared"]
     with tempfile.TemporaryDirectory(prefix="rotq_build_") as tmpdir:
         objs = [os.path.join(tmpdir, os.path.splitext(s)[0] + ".o") for s in SOURCES]
         jobs = [[hipcc, *compile_flags, *extra_flags, "-c", "-x", "hip", os.path.join(CSRC, s), "-o", o]
                 for s, o in zip(SOURCES, objs)]
+        pyobj = os.path.join(tmpdir, "pyrotq.o")
+        jobs.append(_native_compile(hipcc, pyobj))
         with ThreadPoolExecutor(max_workers=min(len(jobs), 6)) as pool:
             list(pool.map(lambda c: _run(c, verbose), jobs))
         tmp = LIB_PATH + ".tmp"
         _run([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", *objs, "-o", tmp], verbose)
-    os.replace(tmp, LIB_PATH)
+        os.replace(tmp, LIB_PATH)
+        tmp = NATIVE_PATH + ".tmp"
+        _run(_native_link(hipcc, pyobj, tmp), verbose)
+        os.replace(tmp, NATIVE_PATH)
     return LIB_PATH
 
 
