@@ -472,35 +472,31 @@ __device__ __forceinline__ u32x4 load16(const uint16_t* p) {
     return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
 }
 
+// Two floats as two 16-bit values of a dword, round to nearest even: one conversion instruction on this chip.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+template <int OUT>
+__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
+    static_assert(OUT == 0 || OUT == 2, "16-bit results");
+    const f32x2 v = {lo, hi};
+    if constexpr (OUT == 0) return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+    else return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
+}
+template <int OUT>
+__device__ __forceinline__ u32x4 pack16(const float (&o)[8]) {
+    return u32x4{pack2<OUT>(o[0], o[1]), pack2<OUT>(o[2], o[3]), pack2<OUT>(o[4], o[5]), pack2<OUT>(o[6], o[7])};
+}
+
 // Eight consecutive results of a lane (carrying the lane's sign in `k`) to columns col .. col + 7.
-// OUT: 0 bf16, 1 fp32, 2 fp16 (round to nearest even).
+// OUT: 0 bf16, 2 fp16 (round to nearest even); fp32 results go through store_block_f32.
 template <int OUT>
 __device__ __forceinline__ void store8(void* Y, int64_t idx, const float (&v)[8], float k, float add0 = 0.0f) {
     float o[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) o[i] = v[i] * k;
     o[0] += add0;
-    if constexpr (OUT == 1) {
-        u32x4* p = reinterpret_cast<u32x4*>(static_cast<float*>(Y) + idx);
-        p[0] = u32x4{__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])};
-        p[1] = u32x4{__float_as_uint(o[4]), __float_as_uint(o[5]), __float_as_uint(o[6]), __float_as_uint(o[7])};
-    } else {
-        uint32_t w[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            uint32_t lo, hi;
-            if constexpr (OUT == 0) {
-                const uint32_t a = __float_as_uint(o[2 * i]), b = __float_as_uint(o[2 * i + 1]);
-                lo = (a + 0x7fffu + ((a >> 16) & 1u)) >> 16;
-                hi = (b + 0x7fffu + ((b >> 16) & 1u)) >> 16;
-            } else {
-                lo = __builtin_bit_cast(uint16_t, (_Float16)o[2 * i]);
-                hi = __builtin_bit_cast(uint16_t, (_Float16)o[2 * i + 1]);
-            }
-            w[i] = lo | (hi << 16);
-        }
-        __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]}, reinterpret_cast<u32x4*>(static_cast<uint16_t*>(Y) + idx));
-    }
+    __builtin_nontemporal_store(pack16<OUT>(o), reinterpret_cast<u32x4*>(static_cast<uint16_t*>(Y) + idx));
 }
 
 // fp32 results of one step of a wave.  The 64 lanes hold 64 chunks of 8 values (32 bytes each) that are consecutive
