@@ -37,23 +37,10 @@ struct RotArgs {
 
 // The lane's 8 consecutive codes (group idx of the row: codes 8 idx .. 8 idx + 7) as a matrix-core
 // operand: four dwords of two bf16 patterns 0x4300 | u each.  Signed codes are two's complement fields:
-// one xor makes them offset binary.  A 3-bit group is 24 bits at byte 3 idx: the dword it starts in and,
-// where it continues there, the next one (lanes whose field ends inside the first dword read that one
-// twice, so nothing beyond the row is touched).  CodeLane holds what depends on the lane alone.
-struct CodeLane {
-    uint32_t off0, off1;      // byte offsets of the two dwords from the group-0 position
-    uint32_t sh;              // bit position of the field in the first dword
-};
-template <int BITS>
-__device__ __forceinline__ CodeLane code_lane(int idx) {
-    if constexpr (BITS == 4) return CodeLane{(uint32_t)idx * 4u, 0u, 0u};
-    const uint32_t byte = 3u * (uint32_t)idx, sh = (byte & 3u) * 8u;
-    const uint32_t off0 = byte & ~3u;
-    return CodeLane{off0, off0 + (sh >= 16u ? 4u : 0u), sh};
-}
+// one xor makes them offset binary.  CodeAt (code_at) holds what depends on the lane alone.
 // base: the packed codes at the lane-independent part of the position (uniform where the wave works on one row)
 template <int BITS, bool ASYM>
-__device__ __forceinline__ u32x4 code_operand(const uint32_t* base, const CodeLane& cl) {
+__device__ __forceinline__ u32x4 code_operand(const uint32_t* base, const CodeAt& cl) {
     const char* p = reinterpret_cast<const char*>(base);
     uint32_t w;
     if constexpr (BITS == 4) {
@@ -96,7 +83,7 @@ __global__ __launch_bounds__(64) void k_wave_rotate(RotArgs a) {
     // packed codes: the constant K = 128 + 2^(b-1) of the patterns leaves through element 0 of the row
     const float corr = (SRC && chunk == 0) ? -(float)(512 * T) * (float)(128 + (1 << (SRC ? SRC - 1 : 0))) : 0.0f;
     const float sgn = (__builtin_popcount(c) & 1) ? -1.0f : 1.0f;
-    const CodeLane cl = code_lane<SRC ? SRC : 4>(chunk);
+    const CodeAt cl = code_at<SRC ? SRC : 4>(chunk);
     for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
         f32x4 acc[T][2];
         u32x4 raw[T];
@@ -174,7 +161,7 @@ __global__ __launch_bounds__(64) void k_wave_rotate_short(RotArgs a) {
     const float k0 = ((__builtin_popcount(c >> 1) & 1) ? -1.0f : 1.0f) * a.inv;  // stages 2.. are the fused ones
     // packed codes: the constant of the patterns (128, plus 2^(b-1) for signed codes) leaves through element 0
     const float corr = (SRC && chunk == 0) ? -(float)(32 << CB) * (float)(128 + (ASYM ? 0 : 1 << (SRC ? SRC - 1 : 0))) : 0.0f;
-    const CodeLane cl = code_lane<SRC ? SRC : 4>(chunk);
+    const CodeAt cl = code_at<SRC ? SRC : 4>(chunk);
     const int64_t n_super = (a.rows + SUPER - 1) / SUPER;
     for (int64_t sgi = blockIdx.x; sgi < n_super; sgi += gridDim.x) {
         const int64_t row0 = sgi * SUPER;

@@ -540,17 +540,34 @@ void k_wave_short(WaveArgs a) {
 // 128-point transform along the columns.  y[column i][j]: register j = 4 h + ip holds block rows
 // 4 j .. 4 j + 3 (one per DPP row g); only the NV = ceil(pb / 4) registers that hold real block rows
 // are carried.  Values carry the lane's flip sign (see lane_stages_fused).  Returns the row's absmax.
-template <bool FULL, int NV, bool F16 = false>
+// SRC = 3, 4: the row comes from packed signed codes of that width (a.codes) as exact fp16 integers.
+template <bool FULL, int NV, bool F16 = false, int SRC = 0>
 __device__ __forceinline__ float block_rotate_row(const WaveArgs& a, int64_t row, int e_base, const u32x4& A0,
                                               const u32x4& A1, const float (&sf)[4], float (&y)[8][NV]) {
     constexpr int NH1 = NV > 4 ? NV - 4 : 0;              // live registers of the second half
     constexpr int NH0 = NV > 4 ? 4 : NV;
-    const uint16_t* xr = a.X + row * a.ld + e_base;
-    const RowView xv = row_view(a.X + row * a.ld, a.d);
     u32x4 R[8];
+    if constexpr (SRC != 0) {
+        constexpr int STEP = 16 * SRC;                   // bytes of a block row
+        const int row_bytes = STEP * (a.d >> 7);
+        const auto rs = __builtin_amdgcn_make_buffer_rsrc(a.codes + row * (row_bytes / 4), 0, row_bytes, 0x00020000);
+        const CodeAt at = code_at<SRC>(e_base >> 3);
+        uint32_t lo[8], hi[8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t)
-        R[t] = FULL ? load16(xr + t * 128) : load_chunk(xv, e_base + t * 128);
+        for (int t = 0; t < 8; ++t) {
+            lo[t] = __builtin_amdgcn_raw_buffer_load_b32(rs, at.off0 + t * STEP, 0, 2);
+            if constexpr (SRC == 3) hi[t] = __builtin_amdgcn_raw_buffer_load_b32(rs, at.off1 + t * STEP, 0, 2);
+        }
+        __builtin_amdgcn_sched_barrier(0);               // every load is issued before the first wait
+#pragma unroll
+        for (int t = 0; t < 8; ++t) R[t] = codes_f16<SRC>(SRC == 4 ? lo[t] : __builtin_amdgcn_alignbit(hi[t], lo[t], at.sh));
+    } else {
+        const uint16_t* xr = a.X + row * a.ld + e_base;
+        const RowView xv = row_view(a.X + row * a.ld, a.d);
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+            R[t] = FULL ? load16(xr + t * 128) : load_chunk(xv, e_base + t * 128);
+    }
 #pragma unroll
     for (int ic = 0; ic < 8; ++ic) {
         u32x4 bm;
@@ -637,7 +654,8 @@ __global__ __launch_bounds__(64) void k_wave_block(WaveArgs a, int pb) {
 }
 
 // Rotation alone for the same block orders (rq_rotate: the online rotation of a tensor that is not
-// quantized, offline weight fusion, the inverse rotation with the transposed block's operand tiles):
+// quantized, offline weight fusion, the inverse rotation with the transposed block's operand tiles) and from
+// packed codes (SRC = 3, 4: rq_dequantize_rotate; the row's scale multiplies once at the end):
 // the row's rotation as above, then one multiply and a 16-byte store per lane and block row (bf16 / fp16);
 // fp32 results pass through LDS so that a store instruction covers 1 KB of consecutive bytes
 // (store_block_f32).
@@ -648,7 +666,7 @@ struct BlockRotArgs {
     float inv;            // 1 / sqrt(n)
 };
 
-template <bool FULL, int NV, bool F16, int OUT>
+template <bool FULL, int NV, bool F16, int OUT, int SRC = 0>
 __global__ __launch_bounds__(64) void k_wave_block_rotate(WaveArgs a, int pb, BlockRotArgs o) {
     const int lane = threadIdx.x;
     const int g = lane >> 4, cphys = lane & 15;
@@ -658,12 +676,13 @@ __global__ __launch_bounds__(64) void k_wave_block_rotate(WaveArgs a, int pb, Bl
     float sf[4];
 #pragma unroll
     for (int b = 0; b < 4; ++b) sf[b] = ((c >> b) & 1) ? -1.0f : 1.0f;
-    const float k = ((__builtin_popcount(c) & 1) ? -1.0f : 1.0f) * o.inv;
+    const float k0 = ((__builtin_popcount(c) & 1) ? -1.0f : 1.0f) * o.inv;
     const int base_g = 8 * g < pb - 8 ? 8 * g : pb - 8;
     const int e_base = base_g * 128 + c * 8;
     for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
         float y[8][NV];
-        (void)block_rotate_row<FULL, NV, F16>(a, row, e_base, A0, A1, sf, y);
+        const float k = SRC ? k0 * a.scales[row] : k0;
+        (void)block_rotate_row<FULL, NV, F16, SRC>(a, row, e_base, A0, A1, sf, y);
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
             const int ao = 4 * j + g;                      // output block row of this register
@@ -1215,28 +1234,57 @@ int wave_block_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float cli
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }
 
+// src: 0 rows of X, 3 / 4 packed codes of that width (whole rows, fp16 operands).
 template <int NV>
-static void launch_block_rotate_nv(bool full, bool f16, int out, unsigned grid, hipStream_t s, const WaveArgs& w, int pb,
+static void launch_block_rotate_nv(int src, bool full, bool f16, int out, unsigned grid, hipStream_t s, const WaveArgs& w, int pb,
                                    const BlockRotArgs& o) {
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, w, pb, o); };
-    auto pick_out = [&](auto full_c, auto f16_c) {
+    auto pick_out = [&](auto full_c, auto f16_c, auto src_c) {
         constexpr bool FL = decltype(full_c)::value, FH = decltype(f16_c)::value;
-        if (out == 0) go(k_wave_block_rotate<FL, NV, FH, 0>);
-        else if (out == 1) go(k_wave_block_rotate<FL, NV, FH, 1>);
-        else go(k_wave_block_rotate<FL, NV, FH, 2>);
+        constexpr int SRC = decltype(src_c)::value;
+        if (out == 0) go(k_wave_block_rotate<FL, NV, FH, 0, SRC>);
+        else if (out == 1) go(k_wave_block_rotate<FL, NV, FH, 1, SRC>);
+        else go(k_wave_block_rotate<FL, NV, FH, 2, SRC>);
     };
-    if (full) {
-        if (f16) pick_out(std::true_type{}, std::true_type{}); else pick_out(std::true_type{}, std::false_type{});
+    using rows = std::integral_constant<int, 0>;
+    if (src == 4) {
+        pick_out(std::true_type{}, std::true_type{}, std::integral_constant<int, 4>{});
+    } else if (src == 3) {
+        pick_out(std::true_type{}, std::true_type{}, std::integral_constant<int, 3>{});
+    } else if (full) {
+        if (f16) pick_out(std::true_type{}, std::true_type{}, rows{}); else pick_out(std::true_type{}, std::false_type{}, rows{});
     } else {
-        if (f16) pick_out(std::false_type{}, std::true_type{}); else pick_out(std::false_type{}, std::false_type{});
+        if (f16) pick_out(std::false_type{}, std::true_type{}, rows{}); else pick_out(std::false_type{}, std::false_type{}, rows{});
     }
 }
 
-bool wave_block_rotate_supports(const rq_hadamard* h, const RowArgs& a, int transpose, const OutArgs& o) {
-    if (!wave_block_supports(h, a)) return false;
-    if (transpose && (!h->d_tiles_t || (a.dtype == RQ_F16 && !h->d_tiles_t_f16))) return false;
+static int launch_block_rotate(int src, const RowArgs& a, const WaveArgs& w, const OutArgs& o, hipStream_t s) {
+    const BlockRotArgs bo{o.Y, o.d_out, o.ld_out, (float)(1.0 / std::sqrt((double)a.n))};
+    const int out = o.dtype == RQ_BF16 ? 0 : o.dtype == RQ_F32 ? 1 : 2;
+    const int pb = a.p << (a.log2m - 7);
+    const int64_t cap = 1 << 24;
+    const unsigned grid = (unsigned)(a.rows < cap ? a.rows : cap);
+    const bool full = a.d == a.n;
+    switch ((pb + 3) / 4) {
+        case 2: launch_block_rotate_nv<2>(src, full, w.f16, out, grid, s, w, pb, bo); break;
+        case 3: launch_block_rotate_nv<3>(src, full, w.f16, out, grid, s, w, pb, bo); break;
+        case 4: launch_block_rotate_nv<4>(src, full, w.f16, out, grid, s, w, pb, bo); break;
+        case 5: launch_block_rotate_nv<5>(src, full, w.f16, out, grid, s, w, pb, bo); break;
+        case 6: launch_block_rotate_nv<6>(src, full, w.f16, out, grid, s, w, pb, bo); break;
+        case 7: launch_block_rotate_nv<7>(src, full, w.f16, out, grid, s, w, pb, bo); break;
+        case 8: launch_block_rotate_nv<8>(src, full, w.f16, out, grid, s, w, pb, bo); break;
+        default: return RQ_ERR_NO_ORDER;
+    }
+    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+}
+
+static bool rotate_out_ok(const OutArgs& o) {
     if ((reinterpret_cast<uintptr_t>(o.Y) & 15) != 0 || (o.d_out & 7) != 0) return false;
     return o.dtype == RQ_F32 ? (o.ld_out & 3) == 0 : (o.ld_out & 7) == 0;
+}
+
+bool wave_block_rotate_supports(const rq_hadamard* h, const RowArgs& a, const OutArgs& o) {
+    return wave_block_supports(h, a) && rotate_out_ok(o);
 }
 
 int wave_block_rotate(const rq_hadamard* h, const RowArgs& a, int transpose, const OutArgs& o, hipStream_t s) {
@@ -1245,23 +1293,21 @@ int wave_block_rotate(const rq_hadamard* h, const RowArgs& a, int transpose, con
     WaveArgs w{static_cast<const uint16_t*>(a.X), a.rows, a.d, a.ld, static_cast<const u32x4*>(tiles), nullptr, nullptr,
                0.0, 0.0};
     w.f16 = f16;
-    const BlockRotArgs bo{o.Y, o.d_out, o.ld_out, (float)(1.0 / std::sqrt((double)a.n))};
-    const int out = o.dtype == RQ_BF16 ? 0 : o.dtype == RQ_F32 ? 1 : 2;
-    const int pb = a.p << (a.log2m - 7);
-    const int64_t cap = 1 << 24;
-    const unsigned grid = (unsigned)(a.rows < cap ? a.rows : cap);
-    const bool full = a.d == a.n;
-    switch ((pb + 3) / 4) {
-        case 2: launch_block_rotate_nv<2>(full, f16, out, grid, s, w, pb, bo); break;
-        case 3: launch_block_rotate_nv<3>(full, f16, out, grid, s, w, pb, bo); break;
-        case 4: launch_block_rotate_nv<4>(full, f16, out, grid, s, w, pb, bo); break;
-        case 5: launch_block_rotate_nv<5>(full, f16, out, grid, s, w, pb, bo); break;
-        case 6: launch_block_rotate_nv<6>(full, f16, out, grid, s, w, pb, bo); break;
-        case 7: launch_block_rotate_nv<7>(full, f16, out, grid, s, w, pb, bo); break;
-        case 8: launch_block_rotate_nv<8>(full, f16, out, grid, s, w, pb, bo); break;
-        default: return RQ_ERR_NO_ORDER;
-    }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_block_rotate(0, a, w, o, s);
+}
+
+// Packed per-token codes back to rows for the same orders.
+bool wave_block_dequant_rotate_supports(const rq_hadamard* h, const RowArgs& a, const float* mins, const OutArgs& o) {
+    const int pb = a.log2m >= 7 ? a.p << (a.log2m - 7) : 0;
+    return h->device >= 0 && h->d_tiles_f16 && !mins && a.p > 1 && pb >= 8 && pb <= 32 && rotate_out_ok(o);
+}
+
+int wave_block_dequant_rotate(const rq_hadamard* h, const RowArgs& a, const uint32_t* codes, const float* scales, int transpose,
+                              const OutArgs& o, hipStream_t s) {
+    WaveArgs w{nullptr, a.rows, a.n, a.n, static_cast<const u32x4*>(transpose ? h->d_tiles_t_f16 : h->d_tiles_f16),
+               const_cast<uint32_t*>(codes), const_cast<float*>(scales), 0.0, 0.0};
+    w.f16 = true;
+    return launch_block_rotate(a.bits, a, w, o, s);
 }
 
 bool wave_supports(const rq_hadamard* h, const RowArgs& a) {

@@ -31,6 +31,35 @@ rq::RowArgs row_args(const rq_hadamard_t* h, const void* X, int dtype, int64_t r
     return rq::RowArgs{X, dtype, rows, d, ld, h->f.n, h->f.p, h->f.log2m, h->d_block, bits};
 }
 
+// The device tables of a handle, gathered on the host and uploaded together.
+struct TableSet {
+    struct Slot { void** where; size_t offset; };
+    std::vector<uint32_t> words;
+    std::vector<Slot> slots;
+    void add(void** where, const std::vector<uint32_t>& t) {
+        slots.push_back(Slot{where, words.size()});
+        words.insert(words.end(), t.begin(), t.end());
+        words.resize((words.size() + 63) / 64 * 64, 0u);             // 256-byte steps
+    }
+    void share(void** where, void** with) {
+        for (const Slot& s : slots)
+            if (s.where == with) {
+                slots.push_back(Slot{where, s.offset});
+                return;
+            }
+    }
+    bool upload(void** pool) {
+        const size_t bytes = words.size() * sizeof(uint32_t);
+        if (hipMalloc(pool, bytes) != hipSuccess) return false;
+        if (hipMemcpy(*pool, words.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
+            (void)hipFree(*pool);
+            return false;
+        }
+        for (const Slot& s : slots) *s.where = static_cast<uint32_t*>(*pool) + s.offset;
+        return true;
+    }
+};
+
 }  // namespace
 
 extern "C" {
@@ -63,37 +92,52 @@ int rq_hadamard_build(int n, rq_hadamard_t** out) {
     }
     h->max_lds = (int)prop.sharedMemPerBlock;
     h->num_cu = prop.multiProcessorCount;
-    const size_t bytes = h->block.size();
-    if (hipMalloc((void**)&h->d_block, bytes) != hipSuccess ||
-        hipMemcpy(h->d_block, h->block.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
-        if (h->d_block) (void)hipFree(h->d_block);
-        delete h;
-        return RQ_ERR_HIP;
-    }
+    // every table goes to the device in one allocation and one copy; a slot may share another's table
+    TableSet tables;
+    std::vector<uint32_t> block_words((h->block.size() + 3) / 4);
+    std::memcpy(block_words.data(), h->block.data(), h->block.size());
+    void* d_block = nullptr;
+    tables.add(&d_block, block_words);
     const bool sylv = f.p == 1 && f.log2m >= 7 && f.log2m <= 13;
     // block orders of the block kernels; the Sylvester orders 2^14, 2^15 ride along with p = 1
     const bool blk = (f.p > 1 && f.log2m >= 7 && (f.p << (f.log2m - 7)) <= 256) ||
                      (f.p == 1 && (f.log2m == 14 || f.log2m == 15));
     const bool blk_short = f.p > 1 && (f.log2m == 5 || f.log2m == 6) && f.p <= 256;   // block rows of 32 / 64
     const bool dense = !sylv && !blk && !blk_short && n <= 4096;
-    if (sylv || blk || blk_short || dense) {
-        std::vector<uint32_t> tiles;
-        bool f16_table = sylv;
+    // tiles of a block in both 16-bit encodings, and those of its transpose (Paley I blocks are not symmetric)
+    auto add_block = [&](const std::vector<int8_t>& bm, int pb, std::vector<uint32_t> (*make)(const std::vector<int8_t>&, int)) {
+        const std::vector<uint32_t> tiles = make(bm, pb);
+        tables.add(&h->d_tiles, tiles);
+        tables.add(&h->d_tiles_f16, rq::tiles_to_f16(tiles));
+        std::vector<int8_t> bt((size_t)pb * pb);
+        for (int i = 0; i < pb; ++i)
+            for (int j = 0; j < pb; ++j) bt[(size_t)i * pb + j] = bm[(size_t)j * pb + i];
+        if (bt == bm) {
+            tables.share(&h->d_tiles_t, &h->d_tiles);
+            tables.share(&h->d_tiles_t_f16, &h->d_tiles_f16);
+        } else {
+            const std::vector<uint32_t> tt = make(bt, pb);
+            tables.add(&h->d_tiles_t, tt);
+            tables.add(&h->d_tiles_t_f16, rq::tiles_to_f16(tt));
+        }
+    };
+    try {
         if (sylv) {
-            tiles = rq::wave_sylvester_tiles();
+            const std::vector<uint32_t> tiles = rq::wave_sylvester_tiles();
+            tables.add(&h->d_tiles, tiles);
+            tables.add(&h->d_tiles_f16, rq::tiles_to_f16(tiles));
         } else if (dense) {
             std::vector<int8_t> hm((size_t)n * n);
             if (rq_hadamard_dense(h, hm.data()) != RQ_OK) {
-                rq_hadamard_free(h);
+                delete h;
                 return RQ_ERR_ARG;
             }
-            tiles = rq::dense_block_tiles(hm, n);
+            tables.add(&h->d_tiles, rq::dense_block_tiles(hm, n));
             h->dense_ok = true;
         } else if (blk_short) {
-            tiles = rq::wg_block_tiles(h->block, f.p);
+            add_block(h->block, f.p, rq::wg_block_tiles);
             h->wg_ok = rq::wg_block_prepare(f.p);
-            f16_table = true;
-        } else {
+        } else if (blk) {
             // block of the strided axis: H_p (x) H_{2^(k-7)}, index a * 2^(k-7) + (high bits of c)
             const int e = 1 << (f.log2m - 7), pb = f.p * e;
             std::vector<int8_t> bm((size_t)pb * pb);
@@ -101,50 +145,24 @@ int rq_hadamard_build(int n, rq_hadamard_t** out) {
                 for (int j = 0; j < pb; ++j)
                     bm[(size_t)i * pb + j] = (int8_t)(h->block[(size_t)(i / e) * f.p + j / e] *
                                                       rq::sylvester_entry(i % e, j % e));
-            tiles = pb <= 32 ? rq::wave_block_tiles(bm, pb) : rq::wg_block_tiles(bm, pb);
+            add_block(bm, pb, pb <= 32 ? rq::wave_block_tiles : rq::wg_block_tiles);
             if (pb > 32) h->wg_ok = rq::wg_block_prepare(pb);
-            f16_table = true;
-            if (pb <= 32) {
-                // the transposed block's tiles: rq_rotate with transpose = 1 (Paley I blocks are not symmetric)
-                std::vector<int8_t> bt((size_t)pb * pb);
-                for (int i = 0; i < pb; ++i)
-                    for (int j = 0; j < pb; ++j) bt[(size_t)i * pb + j] = bm[(size_t)j * pb + i];
-                const std::vector<uint32_t> tt = rq::wave_block_tiles(bt, pb), tth = rq::tiles_to_f16(tt);
-                const size_t bb = tt.size() * sizeof(uint32_t);
-                if (hipMalloc(&h->d_tiles_t, bb) != hipSuccess || hipMalloc(&h->d_tiles_t_f16, bb) != hipSuccess ||
-                    hipMemcpy(h->d_tiles_t, tt.data(), bb, hipMemcpyHostToDevice) != hipSuccess ||
-                    hipMemcpy(h->d_tiles_t_f16, tth.data(), bb, hipMemcpyHostToDevice) != hipSuccess) {
-                    rq_hadamard_free(h);
-                    return RQ_ERR_HIP;
-                }
-            }
             if (pb > 32 && pb <= 64) {
                 // these blocks also have a one-wave kernel (rotate_quantize), with operand tiles of its own
-                const std::vector<uint32_t> t2 = rq::wave_block2_tiles(bm, pb), t2h = rq::tiles_to_f16(t2);
-                const size_t b2 = t2.size() * sizeof(uint32_t);
-                if (hipMalloc(&h->d_tiles2, b2) != hipSuccess || hipMalloc(&h->d_tiles2_f16, b2) != hipSuccess ||
-                    hipMemcpy(h->d_tiles2, t2.data(), b2, hipMemcpyHostToDevice) != hipSuccess ||
-                    hipMemcpy(h->d_tiles2_f16, t2h.data(), b2, hipMemcpyHostToDevice) != hipSuccess) {
-                    rq_hadamard_free(h);
-                    return RQ_ERR_HIP;
-                }
+                const std::vector<uint32_t> t2 = rq::wave_block2_tiles(bm, pb);
+                tables.add(&h->d_tiles2, t2);
+                tables.add(&h->d_tiles2_f16, rq::tiles_to_f16(t2));
             }
         }
-        const size_t tb = tiles.size() * sizeof(uint32_t);
-        if (hipMalloc(&h->d_tiles, tb) != hipSuccess ||
-            hipMemcpy(h->d_tiles, tiles.data(), tb, hipMemcpyHostToDevice) != hipSuccess) {
-            rq_hadamard_free(h);
-            return RQ_ERR_HIP;
-        }
-        if (f16_table) {
-            const std::vector<uint32_t> t16 = rq::tiles_to_f16(tiles);
-            if (hipMalloc(&h->d_tiles_f16, tb) != hipSuccess ||
-                hipMemcpy(h->d_tiles_f16, t16.data(), tb, hipMemcpyHostToDevice) != hipSuccess) {
-                rq_hadamard_free(h);
-                return RQ_ERR_HIP;
-            }
-        }
+    } catch (const std::bad_alloc&) {
+        delete h;
+        return RQ_ERR_NOMEM;
     }
+    if (!tables.upload(&h->d_tables)) {
+        delete h;
+        return RQ_ERR_HIP;
+    }
+    h->d_block = static_cast<int8_t*>(d_block);
     h->device = dev;
     h->generic_ok = rq::generic_prepare(h);
     // set-up time is when the static scratch array's address on this device is asked for; a failure
@@ -156,13 +174,7 @@ int rq_hadamard_build(int n, rq_hadamard_t** out) {
 
 void rq_hadamard_free(rq_hadamard_t* h) {
     if (!h) return;
-    if (h->d_block) (void)hipFree(h->d_block);
-    if (h->d_tiles) (void)hipFree(h->d_tiles);
-    if (h->d_tiles_f16) (void)hipFree(h->d_tiles_f16);
-    if (h->d_tiles_t) (void)hipFree(h->d_tiles_t);
-    if (h->d_tiles_t_f16) (void)hipFree(h->d_tiles_t_f16);
-    if (h->d_tiles2) (void)hipFree(h->d_tiles2);
-    if (h->d_tiles2_f16) (void)hipFree(h->d_tiles2_f16);
+    if (h->d_tables) (void)hipFree(h->d_tables);
     delete h;
 }
 
@@ -326,9 +338,13 @@ int rq_rotate(const rq_hadamard_t* h, const void* X, int dtype, int64_t rows, in
         note(h, "wave_rotate");
         return rq::wave_rotate(h, a, o, static_cast<hipStream_t>(stream));
     }
-    if (h->variant == 0 && rq::wave_block_rotate_supports(h, a, transpose, o)) {
+    if (h->variant == 0 && rq::wave_block_rotate_supports(h, a, o)) {
         note(h, "wave_block_rotate");
         return rq::wave_block_rotate(h, a, transpose, o, static_cast<hipStream_t>(stream));
+    }
+    if (h->variant == 0 && rq::wg_rotate_supports(h, a, o)) {
+        note(h, "wg_block_rotate");
+        return rq::wg_rotate(h, a, transpose, o, static_cast<hipStream_t>(stream));
     }
     if (!rq::generic_supports(h)) return RQ_ERR_NO_ORDER;
     note(h, "generic_rotate");
@@ -354,6 +370,16 @@ int rq_dequantize_rotate(const rq_hadamard_t* h, const void* codes, const float*
         note(h, "wave_dequant_rotate");
         return rq::wave_dequant_rotate(h, a, static_cast<const uint32_t*>(codes), scales, mins, o,
                                        static_cast<hipStream_t>(stream));
+    }
+    if (h->variant == 0 && rq::wave_block_dequant_rotate_supports(h, a, mins, o)) {
+        note(h, "wave_block_dequant_rotate");
+        return rq::wave_block_dequant_rotate(h, a, static_cast<const uint32_t*>(codes), scales, transpose, o,
+                                             static_cast<hipStream_t>(stream));
+    }
+    if (h->variant == 0 && rq::wg_dequant_rotate_supports(h, a, mins, o)) {
+        note(h, "wg_block_dequant_rotate");
+        return rq::wg_dequant_rotate(h, a, static_cast<const uint32_t*>(codes), scales, transpose, o,
+                                     static_cast<hipStream_t>(stream));
     }
     if (!rq::generic_supports(h)) return RQ_ERR_NO_ORDER;
     note(h, "generic_dequant_rotate");

@@ -13,11 +13,12 @@ struct rq_hadamard {
     rq::Factorisation f;
     std::vector<int8_t> block;       // host copy of H_p, row-major p x p
     int device = -1;                 // device the tables live on; -1 = host-only handle
+    void* d_tables = nullptr;        // the one device allocation all tables below lie in
     int8_t* d_block = nullptr;       // device copy of `block`
     void* d_tiles = nullptr;         // device MFMA operand tiles of the block stage (bf16)
-    void* d_tiles_f16 = nullptr;     // the same tiles encoded in fp16 (wave kernels only)
-    void* d_tiles_t = nullptr;       // blocks up to 32: operand tiles of the transposed block (rq_rotate with
-    void* d_tiles_t_f16 = nullptr;   // transpose = 1), bf16 and fp16
+    void* d_tiles_f16 = nullptr;     // the same tiles encoded in fp16 (not the dense-block kernel's)
+    void* d_tiles_t = nullptr;       // operand tiles of the transposed block (rotations with transpose = 1), bf16
+    void* d_tiles_t_f16 = nullptr;   // and fp16; those of the block itself where it is symmetric
     void* d_tiles2 = nullptr;        // blocks of 33 .. 64: operand tiles of the one-wave kernel (d_tiles holds the
     void* d_tiles2_f16 = nullptr;    // workgroup kernel's), bf16 and fp16
     int max_lds = 0;                 // bytes of LDS one workgroup may use on `device`
@@ -121,8 +122,12 @@ int wave_block_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float cli
                                float* scales, hipStream_t s);
 
 // Rotation alone for those orders (H_n, or H_n^T with the transposed block's tiles).
-bool wave_block_rotate_supports(const rq_hadamard* h, const RowArgs& a, int transpose, const OutArgs& o);
+bool wave_block_rotate_supports(const rq_hadamard* h, const RowArgs& a, const OutArgs& o);
 int wave_block_rotate(const rq_hadamard* h, const RowArgs& a, int transpose, const OutArgs& o, hipStream_t s);
+// Packed per-token codes back to rows for those orders.
+bool wave_block_dequant_rotate_supports(const rq_hadamard* h, const RowArgs& a, const float* mins, const OutArgs& o);
+int wave_block_dequant_rotate(const rq_hadamard* h, const RowArgs& a, const uint32_t* codes, const float* scales, int transpose,
+                              const OutArgs& o, hipStream_t s);
 
 // One-wave block kernel for blocks of 33 .. 64 (n <= 8192): bf16 / fp16 rows, 16-byte aligned.
 std::vector<uint32_t> wave_block2_tiles(const std::vector<int8_t>& bm, int pb);
@@ -157,6 +162,15 @@ int dense_block_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float cl
 // or n = p * 64 / p * 32 with 4 <= p <= 256 (several rows per pass); quant_error: the former, bf16.
 std::vector<uint32_t> wg_block_tiles(const std::vector<int8_t>& bm, int pb);
 bool wg_block_prepare(int pb);
+// Shape of a launch of that kernel: block order and lane bits of the column transform; false when it does not serve the order.
+bool wg_shape(const RowArgs& a, int* pb, int* cb);
+// Rotation alone on it, from rows or from packed per-token codes; with transpose the transposed block's tiles.
+bool wg_rotate_prepare(int pb);
+bool wg_rotate_supports(const rq_hadamard* h, const RowArgs& a, const OutArgs& o);
+int wg_rotate(const rq_hadamard* h, const RowArgs& a, int transpose, const OutArgs& o, hipStream_t s);
+bool wg_dequant_rotate_supports(const rq_hadamard* h, const RowArgs& a, const float* mins, const OutArgs& o);
+int wg_dequant_rotate(const rq_hadamard* h, const RowArgs& a, const uint32_t* codes, const float* scales, int transpose,
+                      const OutArgs& o, hipStream_t s);
 bool wg_block_supports(const rq_hadamard* h, const RowArgs& a, bool quant_error = false);
 int wg_block_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float clip, uint32_t* codes,
                              float* scales, hipStream_t s);

@@ -529,6 +529,37 @@ __device__ __forceinline__ void store_block_f32(float* lds, int pos, int lane, c
     put(256 + 4 * lane, hi);
 }
 
+// Eight consecutive signed b-bit codes (the low 8 b bits of `w`) as exact fp16 integers: a code in offset binary, u,
+// becomes the fp16 pattern 0x6400 | u = 1024 + u by bit operations; one packed fp16 subtraction per two codes takes
+// 1024 + 2^(b-1) away, exactly.
+template <int BITS>
+__device__ __forceinline__ u32x4 codes_f16(uint32_t w) {
+    w ^= BITS == 4 ? 0x88888888u : 0x924924u;                              // two's complement -> offset binary
+    constexpr uint32_t kMul = BITS == 4 ? 0x1001u : 0x2001u, kField = BITS == 4 ? 0x000f000fu : 0x00070007u;
+    constexpr float kOff = -1024.0f - (float)(1 << (BITS - 1));
+    const f16x2 off = {(_Float16)kOff, (_Float16)kOff};
+    u32x4 r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t two = (w >> (2 * BITS * j)) & ((1u << (2 * BITS)) - 1u);
+        const uint32_t pat = ((two * kMul) & kField) | 0x64006400u;
+        r[j] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, pat) + off);
+    }
+    return r;
+}
+// Where the codes of group `idx` (8 codes) lie in a packed row: byte offsets of the dwords that hold the field and the
+// field's bit position in the first.  A 3-bit group is 24 bits at byte 3 idx; where the field ends inside the first
+// dword that one is read twice, so nothing beyond the row is touched.
+struct CodeAt {
+    uint32_t off0, off1, sh;
+};
+template <int BITS>
+__device__ __forceinline__ CodeAt code_at(int idx) {
+    if constexpr (BITS == 4) return CodeAt{(uint32_t)idx * 4u, 0u, 0u};
+    const uint32_t byte = 3u * (uint32_t)idx, sh = (byte & 3u) * 8u;
+    return CodeAt{byte & ~3u, (byte & ~3u) + (sh >= 16u ? 4u : 0u), sh};
+}
+
 // Squared quantization error of one rotated row for the clip ratios [k0, k1) (sections 2.1, 3.1):
 // t = y / Delta_k, r = clamp(round(t)), e = y - r Delta_k, sum e^2 - five vector-ALU operations per
 // value and candidate, four candidates at a time (independent chains, interleaved reductions).

@@ -1,0 +1,424 @@
+// Workgroup block kernel: bf16 rows of order n = pb * 128 with a +-1 block of order
+// 32 < pb <= 256 along the strided axis (H_n = B (x) H_128, B = H_p (x) H_{2^(k-7)}; sections
+// 2.3.2, 2.3.3) - e.g. 18944 = 148 * 128 with the order-148 Paley II block; also the Sylvester
+// orders 2^14 and 2^15, which are too long for one wave (B = H_128, H_256).
+//
+// The dense block product Y1[pb x 128] = B * X[pb x 128] is a real contraction (pb adds per
+// output), so it runs on the matrix cores.  NW = ceil(pb / 16) waves share a row, wave w owning
+// the 16 block rows 16 w .. 16 w + 15 on input and on output:
+//   phase 1  the wave loads its block rows (16-byte chunks, 4 per lane), transposes 16-bit
+//            values inside each lane (v_perm_b32) so that consecutive block rows of one column are
+//            adjacent, and writes them to LDS as the data operands of phase 2, one 1 KB block per
+//            matrix-core instruction in lane order (no bank conflicts on either side);
+//   phase 2  the wave computes its 16 output block rows for all 128 columns: 8 column tiles x
+//            KK = ceil(pb / 32) contraction steps of v_mfma_f32_16x16x32_bf16, its KK operand tiles of
+//            B resident in registers, the data operands read from LDS (16 bytes per lane) a few
+//            instructions ahead of their use;
+//   phase 3  128-point transform along the columns: three register stages, four fused DPP
+//            stages, absmax; workgroup absmax through LDS;
+//   phase 4  scale, round/clamp, pack; b = 4 stores dwords, b = 3 assembles the row's bytes in LDS
+//            and all waves copy them out in 16-byte units.
+// Column tile nt holds columns {8 c + nt}, so a lane ends up with 8 consecutive columns of 4
+// block rows.  One wave per 16 block rows keeps a wave near 100 VGPRs, so two workgroups share a
+// CU.  A workgroup loops over rows; barriers order the LDS reuse.
+//
+// Short Sylvester factors (CB < 4): n = p * 2^k with k = CB + 3 = 5 or 6 has block rows of only 32
+// or 64 columns, so RPW = 128 / 2^k consecutive rows of X are laid side by side and taken in one
+// pass: column group c = (row of the pass, 8-column chunk of that row).  The block product treats
+// the 128 columns alike; the column transform then runs over CB lane bits only, and absmax, scale
+// and the output rows are per row of the pass.  Here the block is H_p itself, of any order
+// 4 <= p <= 256.
+#pragma once
+#include "wave_common.h"
+
+namespace rq {
+namespace {
+
+// LDS operand buffer: for every (column tile nt, contraction step kk) one 1 KB block holding the data
+// operand of that matrix-core instruction in lane order - lane (g, c) finds the 8 block rows
+// 32 kk + 8 g .. + 7 of column (c, nt) at byte lane * 16 of the block.  A read instruction thus takes
+// 1 KB of consecutive bytes and a phase-1 write instruction (8 bytes per lane: 4 block rows) 512
+// consecutive bytes: neither meets a bank conflict, with no swizzle and no padding.  (Measured with a
+// read-only probe on this chip: 16-byte reads in lane order move 488 bytes per ns and CU, a layout that
+// gives the 16 lanes of a DPP row 16 different 16-byte slots of a 256-byte window in scattered order only
+// 375.)
+template <int KK>
+constexpr size_t wg_ops_bytes() { return (size_t)8 * KK * 1024; }
+
+template <int KK>
+constexpr size_t wg_lds_bytes() { return wg_ops_bytes<KK>() + (size_t)KK * 32 * 48; }
+
+// Register budget, as waves per SIMD (512 VGPRs per SIMD lane).  The hardware deals the waves of
+// successive workgroups round robin over the four SIMDs, so a CU holds 4 x this many waves:
+//   KK <= 3, KK == 5  6 (80 VGPRs): several small workgroups per CU, or two of 9 - 10 waves (3 of
+//            which may land on one SIMD, so 96 registers would often leave room for one only);
+//   KK == 4, KK >= 6   4 (128): two workgroups of up to 8 waves, or one of up to 16.
+// At 128 registers there is room for the next pass's 16 load registers, so its loads are issued one
+// pass ahead (right after the barrier that ends phase 1) and their latency is covered by phases
+// 2 - 4.  At 80 registers the same prefetch spills, and spill reloads wait on the same counter as the
+// loads: measured slower.  (Touching one byte per 128 of the next row a pass ahead, to bring it into
+// the L2 cache, measured no better than the plain loads either.)
+template <int KK>
+constexpr int wg_waves_per_simd() { return (KK <= 3 || KK == 5) ? 6 : 4; }
+
+// What the kernel does with the rotated row (phase 4), and the arguments that takes beyond WaveArgs:
+//   kWgQuantize  codes and scale of rq_rotate_quantize;
+//   kWgError     squared quantization error per clip ratio (rq_quant_error);
+//   kWgRotate    the values themselves (rq_rotate; rq_dequantize_rotate, whose rows come from packed codes).
+enum WgSink { kWgQuantize, kWgError, kWgRotate };
+struct WgNone {};
+struct QeArgs {
+    ClipList clips;
+    int n_clips;
+    double* partial;      // [rows][n_clips]
+};
+struct WgRotArgs {
+    void* Y;
+    int d_out;
+    int64_t ld_out;
+    float inv;            // 1 / sqrt(n)
+    int out;              // 0 bf16, 1 fp32, 2 fp16
+};
+template <int SINK>
+using WgArgs = std::conditional_t<SINK == kWgError, QeArgs, std::conditional_t<SINK == kWgRotate, WgRotArgs, WgNone>>;
+
+// DPP row, 8-column chunk and row of the pass of a lane, as values the compiler does not keep across the phases.
+template <int CB>
+__device__ __forceinline__ void wg_lane(int lane, int& g, int& cl, int& rsub) {
+    asm volatile("" : "+v"(lane));
+    const int cphys = lane & 15, c = (cphys & 4) ? (cphys ^ 3) : cphys;
+    g = lane >> 4;
+    cl = CB == 4 ? c : c & ((1 << CB) - 1);
+    rsub = CB == 4 ? 0 : c >> CB;
+}
+
+// SRC: 0 = 16-bit rows of X, 3 / 4 = packed signed codes of that width (kWgRotate only): the lane's eight codes of
+// a block row become fp16 integers (codes_f16), the matrix cores contract them exactly, and the
+// row's scale multiplies once at the end.
+template <int KK, int BITS, bool FULL, int SINK, int CB = 4, bool F16 = false, int SRC = 0>
+__global__ __launch_bounds__(128 * KK) __attribute__((amdgpu_waves_per_eu(wg_waves_per_simd<KK>())))
+void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
+    static_assert(CB >= 2 && CB <= 4 && (CB == 4 || !FULL), "unsupported shape");
+    static_assert(SRC == 0 || (SINK == kWgRotate && F16 && !FULL), "packed codes: rotation only, fp16 operands");
+    constexpr bool QE = SINK == kWgError;
+    constexpr int RPW = 16 >> CB;                        // rows of X per pass
+    constexpr int SEG = 8 << CB;                         // columns of one block row (2^k)
+    constexpr bool PF = wg_waves_per_simd<KK>() == 4;    // loads run one pass ahead
+    __shared__ float esum[QE ? 16 : 1][QE ? RPW : 1][QE ? RQ_MAX_CLIPS : 1];   // [wave][row of the pass][clip]
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
+    uint8_t* const ops = lds_raw;                        // [column tile][contraction step] x 1 KB, see wg_ops_bytes
+    uint8_t* const stage = lds_raw + wg_ops_bytes<KK>(); // packed codes of the row (b = 3); fp32 results, 2 KB a wave
+    __shared__ float wmax[16 * RPW];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nw = blockDim.x >> 6;                      // ceil(pb / 16)
+    const int g = lane >> 4, cphys = lane & 15;
+    const int c = (cphys & 4) ? (cphys ^ 3) : cphys;    // logical column group (8 columns)
+    const int rsub = CB == 4 ? 0 : c >> CB;              // row of the pass
+    const int cl = CB == 4 ? c : c & ((1 << CB) - 1);    // 8-column chunk inside that row
+
+    u32x4 A[KK];
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) A[kk] = a.tiles[(wave * KK + kk) * 64 + lane];
+    const float c1h = (float)a.c1, c1l = (float)(a.c1 - (double)c1h);
+    // CB < 4: the first lane stage is the plain one, the fused ones start at the second bit
+    const float flip = (__builtin_popcount(CB == 4 ? c : cl >> 1) & 1) ? -1.0f : 1.0f;
+    const uint32_t sg0 = (c & 1) ? 0x80000000u : 0u;
+
+    // phase-1 geometry: lane (g, c) loads block rows 16 wave + 4 g + t, t = 0..3, at constant
+    // strides from one offset.  A group of four at or beyond pb (a multiple of 4) meets zero columns
+    // of B: any in-bounds data will do, and it reads the last four real rows.
+    const int r0 = 16 * wave + 4 * g;
+    const int eoff0 = (r0 < pb ? r0 : pb - 4) * SEG + cl * 8;
+    // phase-1 writes: the lane's block rows 16 wave + 4 g .. + 3 are one 8-byte half of the unit that
+    // reader lane (2 (wave & 1) + g / 2, c) takes in contraction step wave / 2
+    uint8_t* const wr0 = ops + ((((wave >> 1) * 4 + 2 * (wave & 1) + (g >> 1)) * 16 + cphys) * 16 + (g & 1) * 8);
+    const uint8_t* const rd0 = ops + lane * 16;
+
+    // Units for block rows at or beyond 16 nw are never written by phase 1 but are read by the last
+    // contraction step (against zero columns of B): clear the buffer once so they hold zeros.
+    for (int i = threadIdx.x; i < 8 * KK * 64; i += blockDim.x)
+        reinterpret_cast<u32x4*>(ops)[i] = u32x4{0u, 0u, 0u, 0u};
+    __syncthreads();
+
+    u32x4 R[4];
+    [[maybe_unused]] float rscale = 1.0f;               // packed codes: the row's scale
+    auto load_row = [&](int64_t row) {
+        const uint16_t* xr = a.X + row * a.ld;
+        if constexpr (CB == 4) {
+            const RowView xv = row_view(xr, a.d);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                R[t] = FULL ? load16(xr + eoff0 + t * SEG) : load_chunk(xv, eoff0 + t * SEG);
+        } else {
+            // the lanes of a wave read different rows: per-lane addresses, whole chunks (d % 8 == 0)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                R[t] = eoff0 + t * SEG < a.d ? load16(xr + eoff0 + t * SEG) : u32x4{0u, 0u, 0u, 0u};
+        }
+    };
+    // Rotation only: the rows of a pass as one buffer resource (rows beyond the end lie outside it and read as
+    // zero) with 32-bit lane offsets, which leaves the registers to the transform.
+    auto load_rows = [&](int64_t row0) {
+        const int64_t left = a.rows - row0;
+        const int live_rows = left < RPW ? (int)left : RPW;
+        int gq, cq, rq;
+        wg_lane<CB>(lane, gq, cq, rq);
+        const int b0 = 16 * wave + 4 * gq, br = b0 < pb ? b0 : pb - 4;
+        if constexpr (SRC != 0) {
+            const int row_bytes = (SEG * SRC / 8) * pb;
+            const auto rs = __builtin_amdgcn_make_buffer_rsrc(a.codes + row0 * (row_bytes / 4), 0, live_rows * row_bytes, 0x00020000);
+            const CodeAt at = code_at<SRC>((br << CB) + cq);
+            const uint32_t base = (uint32_t)(rq * row_bytes);
+            constexpr int STEP = SEG * SRC / 8;              // bytes of a block row
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                R[t][0] = __builtin_amdgcn_raw_buffer_load_b32(rs, base + at.off0 + t * STEP, 0, 2);
+                if constexpr (SRC == 3) R[t][1] = __builtin_amdgcn_raw_buffer_load_b32(rs, base + at.off1 + t * STEP, 0, 2);
+            }
+            const auto ss = __builtin_amdgcn_make_buffer_rsrc(a.scales + row0, 0, live_rows * 4, 0x00020000);
+            R[0][2] = __builtin_amdgcn_raw_buffer_load_b32(ss, rq * 4, 0, 0);
+        } else {
+            const int bytes = (int)(((live_rows - 1) * a.ld + a.d) * 2);
+            const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.X) + row0 * a.ld, 0, bytes, 0x00020000);
+            const int base = rq * (int)a.ld;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int e = (br + t) * SEG + cq * 8;
+                const uint32_t off = CB == 4 || e < a.d ? (uint32_t)(base + e) * 2u : 0x80000000u;
+                R[t] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 2));
+            }
+        }
+    };
+    const int64_t n_pass = (a.rows + RPW - 1) / RPW;
+    // CB == 4: one row per pass, uniform over the workgroup; otherwise the lane's own row, the
+    // last row standing in (loads only) for rows beyond the end
+    auto load_pass = [&](int64_t ps) {
+        if constexpr (SINK == kWgRotate) return load_rows(ps * RPW);
+        const int64_t r = ps * RPW + rsub;
+        load_row(CB == 4 || r < a.rows ? r : a.rows - 1);
+    };
+    if (PF && (int64_t)blockIdx.x < n_pass) load_pass(blockIdx.x);
+    for (int64_t pass = blockIdx.x; pass < n_pass; pass += gridDim.x) {
+        const int64_t row = pass * RPW + rsub;
+        const bool live = CB == 4 || row < a.rows;
+        if (!PF) load_pass(pass);
+        if constexpr (SRC != 0) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                if (t == 0) rscale = __uint_as_float(R[0][2]);
+                // (a block row is a whole number of dwords: the field's bit position is that of the chunk in it)
+                R[t] = codes_f16<SRC>(SRC == 4 ? R[t][0] : __builtin_amdgcn_alignbit(R[t][1], R[t][0], (3u * cl & 3u) * 8u));
+            }
+        }
+        // ---- phase 1
+#pragma unroll
+        for (int ic = 0; ic < 8; ++ic) {
+            const uint32_t sel = (ic & 1) ? 0x07060302u : 0x05040100u;
+            uint2 v;
+            v.x = __builtin_amdgcn_perm(R[1][ic >> 1], R[0][ic >> 1], sel);
+            v.y = __builtin_amdgcn_perm(R[3][ic >> 1], R[2][ic >> 1], sel);
+            *reinterpret_cast<uint2*>(wr0 + ic * (KK * 1024)) = v;
+        }
+        __syncthreads();
+        if (PF && pass + gridDim.x < n_pass) load_pass(pass + gridDim.x);
+        // ---- phase 2
+        f32x4 acc[8];
+#pragma unroll
+        for (int nt = 0; nt < 8; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        {
+            // The 8 KK operand reads run DEPTH ahead of the matrix-core instructions that use them, in a ring
+            // of DEPTH register quads; the contraction step is the outer loop, so that consecutive
+            // instructions go to different accumulators and none waits for its predecessor's result.
+            // (3 where the 80-register kernels have room for it, 2 in their padded-row and quant_error forms)
+            constexpr int DEPTH = KK >= 6 ? 4 : (FULL && !QE) ? 3 : 2, ITEMS = 8 * KK;
+            auto read_item = [&](int i) {                // item i = (contraction step i / 8, column tile i % 8)
+                return *reinterpret_cast<const u32x4*>(rd0 + ((i % 8) * KK + i / 8) * 1024);
+            };
+            u32x4 ring[DEPTH];
+#pragma unroll
+            for (int i = 0; i < DEPTH; ++i) ring[i] = read_item(i);
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i) {
+                __builtin_amdgcn_sched_barrier(0);
+                acc[i % 8] = mfma_pm1<F16>(A[i / 8], ring[i % DEPTH], acc[i % 8]);
+                if (i + DEPTH < ITEMS) ring[i % DEPTH] = read_item(i + DEPTH);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // ---- phase 3
+#pragma unroll
+        for (int s = 1; s < 8; s <<= 1)
+#pragma unroll
+            for (int nt = 0; nt < 8; ++nt)
+                if (!(nt & s)) {
+                    const f32x4 u = acc[nt], v = acc[nt | s];
+                    acc[nt] = u + v;
+                    acc[nt | s] = u - v;
+                }
+        [[maybe_unused]] float m = 0.0f;
+        // rotation only: nothing else of this pass needs the workgroup, the operand buffer is free from here on
+        if constexpr (SINK == kWgRotate) __syncthreads();
+        // the stage signs are rebuilt from the column group every pass (two instructions each) rather
+        // than held in registers across phases 1 and 2
+        int cs = c;
+        asm volatile("" : "+v"(cs));
+        float sf[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) sf[b] = __uint_as_float(0x3F800000u | ((uint32_t)(cs >> b) << 31));
+#pragma unroll
+        for (int nt = 0; nt < 8; ++nt) {
+            f32x4 v = acc[nt];
+            if constexpr (CB == 4) {
+                lane_stages_fused(v, sf[0], sf[1], sf[2], sf[3]);
+            } else {
+                lane_stage<kDppXor1>(v, sg0);
+                lane_stages_tail<CB>(v, sf);
+            }
+            acc[nt] = v;
+            if constexpr (SINK != kWgRotate) m = absmax4(m, v);
+        }
+        if constexpr (SINK == kWgRotate) {
+            // the pass's rows of Y as one buffer resource; what lies beyond it (rows past the end, and with one
+            // row per pass the columns from d_out on) is not stored
+            int gq, cq, rq;
+            wg_lane<CB>(lane, gq, cq, rq);
+            const float k = ((__builtin_popcount(CB == 4 ? cq : cq >> 1) & 1) ? -sa.inv : sa.inv) * rscale;
+            const int64_t row0 = pass * RPW, left = a.rows - row0;
+            const int live_rows = left < RPW ? (int)left : RPW;
+            const int esz = sa.out == 1 ? 4 : 2;
+            const auto ys = __builtin_amdgcn_make_buffer_rsrc(static_cast<char*>(sa.Y) + row0 * sa.ld_out * esz, 0,
+                                                              (int)(((live_rows - 1) * sa.ld_out + sa.d_out) * esz), 0x00020000);
+#pragma unroll
+            for (int ip = 0; ip < 4; ++ip) {
+                const int ao0 = 16 * wave + 4 * ip;                      // first of the four output block rows of this register
+                float o[8];
+#pragma unroll
+                for (int nt = 0; nt < 8; ++nt) o[nt] = acc[nt][ip];
+                if (sa.out == 1) {
+                    // block rows ao0 .. ao0 + 3 of each row of the pass are 4 SEG consecutive values
+                    store_block_f32(reinterpret_cast<float*>(stage) + wave * 512, ((rq * 4 + gq) << CB) + cq, lane, o, k, 0.0f,
+                                    [&](int e, const u32x4& unit) {
+                        const int rs = CB == 4 ? 0 : e / (4 * SEG), col = ao0 * SEG + (CB == 4 ? e : e % (4 * SEG));
+                        const uint32_t off = CB == 4 || col < sa.d_out ? (uint32_t)(rs * (int)sa.ld_out + col) * 4u : 0x80000000u;
+                        __builtin_amdgcn_raw_buffer_store_b128(unit,
+                                                               ys, off, 0, 2);
+                    });
+                } else {
+#pragma unroll
+                    for (int nt = 0; nt < 8; ++nt) o[nt] *= k;
+                    const u32x4 unit = sa.out == 0 ? pack16<0>(o) : pack16<2>(o);
+                    const int col = (ao0 + gq) * SEG + cq * 8;
+                    const uint32_t off = CB == 4 || col < sa.d_out ? (uint32_t)(rq * (int)sa.ld_out + col) * 2u : 0x80000000u;
+                    __builtin_amdgcn_raw_buffer_store_b128(unit,
+                                                           ys, off, 0, 2);
+                }
+            }
+            continue;
+        } else {
+        m = wave_absmax<CB>(m);                          // over the lanes that share the row
+        if (g == 0 && cl == 0) wmax[wave * RPW + rsub] = m;
+        __syncthreads();    // also: every wave is done reading this row's operands from LDS
+        m = wmax[rsub];
+        for (int w = 1; w < nw; ++w) m = fmaxf(m, wmax[w * RPW + rsub]);
+        // ---- phase 4
+        if constexpr (QE) {
+            float v[32];
+#pragma unroll
+            for (int nt = 0; nt < 8; ++nt)
+#pragma unroll
+                for (int ip = 0; ip < 4; ++ip) v[nt * 4 + ip] = acc[nt][ip];
+            // the sums run over the lanes that share a row of the pass: CB lane bits and the four DPP rows
+            qe_candidates<32, BITS, CB>(v, m, flip, sa.clips, 0, sa.n_clips, [&](int k, float e2) {
+                if (g == 0 && cl == 0) esum[wave][rsub][k] = e2;
+            });
+            __syncthreads();   // the next row writes esum only after two more barriers
+            for (int i = threadIdx.x; i < RPW * sa.n_clips; i += blockDim.x) {
+                const int rs = i / sa.n_clips, k = i - rs * sa.n_clips;
+                const int64_t orow = pass * RPW + rs;
+                if (orow < a.rows) {
+                    float t = 0.0f;
+                    for (int w = 0; w < nw; ++w) t += esum[w][rs][k];
+                    const double nn = (double)pb * (double)SEG;
+                    sa.partial[orow * sa.n_clips + k] = (double)t / (nn * nn);
+                }
+            }
+            continue;
+        }
+        // (2^b - 1) / (clip m) from a float pair of the constant: reciprocal, Newton step, correction
+        const float s = m > 0.0f ? flip * div_pair(c1h, c1l, m) : 0.0f;
+        uint32_t* out = a.codes + row * (int64_t)(SEG * BITS / 32) * pb;   // used by live lanes only
+#pragma unroll
+        for (int ip = 0; ip < 4; ++ip) {
+            const int ao = 16 * wave + 4 * ip + g;      // output block row of this register
+            const uint32_t w = Quant<BITS>::pack8(acc[0][ip], acc[1][ip], acc[2][ip], acc[3][ip],
+                                                  acc[4][ip], acc[5][ip], acc[6][ip], acc[7][ip], s);
+            if constexpr (CB == 4) {
+                const int word = ao * 16 + c;
+                if (BITS == 4) {
+                    if (ao < pb) store_codes(out + word, w);
+                } else {
+                    stage24(stage, word, w);            // block rows >= pb land beyond the copied part
+                }
+            } else if (ao < pb) {
+                // the pass's rows are staged one after the other, each pb * 2^CB groups of 8 codes
+                if (BITS == 4) {
+                    if (live) store_codes(out + (ao << CB) + cl, w);
+                } else {
+                    stage24(stage, ((rsub * pb + ao) << CB) + cl, w);
+                }
+            }
+        }
+        if (BITS == 3 && CB < 4) {
+            // as below; a wave's 16 block rows are 3 * 2^CB 16-byte units in each row of the pass
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            constexpr int UPR = 3 << CB;
+            const int rs = lane / UPR;
+            const int unit = UPR * wave + lane % UPR;   // the row has pb * UPR / 16 units
+            const int64_t orow = pass * RPW + rs;
+            if (lane < 48 && unit * 16 < pb * UPR && orow < a.rows)
+                __builtin_nontemporal_store(
+                    *reinterpret_cast<const u32x4*>(stage + (size_t)rs * pb * UPR + unit * 16),
+                    reinterpret_cast<u32x4*>(a.codes + orow * (int64_t)(SEG * 3 / 32) * pb) + unit);
+        }
+        if (BITS == 3 && CB == 4) {
+            // a wave's 16 block rows are 768 contiguous bytes of the packed row, written and read
+            // back by the same wave: no workgroup barrier, only the wave's own LDS ordering
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const int unit = 48 * wave + lane;          // 16-byte units; the row has 3 pb of them
+            if (lane < 48 && unit < 3 * pb)
+                __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(stage + unit * 16),
+                                            reinterpret_cast<u32x4*>(out) + unit);
+        }
+        if (wave == 0 && g == 0 && cl == 0 && live) a.scales[row] = (float)(a.c2 * (double)m);
+        }
+    }
+}
+
+
+template <int SINK>
+using WgKernel = void (*)(WaveArgs, int, WgArgs<SINK>);
+
+// One launch: as many workgroups as fit the chip (registers, LDS), each looping over rows.
+template <int KK, int SINK>
+int wg_launch(const rq_hadamard* h, WgKernel<SINK> fn, const WaveArgs& a, int pb, int cb, size_t lds, const WgArgs<SINK>& sa,
+              hipStream_t s) {
+    const int nw = (pb + 15) / 16;
+    int per_cu = (int)((size_t)h->max_lds / (lds + 128));
+    const int by_waves = 4 * wg_waves_per_simd<KK>() / nw;   // see the register budget note at the kernel
+    if (per_cu > by_waves) per_cu = by_waves;
+    if (per_cu < 1) per_cu = 1;
+    const int64_t cap = (int64_t)h->num_cu * per_cu;
+    const int rpw = 16 >> cb;
+    const int64_t passes = (a.rows + rpw - 1) / rpw;
+    const unsigned grid = (unsigned)(passes < cap ? passes : cap);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(64 * nw), lds, s, a, pb, sa);
+    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+}
+
+}  // namespace
+}  // namespace rq

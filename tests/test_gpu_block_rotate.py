@@ -1,0 +1,74 @@
+"""GPU parity of rq_rotate and rq_dequantize_rotate on the block orders (one-wave and workgroup kernels) against
+the oracle: every number of contraction steps, symmetric and unsymmetric blocks, several rows per pass with a
+ragged end, zero-padded input, narrowed output, every input / output type, both directions."""
+import numpy as np
+import pytest
+
+import parity
+import rotq_oracle as oracle
+from paper_2504_13989_amd import binding, workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+# (order, input width, output width, rows, kernel): blocks x columns 12 x 128, 28 x 128, 20 x 256 (40), 44 x 256 (88),
+# 108 x 128, 148 x 128, 44 x 512 (176), 28 x 1024 (224), H_128 x 128; several rows per pass: 28 x 32, 76 x 64, 140 x 64
+SHAPES = [(1536, 1536, 1536, 3, "wave_block"), (3584, 3584, 3000, 9, "wave_block"), (5120, 5000, 5120, 5, "wg_block"),
+          (11264, 11008, 11008, 5, "wg_block"), (13824, 13824, 13824, 3, "wg_block"), (18944, 18944, 18944, 4, "wg_block"),
+          (22528, 22528, 20000, 3, "wg_block"), (28672, 28672, 28672, 2, "wg_block"), (16384, 16384, 16384, 2, "wg_block"),
+          (896, 896, 896, 9, "wg_block"), (4864, 4800, 4856, 5, "wg_block"), (8960, 8960, 8960, 3, "wg_block")]
+
+
+def _close(got, want, out_dtype, what):
+    amax = np.abs(want).max(axis=1, keepdims=True)
+    # fp32 sums: 1e-5 of the row's maximum; one rounding to the output format on top
+    step = {"f32": 0.0, "bf16": 2.0 ** -8, "f16": 2.0 ** -11}[out_dtype]
+    err = np.abs(got.double().cpu().numpy() - want)
+    assert np.all(err <= 1e-5 * amax + step * np.abs(want) + (6.2e-5 if out_dtype == "f16" else 0.0)), f"{what}: {err.max()}"
+
+
+@pytest.mark.parametrize("n,d,d_out,rows,kernel", SHAPES)
+def test_rotate(n, d, d_out, rows, kernel):
+    import torch
+    types = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
+    rng = np.random.default_rng(n + rows)
+    h = binding.hadamard_build(n)
+    for i, (in_dtype, out_dtype) in enumerate([("bf16", "bf16"), ("f16", "f16"), ("bf16", "f32"), ("f16", "f32")]):
+        xf = rng.standard_normal((rows, d + 8)).astype(np.float32)
+        full = wl.f32_to_bf16_bits(xf) if in_dtype == "bf16" else xf.astype(np.float16)
+        x = np.ascontiguousarray(full[:, :d])
+        for transpose in (False, True):
+            if transpose:
+                xp = np.zeros((rows, n))
+                xp[:, :d] = oracle.as_f64(x)
+                want = oracle.rotate_back(xp, n)
+            else:
+                want = oracle.rotate(x, n)
+            buf = torch.full((rows + 1, d_out + 8), 7.0, dtype=types[out_dtype], device="cuda")
+            binding.rotate(h, parity.to_device(full)[:, :d], transpose=transpose, d_out=d_out, out=buf[:rows, :d_out])
+            torch.cuda.synchronize()
+            assert h.last_kernel == f"{kernel}_rotate"
+            _close(buf[:rows, :d_out], want[:, :d_out], out_dtype, f"n={n} {in_dtype}->{out_dtype} transpose={transpose}")
+            assert bool((buf[:, d_out:] == 7.0).all()) and bool((buf[rows:] == 7.0).all())
+
+
+@pytest.mark.parametrize("b", [3, 4])
+@pytest.mark.parametrize("n,d,d_out,rows,kernel", SHAPES)
+def test_dequantize_rotate(n, d, d_out, rows, kernel, b):
+    import torch
+    types = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
+    rng = np.random.default_rng(n + rows + b)
+    h = binding.hadamard_build(n)
+    q = rng.integers(-(2 ** (b - 1)), 2 ** (b - 1), size=(rows, n))
+    scales = rng.uniform(0.5, 2.0, size=rows).astype(np.float32)
+    packed = torch.from_numpy(oracle.pack_codes(q, b)).cuda()
+    y = oracle.dequantize(q, scales.astype(np.float64))
+    for transpose in (True, False):
+        want = oracle.rotate_back(y, n) if transpose else oracle.rotate(y, n)
+        for out_dtype in ("bf16", "f16", "f32"):
+            buf = torch.full((rows + 1, d_out + 8), 7.0, dtype=types[out_dtype], device="cuda")
+            binding.dequantize_rotate(h, packed, torch.from_numpy(scales).cuda(), b, transpose=transpose, d_out=d_out,
+                                      out=buf[:rows, :d_out])
+            torch.cuda.synchronize()
+            assert h.last_kernel == f"{kernel}_dequant_rotate"
+            _close(buf[:rows, :d_out], want[:, :d_out], out_dtype, f"n={n} b={b} ->{out_dtype} transpose={transpose}")
+            assert bool((buf[:, d_out:] == 7.0).all()) and bool((buf[rows:] == 7.0).all())
