@@ -104,6 +104,7 @@ int rq_hadamard_build(int n, rq_hadamard_t** out) {
                      (f.p == 1 && (f.log2m == 14 || f.log2m == 15));
     const bool blk_short = f.p > 1 && (f.log2m == 5 || f.log2m == 6) && f.p <= 256;   // block rows of 32 / 64
     const bool dense = !sylv && !blk && !blk_short && n <= 4096;
+    if (f.p > 1 && f.log2m >= 5 && f.p <= rq::kMaxPaleyOrder) tables.add(&h->d_signs, rq::f64_block_signs(h->block, f.p));
     // tiles of a block in both 16-bit encodings, and those of its transpose (Paley I blocks are not symmetric)
     auto add_block = [&](const std::vector<int8_t>& bm, int pb, std::vector<uint32_t> (*make)(const std::vector<int8_t>&, int)) {
         const std::vector<uint32_t> tiles = make(bm, pb);
@@ -165,6 +166,7 @@ int rq_hadamard_build(int n, rq_hadamard_t** out) {
     h->d_block = static_cast<int8_t*>(d_block);
     h->device = dev;
     h->generic_ok = rq::generic_prepare(h);
+    h->f64_ok = h->generic_f64_ok && rq::f64_prepare(h);
     // set-up time is when the static scratch array's address on this device is asked for; a failure
     // only makes rq_quant_error_noalloc return RQ_ERR_HIP
     (void)rq::static_scratch(dev);
@@ -250,6 +252,10 @@ int rq_rotate_quantize(const rq_hadamard_t* h, const void* X, int dtype, int64_t
     if (h->variant == 0 && rq::dense_block_supports(h, a)) {
         note(h, "dense_block");
         return rq::dense_block_rotate_quantize(h, a, clip, static_cast<uint32_t*>(codes), scales, s);
+    }
+    if (h->variant == 0 && rq::f64_rows_supports(h, a)) {
+        note(h, "f64_rows");
+        return rq::f64_rotate_quantize(h, a, clip, static_cast<uint32_t*>(codes), scales, s);
     }
     if (!rq::generic_supports(h)) return RQ_ERR_NO_ORDER;
     note(h, "generic_lds");

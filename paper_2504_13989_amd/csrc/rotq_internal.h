@@ -19,6 +19,7 @@ struct rq_hadamard {
     void* d_tiles_f16 = nullptr;     // the same tiles encoded in fp16 (not the dense-block kernel's)
     void* d_tiles_t = nullptr;       // operand tiles of the transposed block (rotations with transpose = 1), bf16
     void* d_tiles_t_f16 = nullptr;   // and fp16; those of the block itself where it is symmetric
+    void* d_signs = nullptr;         // sign masks of the block for the fp64 kernel of fp32 rows
     void* d_tiles2 = nullptr;        // blocks of 33 .. 64: operand tiles of the one-wave kernel (d_tiles holds the
     void* d_tiles2_f16 = nullptr;    // workgroup kernel's), bf16 and fp16
     int max_lds = 0;                 // bytes of LDS one workgroup may use on `device`
@@ -27,6 +28,7 @@ struct rq_hadamard {
     bool dense_ok = false;           // d_tiles holds the whole matrix for the dense-block kernel
     bool generic_ok = false;         // the general LDS kernel can hold a row of this order
     bool generic_f64_ok = false;     // ... and an fp64 copy of it (how fp32 rows are quantized)
+    bool f64_ok = false;             // fp32 rows of this order have the fp64 kernel of their own
     // test / measurement hook (rq_hadamard_set_variant); atomic so that a hot-path call on another
     // thread reads a whole value
     std::atomic<int> variant{0};     // 0 auto, 1 general LDS kernel
@@ -157,6 +159,12 @@ std::vector<uint32_t> dense_block_tiles(const std::vector<int8_t>& hm, int n);
 bool dense_block_supports(const rq_hadamard* h, const RowArgs& a);
 int dense_block_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float clip, uint32_t* codes,
                                 float* scales, hipStream_t s);
+
+// fp32 rows, quantized in fp64: orders p * 2^k with 2^k >= 32.
+std::vector<uint32_t> f64_block_signs(const std::vector<int8_t>& block, int p);
+bool f64_prepare(const rq_hadamard* h);
+bool f64_rows_supports(const rq_hadamard* h, const RowArgs& a);
+int f64_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float clip, uint32_t* codes, float* scales, hipStream_t s);
 
 // Workgroup block kernel: bf16 or fp16 rows, n = pb * 128 with 32 < pb <= 256 (e.g. 18944 = 148 * 128),
 // or n = p * 64 / p * 32 with 4 <= p <= 256 (several rows per pass); quant_error: the former, bf16.
