@@ -924,8 +924,8 @@ __global__ __launch_bounds__(64) void k_wave_short_qe_asym(WaveArgs a, ClipList 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Rotation-free quantizer (section 2.1 with the clip ratio of section 3.1 on the row itself): one
-// wave per bf16 row of d <= 512 T values, the row held in registers between the absmax pass and
+// Rotation-free quantizer (section 2.1 with the clip ratio of section 3.1 on the row itself): W waves
+// per 16-bit row of d <= 512 T W values, the row held in registers between the absmax pass and
 // the quantization pass.  Un-rotated bf16 values sit on a coarse grid, so x / Delta lands on or
 // next to a rounding tie far more often than rotated values do; every code whose fp32 residual
 // is within 2e-5 of a tie is therefore retaken with the exact fp64 quotient.
@@ -952,9 +952,11 @@ struct PlainArgs {
     bool f16;
 };
 
-template <int T, int BITS, bool F16 = false>
-__global__ __launch_bounds__(64) void k_plain_wave(PlainArgs a) {
-    const int lane = threadIdx.x;
+template <int T, int W, int BITS, bool F16>
+__global__ __launch_bounds__(64 * W) void k_plain_wave(PlainArgs a) {
+    __shared__ float wmax[W];
+    const int lane = threadIdx.x & 63;
+    const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nchunks = a.d >> 3;
     const int row_dwords = a.d * BITS / 32;
     constexpr double kLvl = (double)((1 << BITS) - 1);
@@ -964,7 +966,7 @@ __global__ __launch_bounds__(64) void k_plain_wave(PlainArgs a) {
         u32x4 raw[T];
 #pragma unroll
         for (int t = 0; t < T; ++t) {
-            raw[t] = load_chunk(xv, (t * 64 + lane) * 8);
+            raw[t] = load_chunk(xv, ((t * W + wave) * 64 + lane) * 8);
         }
         float m = 0.0f;
 #pragma unroll
@@ -976,12 +978,19 @@ __global__ __launch_bounds__(64) void k_plain_wave(PlainArgs a) {
                 m = __builtin_fmaxf(m, __builtin_fabsf(half_hi<F16>(w)));
             }
         m = wave_absmax<4>(m);
+        if constexpr (W > 1) {
+            if (lane == 0) wmax[wave] = m;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < W; ++w) m = __builtin_fmaxf(m, wmax[w]);
+            __syncthreads();                             // before the next row's
+        }
         const double delta = a.clip * (double)m / kLvl;
         const float s = m > 0.0f ? (float)(kLvl / (a.clip * (double)m)) : 0.0f;
         uint32_t* out = a.codes + row * (int64_t)row_dwords;
 #pragma unroll
         for (int t = 0; t < T; ++t) {
-            const int idx = t * 64 + lane;
+            const int idx = (t * W + wave) * 64 + lane;
             float x[8];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -1009,19 +1018,20 @@ __global__ __launch_bounds__(64) void k_plain_wave(PlainArgs a) {
                 if (idx < nchunks && qpos < 3) store_codes(out + (idx >> 2) * 3 + qpos, dw);
             }
         }
-        if (lane == 0) a.scales[row] = (float)delta;
+        if (threadIdx.x == 0) a.scales[row] = (float)delta;
     }
 }
 
-template <int T>
+template <int T, int W = 1>
 int launch_plain(const PlainArgs& a, int bits, hipStream_t s) {
     const int64_t cap = 1 << 24;
-    const unsigned grid = (unsigned)(a.rows < cap ? a.rows : cap);
+    const dim3 grid((unsigned)(a.rows < cap ? a.rows : cap)), block(64 * W);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, a); };
     if (a.f16) {
-        if (bits == 4) hipLaunchKernelGGL((k_plain_wave<T, 4, true>), dim3(grid), dim3(64), 0, s, a);
-        else hipLaunchKernelGGL((k_plain_wave<T, 3, true>), dim3(grid), dim3(64), 0, s, a);
-    } else if (bits == 4) hipLaunchKernelGGL((k_plain_wave<T, 4>), dim3(grid), dim3(64), 0, s, a);
-    else hipLaunchKernelGGL((k_plain_wave<T, 3>), dim3(grid), dim3(64), 0, s, a);
+        if (bits == 4) go(k_plain_wave<T, W, 4, true>); else go(k_plain_wave<T, W, 3, true>);
+    } else {
+        if (bits == 4) go(k_plain_wave<T, W, 4, false>); else go(k_plain_wave<T, W, 3, false>);
+    }
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }
 
@@ -1501,13 +1511,19 @@ int plain_wave_quantize(const void* X, int dtype, int64_t rows, int d, int64_t l
                         uint32_t* codes, float* scales, hipStream_t s) {
     const PlainArgs a{static_cast<const uint16_t*>(X), rows, d, ld, codes, scales, (double)clip, dtype == RQ_F16};
     const int t = (d + 511) / 512;
+    // Waves per row.  One wave with a row of more than 4096 values in its registers leaves two waves per SIMD, so
+    // those rows are split over 4 waves, and over 8 beyond 8192 values or where there are few of them (4096 x 18944:
+    // 97 -> 34 us, 4096 x 8192: 21.0 -> 14.7, with 8 waves 16.2).  Shorter rows are split while the launch has fewer
+    // waves than the chip wants (2048 x 4096: 6.5 -> 5.6 us, 4096 x 4096: 8.4 -> 9.2; 512 x 896: 3.29 -> 3.25,
+    // 1024 x 896: 3.64 -> 3.76).
+    if (t > 16) return t <= 24 ? launch_plain<3, 8>(a, bits, s) : launch_plain<5, 8>(a, bits, s);
+    if (t > 8) return rows <= 512 ? launch_plain<2, 8>(a, bits, s) : launch_plain<4, 4>(a, bits, s);
+    if (t > 2 && rows <= 2048) return t <= 4 ? launch_plain<1, 4>(a, bits, s) : launch_plain<2, 4>(a, bits, s);
+    if (t == 2 && rows <= 512) return launch_plain<1, 4>(a, bits, s);
     if (t <= 1) return launch_plain<1>(a, bits, s);
     if (t <= 2) return launch_plain<2>(a, bits, s);
     if (t <= 4) return launch_plain<4>(a, bits, s);
-    if (t <= 8) return launch_plain<8>(a, bits, s);
-    if (t <= 16) return launch_plain<16>(a, bits, s);
-    if (t <= 24) return launch_plain<24>(a, bits, s);
-    return launch_plain<40>(a, bits, s);
+    return launch_plain<8>(a, bits, s);
 }
 
 bool wave_asym_supports(const rq_hadamard* h, const RowArgs& a) {
