@@ -272,9 +272,9 @@ int launch_dense(const WaveArgs& a, int n, int bits, hipStream_t s) {
     const size_t rows_lds = (size_t)16 * NT * n * bits / 8, stage_lds = (size_t)2 * 16 * NT * (64 * kDenseGroup + 16);
     const size_t lds = rows_lds > stage_lds ? rows_lds : stage_lds;
     if (bits == 4)
-        hipLaunchKernelGGL((k_dense_block<MTW, NT, 4>), dim3((unsigned)groups), dim3(64 * kDenseWaves), lds, s, a, n);
+        launch_kernel((k_dense_block<MTW, NT, 4>), dim3((unsigned)groups), dim3(64 * kDenseWaves), lds, s, a, n);
     else
-        hipLaunchKernelGGL((k_dense_block<MTW, NT, 3>), dim3((unsigned)groups), dim3(64 * kDenseWaves), lds, s, a, n);
+        launch_kernel((k_dense_block<MTW, NT, 3>), dim3((unsigned)groups), dim3(64 * kDenseWaves), lds, s, a, n);
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }
 

@@ -97,11 +97,11 @@ int dequantize_rows(const uint32_t* codes, const float* scales, const float* min
     const bool y16 = (reinterpret_cast<uintptr_t>(Y) & 15) == 0;     // rows are n * 4 bytes, n a multiple of 8
     const uint8_t* c = reinterpret_cast<const uint8_t*>(codes);
     if (mins) {
-        if (bits == 4) hipLaunchKernelGGL((k_dequantize<4, true>), grid, dim3(kThreads), 0, s, c, scales, mins, rows, n, magic, rows_per_group, Y, y16);
-        else hipLaunchKernelGGL((k_dequantize<3, true>), grid, dim3(kThreads), 0, s, c, scales, mins, rows, n, magic, rows_per_group, Y, y16);
+        if (bits == 4) launch_kernel((k_dequantize<4, true>), grid, dim3(kThreads), 0, s, c, scales, mins, rows, n, magic, rows_per_group, Y, y16);
+        else launch_kernel((k_dequantize<3, true>), grid, dim3(kThreads), 0, s, c, scales, mins, rows, n, magic, rows_per_group, Y, y16);
     } else {
-        if (bits == 4) hipLaunchKernelGGL((k_dequantize<4, false>), grid, dim3(kThreads), 0, s, c, scales, mins, rows, n, magic, rows_per_group, Y, y16);
-        else hipLaunchKernelGGL((k_dequantize<3, false>), grid, dim3(kThreads), 0, s, c, scales, mins, rows, n, magic, rows_per_group, Y, y16);
+        if (bits == 4) launch_kernel((k_dequantize<4, false>), grid, dim3(kThreads), 0, s, c, scales, mins, rows, n, magic, rows_per_group, Y, y16);
+        else launch_kernel((k_dequantize<3, false>), grid, dim3(kThreads), 0, s, c, scales, mins, rows, n, magic, rows_per_group, Y, y16);
     }
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }

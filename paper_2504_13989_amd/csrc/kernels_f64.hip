@@ -281,7 +281,7 @@ int f64_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float clip, uint
     const F64Args f{static_cast<const float*>(a.X), a.rows, a.d, a.ld, a.p, static_cast<const uint32_t*>(h->d_signs), codes,
                     scales, (double)clip,
                     1.0 / (std::sqrt((double)a.n) * (double)((1 << a.bits) - 1))};
-    hipLaunchKernelGGL(pick(a.log2m, a.p > 1, a.bits), dim3((unsigned)groups), dim3(sh.threads), sh.lds, s, f);
+    launch_kernel(pick(a.log2m, a.p > 1, a.bits), dim3((unsigned)groups), dim3(sh.threads), sh.lds, s, f);
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }
 

@@ -491,10 +491,10 @@ int generic_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float clip, 
     if (a.rows > 0x7fffffffLL) return RQ_ERR_ARG;
     if (a.dtype == RQ_F32) {
         if (!h->generic_f64_ok) return RQ_ERR_NO_ORDER;
-        hipLaunchKernelGGL(k_generic_rotate_quantize<double>, dim3((unsigned)a.rows), dim3(kThreads), 2 * bytes,
+        launch_kernel(k_generic_rotate_quantize<double>, dim3((unsigned)a.rows), dim3(kThreads), 2 * bytes,
                            s, a, clip, codes, scales);
     } else {
-        hipLaunchKernelGGL(k_generic_rotate_quantize<float>, dim3((unsigned)a.rows), dim3(kThreads), bytes, s, a,
+        launch_kernel(k_generic_rotate_quantize<float>, dim3((unsigned)a.rows), dim3(kThreads), bytes, s, a,
                            clip, codes, scales);
     }
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
@@ -506,10 +506,10 @@ int generic_rotate_quantize_asym(const rq_hadamard* h, const RowArgs& a, float c
     if (a.rows > 0x7fffffffLL || a.n % 128 != 0) return RQ_ERR_ARG;
     if (a.dtype == RQ_F32) {
         if (!h->generic_f64_ok) return RQ_ERR_NO_ORDER;
-        hipLaunchKernelGGL(k_generic_rotate_quantize_asym<double>, dim3((unsigned)a.rows), dim3(kThreads),
+        launch_kernel(k_generic_rotate_quantize_asym<double>, dim3((unsigned)a.rows), dim3(kThreads),
                            2 * bytes, s, a, clip, codes, scales, mins);
     } else {
-        hipLaunchKernelGGL(k_generic_rotate_quantize_asym<float>, dim3((unsigned)a.rows), dim3(kThreads), bytes,
+        launch_kernel(k_generic_rotate_quantize_asym<float>, dim3((unsigned)a.rows), dim3(kThreads), bytes,
                            s, a, clip, codes, scales, mins);
     }
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
@@ -518,7 +518,7 @@ int generic_rotate_quantize_asym(const rq_hadamard* h, const RowArgs& a, float c
 int generic_rotate(const rq_hadamard* h, const RowArgs& a, int transpose, const OutArgs& o,
                    hipStream_t s) {
     if (a.rows > 0x7fffffffLL) return RQ_ERR_ARG;
-    hipLaunchKernelGGL(k_generic_rotate, dim3((unsigned)a.rows), dim3(kThreads), lds_bytes(h), s, a,
+    launch_kernel(k_generic_rotate, dim3((unsigned)a.rows), dim3(kThreads), lds_bytes(h), s, a,
                        transpose, o);
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }
@@ -527,7 +527,7 @@ int generic_dequant_rotate(const rq_hadamard* h, const RowArgs& a, const uint32_
                            const float* scales, const float* mins, int transpose, const OutArgs& o,
                            hipStream_t s) {
     if (a.rows > 0x7fffffffLL) return RQ_ERR_ARG;
-    hipLaunchKernelGGL(k_generic_dequant_rotate, dim3((unsigned)a.rows), dim3(kThreads), lds_bytes(h), s,
+    launch_kernel(k_generic_dequant_rotate, dim3((unsigned)a.rows), dim3(kThreads), lds_bytes(h), s,
                        a, codes, scales, mins, transpose, o);
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }
@@ -535,7 +535,7 @@ int generic_dequant_rotate(const rq_hadamard* h, const RowArgs& a, const uint32_
 int plain_quantize(const void* X, int dtype, int64_t rows, int d, int64_t ld, int bits, float clip,
                    uint32_t* codes, float* scales, hipStream_t s) {
     if (rows > 0x7fffffffLL) return RQ_ERR_ARG;
-    hipLaunchKernelGGL(k_plain_quantize, dim3((unsigned)rows), dim3(kThreads), 0, s, X, dtype, d, ld,
+    launch_kernel(k_plain_quantize, dim3((unsigned)rows), dim3(kThreads), 0, s, X, dtype, d, ld,
                        bits, clip, codes, scales);
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }
@@ -544,11 +544,11 @@ int reduce_partials(double* partial, int64_t rows, int n_clips, float* mse, hipS
     if (rows > 16 * kChunkRows) {
         const int64_t chunks = (rows + kChunkRows - 1) / kChunkRows;
         if (chunks > 0x7fffffffLL) return RQ_ERR_ARG;
-        hipLaunchKernelGGL(k_reduce_chunks, dim3((unsigned)chunks), dim3(kThreads), 0, s, partial, rows, n_clips);
-        hipLaunchKernelGGL(k_reduce_partials, dim3(n_clips), dim3(kThreads), 0, s, partial, chunks,
+        launch_kernel(k_reduce_chunks, dim3((unsigned)chunks), dim3(kThreads), 0, s, partial, rows, n_clips);
+        launch_kernel(k_reduce_partials, dim3(n_clips), dim3(kThreads), 0, s, partial, chunks,
                            (int64_t)kChunkRows, rows, n_clips, mse);
     } else {
-        hipLaunchKernelGGL(k_reduce_partials, dim3(n_clips), dim3(kThreads), 0, s, partial, rows, (int64_t)1,
+        launch_kernel(k_reduce_partials, dim3(n_clips), dim3(kThreads), 0, s, partial, rows, (int64_t)1,
                            rows, n_clips, mse);
     }
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
@@ -559,7 +559,7 @@ int generic_quant_error_asym(const rq_hadamard* h, const RowArgs& a, const ClipL
     const size_t bytes = lds_bytes(h);
     if (a.rows > 0x7fffffffLL || a.n % 128 != 0) return RQ_ERR_ARG;
     if (a.rows > 0) {
-        hipLaunchKernelGGL(k_generic_quant_error_asym, dim3((unsigned)a.rows), dim3(kThreads), bytes, s, a,
+        launch_kernel(k_generic_quant_error_asym, dim3((unsigned)a.rows), dim3(kThreads), bytes, s, a,
                            clips, n_clips, partial);
         if (hipGetLastError() != hipSuccess) return RQ_ERR_HIP;
     }
@@ -571,7 +571,7 @@ int generic_quant_error(const rq_hadamard* h, const RowArgs& a, const ClipList& 
     const size_t bytes = lds_bytes(h);
     if (a.rows > 0x7fffffffLL) return RQ_ERR_ARG;
     if (a.rows > 0) {
-        hipLaunchKernelGGL(k_generic_quant_error, dim3((unsigned)a.rows), dim3(kThreads), bytes, s, a,
+        launch_kernel(k_generic_quant_error, dim3((unsigned)a.rows), dim3(kThreads), bytes, s, a,
                            clips, n_clips, partial);
         if (hipGetLastError() != hipSuccess) return RQ_ERR_HIP;
     }

@@ -287,8 +287,8 @@ void launch_short(int bits, hipStream_t s, const void* X, int64_t rows, int d, i
     const int64_t iters = (rows + (64 / LPR) * U - 1) / ((64 / LPR) * U);
     const int64_t cap = 1 << 24;
     const unsigned grid = (unsigned)(iters < cap ? iters : cap);
-    if (bits == 4) hipLaunchKernelGGL((k_plain_short<4, DT, LPR, U>), dim3(grid), dim3(64), 0, s, X, rows, d, ld, clip, codes, scales);
-    else hipLaunchKernelGGL((k_plain_short<3, DT, LPR, U>), dim3(grid), dim3(64), 0, s, X, rows, d, ld, clip, codes, scales);
+    if (bits == 4) launch_kernel((k_plain_short<4, DT, LPR, U>), dim3(grid), dim3(64), 0, s, X, rows, d, ld, clip, codes, scales);
+    else launch_kernel((k_plain_short<3, DT, LPR, U>), dim3(grid), dim3(64), 0, s, X, rows, d, ld, clip, codes, scales);
 }
 
 template <int DT>
@@ -304,7 +304,7 @@ void launch_dt(bool aligned, int bits, unsigned grid, hipStream_t s, const void*
                int64_t ld, double clip, uint32_t* codes, float* scales, float* mins) {
     const int gpr_shift = (gpr & (gpr - 1)) == 0 ? __builtin_ctz((unsigned)gpr) : -1;
     const uint32_t gpr_magic = (uint32_t)((((uint64_t)1 << 32) + gpr - 1) / gpr);   // gpr >= 2 where it is used
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, X, n_groups, gpr, gpr_shift, gpr_magic, ld, clip, codes, scales, mins); };
+    auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, X, n_groups, gpr, gpr_shift, gpr_magic, ld, clip, codes, scales, mins); };
     if (aligned) {
         if (bits == 4) go(k_plain_asym<4, DT, true, 4>); else go(k_plain_asym<3, DT, true, 4>);
     } else {

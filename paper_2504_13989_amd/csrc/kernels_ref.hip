@@ -43,8 +43,8 @@ int stream_reference(const void* X, int64_t rows, int n, int64_t ld, int bits, u
     const int64_t cap = 1 << 24;
     const dim3 grid((unsigned)(rows < cap ? rows : cap)), block(64);
     const uint16_t* x = static_cast<const uint16_t*>(X);
-    if (bits == 4) hipLaunchKernelGGL(k_stream_reference<4>, grid, block, 0, s, x, rows, n / 512, ld, codes, scales);
-    else hipLaunchKernelGGL(k_stream_reference<3>, grid, block, 0, s, x, rows, n / 512, ld, codes, scales);
+    if (bits == 4) launch_kernel(k_stream_reference<4>, grid, block, 0, s, x, rows, n / 512, ld, codes, scales);
+    else launch_kernel(k_stream_reference<3>, grid, block, 0, s, x, rows, n / 512, ld, codes, scales);
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }
 

@@ -213,7 +213,7 @@ __global__ __launch_bounds__(64) void k_wave_rotate_short(RotArgs a) {
 
 template <int T>
 void launch_long(const RotArgs& a, bool f16, int out, unsigned grid, hipStream_t s) {
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, a); };
+    auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, a); };
     if (f16) {
         if (out == 0) go(k_wave_rotate<T, true, 0>); else if (out == 1) go(k_wave_rotate<T, true, 1>); else go(k_wave_rotate<T, true, 2>);
     } else {
@@ -227,7 +227,7 @@ void launch_short(const RotArgs& a, bool f16, int out, hipStream_t s) {
     const int64_t items = (a.rows + (16 >> CB) * U - 1) / ((16 >> CB) * U);
     const int64_t cap = 1 << 24;
     const unsigned grid = (unsigned)(items < cap ? items : cap);
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, a); };
+    auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, a); };
     if (f16) {
         if (out == 0) go(k_wave_rotate_short<CB, U, true, 0>); else if (out == 1) go(k_wave_rotate_short<CB, U, true, 1>); else go(k_wave_rotate_short<CB, U, true, 2>);
     } else {
@@ -237,7 +237,7 @@ void launch_short(const RotArgs& a, bool f16, int out, hipStream_t s) {
 
 template <int T>
 void launch_long_codes(const RotArgs& a, int bits, int out, unsigned grid, hipStream_t s) {
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, a); };
+    auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, a); };
     if (bits == 4) {
         if (out == 0) go(k_wave_rotate<T, false, 0, 4>); else if (out == 1) go(k_wave_rotate<T, false, 1, 4>); else go(k_wave_rotate<T, false, 2, 4>);
     } else {
@@ -251,7 +251,7 @@ void launch_short_codes(const RotArgs& a, int bits, int out, hipStream_t s) {
     const int64_t items = (a.rows + (16 >> CB) * U - 1) / ((16 >> CB) * U);
     const int64_t cap = 1 << 24;
     const unsigned grid = (unsigned)(items < cap ? items : cap);
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, a); };
+    auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, a); };
     if (bits == 4) {
         if (out == 0) go(k_wave_rotate_short<CB, U, false, 0, 4, ASYM>); else if (out == 1) go(k_wave_rotate_short<CB, U, false, 1, 4, ASYM>); else go(k_wave_rotate_short<CB, U, false, 2, 4, ASYM>);
     } else {

@@ -1026,7 +1026,7 @@ template <int T, int W = 1>
 int launch_plain(const PlainArgs& a, int bits, hipStream_t s) {
     const int64_t cap = 1 << 24;
     const dim3 grid((unsigned)(a.rows < cap ? a.rows : cap)), block(64 * W);
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, a); };
+    auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, a); };
     if (a.f16) {
         if (bits == 4) go(k_plain_wave<T, W, 4, true>); else go(k_plain_wave<T, W, 3, true>);
     } else {
@@ -1044,7 +1044,7 @@ int launch_wave(K kernel, const rq_hadamard* h, const WaveArgs& a, int64_t items
     (void)waves_per_simd;
     const int64_t cap = 1 << 24;
     const unsigned grid = (unsigned)(items < cap ? items : cap);
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, a);
+    launch_kernel(kernel, dim3(grid), dim3(64), 0, s, a);
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }
 
@@ -1052,7 +1052,7 @@ template <int T, int S>
 int launch_split(const WaveArgs& a, int bits, hipStream_t s) {
     const bool full = a.d == 512 * T;
     const dim3 grid((unsigned)a.rows), block(64 * S);
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, a); };
+    auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, a); };
     if (a.f16) {
         if (bits == 4) { if (full) go(k_wave_sylvester_split<T, 4, true, S, true>); else go(k_wave_sylvester_split<T, 4, false, S, true>); }
         else { if (full) go(k_wave_sylvester_split<T, 3, true, S, true>); else go(k_wave_sylvester_split<T, 3, false, S, true>); }
@@ -1167,20 +1167,20 @@ template <int NV>
 static void launch_block_nv(int bits, bool full, unsigned grid, hipStream_t s, const WaveArgs& w, int pb) {
     if (w.f16) {
         if (bits == 4) {
-            if (full) hipLaunchKernelGGL((k_wave_block<4, true, NV, true>), dim3(grid), dim3(64), 0, s, w, pb);
-            else hipLaunchKernelGGL((k_wave_block<4, false, NV, true>), dim3(grid), dim3(64), 0, s, w, pb);
+            if (full) launch_kernel((k_wave_block<4, true, NV, true>), dim3(grid), dim3(64), 0, s, w, pb);
+            else launch_kernel((k_wave_block<4, false, NV, true>), dim3(grid), dim3(64), 0, s, w, pb);
         } else {
-            if (full) hipLaunchKernelGGL((k_wave_block<3, true, NV, true>), dim3(grid), dim3(64), 0, s, w, pb);
-            else hipLaunchKernelGGL((k_wave_block<3, false, NV, true>), dim3(grid), dim3(64), 0, s, w, pb);
+            if (full) launch_kernel((k_wave_block<3, true, NV, true>), dim3(grid), dim3(64), 0, s, w, pb);
+            else launch_kernel((k_wave_block<3, false, NV, true>), dim3(grid), dim3(64), 0, s, w, pb);
         }
         return;
     }
     if (bits == 4) {
-        if (full) hipLaunchKernelGGL((k_wave_block<4, true, NV>), dim3(grid), dim3(64), 0, s, w, pb);
-        else hipLaunchKernelGGL((k_wave_block<4, false, NV>), dim3(grid), dim3(64), 0, s, w, pb);
+        if (full) launch_kernel((k_wave_block<4, true, NV>), dim3(grid), dim3(64), 0, s, w, pb);
+        else launch_kernel((k_wave_block<4, false, NV>), dim3(grid), dim3(64), 0, s, w, pb);
     } else {
-        if (full) hipLaunchKernelGGL((k_wave_block<3, true, NV>), dim3(grid), dim3(64), 0, s, w, pb);
-        else hipLaunchKernelGGL((k_wave_block<3, false, NV>), dim3(grid), dim3(64), 0, s, w, pb);
+        if (full) launch_kernel((k_wave_block<3, true, NV>), dim3(grid), dim3(64), 0, s, w, pb);
+        else launch_kernel((k_wave_block<3, false, NV>), dim3(grid), dim3(64), 0, s, w, pb);
     }
 }
 
@@ -1248,7 +1248,7 @@ int wave_block_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float cli
 template <int NV>
 static void launch_block_rotate_nv(int src, bool full, bool f16, int out, unsigned grid, hipStream_t s, const WaveArgs& w, int pb,
                                    const BlockRotArgs& o) {
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, w, pb, o); };
+    auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, w, pb, o); };
     auto pick_out = [&](auto full_c, auto f16_c, auto src_c) {
         constexpr bool FL = decltype(full_c)::value, FH = decltype(f16_c)::value;
         constexpr int SRC = decltype(src_c)::value;
@@ -1350,7 +1350,7 @@ static int launch_qe(const rq_hadamard* h, const WaveArgs& w, const ClipList& cl
     const int64_t items = w.rows * ksplit;
     const int64_t cap = 1 << 24;
     const unsigned grid = (unsigned)(items < cap ? items : cap);
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, w, clips, n_clips, ksplit, partial); };
+    auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, w, clips, n_clips, ksplit, partial); };
     if (w.f16) {
         if (bits == 4) go(k_wave_quant_error<T, 4, true>); else go(k_wave_quant_error<T, 3, true>);
     } else {
@@ -1367,7 +1367,7 @@ static int launch_block_qe(const rq_hadamard* h, const WaveArgs& w, int pb, cons
     const int64_t cap = 1 << 24;
     const dim3 grid((unsigned)(items < cap ? items : cap)), block(64);
     const bool full = w.d == pb * 128;
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, w, pb, clips, n_clips, ksplit, partial); };
+    auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, w, pb, clips, n_clips, ksplit, partial); };
     if (w.f16) {
         if (bits == 4) { if (full) go(k_wave_block_qe<4, true, NV, true>); else go(k_wave_block_qe<4, false, NV, true>); }
         else { if (full) go(k_wave_block_qe<3, true, NV, true>); else go(k_wave_block_qe<3, false, NV, true>); }
@@ -1384,7 +1384,7 @@ static int launch_short_qe(const WaveArgs& w, const ClipList& clips, int n_clips
     const int64_t passes = (w.rows + (16 >> CB) - 1) / (16 >> CB);
     const int64_t cap = 1 << 24;
     const dim3 grid((unsigned)(passes < cap ? passes : cap)), block(64);
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, w, clips, n_clips, partial); };
+    auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, w, clips, n_clips, partial); };
     if (w.f16) {
         if (bits == 4) go(k_wave_short_qe<CB, 4, true>); else go(k_wave_short_qe<CB, 3, true>);
     } else {
@@ -1402,7 +1402,7 @@ int wave_quant_error_asym(const rq_hadamard* h, const RowArgs& a, const ClipList
     const int64_t passes = (w.rows + 3) / 4;
     const int64_t cap = 1 << 24;
     const dim3 grid((unsigned)(passes < cap ? passes : cap)), block(64);
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, w, clips, n_clips, partial); };
+    auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, w, clips, n_clips, partial); };
     if (f16) {
         if (a.bits == 4) go(k_wave_short_qe_asym<4, true>); else go(k_wave_short_qe_asym<3, true>);
     } else {
@@ -1472,7 +1472,7 @@ static int launch_plain_short_u(const WaveArgs& a, int bits, hipStream_t s) {
     const int64_t items = (a.rows + SUPER - 1) / SUPER;
     const int64_t cap = 1 << 24;
     const dim3 grid((unsigned)(items < cap ? items : cap)), block(64);
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, a); };
+    auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, a); };
     if (a.f16) {
         if (bits == 4) go(k_wave_short<CB, 4, U, false, true, true>); else go(k_wave_short<CB, 3, U, false, true, true>);
     } else {

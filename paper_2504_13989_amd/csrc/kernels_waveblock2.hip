@@ -117,7 +117,7 @@ __global__ __launch_bounds__(64) void k_wave_block2(WaveArgs a, int pb) {
 
 template <int NV>
 void launch_nv(const WaveArgs& w, int bits, bool full, unsigned grid, int pb, hipStream_t s) {
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, w, pb); };
+    auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, w, pb); };
     if (w.f16) {
         if (bits == 4) { if (full) go(k_wave_block2<4, true, NV, true>); else go(k_wave_block2<4, false, NV, true>); }
         else { if (full) go(k_wave_block2<3, true, NV, true>); else go(k_wave_block2<3, false, NV, true>); }

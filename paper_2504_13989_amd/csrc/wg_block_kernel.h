@@ -416,7 +416,7 @@ int wg_launch(const rq_hadamard* h, WgKernel<SINK> fn, const WaveArgs& a, int pb
     const int rpw = 16 >> cb;
     const int64_t passes = (a.rows + rpw - 1) / rpw;
     const unsigned grid = (unsigned)(passes < cap ? passes : cap);
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(64 * nw), lds, s, a, pb, sa);
+    launch_kernel(fn, dim3(grid), dim3(64 * nw), lds, s, a, pb, sa);
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }
 
