@@ -153,14 +153,47 @@ struct Out {
         Py_INCREF(o);
         ref = o;
     }
-    void make(PyObject* o, at::IntArrayRef size, at::ScalarType t, c10::Device device) {
-        if (o != Py_None) return given(o);
-        at::Tensor y(at::detail::empty_cuda(size, t, device, std::nullopt));
+    void adopt(at::Tensor&& y) {
         data = y.data_ptr();
         ref = THPVariable_Wrap(std::move(y));
         if (!ref) throw Raised{};
     }
+    void make(PyObject* o, at::IntArrayRef size, at::ScalarType t, c10::Device device) {
+        if (o != Py_None) return given(o);
+        adopt(at::Tensor(at::detail::empty_cuda(size, t, device, std::nullopt)));
+    }
 };
+
+// The results of a quantizing call: codes [rows, row_bytes], then one or two float tensors of `size`.  Where the
+// caller gives none of them they are cut from one allocation (the floats are a few per mille of it and belong
+// with the codes): taking and returning a block of the allocator is most of what a result costs the host.
+void make_results(c10::Device device, int64_t rows, int64_t row_bytes, at::IntArrayRef size, std::initializer_list<PyObject*> given,
+                  std::initializer_list<Out*> outs) {
+    PyObject* const* g = given.begin();
+    Out* const* o = outs.begin();
+    const size_t k = outs.size();
+    bool none = true;
+    for (size_t i = 0; i < k; ++i) none = none && g[i] == Py_None;
+    if (!none) {
+        o[0]->make(g[0], {rows, row_bytes}, at::kByte, device);
+        for (size_t i = 1; i < k; ++i) o[i]->make(g[i], size, at::kFloat, device);
+        return;
+    }
+    int64_t count = 1;
+    for (int64_t n : size) count *= n;
+    constexpr int64_t kStep = 512;                       // the allocator's own granularity
+    const int64_t code_step = (rows * row_bytes + kStep - 1) / kStep * kStep, float_step = (count * 4 + kStep - 1) / kStep * kStep;
+    at::Tensor codes(at::detail::empty_cuda({code_step + (int64_t)(k - 1) * float_step}, at::kByte, device, std::nullopt));
+    for (size_t i = 1; i < k; ++i) {
+        auto impl = c10::make_intrusive<c10::TensorImpl>(c10::Storage(codes.storage()), codes.key_set(),
+                                                         c10::scalarTypeToTypeMeta(at::kFloat));
+        impl->set_storage_offset((code_step + (int64_t)(i - 1) * float_step) / 4);
+        impl->set_sizes_contiguous(size);
+        o[i]->adopt(at::Tensor(std::move(impl)));
+    }
+    codes.unsafeGetTensorImpl()->set_sizes_contiguous({rows, row_bytes});
+    o[0]->adopt(std::move(codes));
+}
 
 template <typename F>
 int unlocked(F f) {
@@ -230,8 +263,7 @@ PyObject* rotate_quantize(PyObject* const* a) {
     const float clip = real(a[3]);
     void* s = stream(a[6]);
     Out codes, scales;
-    codes.make(a[4], {x.rows, (int64_t)n * bits / 8}, at::kByte, x.device);
-    scales.make(a[5], {x.rows}, at::kFloat, x.device);
+    make_results(x.device, x.rows, (int64_t)n * bits / 8, {x.rows}, {a[4], a[5]}, {&codes, &scales});
     check(unlocked([&] {
         return rq_rotate_quantize(h, x.X, x.dtype, x.rows, x.d, x.ld, bits, clip, codes.data,
                                   static_cast<float*>(scales.data), s);
@@ -249,9 +281,7 @@ PyObject* rotate_quantize_asym(PyObject* const* a) {
     void* s = stream(a[7]);
     const int64_t groups = n >= RQ_GROUP ? n / RQ_GROUP : 1;
     Out codes, scales, mins;
-    codes.make(a[4], {x.rows, (int64_t)n * bits / 8}, at::kByte, x.device);
-    scales.make(a[5], {x.rows, groups}, at::kFloat, x.device);
-    mins.make(a[6], {x.rows, groups}, at::kFloat, x.device);
+    make_results(x.device, x.rows, (int64_t)n * bits / 8, {x.rows, groups}, {a[4], a[5], a[6]}, {&codes, &scales, &mins});
     check(unlocked([&] {
         return rq_rotate_quantize_asym(h, x.X, x.dtype, x.rows, x.d, x.ld, bits, clip, codes.data,
                                        static_cast<float*>(scales.data), static_cast<float*>(mins.data), s);
@@ -267,8 +297,7 @@ PyObject* quantize(PyObject* const* a) {
     const float clip = real(a[2]);
     void* s = stream(a[5]);
     Out codes, scales;
-    codes.make(a[3], {x.rows, (int64_t)x.d * bits / 8}, at::kByte, x.device);
-    scales.make(a[4], {x.rows}, at::kFloat, x.device);
+    make_results(x.device, x.rows, (int64_t)x.d * bits / 8, {x.rows}, {a[3], a[4]}, {&codes, &scales});
     check(unlocked([&] {
         return rq_quantize(x.X, x.dtype, x.rows, x.d, x.ld, bits, clip, codes.data, static_cast<float*>(scales.data), s);
     }), where);
@@ -284,9 +313,7 @@ PyObject* quantize_asym(PyObject* const* a) {
     void* s = stream(a[6]);
     const int64_t groups = x.d >= RQ_GROUP ? x.d / RQ_GROUP : 1;
     Out codes, scales, mins;
-    codes.make(a[3], {x.rows, (int64_t)x.d * bits / 8}, at::kByte, x.device);
-    scales.make(a[4], {x.rows, groups}, at::kFloat, x.device);
-    mins.make(a[5], {x.rows, groups}, at::kFloat, x.device);
+    make_results(x.device, x.rows, (int64_t)x.d * bits / 8, {x.rows, groups}, {a[3], a[4], a[5]}, {&codes, &scales, &mins});
     check(unlocked([&] {
         return rq_quantize_asym(x.X, x.dtype, x.rows, x.d, x.ld, bits, clip, codes.data,
                                 static_cast<float*>(scales.data), static_cast<float*>(mins.data), s);
