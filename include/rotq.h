@@ -331,12 +331,14 @@ size_t rq_gbs_workspace(int64_t rows);
  * f(x) < f(m) becomes the new middle and the far bracket end moves to the old middle, otherwise
  * the bracket end on the probe's side moves to the probe; stops when b - a <= eps or after
  * max_evals evaluations of f.  The probes and their values are those of that loop taken one at a
- * time; they are evaluated ahead in batches (one rq_quant_error launch covers every probe the next
- * few steps can ask for, whatever the comparisons give), each batch followed by a synchronisation of
- * `stream`: a calibration call, not a hot-path call.  The values of a batch come back through 256
- * bytes of pinned host memory that the library allocates at the first search of a host thread on a
- * device and keeps until the process ends (copied back on `stream` instead where that allocation
- * fails); nothing else is allocated.
+ * time; they are evaluated ahead in batches (every probe the next few steps can ask for, whatever the
+ * comparisons give), and the comparisons are taken on the device: rows the chip can hold in registers
+ * are rotated once and searched in one launch, other tensors take a few launches enqueued together.
+ * The call waits for the result: a calibration call, not a hot-path call (not for a stream under
+ * capture).  A search uses about 260 KB of device memory and 2 KB of pinned host memory that the
+ * library allocates and keeps for the next one, as many sets per device as searches ever ran at the
+ * same time; nothing else is allocated.  Searches may run on any number of threads and streams; one at
+ * a time per device takes the single-launch form.
  *   eps          [in]  bracket width to stop at, > 0
  *   max_evals    [in]  1 .. 256
  *   workspace    [in]  DEVICE, >= rq_gbs_workspace(rows) bytes, 8-byte aligned, scratch

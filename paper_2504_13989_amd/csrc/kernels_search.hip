@@ -1,0 +1,485 @@
+// The clip-ratio search of Algorithm 1 (section 4.1) on the device, in two forms.
+//
+// Batches (any tensor): between the batches of objective values a search
+// needs (one quant_error pass each), a kernel of one workgroup averages the batch, walks the search with it and writes
+// the clip ratios of the next batch to device memory, where the next pass reads them.  The host enqueues all of it and
+// waits once; a trip to the host between the batches cost about 8 us each, as much as a pass on a small tensor.
+//
+// The probes are taken in the listing's order, but evaluated ahead of time in batches: where a probe lies depends only
+// on the outcomes of the comparisons before it, so one batch covers every probe the next `depth` steps can ask for, a
+// binary tree over those outcomes.  The sequence of probes is that of the one-at-a-time loop.
+#include "row_rotation.h"
+
+namespace rq {
+
+// Search state: the best point so far and the nearest evaluated point on either side of it; probes go to the midpoint
+// towards the left and the right neighbour in turn.
+struct GbsState {
+    double left, right;   // nearest evaluated points left and right of the best
+    double best;
+    int side;             // neighbour the next probe goes towards: 0 left, 1 right
+    __host__ __device__ double width() const { return right - left; }
+    __host__ __device__ double probe() const { return 0.5 * ((side ? right : left) + best); }
+    // after probing x = probe(): `better` = the probe beat the best point, which then bounds the far side
+    __host__ __device__ void next(double x, bool better) {
+        const bool to_left = better ? side == 1 : side == 0;
+        const double bound = better ? best : x;
+        left = to_left ? bound : left;
+        right = to_left ? right : bound;
+        best = better ? x : best;
+        side = 1 - side;
+    }
+};
+__host__ __device__ inline GbsState gbs_start() { return GbsState{0.0, 1.0, 0.5, 0}; }
+
+// Probe of node i (1 .. 2^depth - 1) of the tree below `st`, in heap order (children 2 i for "better", 2 i + 1 for "not
+// better"); false where the search ends before it gets there.
+__host__ __device__ inline bool gbs_node(GbsState st, double eps, int depth, int i, double* x) {
+    bool live = st.width() > eps;
+    for (int b = depth - 2; b >= 0; --b)
+        if (i >> (b + 1)) {                               // below the node's leading bit
+            st.next(st.probe(), !((i >> b) & 1));
+            live = live && st.width() > eps;
+        }
+    *x = st.probe();
+    return live;
+}
+
+struct GbsDev {
+    ClipList clips;       // the next batch
+    GbsState st;
+    float fm;             // objective at the best point
+    int evals;
+    int done;
+    float trace_clips[256], trace_mse[256];
+};
+
+namespace {
+
+constexpr int kStepThreads = 1024;
+
+// partial: [count] sums per clip ratio, `stride` rows apart, in rows of as many values as the batch has clip ratios.
+// What the kernel costs is latency: it is one workgroup in the middle of a chain of launches.  All loads of a thread are
+// issued before the first wait, every lane of the first wave works out its own node of the tree, and host memory is
+// written once, at the end of the search (a store over the bus holds the end of the kernel up).
+__global__ __launch_bounds__(kStepThreads) void k_gbs_step(GbsDev* state, GbsOut* out, int first, double eps, int depth, int max_evals,
+                                                           double levels, const double* partial, int64_t rows, int64_t count,
+                                                           int64_t stride) {
+    __shared__ double part[kStepThreads];
+    __shared__ float value[RQ_MAX_CLIPS];
+    __shared__ double node_x[RQ_MAX_CLIPS];
+    __shared__ int node_slot[RQ_MAX_CLIPS];
+    __shared__ GbsState next_st;
+    __shared__ int n_evals, finished;
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (!first && state->done) return;                    // a batch enqueued beyond the end of the search
+    const int nodes = 1 << depth;
+    const GbsState st0 = first ? gbs_start() : state->st;
+    const float fm0 = first ? 0.0f : state->fm;
+    const int evals0 = first ? 0 : state->evals;
+    const int lead = first ? 1 : 0;                       // the starting point leads the first batch
+    // (every wave works the tree out for itself: the batch's size is needed at once)
+    double x;
+    const bool live = gbs_node(st0, eps, depth, lane, &x) && lane >= 1 && lane < nodes;
+    const uint64_t mask = __ballot(live);
+    const int n = lead + __popcll(mask);
+    if (tid < 64) {
+        node_x[lane] = x;
+        node_slot[lane] = lead + __popcll(mask & ((1ull << lane) - 1ull));
+    }
+    int kp = 1;
+    while (kp < n) kp <<= 1;
+    {
+        // consecutive threads read consecutive values: clip ratio tid % kp of row tid / kp, a fixed order of summation
+        const int k = tid & (kp - 1), lanes = kStepThreads / kp;
+        const int kc = k < n ? k : n - 1;
+        double acc = 0.0;
+        constexpr int U = 8;
+        for (int64_t r0 = tid / kp; r0 < count; r0 += (int64_t)U * lanes) {
+            double v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t r = r0 + (int64_t)u * lanes;
+                v[u] = partial[(r < count ? r : count - 1) * stride * n + kc];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) acc += r0 + (int64_t)u * lanes < count ? v[u] : 0.0;
+        }
+        part[tid] = acc;
+        for (int s = kStepThreads / 2; s >= kp; s >>= 1) {
+            __syncthreads();
+            if (tid < s) part[tid] += part[tid + s];
+        }
+        if (tid < n) value[tid] = (float)(part[tid] / (double)rows);
+        __syncthreads();
+    }
+    if (tid == 0) {
+        GbsState st = st0;
+        float fm = fm0;
+        int evals = evals0;
+        auto record = [&](float c, float v) {
+            state->trace_clips[evals] = c;
+            state->trace_mse[evals] = v;
+            ++evals;
+        };
+        if (first) {
+            fm = value[0];
+            record((float)st.best, fm);
+        }
+        int idx = 1;
+        for (int lvl = 0; lvl < depth && st.width() > eps && evals < max_evals; ++lvl) {
+            const double p = node_x[idx];
+            const float fx = value[node_slot[idx]];
+            record((float)p, fx);
+            const bool better = fx < fm;
+            if (better) fm = fx;
+            st.next(p, better);
+            idx = 2 * idx + (better ? 0 : 1);
+        }
+        finished = st.width() <= eps || evals >= max_evals;
+        n_evals = evals;
+        next_st = st;
+        state->st = st;
+        state->fm = fm;
+        state->evals = evals;
+        state->done = finished;
+        if (finished) {
+            state->clips.n = 0;
+            out->clip = (float)st.best;
+            out->mse = fm;
+            out->evals = evals;
+        }
+    }
+    __syncthreads();
+    if (finished) {
+        // (the trace was written by this workgroup: visible to it after the barrier)
+        if (tid < n_evals) {
+            out->trace_clips[tid] = state->trace_clips[tid];
+            out->trace_mse[tid] = state->trace_mse[tid];
+        }
+        if (tid == 0) out->done = 1;                      // (the host reads the results after the stream is done)
+        return;
+    }
+    if (tid < 64) {
+        const bool more = gbs_node(next_st, eps, depth, lane, &x) && lane >= 1 && lane < nodes;
+        const uint64_t m = __ballot(more);
+        if (more) state->clips.set(__popcll(m & ((1ull << lane) - 1ull)), (float)x, levels);
+        if (tid == 0) state->clips.n = __popcll(m);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Resident form: the tensor is rotated once, into the registers of as many waves as hold it, and stays there for the
+// whole search - one launch.  Each step looks three probes ahead (seven clip ratios, with the starting point eight at
+// first); the workgroups' sums meet through a small exchange buffer in device memory, and every workgroup averages all
+// of them in the same order and so takes the same decisions.  A step costs the arithmetic of its ratios and one
+// exchange between the workgroups (about 3 us, whence three probes a step); the batched form pays two launches and a
+// repeated rotation for four steps.
+//
+// Exchange: a sum travels in one 64-bit word, the upper 48 bits of the fp64 value and the number of the step below them,
+// so that a word is its own flag; two sets of words alternate, which is enough, because a workgroup that is two steps
+// ahead has seen every other one publish the step between.  At most one workgroup per compute unit is launched, so
+// all are resident together unless other work holds the chip; a workgroup that waits longer than kWaitTicks gives the
+// search up (everyone does in the end), and the host takes the batched form.
+constexpr int kMaxGroups = 1024;
+constexpr uint64_t kWaitTicks = 1000000;                  // of the 100 MHz clock: 10 ms
+constexpr int kAhead = 3, kSlots = 1 << kAhead;           // probes a step looks ahead, clip ratios of a step
+
+struct ResidentArgs {
+    GbsOut* out;
+    uint64_t* exchange;       // [2][kMaxGroups][kSlots]
+    uint32_t epoch;           // 16-bit number of the first step; no word in the buffer has it or one of the next 511
+    double eps, levels;
+    int max_evals;
+    int rows_per_group;
+};
+
+// A Sylvester row of 512 T values over W waves, T / W register sets each.
+template <int T, int W_, bool F16>
+struct SylvesterRows {
+    static constexpr int W = W_, NVAL = T / W * 8;
+    static __device__ __forceinline__ float rotate(const WaveArgs& a, int, int64_t row, int seg, int lane, float (&v)[NVAL], float* flip) {
+        const int g = lane >> 4, cphys = lane & 15, c = (cphys & 4) ? (cphys ^ 3) : cphys;
+        const u32x4 A0 = a.tiles[lane], A1 = a.tiles[64 + lane];
+        f32x4 acc[T / W][2];
+        const float m = split_rotate_row<T, false, W, F16>(a, row, seg, c, (g << 4) + c, A0, A1, acc);
+#pragma unroll
+        for (int t = 0; t < T / W; ++t)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[(t * 2 + h) * 4 + i] = acc[t][h][i];
+        *flip = split_flip<T, W>(c);
+        return wave_absmax<4>(m);
+    }
+};
+// A row of a block order, pb <= 32: W waves with 16 output block rows each.
+template <int W_, bool F16>
+struct BlockRows {
+    static constexpr int W = W_, NVAL = 32;
+    static __device__ __forceinline__ float rotate(const WaveArgs& a, int pb, int64_t row, int seg, int lane, float (&v)[NVAL], float* flip) {
+        const int g = lane >> 4, cphys = lane & 15, c = (cphys & 4) ? (cphys ^ 3) : cphys;
+        const u32x4 A = a.tiles[seg * 64 + lane];
+        float sf[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) sf[b] = ((c >> b) & 1) ? -1.0f : 1.0f;
+        const int base_g = 8 * g < pb - 8 ? 8 * g : pb - 8;
+        float y[8][4];
+        const float m = block_rotate_row<false, 4, F16>(a, row, base_g * 128 + c * 8, A, A, sf, y);
+#pragma unroll
+        for (int ic = 0; ic < 8; ++ic)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[ic * 4 + j] = y[ic][j];
+        *flip = (__builtin_popcount(c) & 1) ? -1.0f : 1.0f;
+        return m;
+    }
+};
+
+template <typename Rows, int BITS>
+__global__ __launch_bounds__(1024) void k_gbs_resident(WaveArgs a, int pb, double inv_norm, ResidentArgs r) {
+    constexpr int W = Rows::W, NVAL = Rows::NVAL;
+    __shared__ float wmax[16];
+    __shared__ __attribute__((aligned(16))) float esum[kSlots][16];      // [slot][wave], zero beyond the waves there are
+    __shared__ __attribute__((aligned(16))) double gsum[kSlots][16];
+    __shared__ int gave_up;
+    __shared__ float trace_clips[256], trace_mse[256];    // (kept by the first workgroup)
+    const int tid = threadIdx.x, lane = tid & 63, nt = (int)blockDim.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rsub = wave / W, seg = wave - rsub * W;
+    const int64_t row = (int64_t)blockIdx.x * r.rows_per_group + rsub;
+    const bool live = row < a.rows;
+    float v[NVAL], flip = 1.0f;
+    float m = 0.0f;
+    if (live) {
+        m = Rows::rotate(a, pb, row, seg, lane, v, &flip);
+    } else {
+#pragma unroll
+        for (int i = 0; i < NVAL; ++i) v[i] = 0.0f;
+    }
+    if (lane == 0) wmax[wave] = m;
+    for (int i = tid; i < kSlots * 16; i += nt) {
+        esum[i >> 4][i & 15] = 0.0f;
+        gsum[i >> 4][i & 15] = 0.0;
+    }
+    if (tid == 0) gave_up = 0;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < W; ++w) m = __builtin_fmaxf(m, wmax[rsub * W + w]);
+    const double inv_m = m > 0.0f ? 1.0 / (double)m : 0.0, inv_rows = 1.0 / (double)a.rows;
+    const double m_over_levels = (double)m / r.levels;
+    const int words = (int)gridDim.x * kSlots;
+
+    GbsState st = gbs_start();
+    float fm = 0.0f;
+    int evals = 0;
+    for (uint32_t step = 0;; ++step) {
+        // the step's clip ratios, one lane a slot (first step: the starting point, then nodes 1 .. 7; later nodes 1 .. 7); a
+        // slot the search cannot reach repeats the best point
+        const int lead = step == 0 ? 1 : 0;
+        const int node = (lane & (kSlots - 1)) + 1 - lead;
+        double x = st.best;
+        bool reach = node == 0;
+        if (node >= 1 && node < kSlots) {
+            double p;
+            reach = gbs_node(st, r.eps, kAhead, node, &p);
+            if (reach) x = p;
+        }
+        const uint32_t wanted = (uint32_t)__ballot(reach) & ((1u << kSlots) - 1u);
+        const double cf = (double)(float)x;
+        const float s_slot = (float)(r.levels / cf * inv_m), d_slot = (float)(cf * m_over_levels);
+        constexpr float kQmax = (float)((1 << (BITS - 1)) - 1), kQmin = -(float)(1 << (BITS - 1));
+        // four slots at a time (independent chains); the last step of a search often wants only the first
+#pragma unroll
+        for (int k0 = 0; k0 < kSlots; k0 += 4) {
+            if (!(wanted >> k0 & 15u)) continue;
+            float sk[4], ndk[4], e2[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                sk[k] = flip * __uint_as_float((uint32_t)__builtin_amdgcn_readlane(__float_as_uint(s_slot), k0 + k));
+                ndk[k] = -flip * __uint_as_float((uint32_t)__builtin_amdgcn_readlane(__float_as_uint(d_slot), k0 + k));
+                e2[k] = 0.0f;
+            }
+#pragma unroll
+            for (int i = 0; i < NVAL; ++i)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float q = __builtin_amdgcn_fmed3f(__builtin_rintf(v[i] * sk[k]), kQmin, kQmax);
+                    const float e = fmaf(q, ndk[k], v[i]);
+                    e2[k] = fmaf(e, e, e2[k]);
+                }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) e2[k] += dpp_f<kDppXor1>(e2[k]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) e2[k] += dpp_f<kDppXor2>(e2[k]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) e2[k] += dpp_f<kDppHalfMirror>(e2[k]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) e2[k] += dpp_f<kDppRor8>(e2[k]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                e2[k] = rows_sum(e2[k]);
+                if (lane == k) esum[k0 + k][wave] = e2[k];
+            }
+        }
+        __syncthreads();
+        const uint64_t tag = (r.epoch + step) & 0xffffu;
+        uint64_t* const set = r.exchange + (size_t)(step & 1) * kMaxGroups * kSlots;
+        if (tid < kSlots) {
+            double t = 0.0;
+#pragma unroll
+            for (int w = 0; w < 16; ++w) t += (double)esum[tid][w];
+            const uint64_t bits = (uint64_t)__double_as_longlong(t * inv_norm);
+            __hip_atomic_store(set + (size_t)blockIdx.x * kSlots + tid, (bits & ~0xffffull) | tag, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        }
+        // everyone's sums, in a fixed order: consecutive lanes read consecutive words (reading a workgroup's words one after
+        // the other in a lane multiplied the traffic by eight: 7 us a step)
+        double f = 0.0;
+        const uint64_t began = wall_clock64();
+        bool lost = false;
+        for (int i0 = tid; i0 < words && !lost; i0 += 4 * nt) {
+            uint64_t w[4];
+            for (;;) {
+                bool ready = true;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int i = i0 + u * nt;
+                    w[u] = __hip_atomic_load(set + (i < words ? i : i0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) ready = ready && (w[u] & 0xffffull) == tag;
+                if (ready) break;
+                if (wall_clock64() - began > kWaitTicks) {
+                    lost = true;
+                    break;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) f += i0 + u * nt < words ? __longlong_as_double((long long)(w[u] & ~0xffffull)) : 0.0;
+        }
+        if (lost) gave_up = 1;
+        for (int sh = kSlots; sh < 64; sh <<= 1) f += __shfl_xor(f, sh, 64);
+        if (lane < kSlots) gsum[lane][wave] = f;
+        __syncthreads();
+        if (gave_up) return;                              // the whole workgroup; the others run into the same limit
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) t += gsum[lane & (kSlots - 1)][w];
+        const float mean = (float)(t * inv_rows);         // lane k: the objective at slot k
+        auto value = [&](int slot) {
+            return __uint_as_float((uint32_t)__builtin_amdgcn_readlane(__float_as_uint(mean), __builtin_amdgcn_readfirstlane(slot)));
+        };
+        auto record = [&](float c, float f1) {
+            if (blockIdx.x == 0 && tid == 0) {
+                trace_clips[evals] = c;
+                trace_mse[evals] = f1;
+            }
+            ++evals;
+        };
+        if (lead) {
+            fm = value(0);
+            record((float)st.best, fm);
+        }
+        int at = 1;
+        for (int lvl = 0; lvl < kAhead && st.width() > r.eps && evals < r.max_evals; ++lvl) {
+            const double p = st.probe();
+            const float fx = value(at - 1 + lead);
+            record((float)p, fx);
+            const bool better = fx < fm;
+            if (better) fm = fx;
+            st.next(p, better);
+            at = 2 * at + (better ? 0 : 1);
+        }
+        if (st.width() <= r.eps || evals >= r.max_evals) break;
+    }
+    if (blockIdx.x == 0 && wave == 0) {
+        // results to host memory by one wave, the flag when they have arrived there
+        auto put = [](auto* to, auto x) { __hip_atomic_store(to, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); };
+        for (int i = lane; i < evals; i += 64) {
+            put(&r.out->trace_clips[i], trace_clips[i]);
+            put(&r.out->trace_mse[i], trace_mse[i]);
+        }
+        if (lane == 0) {
+            put(&r.out->clip, (float)st.best);
+            put(&r.out->mse, fm);
+            put(&r.out->evals, evals);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (lane == 0) put(&r.out->done, 1);
+    }
+}
+
+// Waves per row of the resident form, 0 where the order has none.
+int resident_waves(const RowArgs& a) {
+    if (a.p == 1) return a.log2m == 10 ? 1 : a.log2m == 11 ? 2 : a.log2m == 12 || a.log2m == 13 ? 4 : 0;
+    return (a.p << (a.log2m - 7)) <= 16 ? 1 : 2;
+}
+
+template <int BITS, bool F16>
+int launch_resident(const RowArgs& a, const WaveArgs& w, double inv_norm, const ResidentArgs& r, dim3 grid, dim3 block, hipStream_t s) {
+    const int pb = a.p > 1 ? a.p << (a.log2m - 7) : 0;
+    auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, w, pb, inv_norm, r); };
+    if (a.p > 1) {
+        if (pb <= 16) go(k_gbs_resident<BlockRows<1, F16>, BITS>); else go(k_gbs_resident<BlockRows<2, F16>, BITS>);
+    } else {
+        switch (a.log2m) {
+            case 10: go(k_gbs_resident<SylvesterRows<2, 1, F16>, BITS>); break;
+            case 11: go(k_gbs_resident<SylvesterRows<4, 2, F16>, BITS>); break;
+            case 12: go(k_gbs_resident<SylvesterRows<8, 4, F16>, BITS>); break;
+            case 13: go(k_gbs_resident<SylvesterRows<16, 4, F16>, BITS>); break;
+            default: return RQ_ERR_NO_ORDER;
+        }
+    }
+    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+}
+
+}  // namespace
+
+bool gbs_resident_supports(const rq_hadamard* h, const RowArgs& a) {
+    if (!wave_quant_error_supports(h, a)) return false;
+    const int w = resident_waves(a);
+    if (w == 0) return false;
+    const int groups = h->num_cu < kMaxGroups ? h->num_cu : kMaxGroups;
+    return a.rows <= (int64_t)groups * (16 / w);          // 16 waves per compute unit
+}
+
+size_t gbs_exchange_bytes() { return (size_t)2 * kMaxGroups * kSlots * sizeof(uint64_t); }
+
+int gbs_resident(const rq_hadamard* h, const RowArgs& a, GbsOut* out, uint64_t* exchange, uint32_t epoch, double eps, int max_evals,
+                 hipStream_t s) {
+    const int w = resident_waves(a);
+    const int groups = h->num_cu < kMaxGroups ? h->num_cu : kMaxGroups;
+    const int per = (int)((a.rows + groups - 1) / groups);
+    const bool f16 = a.dtype == RQ_F16;
+    WaveArgs wa{static_cast<const uint16_t*>(a.X), a.rows, a.d, a.ld,
+                static_cast<const u32x4*>(f16 ? h->d_tiles_f16 : h->d_tiles), nullptr, nullptr, 0.0, 0.0};
+    wa.f16 = f16;
+    const ResidentArgs r{out, exchange, epoch, eps, (double)((1 << a.bits) - 1), max_evals, per};
+    const double inv_norm = 1.0 / ((double)a.n * (double)a.n);
+    const dim3 grid((unsigned)((a.rows + per - 1) / per)), block((unsigned)(64 * per * w));
+    if (f16)
+        return a.bits == 4 ? launch_resident<4, true>(a, wa, inv_norm, r, grid, block, s) : launch_resident<3, true>(a, wa, inv_norm, r, grid, block, s);
+    return a.bits == 4 ? launch_resident<4, false>(a, wa, inv_norm, r, grid, block, s) : launch_resident<3, false>(a, wa, inv_norm, r, grid, block, s);
+}
+
+size_t gbs_state_bytes() { return sizeof(GbsDev); }
+const ClipList* gbs_state_clips(const GbsDev* state) { return &state->clips; }
+
+void gbs_first_batch(double eps, int depth, int bits, ClipList* out) {
+    const double levels = (double)((1 << bits) - 1);
+    const GbsState st = gbs_start();
+    out->n = 0;
+    out->set(out->n++, (float)st.best, levels);
+    double x;
+    for (int i = 1; i < (1 << depth); ++i)
+        if (gbs_node(st, eps, depth, i, &x)) out->set(out->n++, (float)x, levels);
+}
+
+int gbs_step(GbsDev* state, GbsOut* out, bool first, double eps, int depth, int max_evals, int bits, const double* partial,
+             int64_t rows, int64_t count, int64_t stride, hipStream_t s) {
+    launch_kernel(k_gbs_step, dim3(1), dim3(kStepThreads), 0, s, state, out, first ? 1 : 0, eps, depth, max_evals,
+                  (double)((1 << bits) - 1), partial, rows, count, stride);
+    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+}
+
+}  // namespace rq

@@ -21,7 +21,7 @@
 // number with the two low bits complemented when bit 2 is set.
 #include <type_traits>
 
-#include "wave_common.h"
+#include "row_rotation.h"
 
 namespace rq {
 namespace {
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(64) void k_wave_sylvester(WaveArgs a) {
 // products of all S input segments accumulate into one accumulator, with the negated operand
 // tile where H_S has -1.  Every wave therefore loads the whole row (S times the L1 traffic, the
 // same HBM traffic) but carries only T / S accumulator sets through the vector-ALU stages; the
-// waves exchange nothing but their absmax.
+// waves exchange nothing but their absmax.  (split_rotate_row: the rotation.)
 template <int T, int BITS, bool FULL, int S, bool F16 = false>
 __global__ __launch_bounds__(64 * S) void k_wave_sylvester_split(WaveArgs a) {
     static_assert(T % S == 0 && (S == 2 || S == 4), "unsupported split");
@@ -130,82 +130,17 @@ __global__ __launch_bounds__(64 * S) void k_wave_sylvester_split(WaveArgs a) {
     const int chunk = (g << 4) + c;
 
     const u32x4 A0 = a.tiles[lane], A1 = a.tiles[64 + lane];
-    // operand tiles per input segment: negated where H_S[seg][sp] = -1 (Sylvester sign; bit 15 is the
-    // sign of a bf16 and of an fp16 alike)
-    u32x4 P0[S], P1[S];
-#pragma unroll
-    for (int sp = 0; sp < S; ++sp) {
-        const uint32_t sg = (__builtin_popcount(seg & sp) & 1) ? 0x80008000u : 0u;
-        const u32x4 sgn = {sg, sg, sg, sg};
-        P0[sp] = A0 ^ sgn;
-        P1[sp] = A1 ^ sgn;
-    }
-    float sf[4];
-#pragma unroll
-    for (int b = 0; b < 4; ++b) sf[b] = ((c >> b) & 1) ? -1.0f : 1.0f;
-    const float flip = (__builtin_popcount(c) & 1) ? -1.0f : 1.0f;
-
     const int64_t row = blockIdx.x;
     if (row >= a.rows) return;                           // whole workgroup: no barrier is skipped
-    const uint16_t* xr = a.X + row * a.ld;
-    const RowView xv = row_view(xr, a.d);
     f32x4 acc[TS][2];
-    // all T loads of the row first (see k_wave_sylvester); plain (cached) loads: the S waves of the
-    // workgroup read the same lines
-    u32x4 raw[TS][S];
-#pragma unroll
-    for (int t = 0; t < TS; ++t)
-#pragma unroll
-        for (int sp = 0; sp < S; ++sp) {
-            const int e0 = ((sp * TS + t) * 64 + chunk) * 8;
-            raw[t][sp] = FULL ? *reinterpret_cast<const u32x4*>(xr + e0) : load_chunk(xv, e0);
-        }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int t = 0; t < TS; ++t) {
-        acc[t][0] = f32x4{0.f, 0.f, 0.f, 0.f};
-        acc[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int sp = 0; sp < S; ++sp) {
-            acc[t][0] = mfma_pm1<F16>(P0[sp], raw[t][sp], acc[t][0]);
-            acc[t][1] = mfma_pm1<F16>(P1[sp], raw[t][sp], acc[t][1]);
-        }
-    }
-#pragma unroll
-    for (int s = 1; s < TS; s <<= 1)
-#pragma unroll
-        for (int t = 0; t < TS; ++t)
-            if (!(t & s))
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const f32x4 u = acc[t][h], v = acc[t | s][h];
-                    acc[t][h] = u + v;
-                    acc[t | s][h] = u - v;
-                }
-    float m = 0.0f;
-#pragma unroll
-    for (int t = 0; t < TS; ++t)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            f32x4 v = acc[t][h];
-            if (TS == 1) {                               // straight from the matrix cores: see lane_stages_tail
-                const uint32_t sg0 = (c & 1) ? 0x80000000u : 0u;
-                lane_stage<kDppXor1>(v, sg0);
-                lane_stages_tail<4>(v, sf);
-            } else {
-                lane_stages_fused(v, sf[0], sf[1], sf[2], sf[3]);
-            }
-            acc[t][h] = v;
-            m = absmax4(m, v);
-        }
+    float m = split_rotate_row<T, FULL, S, F16>(a, row, seg, c, chunk, A0, A1, acc);
     m = wave_absmax<4>(m);
     if (lane == 0) wmax[seg] = m;
     __syncthreads();
     m = wmax[0];
 #pragma unroll
     for (int w = 1; w < S; ++w) m = __builtin_fmaxf(m, wmax[w]);
-    const float fl = TS == 1 ? ((__builtin_popcount(c >> 1) & 1) ? -1.0f : 1.0f) : flip;
-    const float s = m > 0.0f ? fl * (float)(a.c1 / (double)m) : 0.0f;
+    const float s = m > 0.0f ? split_flip<T, S>(c) * (float)(a.c1 / (double)m) : 0.0f;
 
     uint32_t* out = a.codes + row * (int64_t)ROW_DWORDS + seg * SEG_DWORDS;
     uint8_t* stage = stage_all + (BITS == 3 ? seg * SEG_DWORDS * 4 : 0);
@@ -536,77 +471,6 @@ void k_wave_short(WaveArgs a) {
 // loads into one operand (a 16-bit transpose inside the lane, v_perm_b32).  Outputs come back
 // with 8 block rows x 8 consecutive columns per lane; butterflies over i (registers) and c
 // (DPP), quantization and packing then work exactly as in the Sylvester kernel.
-// The rotation of one row for the block kernels: loads, block product on the matrix cores, the
-// 128-point transform along the columns.  y[column i][j]: register j = 4 h + ip holds block rows
-// 4 j .. 4 j + 3 (one per DPP row g); only the NV = ceil(pb / 4) registers that hold real block rows
-// are carried.  Values carry the lane's flip sign (see lane_stages_fused).  Returns the row's absmax.
-// SRC = 3, 4: the row comes from packed signed codes of that width (a.codes) as exact fp16 integers.
-template <bool FULL, int NV, bool F16 = false, int SRC = 0>
-__device__ __forceinline__ float block_rotate_row(const WaveArgs& a, int64_t row, int e_base, const u32x4& A0,
-                                              const u32x4& A1, const float (&sf)[4], float (&y)[8][NV]) {
-    constexpr int NH1 = NV > 4 ? NV - 4 : 0;              // live registers of the second half
-    constexpr int NH0 = NV > 4 ? 4 : NV;
-    u32x4 R[8];
-    if constexpr (SRC != 0) {
-        constexpr int STEP = 16 * SRC;                   // bytes of a block row
-        const int row_bytes = STEP * (a.d >> 7);
-        const auto rs = __builtin_amdgcn_make_buffer_rsrc(a.codes + row * (row_bytes / 4), 0, row_bytes, 0x00020000);
-        const CodeAt at = code_at<SRC>(e_base >> 3);
-        uint32_t lo[8], hi[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            lo[t] = __builtin_amdgcn_raw_buffer_load_b32(rs, at.off0 + t * STEP, 0, 2);
-            if constexpr (SRC == 3) hi[t] = __builtin_amdgcn_raw_buffer_load_b32(rs, at.off1 + t * STEP, 0, 2);
-        }
-        __builtin_amdgcn_sched_barrier(0);               // every load is issued before the first wait
-#pragma unroll
-        for (int t = 0; t < 8; ++t) R[t] = codes_f16<SRC>(SRC == 4 ? lo[t] : __builtin_amdgcn_alignbit(hi[t], lo[t], at.sh));
-    } else {
-        const uint16_t* xr = a.X + row * a.ld + e_base;
-        const RowView xv = row_view(a.X + row * a.ld, a.d);
-#pragma unroll
-        for (int t = 0; t < 8; ++t)
-            R[t] = FULL ? load16(xr + t * 128) : load_chunk(xv, e_base + t * 128);
-    }
-#pragma unroll
-    for (int ic = 0; ic < 8; ++ic) {
-        u32x4 bm;
-        const uint32_t sel = (ic & 1) ? 0x07060302u : 0x05040100u;
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-            bm[w] = __builtin_amdgcn_perm(R[2 * w + 1][ic >> 1], R[2 * w][ic >> 1], sel);
-        const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-        const f32x4 d0 = mfma_pm1<F16>(A0, bm, z);
-#pragma unroll
-        for (int j = 0; j < NH0; ++j) y[ic][j] = d0[j];
-        if constexpr (NH1 > 0) {
-            const f32x4 d1 = mfma_pm1<F16>(A1, bm, z);
-#pragma unroll
-            for (int j = 0; j < NH1; ++j) y[ic][4 + j] = d1[j];
-        }
-    }
-#pragma unroll
-    for (int s = 1; s < 8; s <<= 1)
-#pragma unroll
-        for (int ic = 0; ic < 8; ++ic)
-            if (!(ic & s))
-#pragma unroll
-                for (int j = 0; j < NV; ++j) {
-                    const float u = y[ic][j], v = y[ic | s][j];
-                    y[ic][j] = u + v;
-                    y[ic | s][j] = u - v;
-                }
-    float m = 0.0f;
-#pragma unroll
-    for (int ic = 0; ic < 8; ++ic) {
-        fused_group<NH0>(&y[ic][0], sf);
-        if constexpr (NH1 > 0) fused_group<NH1>(&y[ic][4], sf);
-#pragma unroll
-        for (int j = 0; j < NV; ++j) m = __builtin_fmaxf(m, __builtin_fabsf(y[ic][j]));
-    }
-    return wave_absmax<4>(m);
-}
-
 template <int BITS, bool FULL, int NV, bool F16 = false>
 __global__ __launch_bounds__(64) void k_wave_block(WaveArgs a, int pb) {
     constexpr int ROW_DWORDS_PER_A = 128 * BITS / 32;
@@ -710,8 +574,9 @@ __global__ __launch_bounds__(64) void k_wave_block_rotate(WaveArgs a, int pb, Bl
 // row are spread over several waves (each repeats the rotation) so the chip is filled.
 // partial[row][k] receives sum e^2 / n^2, the row's mean squared error in the normalised domain.
 template <int T, int BITS, bool F16 = false>
-__global__ __launch_bounds__(64) void k_wave_quant_error(WaveArgs a, ClipList clips, int n_clips,
-                                                         int ksplit, double* partial) {
+__global__ __launch_bounds__(64) void k_wave_quant_error(WaveArgs a, ClipArg ca, int ksplit, double* partial) {
+    const ClipView clips = clip_view(ca);
+    const int n_clips = clips.n;
     constexpr int N = 512 * T;
     const int lane = threadIdx.x;
     const int g = lane >> 4, cphys = lane & 15;
@@ -775,10 +640,55 @@ __global__ __launch_bounds__(64) void k_wave_quant_error(WaveArgs a, ClipList cl
     }
 }
 
+// Few rows: a row split over the S waves of a workgroup as in k_wave_sylvester_split, every wave with all clip ratios
+// of the workgroup's share on its T / S register sets; the rotation is not repeated for each share of the ratios as
+// it is where whole rows are given to several waves (512 x 4096, 15 ratios: see qe_split).
+template <int T, int BITS, int S, bool F16>
+__global__ __launch_bounds__(64 * S) void k_wave_quant_error_split(WaveArgs a, ClipArg ca, int ksplit, double* partial) {
+    constexpr int N = 512 * T, TS = T / S;
+    __shared__ float wmax[S], esum[S][RQ_MAX_CLIPS];
+    const ClipView clips = clip_view(ca);
+    const int lane = threadIdx.x & 63;
+    const int seg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = lane >> 4, cphys = lane & 15;
+    const int c = (cphys & 4) ? (cphys ^ 3) : cphys;
+    const int64_t row = blockIdx.x / ksplit;
+    if (row >= a.rows) return;
+    const int part = (int)(blockIdx.x - row * ksplit);
+    const int per = (clips.n + ksplit - 1) / ksplit;
+    const int k0 = part * per, k1 = k0 + per < clips.n ? k0 + per : clips.n;
+    const u32x4 A0 = a.tiles[lane], A1 = a.tiles[64 + lane];
+    f32x4 acc[TS][2];
+    float m = split_rotate_row<T, false, S, F16>(a, row, seg, c, (g << 4) + c, A0, A1, acc);
+    m = wave_absmax<4>(m);
+    if (lane == 0) wmax[seg] = m;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < S; ++w) m = __builtin_fmaxf(m, wmax[w]);
+    float v[TS * 8];
+#pragma unroll
+    for (int t = 0; t < TS; ++t)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[(t * 2 + h) * 4 + i] = acc[t][h][i];
+    qe_candidates<TS * 8, BITS, 4>(v, m, split_flip<T, S>(c), clips, k0, k1, [&](int k, float e2) {
+        if (lane == 0) esum[seg][k] = e2;
+    });
+    __syncthreads();
+    for (int k = k0 + (int)threadIdx.x; k < k1; k += 64 * S) {
+        float t = 0.0f;
+#pragma unroll
+        for (int w = 0; w < S; ++w) t += esum[w][k];
+        partial[row * clips.n + k] = (double)t / ((double)N * (double)N);
+    }
+}
+
 // The same for the block orders of k_wave_block (n = pb * 128, pb <= 32).
 template <int BITS, bool FULL, int NV, bool F16 = false>
-__global__ __launch_bounds__(64) void k_wave_block_qe(WaveArgs a, int pb, ClipList clips, int n_clips, int ksplit,
-                                                      double* partial) {
+__global__ __launch_bounds__(64) void k_wave_block_qe(WaveArgs a, int pb, ClipArg ca, int ksplit, double* partial) {
+    const ClipView clips = clip_view(ca);
+    const int n_clips = clips.n;
     const int lane = threadIdx.x;
     const int g = lane >> 4, cphys = lane & 15;
     const int c = (cphys & 4) ? (cphys ^ 3) : cphys;
@@ -812,7 +722,9 @@ __global__ __launch_bounds__(64) void k_wave_block_qe(WaveArgs a, int pb, ClipLi
 // The same for short rows (n = 32 << CB: the KV head rows): 16 >> CB rows per wave pass, every
 // clip ratio for every row (there are always enough rows to fill the chip).
 template <int CB, int BITS, bool F16 = false>
-__global__ __launch_bounds__(64) void k_wave_short_qe(WaveArgs a, ClipList clips, int n_clips, double* partial) {
+__global__ __launch_bounds__(64) void k_wave_short_qe(WaveArgs a, ClipArg ca, int ksplit, double* partial) {
+    const ClipView clips = clip_view(ca);
+    const int n_clips = clips.n;
     constexpr int RPW = 16 >> CB;
     constexpr int N = 32 << CB;
     const int lane = threadIdx.x;
@@ -827,9 +739,11 @@ __global__ __launch_bounds__(64) void k_wave_short_qe(WaveArgs a, ClipList clips
     for (int b = 0; b < 4; ++b) sf[b] = ((c >> b) & 1) ? -1.0f : 1.0f;
     const uint32_t sg0 = (c & 1) ? 0x80000000u : 0u;
     const float flip = (__builtin_popcount(c >> 1) & 1) ? -1.0f : 1.0f;   // stages 2.. are the fused ones
-    const int64_t n_pass = (a.rows + RPW - 1) / RPW;
-    for (int64_t pass = blockIdx.x; pass < n_pass; pass += gridDim.x) {
-        const int64_t row = pass * RPW + rsub;
+    const int64_t n_items = (a.rows + RPW - 1) / RPW * ksplit;
+    const int per = ((n_clips + ksplit - 1) / ksplit + 3) & ~3;           // (ratios are taken four at a time)
+    for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
+        const int64_t pass = item / ksplit, row = pass * RPW + rsub;
+        const int k0 = (int)(item - pass * ksplit) * per, k1 = k0 + per < n_clips ? k0 + per : n_clips;
         const bool live = row < a.rows;
         const bool in = live && chunk * 8 < a.d;
         u32x4 raw = load16(a.X + (in ? row * a.ld + chunk * 8 : 0));
@@ -844,7 +758,7 @@ __global__ __launch_bounds__(64) void k_wave_short_qe(WaveArgs a, ClipList clips
         float m = absmax4(absmax4(0.0f, v0), v1);
         m = wave_absmax<CB>(m);
         const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-        qe_candidates<8, BITS, CB>(v, m, flip, clips, 0, n_clips, [&](int k, float e2) {
+        qe_candidates<8, BITS, CB>(v, m, flip, clips, k0, k1, [&](int k, float e2) {
             if (live && g == 0 && c == 0) partial[row * n_clips + k] = (double)e2 / ((double)N * (double)N);
         });
     }
@@ -854,7 +768,9 @@ __global__ __launch_bounds__(64) void k_wave_short_qe(WaveArgs a, ClipList clips
 // 5.1): per clip ratio lo = clip min, Delta = clip (max - min) / (2^b - 1), e = (y - lo) - code Delta;
 // six vector-ALU operations per value and candidate, four candidates at a time.
 template <int BITS, bool F16 = false>
-__global__ __launch_bounds__(64) void k_wave_short_qe_asym(WaveArgs a, ClipList clips, int n_clips, double* partial) {
+__global__ __launch_bounds__(64) void k_wave_short_qe_asym(WaveArgs a, ClipArg ca, int ksplit, double* partial) {
+    const ClipView clips = clip_view(ca);
+    const int n_clips = clips.n;
     constexpr int CB = 2, RPW = 4, N = 128;
     constexpr float kL = (float)((1 << BITS) - 1);
     const int lane = threadIdx.x;
@@ -867,9 +783,11 @@ __global__ __launch_bounds__(64) void k_wave_short_qe_asym(WaveArgs a, ClipList 
     for (int b = 0; b < 4; ++b) sf[b] = ((c >> b) & 1) ? -1.0f : 1.0f;
     const uint32_t sg0 = (c & 1) ? 0x80000000u : 0u;
     const float flip = (c & 2) ? -1.0f : 1.0f;            // the one fused stage (xor-2)
-    const int64_t n_pass = (a.rows + RPW - 1) / RPW;
-    for (int64_t pass = blockIdx.x; pass < n_pass; pass += gridDim.x) {
-        const int64_t row = pass * RPW + rsub;
+    const int64_t n_items = (a.rows + RPW - 1) / RPW * ksplit;
+    const int per = ((n_clips + ksplit - 1) / ksplit + 3) & ~3;           // (ratios are taken four at a time)
+    for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
+        const int64_t pass = item / ksplit, row = pass * RPW + rsub;
+        const int k0 = (int)(item - pass * ksplit) * per, k1 = k0 + per < n_clips ? k0 + per : n_clips;
         const bool live = row < a.rows;
         const bool in = live && chunk * 8 < a.d;
         u32x4 raw = load16(a.X + (in ? row * a.ld + chunk * 8 : 0));
@@ -888,15 +806,15 @@ __global__ __launch_bounds__(64) void k_wave_short_qe_asym(WaveArgs a, ClipList 
         quad_rows_max_pair(mx, nm);
         const double mn64 = -(double)nm, r64 = (double)mx + (double)nm;
         const double inv_r = r64 > 0.0 ? 1.0 / r64 : 0.0;
-        for (int kb = 0; kb < n_clips; kb += 4) {
+        for (int kb = k0; kb < k1; kb += 4) {
             float los[4], sk[4], ndk[4], e2[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int k = kb + j < n_clips ? kb + j : n_clips - 1;
+                const int k = kb + j < k1 ? kb + j : k1 - 1;
                 // the row-independent factors (levels / clip, clip / levels) come with the clip list
-                los[j] = flip * (float)((double)clips.v[k] * mn64);               // lane sign folded in
-                sk[j] = flip * (float)(clips.lvl_over_clip[k] * inv_r);
-                ndk[j] = -flip * (float)(clips.clip_over_lvl[k] * r64);
+                los[j] = flip * (float)((double)clips.v(k) * mn64);               // lane sign folded in
+                sk[j] = flip * (float)(clips.lvl_over_clip(k) * inv_r);
+                ndk[j] = -flip * (float)(clips.clip_over_lvl(k) * r64);
                 e2[j] = 0.0f;
             }
 #pragma unroll
@@ -917,7 +835,7 @@ __global__ __launch_bounds__(64) void k_wave_short_qe_asym(WaveArgs a, ClipList 
             for (int j = 0; j < 4; ++j) e2[j] = rows_sum(e2[j]);
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (live && g == 0 && c == 0 && kb + j < n_clips)
+                if (live && g == 0 && c == 0 && kb + j < k1)
                     partial[row * n_clips + kb + j] = (double)e2[j] / ((double)N * (double)N);
         }
     }
@@ -1344,30 +1262,60 @@ static int qe_ksplit(const rq_hadamard* h, int64_t rows, int n_clips) {
 }
 
 template <int T>
-static int launch_qe(const rq_hadamard* h, const WaveArgs& w, const ClipList& clips, int n_clips,
+static int launch_qe(const rq_hadamard* h, const WaveArgs& w, const ClipArg& clips, int n_clips,
                      int bits, double* partial, hipStream_t s) {
-    const int ksplit = qe_ksplit(h, w.rows, n_clips);
-    const int64_t items = w.rows * ksplit;
-    const int64_t cap = 1 << 24;
-    const unsigned grid = (unsigned)(items < cap ? items : cap);
-    auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, w, clips, n_clips, ksplit, partial); };
-    if (w.f16) {
-        if (bits == 4) go(k_wave_quant_error<T, 4, true>); else go(k_wave_quant_error<T, 3, true>);
-    } else {
-        if (bits == 4) go(k_wave_quant_error<T, 4, false>); else go(k_wave_quant_error<T, 3, false>);
+    // Waves per row: the register sets of a row over two or four waves, as long as each keeps at least two (the sums of a
+    // ratio cross the lanes once per wave).  Orders of 2^13 always - a whole row leaves two waves per SIMD (8192 rows, 32
+    // ratios: 316 -> 267 us) -, shorter ones while there are few rows (512 x 4096, 16 ratios: 12.1 -> 11.7 us, 64 rows:
+    // 8.4 -> 7.2; 2048 rows, 32 ratios: two waves 43.6 -> 42.4, four 45.0; 8192 rows: no difference).  With fewer
+    // rows still, the ratios are divided over workgroups on top.
+    const int64_t simds = (int64_t)h->num_cu * 4;
+    constexpr int SMAX = T >= 8 ? 4 : T >= 4 ? 2 : 1;
+    const int split = T == 16 ? 4 : w.rows > 2 * simds ? 1 : T == 8 && w.rows * 2 > simds ? 2 : SMAX;
+    if (split > 1) {
+        int64_t ksplit = 2 * simds / (w.rows * split);
+        ksplit = ksplit < 1 ? 1 : ksplit > 8 ? 8 : ksplit;
+        if (ksplit > n_clips) ksplit = n_clips;
+        const dim3 grid((unsigned)(w.rows * ksplit));         // (rows * 8 ratios of a workspace: far below 2^31)
+        auto go = [&](auto kernel, int S) { launch_kernel(kernel, grid, dim3(64 * S), 0, s, w, clips, (int)ksplit, partial); };
+        auto pick = [&](auto s_c) {
+            constexpr int S = decltype(s_c)::value;
+            if (w.f16) {
+                if (bits == 4) go(k_wave_quant_error_split<T, 4, S, true>, S); else go(k_wave_quant_error_split<T, 3, S, true>, S);
+            } else {
+                if (bits == 4) go(k_wave_quant_error_split<T, 4, S, false>, S); else go(k_wave_quant_error_split<T, 3, S, false>, S);
+            }
+        };
+        if constexpr (SMAX == 4)
+            if (split == 4) pick(std::integral_constant<int, 4>{});
+        if constexpr (SMAX >= 2 && T != 16)
+            if (split == 2) pick(std::integral_constant<int, 2>{});
+        return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    }
+    if constexpr (T < 16) {
+        const int ksplit = qe_ksplit(h, w.rows, n_clips);
+        const int64_t items = w.rows * ksplit;
+        const int64_t cap = 1 << 24;
+        const unsigned grid = (unsigned)(items < cap ? items : cap);
+        auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, w, clips, ksplit, partial); };
+        if (w.f16) {
+            if (bits == 4) go(k_wave_quant_error<T, 4, true>); else go(k_wave_quant_error<T, 3, true>);
+        } else {
+            if (bits == 4) go(k_wave_quant_error<T, 4, false>); else go(k_wave_quant_error<T, 3, false>);
+        }
     }
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }
 
 template <int NV>
-static int launch_block_qe(const rq_hadamard* h, const WaveArgs& w, int pb, const ClipList& clips, int n_clips,
+static int launch_block_qe(const rq_hadamard* h, const WaveArgs& w, int pb, const ClipArg& clips, int n_clips,
                            int bits, double* partial, hipStream_t s) {
     const int ksplit = qe_ksplit(h, w.rows, n_clips);
     const int64_t items = w.rows * ksplit;
     const int64_t cap = 1 << 24;
     const dim3 grid((unsigned)(items < cap ? items : cap)), block(64);
     const bool full = w.d == pb * 128;
-    auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, w, pb, clips, n_clips, ksplit, partial); };
+    auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, w, pb, clips, ksplit, partial); };
     if (w.f16) {
         if (bits == 4) { if (full) go(k_wave_block_qe<4, true, NV, true>); else go(k_wave_block_qe<4, false, NV, true>); }
         else { if (full) go(k_wave_block_qe<3, true, NV, true>); else go(k_wave_block_qe<3, false, NV, true>); }
@@ -1378,13 +1326,21 @@ static int launch_block_qe(const rq_hadamard* h, const WaveArgs& w, int pb, cons
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }
 
+// Short rows: passes of a launch and, with fewer of them than two to a SIMD, workgroups that share a pass's ratios.
+static dim3 short_qe_grid(const rq_hadamard* h, int64_t rows, int rpw, int n_clips, int* ksplit) {
+    const int64_t passes = (rows + rpw - 1) / rpw, want = (int64_t)h->num_cu * 8 / passes;
+    const int most = (n_clips + 3) / 4;
+    *ksplit = want < 1 ? 1 : want > most ? most : (int)want;
+    const int64_t items = passes * *ksplit, cap = 1 << 24;
+    return dim3((unsigned)(items < cap ? items : cap));
+}
+
 template <int CB>
-static int launch_short_qe(const WaveArgs& w, const ClipList& clips, int n_clips, int bits, double* partial,
+static int launch_short_qe(const rq_hadamard* h, const WaveArgs& w, const ClipArg& clips, int n_clips, int bits, double* partial,
                            hipStream_t s) {
-    const int64_t passes = (w.rows + (16 >> CB) - 1) / (16 >> CB);
-    const int64_t cap = 1 << 24;
-    const dim3 grid((unsigned)(passes < cap ? passes : cap)), block(64);
-    auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, w, clips, n_clips, partial); };
+    int ksplit;
+    const dim3 grid = short_qe_grid(h, w.rows, 16 >> CB, n_clips, &ksplit), block(64);
+    auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, w, clips, ksplit, partial); };
     if (w.f16) {
         if (bits == 4) go(k_wave_short_qe<CB, 4, true>); else go(k_wave_short_qe<CB, 3, true>);
     } else {
@@ -1393,16 +1349,15 @@ static int launch_short_qe(const WaveArgs& w, const ClipList& clips, int n_clips
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }
 
-int wave_quant_error_asym(const rq_hadamard* h, const RowArgs& a, const ClipList& clips, int n_clips,
-                          double* partial, hipStream_t s) {
+int wave_quant_error_asym(const rq_hadamard* h, const RowArgs& a, const ClipArg& clips, int n_clips, double* partial,
+                          hipStream_t s) {
     const bool f16 = a.dtype == RQ_F16;
     WaveArgs w{static_cast<const uint16_t*>(a.X), a.rows, a.d, a.ld,
                static_cast<const u32x4*>(f16 ? h->d_tiles_f16 : h->d_tiles), nullptr, nullptr, 0.0, 0.0};
     w.f16 = f16;
-    const int64_t passes = (w.rows + 3) / 4;
-    const int64_t cap = 1 << 24;
-    const dim3 grid((unsigned)(passes < cap ? passes : cap)), block(64);
-    auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, w, clips, n_clips, partial); };
+    int ksplit;
+    const dim3 grid = short_qe_grid(h, w.rows, 4, n_clips, &ksplit), block(64);
+    auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, w, clips, ksplit, partial); };
     if (f16) {
         if (a.bits == 4) go(k_wave_short_qe_asym<4, true>); else go(k_wave_short_qe_asym<3, true>);
     } else {
@@ -1411,7 +1366,7 @@ int wave_quant_error_asym(const rq_hadamard* h, const RowArgs& a, const ClipList
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }
 
-int wave_quant_error(const rq_hadamard* h, const RowArgs& a, const ClipList& clips, int n_clips,
+int wave_quant_error(const rq_hadamard* h, const RowArgs& a, const ClipArg& clips, int n_clips,
                      double* partial, hipStream_t s) {
     const bool f16 = a.dtype == RQ_F16;
     WaveArgs w{static_cast<const uint16_t*>(a.X), a.rows, a.d, a.ld,
@@ -1431,9 +1386,9 @@ int wave_quant_error(const rq_hadamard* h, const RowArgs& a, const ClipList& cli
         }
     }
     switch (a.log2m) {
-        case 7: return launch_short_qe<2>(w, clips, n_clips, a.bits, partial, s);
-        case 8: return launch_short_qe<3>(w, clips, n_clips, a.bits, partial, s);
-        case 9: return launch_short_qe<4>(w, clips, n_clips, a.bits, partial, s);
+        case 7: return launch_short_qe<2>(h, w, clips, n_clips, a.bits, partial, s);
+        case 8: return launch_short_qe<3>(h, w, clips, n_clips, a.bits, partial, s);
+        case 9: return launch_short_qe<4>(h, w, clips, n_clips, a.bits, partial, s);
         case 10: return launch_qe<2>(h, w, clips, n_clips, a.bits, partial, s);
         case 11: return launch_qe<4>(h, w, clips, n_clips, a.bits, partial, s);
         case 12: return launch_qe<8>(h, w, clips, n_clips, a.bits, partial, s);

@@ -134,8 +134,8 @@ static int launch_by_kk(const rq_hadamard* h, const WaveArgs& w, int bits, int p
     }
 }
 
-int wg_block_quant_error(const rq_hadamard* h, const RowArgs& a, const ClipList& clips, int n_clips,
-                         double* partial, hipStream_t s) {
+int wg_block_quant_error(const rq_hadamard* h, const RowArgs& a, const ClipArg& clips, int max_clips, double* partial,
+                         hipStream_t s) {
     int pb, cb;
     if (!wg_shape(a, &pb, &cb)) return RQ_ERR_NO_ORDER;
     const bool f16 = a.dtype == RQ_F16;
@@ -144,8 +144,8 @@ int wg_block_quant_error(const rq_hadamard* h, const RowArgs& a, const ClipList&
     w.f16 = f16;
     QeArgs qe;
     qe.clips = clips;
-    qe.n_clips = n_clips;
     qe.partial = partial;
+    qe.max_shares = (max_clips + 3) / 4;                 // (ratios are taken four at a time)
     return launch_by_kk<kWgError>(h, w, a.bits, pb, cb, s, qe);
 }
 

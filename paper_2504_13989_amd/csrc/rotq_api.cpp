@@ -1,6 +1,10 @@
 // C ABI: argument validation, handle management and kernel dispatch.
+#include <algorithm>
+#include <chrono>
 #include <cmath>
+#include <cstddef>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -430,6 +434,31 @@ size_t rq_quant_error_workspace(int64_t rows, int n_clips) {
 
 }  // extern "C"
 
+// The pass over the rows of a quant_error evaluation: partial[rows][number of clips].
+static int quant_error_rows(const rq_hadamard_t* h, const rq::RowArgs& a, const rq::ClipArg& cl, int max_clips, double* partial,
+                            bool asym, hipStream_t s) {
+    if (asym) {
+        if (h->variant == 0 && a.rows > 0 && rq::wave_asym_supports(h, a)) {
+            note(h, "wave_quant_error_asym");
+            return rq::wave_quant_error_asym(h, a, cl, max_clips, partial, s);
+        }
+        if (!rq::generic_supports(h)) return RQ_ERR_NO_ORDER;
+        note(h, "generic_lds_asym");
+        return rq::generic_quant_error_asym(h, a, cl, partial, s);
+    }
+    if (h->variant == 0 && a.rows > 0 && rq::wave_quant_error_supports(h, a)) {
+        note(h, "wave_quant_error");
+        return rq::wave_quant_error(h, a, cl, max_clips, partial, s);
+    }
+    if (h->variant == 0 && a.rows > 0 && rq::wg_block_supports(h, a, true)) {
+        note(h, "wg_block_quant_error");
+        return rq::wg_block_quant_error(h, a, cl, max_clips, partial, s);
+    }
+    if (!rq::generic_supports(h)) return RQ_ERR_NO_ORDER;
+    note(h, "generic_lds");
+    return rq::generic_quant_error(h, a, cl, partial, s);
+}
+
 int rq::quant_error_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t rows, int d,
                          int64_t ld, int bits, const float* clips, int n_clips, float* mse,
                          void* workspace, size_t workspace_bytes, void* stream, bool asym) {
@@ -439,44 +468,20 @@ int rq::quant_error_impl(const rq_hadamard_t* h, const void* X, int dtype, int64
     if (!clips || n_clips < 1 || n_clips > RQ_MAX_CLIPS) return RQ_ERR_ARG;
     if (!mse || !aligned(mse, 4) || !workspace || !aligned(workspace, 8)) return RQ_ERR_ARG;
     if (workspace_bytes < rq_quant_error_workspace(rows, n_clips)) return RQ_ERR_ARG;
-    rq::ClipList cl;
+    rq::ClipArg cl;
     std::memset(&cl, 0, sizeof cl);
+    cl.list.n = n_clips;
     for (int k = 0; k < n_clips; ++k) {
         if (!clip_ok(clips[k])) return RQ_ERR_ARG;
-        cl.v[k] = clips[k];
-        const double lvl = (double)((1 << bits) - 1);
-        cl.lvl_over_clip[k] = lvl / (double)clips[k];
-        cl.clip_over_lvl[k] = (double)clips[k] / lvl;
+        cl.list.set(k, clips[k], (double)((1 << bits) - 1));
     }
     if (h->device < 0) return RQ_ERR_HIP;
     const rq::RowArgs a = row_args(h, X, dtype, rows, d, ld, bits);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (asym) {
-        if (h->variant == 0 && rows > 0 && rq::wave_asym_supports(h, a)) {
-            note(h, "wave_quant_error_asym");
-            rc = rq::wave_quant_error_asym(h, a, cl, n_clips, static_cast<double*>(workspace), s);
-            if (rc != RQ_OK) return rc;
-            return rq::reduce_partials(static_cast<double*>(workspace), rows, n_clips, mse, s);
-        }
-        if (!rq::generic_supports(h)) return RQ_ERR_NO_ORDER;
-        note(h, "generic_lds_asym");
-        return rq::generic_quant_error_asym(h, a, cl, n_clips, mse, static_cast<double*>(workspace), s);
-    }
-    if (h->variant == 0 && rows > 0 && rq::wave_quant_error_supports(h, a)) {
-        note(h, "wave_quant_error");
-        rc = rq::wave_quant_error(h, a, cl, n_clips, static_cast<double*>(workspace), s);
-        if (rc != RQ_OK) return rc;
-        return rq::reduce_partials(static_cast<double*>(workspace), rows, n_clips, mse, s);
-    }
-    if (h->variant == 0 && rows > 0 && rq::wg_block_supports(h, a, true)) {
-        note(h, "wg_block_quant_error");
-        rc = rq::wg_block_quant_error(h, a, cl, n_clips, static_cast<double*>(workspace), s);
-        if (rc != RQ_OK) return rc;
-        return rq::reduce_partials(static_cast<double*>(workspace), rows, n_clips, mse, s);
-    }
-    if (!rq::generic_supports(h)) return RQ_ERR_NO_ORDER;
-    note(h, "generic_lds");
-    return rq::generic_quant_error(h, a, cl, n_clips, mse, static_cast<double*>(workspace), s);
+    double* partial = static_cast<double*>(workspace);
+    rc = quant_error_rows(h, a, cl, n_clips, partial, asym, s);
+    if (rc != RQ_OK) return rc;
+    return rq::reduce_partials(partial, rows, n_clips, mse, s);
 }
 
 extern "C" {
@@ -496,11 +501,96 @@ int rq_quant_error_asym(const rq_hadamard_t* h, const void* X, int dtype, int64_
 }
 
 namespace {
-// Probes evaluated per batch of the search: 5 steps ahead (the 31 nodes of the outcome tree, plus the
-// starting point in the first batch) on small tensors, 3 steps (7 nodes + 1) on large ones, where the
-// extra candidates would cost more than the launches they save.
+// Steps a batch of the search looks ahead: up to 5 (the 31 nodes of the outcome tree, plus the starting point in the
+// first batch) on small tensors, up to 3 (7 nodes + 1) on large ones, where the extra candidates would cost more than
+// the passes they save.
 constexpr int64_t kGbsSmall = (int64_t)1 << 22;              // rows * n up to which 5 steps are taken
 int gbs_depth(int64_t rows, int n) { return (double)rows * (double)n <= (double)kGbsSmall ? 5 : 3; }
+
+// Most steps a search down to a bracket of eps can take: two steps halve the bracket (from 1, by way of 3/4).
+int gbs_most_steps(double eps, int limit) {
+    int steps = 0;
+    for (double w = 1.0; w > eps && steps < limit; ++steps) w = steps % 2 == 0 ? w * 0.75 : w / 1.5;
+    return steps;
+}
+
+// What a search needs besides the caller's workspace: its state on the device and the results in host memory the device
+// writes.  Sets are kept for the next search on the same device, as many as ever ran at one time.
+struct SearchMem {
+    int device;
+    uint32_t epoch;           // first step number that is not in `exchange`
+    uint64_t* exchange;       // of the resident form: two buffers, taken in turn
+    rq::GbsDev* state;
+    rq::GbsOut* out;          // pinned, mapped
+    rq::GbsOut* out_dev;
+};
+// Devices on which a resident search is under way: one at a time, since two of them could each keep the other's
+// workgroups from running (a second one takes the batched form).
+std::mutex g_search_lock;
+std::vector<int>& resident_on() {
+    static std::vector<int>* devices = new std::vector<int>;
+    return *devices;
+}
+class ResidentTurn {
+    int device_;
+    bool mine_ = false;
+public:
+    explicit ResidentTurn(int device) : device_(device) {       // (negative: none is wanted)
+        if (device < 0) return;
+        std::lock_guard<std::mutex> hold(g_search_lock);
+        std::vector<int>& on = resident_on();
+        if (std::find(on.begin(), on.end(), device) == on.end()) {
+            on.push_back(device);
+            mine_ = true;
+        }
+    }
+    ~ResidentTurn() {
+        if (!mine_) return;
+        std::lock_guard<std::mutex> hold(g_search_lock);
+        std::vector<int>& on = resident_on();
+        on.erase(std::find(on.begin(), on.end(), device_));
+    }
+    ResidentTurn(const ResidentTurn&) = delete;
+    ResidentTurn& operator=(const ResidentTurn&) = delete;
+    explicit operator bool() const { return mine_; }
+};
+std::vector<SearchMem>& search_pool() {
+    static std::vector<SearchMem>* pool = new std::vector<SearchMem>;     // not torn down before the runtime is
+    return *pool;
+}
+
+int take_search_mem(int device, SearchMem* m) {
+    {
+        std::lock_guard<std::mutex> hold(g_search_lock);
+        std::vector<SearchMem>& pool = search_pool();
+        for (size_t i = 0; i < pool.size(); ++i)
+            if (pool[i].device == device) {
+                *m = pool[i];
+                pool.erase(pool.begin() + (std::ptrdiff_t)i);
+                return RQ_OK;
+            }
+    }
+    int cur = -1;
+    void *state = nullptr, *out = nullptr, *out_dev = nullptr;
+    const size_t ex = 2 * rq::gbs_exchange_bytes();       // (the state follows it in the same allocation)
+    if (hipGetDevice(&cur) == hipSuccess && cur == device && hipMalloc(&state, ex + rq::gbs_state_bytes()) == hipSuccess &&
+        hipMemset(state, 0, ex) == hipSuccess && hipDeviceSynchronize() == hipSuccess &&
+        hipHostMalloc(&out, sizeof(rq::GbsOut), hipHostMallocMapped) == hipSuccess &&
+        hipHostGetDevicePointer(&out_dev, out, 0) == hipSuccess && out_dev) {
+        *m = SearchMem{device, 1u, static_cast<uint64_t*>(state),
+                       reinterpret_cast<rq::GbsDev*>(static_cast<char*>(state) + ex), static_cast<rq::GbsOut*>(out), static_cast<rq::GbsOut*>(out_dev)};
+        return RQ_OK;
+    }
+    if (state) (void)hipFree(state);
+    if (out) (void)hipHostFree(out);
+    (void)hipGetLastError();
+    return RQ_ERR_HIP;
+}
+
+void give_search_mem(const SearchMem& m) {
+    std::lock_guard<std::mutex> hold(g_search_lock);
+    search_pool().push_back(m);
+}
 }  // namespace
 
 size_t rq_gbs_workspace(int64_t rows) {
@@ -510,75 +600,6 @@ size_t rq_gbs_workspace(int64_t rows) {
     const size_t q = rq_quant_error_workspace(rows, cands);
     return q ? q + 256 : 0;
 }
-
-namespace {
-
-// State of Algorithm 1's inner loop (section 4.1): bracket [a, b], best point m, iteration parity.
-// RQ_MAX_CLIPS floats of pinned host memory and their device address, one buffer per host thread and device,
-// allocated at the first search of that thread on that device and kept until the process ends (a search is a
-// host loop that synchronises its stream, so the buffer is never in use by two searches at once).
-struct MappedVals {
-    float* host = nullptr;
-    float* dev = nullptr;
-};
-
-MappedVals mapped_vals(int device) {
-    struct Entry { int device; MappedVals mv; };
-    thread_local std::vector<Entry> cache;
-    for (const Entry& e : cache)
-        if (e.device == device) return e.mv;
-    MappedVals mv;
-    int cur = -1;
-    void* hp = nullptr;
-    void* dp = nullptr;
-    if (hipGetDevice(&cur) == hipSuccess && cur == device &&
-        hipHostMalloc(&hp, sizeof(float) * RQ_MAX_CLIPS, hipHostMallocMapped) == hipSuccess) {
-        if (hipHostGetDevicePointer(&dp, hp, 0) == hipSuccess && dp) {
-            mv.host = static_cast<float*>(hp);
-            mv.dev = static_cast<float*>(dp);
-        } else {
-            (void)hipHostFree(hp);
-        }
-    }
-    (void)hipGetLastError();
-    cache.push_back(Entry{device, mv});
-    return mv;
-}
-
-// State of the search of Algorithm 1 (section 4.1): the best point so far and the nearest evaluated
-// point on either side of it; probes go to the midpoint towards the left and the right neighbour in turn.
-struct GbsState {
-    double near[2];       // nearest evaluated points: [0] left of best, [1] right of best
-    double best;
-    int side;             // neighbour the next probe goes towards
-    double width() const { return near[1] - near[0]; }
-    double probe() const { return 0.5 * (near[side] + best); }
-    // after probing x = probe(): `better` = the probe beat the best point, which then bounds the far side
-    GbsState next(double x, bool better) const {
-        GbsState n = *this;
-        if (better) {
-            n.near[1 - side] = best;
-            n.best = x;
-        } else {
-            n.near[side] = x;
-        }
-        n.side = 1 - side;
-        return n;
-    }
-};
-
-// Probes of the next `depth` steps for every outcome of the comparisons on the way, in heap order
-// (node i: children 2 i for "better", 2 i + 1 for "not better"); the positions do not depend on the
-// objective values, only on the outcomes.  x[i] < 0 marks a node the search cannot reach.
-void gbs_tree(const GbsState& st, double eps, int depth, int idx, double* x) {
-    if (depth == 0 || st.width() <= eps) return;
-    const double p = st.probe();
-    x[idx] = p;
-    gbs_tree(st.next(p, true), eps, depth - 1, 2 * idx, x);
-    gbs_tree(st.next(p, false), eps, depth - 1, 2 * idx + 1, x);
-}
-
-}  // namespace
 
 static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t rows, int d, int64_t ld,
                     int bits, float eps, int max_evals, void* workspace, size_t workspace_bytes,
@@ -591,84 +612,74 @@ static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t ro
     if (!clip_out || !mse_out || !workspace || !aligned(workspace, 8)) return RQ_ERR_ARG;
     if (workspace_bytes < rq_gbs_workspace(rows)) return RQ_ERR_ARG;
     if (h->device < 0) return RQ_ERR_HIP;
-    // layout of the workspace: [0, 256) the objective values of one batch, then the quant_error scratch
-    float* d_mse = static_cast<float*>(workspace);
-    void* qws = static_cast<char*>(workspace) + 256;
-    const size_t qws_bytes = workspace_bytes - 256;
+    double* partial = static_cast<double*>(workspace);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // The probes of Algorithm 1 are taken in the listing's order, but evaluated ahead of time in
-    // batches: one quant_error launch covers every probe the next `depth` steps can ask for (a binary
-    // tree over the comparison outcomes), then the host walks the tree with the values.  The values
-    // and the sequence of probes are those of the one-at-a-time loop; what changes is the number of
-    // launches and stream synchronisations (each costs more than a candidate on a small tensor).
-    // Small tensors look 5 steps ahead (31 candidates), large ones 3 (7 candidates: about the work
-    // of the 3 rotations it saves).
-    const int depth = gbs_depth(rows, h->f.n);
-    float vals[RQ_MAX_CLIPS];
-    float clips[RQ_MAX_CLIPS];
-    // The objective values of a batch come back through pinned host memory that the reduction kernel writes
-    // itself (mapped into the device's address space): a batch then costs one synchronisation of the caller's
-    // stream and no copy.  Where that memory cannot be had, they are copied back on the same stream.
-    const MappedVals mv = mapped_vals(h->device);
-    auto evaluate = [&](int count) -> int {
-        float* out = mv.dev ? mv.dev : d_mse;
-        int r = rq::quant_error_impl(h, X, dtype, rows, d, ld, bits, clips, count, out, qws, qws_bytes, stream, asym);
-        if (r != RQ_OK) return r;
-        if (mv.dev) {
-            if (hipStreamSynchronize(s) != hipSuccess) return RQ_ERR_HIP;
-            std::memcpy(vals, mv.host, sizeof(float) * count);
-            return RQ_OK;
+    const rq::RowArgs a = row_args(h, X, dtype, rows, d, ld, bits);
+    SearchMem mem;
+    rc = take_search_mem(h->device, &mem);
+    if (rc != RQ_OK) return rc;
+    mem.out->done = 0;
+    const volatile int* done = &mem.out->done;
+    auto finish = [&](int code) {
+        if (code == RQ_OK) {
+            const rq::GbsOut& o = *mem.out;
+            *clip_out = o.clip;
+            *mse_out = o.mse;
+            if (trace_clips) std::memcpy(trace_clips, o.trace_clips, sizeof(float) * (size_t)o.evals);
+            if (trace_mse) std::memcpy(trace_mse, o.trace_mse, sizeof(float) * (size_t)o.evals);
+            if (n_evals) *n_evals = o.evals;
         }
-        // read back on the caller's stream: no other stream is made to wait
-        if (hipMemcpyAsync(vals, d_mse, sizeof(float) * count, hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            return RQ_ERR_HIP;
-        return RQ_OK;
+        give_search_mem(mem);
+        return code;
     };
-    int evals = 0;
-    auto record = [&](float c, float v) {
-        if (trace_clips) trace_clips[evals] = c;
-        if (trace_mse) trace_mse[evals] = v;
-        ++evals;
-    };
-    GbsState st{{0.0, 1.0}, 0.5, 0};
-    float fm = 0.0f;
-    bool first = true;
-    while (first || (st.width() > (double)eps && evals < max_evals)) {
-        double x[64];
-        int slot[64];
-        for (int i = 0; i < 64; ++i) x[i] = -1.0;
-        gbs_tree(st, (double)eps, depth, 1, x);
-        int count = 0;
-        if (first) clips[count++] = (float)st.best;          // the starting point rides along with the first batch
-        for (int i = 1; i < (1 << depth); ++i)
-            if (x[i] >= 0.0) {
-                slot[i] = count;
-                clips[count++] = (float)x[i];
-            }
-        if (count == 0) break;
-        rc = evaluate(count);
-        if (rc != RQ_OK) return rc;
-        if (first) {
-            fm = vals[0];
-            record(clips[0], fm);
-            first = false;
+    const bool can_stay = !asym && h->variant == 0 && rq::gbs_resident_supports(h, a);
+    if (const ResidentTurn turn{can_stay ? h->device : -1}; can_stay && turn) {
+        note(h, "wave_quant_error");
+        // step numbers have 16 bits: when they are used up, the buffers are cleared and they start again
+        constexpr uint32_t kSteps = 512;                     // more than the steps of any search
+        if (mem.epoch + kSteps > 0xffffu) {
+            if (hipMemsetAsync(mem.exchange, 0, 2 * rq::gbs_exchange_bytes(), s) != hipSuccess) return finish(RQ_ERR_HIP);
+            mem.epoch = 1;
         }
-        int idx = 1;
-        for (int lvl = 0; lvl < depth && st.width() > (double)eps && evals < max_evals; ++lvl) {
-            const double p = x[idx];
-            const float fx = vals[slot[idx]];
-            record((float)p, fx);
-            const bool better = fx < fm;
-            if (better) fm = fx;
-            st = st.next(p, better);
-            idx = 2 * idx + (better ? 0 : 1);
+        // (searches take the buffers in turn: the host goes on when the result has arrived, and a workgroup of this
+        // search may then still be reading the last step's words)
+        uint64_t* const buf = mem.exchange + (mem.epoch / kSteps & 1) * (rq::gbs_exchange_bytes() / sizeof(uint64_t));
+        rc = rq::gbs_resident(h, a, mem.out_dev, buf, mem.epoch, (double)eps, max_evals, s);
+        mem.epoch += kSteps;
+        if (rc != RQ_OK) return finish(rc);
+        // The result arrives in host memory before the runtime reports the stream done: worth about 5 us to look there.
+        const auto began = std::chrono::steady_clock::now();
+        for (int spin = 1; !*done; ++spin) {
+            __builtin_ia32_pause();
+            if (spin % 256 == 0 && std::chrono::steady_clock::now() - began > std::chrono::milliseconds(5)) break;
         }
+        std::atomic_thread_fence(std::memory_order_acquire);
+        if (*done) return finish(RQ_OK);
+        if (hipStreamSynchronize(s) != hipSuccess) return finish(RQ_ERR_HIP);
+        if (*done) return finish(RQ_OK);
+        // other work kept part of the search from running: the batched form needs no two workgroups at one time
     }
-    *clip_out = (float)st.best;
-    *mse_out = fm;
-    if (n_evals) *n_evals = evals;
-    return RQ_OK;
+    // as few batches as the depth allows, each no deeper than that number needs (16 steps: four batches of four, 61
+    // candidates, where batches of five would evaluate 95)
+    const int steps = gbs_most_steps((double)eps, max_evals - 1);
+    const int deepest = gbs_depth(rows, h->f.n);
+    const int batches = steps > 0 ? (steps + deepest - 1) / deepest : 1;
+    const int depth = steps > 0 ? (steps + batches - 1) / batches : 1;
+    const int most = 1 << depth;                             // clip ratios of a batch
+    rq::ClipArg cl;
+    std::memset(&cl, 0, sizeof cl);
+    rq::gbs_first_batch((double)eps, depth, bits, &cl.list);
+    for (int b = 0; b < batches && rc == RQ_OK && !*done; ++b) {
+        const bool first = b == 0;
+        if (!first) cl.dev = rq::gbs_state_clips(mem.state);
+        int64_t count = 0, stride = 0;
+        rc = quant_error_rows(h, a, cl, most, partial, asym, s);
+        if (rc == RQ_OK) rc = rq::reduce_chunks(partial, rows, first ? cl.list.n : most, cl.dev, &count, &stride, s);
+        if (rc == RQ_OK)
+            rc = rq::gbs_step(mem.state, mem.out_dev, first, (double)eps, depth, max_evals, bits, partial, rows, count, stride, s);
+    }
+    if (hipStreamSynchronize(s) != hipSuccess && rc == RQ_OK) rc = RQ_ERR_HIP;
+    return finish(rc == RQ_OK && !*done ? RQ_ERR_HIP : rc);
 }
 
 int rq_gbs_search(const rq_hadamard_t* h, const void* X, int dtype, int64_t rows, int d, int64_t ld,

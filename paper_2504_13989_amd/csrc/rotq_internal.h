@@ -73,18 +73,31 @@ struct OutArgs {
 
 struct ClipList {
     float v[RQ_MAX_CLIPS];
-    // row-independent factors of the candidate scales, formed once on the host in fp64:
-    // levels / clip and clip / levels, levels = 2^b - 1
+    // row-independent factors of the candidate scales, formed once in fp64: levels / clip and clip / levels,
+    // levels = 2^b - 1
     double lvl_over_clip[RQ_MAX_CLIPS];
     double clip_over_lvl[RQ_MAX_CLIPS];
+    int n;
+    __host__ __device__ void set(int k, float clip, double levels) {
+        v[k] = clip;
+        lvl_over_clip[k] = levels / (double)clip;
+        clip_over_lvl[k] = (double)clip / levels;
+    }
+};
+// The clip ratios of a launch: those handed over with it, or a list in device memory that an earlier kernel on the
+// stream wrote (the search, whose next ratios depend on values only the device has seen).
+struct ClipArg {
+    ClipList list;
+    const ClipList* dev;
 };
 
 // General LDS kernels: one workgroup per row, any supported order that fits in LDS.
 // Return RQ_OK / RQ_ERR_*.
 int generic_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float clip, uint32_t* codes,
                             float* scales, hipStream_t s);
-int generic_quant_error(const rq_hadamard* h, const RowArgs& a, const ClipList& clips, int n_clips,
-                        float* mse, double* partial, hipStream_t s);
+// quant_error: the row kernels fill partial[rows][number of clips]; `max_clips` bounds that number for the launch
+// where only the device knows it.  reduce_partials then averages over rows.
+int generic_quant_error(const rq_hadamard* h, const RowArgs& a, const ClipArg& clips, double* partial, hipStream_t s);
 int generic_rotate_quantize_asym(const rq_hadamard* h, const RowArgs& a, float clip, uint32_t* codes,
                                  float* scales, float* mins, hipStream_t s);
 // Rotation with a floating-point result (H_n or H_n^T), from rows or from packed codes.
@@ -119,16 +132,16 @@ int wave_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float clip, uin
 bool wave_asym_supports(const rq_hadamard* h, const RowArgs& a);
 int wave_rotate_quantize_asym(const rq_hadamard* h, const RowArgs& a, float clip, uint32_t* codes,
                               float* scales, float* mins, hipStream_t s);
-// quant_error on the wave path (bf16, Sylvester orders 1024 .. 8192): fills partial[rows][n_clips];
-// reduce_partials then averages over rows.
 bool wave_quant_error_supports(const rq_hadamard* h, const RowArgs& a);
-int wave_quant_error(const rq_hadamard* h, const RowArgs& a, const ClipList& clips, int n_clips,
+int wave_quant_error(const rq_hadamard* h, const RowArgs& a, const ClipArg& clips, int max_clips,
                      double* partial, hipStream_t s);
-int wave_quant_error_asym(const rq_hadamard* h, const RowArgs& a, const ClipList& clips, int n_clips,
-                          double* partial, hipStream_t s);
-int generic_quant_error_asym(const rq_hadamard* h, const RowArgs& a, const ClipList& clips, int n_clips,
-                             float* mse, double* partial, hipStream_t s);
+int wave_quant_error_asym(const rq_hadamard* h, const RowArgs& a, const ClipArg& clips, int max_clips, double* partial,
+                          hipStream_t s);
+int generic_quant_error_asym(const rq_hadamard* h, const RowArgs& a, const ClipArg& clips, double* partial, hipStream_t s);
 int reduce_partials(double* partial, int64_t rows, int n_clips, float* mse, hipStream_t s);
+// First level of that reduction for many rows: sums over chunks of rows, each left in the chunk's own first row of
+// `partial`.  Returns the number of sums per clip ratio and their distance in rows; RQ_OK or an error.
+int reduce_chunks(double* partial, int64_t rows, int n_clips, const ClipList* dev, int64_t* count, int64_t* stride, hipStream_t s);
 // Block kernel: bf16 rows, n = pb * 128 with a +-1 block of order pb <= 32 (Paley (x) small
 // Sylvester) on the matrix cores.
 std::vector<uint32_t> wave_block_tiles(const std::vector<int8_t>& bm, int pb);
@@ -195,8 +208,29 @@ int wg_dequant_rotate(const rq_hadamard* h, const RowArgs& a, const uint32_t* co
 bool wg_block_supports(const rq_hadamard* h, const RowArgs& a, bool quant_error = false);
 int wg_block_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float clip, uint32_t* codes,
                              float* scales, hipStream_t s);
-int wg_block_quant_error(const rq_hadamard* h, const RowArgs& a, const ClipList& clips, int n_clips,
-                         double* partial, hipStream_t s);
+int wg_block_quant_error(const rq_hadamard* h, const RowArgs& a, const ClipArg& clips, int max_clips, double* partial,
+                         hipStream_t s);
+
+// One step of the clip search on the device (kernels_search.hip): the batch of objective values in `partial` is
+// averaged, the search walks on with them and leaves its next batch of clip ratios in *state.
+struct GbsDev;
+struct GbsOut {               // host memory the device writes (pinned, mapped)
+    float clip, mse;          // the best point and its objective
+    int evals;
+    int done;                 // set last
+    float trace_clips[256], trace_mse[256];
+};
+size_t gbs_state_bytes();
+const ClipList* gbs_state_clips(const GbsDev* state);
+// The first batch of a search, `depth` steps ahead: the starting point and every probe those steps can ask for.
+void gbs_first_batch(double eps, int depth, int bits, ClipList* out);
+// The whole search in one launch, for rows the chip holds in registers all at once; false where it does not.
+bool gbs_resident_supports(const rq_hadamard* h, const RowArgs& a);
+size_t gbs_exchange_bytes();
+int gbs_resident(const rq_hadamard* h, const RowArgs& a, GbsOut* out, uint64_t* exchange, uint32_t epoch, double eps, int max_evals,
+                 hipStream_t s);
+int gbs_step(GbsDev* state, GbsOut* out, bool first, double eps, int depth, int max_evals, int bits, const double* partial,
+             int64_t rows, int64_t count, int64_t stride, hipStream_t s);
 
 // The shared body of rq_quant_error / rq_quant_error_asym (argument checks, dispatch, reduction).
 int quant_error_impl(const rq_hadamard* h, const void* X, int dtype, int64_t rows, int d, int64_t ld, int bits,

@@ -560,6 +560,24 @@ __device__ __forceinline__ CodeAt code_at(int idx) {
     return CodeAt{byte & ~3u, (byte & ~3u) + (sh >= 16u ? 4u : 0u), sh};
 }
 
+// The clip ratios of a launch as the kernels read them: scalar loads from the constant address space, from the launch's
+// own arguments or from the list in device memory.
+#define RQ_CONST __attribute__((address_space(4)))
+struct ClipView {
+    const RQ_CONST ClipList* p;
+    int n;
+    __device__ __forceinline__ float v(int k) const { return p->v[k]; }
+    __device__ __forceinline__ double lvl_over_clip(int k) const { return p->lvl_over_clip[k]; }
+    __device__ __forceinline__ double clip_over_lvl(int k) const { return p->clip_over_lvl[k]; }
+};
+__device__ __forceinline__ ClipView clip_view(const ClipArg& a) {
+    const ClipList* l = a.dev ? a.dev : &a.list;
+    ClipView c;
+    c.p = (const RQ_CONST ClipList*)l;
+    c.n = c.p->n;
+    return c;
+}
+
 // Squared quantization error of one rotated row for the clip ratios [k0, k1) (sections 2.1, 3.1):
 // t = y / Delta_k, r = clamp(round(t)), e = y - r Delta_k, sum e^2 - five vector-ALU operations per
 // value and candidate, four candidates at a time (independent chains, interleaved reductions).
@@ -567,7 +585,7 @@ __device__ __forceinline__ CodeAt code_at(int idx) {
 // m: the row's absmax.  The sum runs over the lanes that share the row: ROW_BITS lane bits inside a
 // DPP row plus the four DPP rows.  emit(k, sum) is called by every lane with the reduced sum.
 template <int NVAL, int BITS, int ROW_BITS, typename Emit>
-__device__ __forceinline__ void qe_candidates(const float (&v)[NVAL], float m, float flip, const ClipList& clips,
+__device__ __forceinline__ void qe_candidates(const float (&v)[NVAL], float m, float flip, const ClipView& clips,
                                               int k0, int k1, Emit emit) {
     constexpr float kQmax = (float)((1 << (BITS - 1)) - 1), kQmin = -(float)(1 << (BITS - 1));
     const double inv_m = m > 0.0f ? 1.0 / (double)m : 0.0;
@@ -578,8 +596,8 @@ __device__ __forceinline__ void qe_candidates(const float (&v)[NVAL], float m, f
             const int k = kb + j < k1 ? kb + j : k1 - 1;
             // 1 / Delta_k = (levels / clip_k) / amax and Delta_k = (clip_k / levels) amax: the
             // row-independent factors come with the clip list, so a candidate costs two fp64 products
-            sk[j] = flip * (float)(clips.lvl_over_clip[k] * inv_m);          // lane sign folded in
-            ndk[j] = -flip * (float)(clips.clip_over_lvl[k] * (double)m);
+            sk[j] = flip * (float)(clips.lvl_over_clip(k) * inv_m);          // lane sign folded in
+            ndk[j] = -flip * (float)(clips.clip_over_lvl(k) * (double)m);
             e2[j] = 0.0f;
         }
 #pragma unroll

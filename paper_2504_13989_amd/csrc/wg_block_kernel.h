@@ -68,9 +68,9 @@ constexpr int wg_waves_per_simd() { return (KK <= 3 || KK == 5) ? 6 : 4; }
 enum WgSink { kWgQuantize, kWgError, kWgRotate };
 struct WgNone {};
 struct QeArgs {
-    ClipList clips;
-    int n_clips;
-    double* partial;      // [rows][n_clips]
+    ClipArg clips;
+    double* partial;      // [rows][number of clips]
+    int max_shares;       // workgroups that may share the clip ratios of a pass (grid y; each repeats the rotation)
 };
 struct WgRotArgs {
     void* Y;
@@ -323,24 +323,26 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
         for (int w = 1; w < nw; ++w) m = fmaxf(m, wmax[w * RPW + rsub]);
         // ---- phase 4
         if constexpr (QE) {
+            const ClipView clips = clip_view(sa.clips);
+            const int per = (clips.n + (int)gridDim.y - 1) / (int)gridDim.y, k0 = (int)blockIdx.y * per, k1 = k0 + per < clips.n ? k0 + per : clips.n;
             float v[32];
 #pragma unroll
             for (int nt = 0; nt < 8; ++nt)
 #pragma unroll
                 for (int ip = 0; ip < 4; ++ip) v[nt * 4 + ip] = acc[nt][ip];
             // the sums run over the lanes that share a row of the pass: CB lane bits and the four DPP rows
-            qe_candidates<32, BITS, CB>(v, m, flip, sa.clips, 0, sa.n_clips, [&](int k, float e2) {
+            qe_candidates<32, BITS, CB>(v, m, flip, clips, k0, k1, [&](int k, float e2) {
                 if (g == 0 && cl == 0) esum[wave][rsub][k] = e2;
             });
             __syncthreads();   // the next row writes esum only after two more barriers
-            for (int i = threadIdx.x; i < RPW * sa.n_clips; i += blockDim.x) {
-                const int rs = i / sa.n_clips, k = i - rs * sa.n_clips;
+            for (int i = threadIdx.x; i < RPW * (k1 - k0); i += blockDim.x) {
+                const int rs = i / (k1 - k0), k = k0 + i - rs * (k1 - k0);
                 const int64_t orow = pass * RPW + rs;
                 if (orow < a.rows) {
                     float t = 0.0f;
                     for (int w = 0; w < nw; ++w) t += esum[w][rs][k];
                     const double nn = (double)pb * (double)SEG;
-                    sa.partial[orow * sa.n_clips + k] = (double)t / (nn * nn);
+                    sa.partial[orow * clips.n + k] = (double)t / (nn * nn);
                 }
             }
             continue;
@@ -415,8 +417,16 @@ int wg_launch(const rq_hadamard* h, WgKernel<SINK> fn, const WaveArgs& a, int pb
     const int64_t cap = (int64_t)h->num_cu * per_cu;
     const int rpw = 16 >> cb;
     const int64_t passes = (a.rows + rpw - 1) / rpw;
+    unsigned shares = 1;
+    if constexpr (SINK == kWgError) {
+        // few rows: the clip ratios of a pass over as many workgroups as make about ten waves per compute unit (32 x 8960, 32
+        // ratios: 31.9 -> 12.8 us; beyond that the repeated rotations cost more than the idle units: 512 x 5120 with four
+        // shares 16.4 -> 20.4)
+        const int64_t want = (int64_t)h->num_cu * 10 / (passes * nw);
+        shares = (unsigned)(want < 1 ? 1 : want > sa.max_shares ? sa.max_shares : want);
+    }
     const unsigned grid = (unsigned)(passes < cap ? passes : cap);
-    launch_kernel(fn, dim3(grid), dim3(64 * nw), lds, s, a, pb, sa);
+    launch_kernel(fn, dim3(grid, shares), dim3(64 * nw), lds, s, a, pb, sa);
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }
 

@@ -1,0 +1,60 @@
+"""GPU: the resident form of the clip search (one launch) against the batched form and Algorithm 1 run on quant_error's own
+values: every waves-per-row form, one row to the most rows a chip holds, ragged last workgroup, an evaluation limit."""
+import numpy as np
+import pytest
+
+import parity
+import rotq_oracle as oracle
+from paper_2504_13989_amd import binding, workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,d,rows", [(1024, 1024, 4096), (2048, 2000, 515), (4096, 4096, 1), (4096, 4096, 1023), (8192, 8192, 300),
+                                      (1536, 1536, 257), (3584, 3584, 700), (3072, 3000, 2048), (4096, 4096, 1025)])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_search_takes_the_steps_of_algorithm_1(n, d, rows, dtype):
+    rng = np.random.default_rng(n + rows)
+    xf = rng.standard_normal((rows, d)).astype(np.float32)
+    xf[rows // 2] *= 20.0
+    x = parity.to_device(wl.f32_to_bf16_bits(xf) if dtype == "bf16" else xf.astype(np.float16))
+    h = binding.hadamard_build(n)
+    for b in (3, 4):
+        clip, mse, trace = binding.gbs_search(h, x, b, 1.0 / 100)
+        # Algorithm 1 with the values of the trace as its objective asks for the trace's probes, in its order
+        seen = dict(trace)
+        m, fm, otrace = oracle.gbs_search(lambda c: seen[np.float32(c)], 1.0 / 100)
+        assert [np.float32(c) for c, _ in otrace] == [np.float32(c) for c, _ in trace]
+        assert clip == np.float32(m) and mse == fm
+        # and the values are quant_error's
+        want = binding.quant_error(h, x, b, [c for c, _ in trace]).cpu().numpy()
+        assert np.allclose([v for _, v in trace], want, rtol=2e-6, atol=0.0)
+        _, _, short = binding.gbs_search(h, x, b, 1.0 / 100, max_evals=4)
+        assert short == trace[:4]
+
+
+def test_searches_of_several_threads_and_streams():
+    import threading
+    import torch
+    h = binding.hadamard_build(4096)
+    rng = np.random.default_rng(5)
+    xs = [parity.to_device(wl.f32_to_bf16_bits(rng.standard_normal((r, 4096)).astype(np.float32))) for r in (512, 300, 512, 40)]
+    want = [binding.gbs_search(h, x, 3, 1.0 / 256) for x in xs]
+    torch.cuda.synchronize()
+    got = [[] for _ in xs]
+
+    def work(i):
+        s = torch.cuda.Stream()
+        for _ in range(10):
+            got[i].append(binding.gbs_search(h, xs[i], 3, 1.0 / 256, stream=s))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(xs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for i, (clip, mse, trace) in enumerate(want):
+        assert len(got[i]) == 10
+        for c, m, tr in got[i]:
+            assert c == clip and [p for p, _ in tr] == [p for p, _ in trace]
+            assert np.allclose([v for _, v in tr], [v for _, v in trace], rtol=2e-6, atol=0.0)
