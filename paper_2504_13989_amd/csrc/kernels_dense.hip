@@ -1,13 +1,13 @@
-// Dense-block kernel: bf16 rows of an order n <= 4096 whose factorisation leaves no long
+// Dense-block kernel: 16-bit rows of an order n <= 4096 whose factorisation leaves no long
 // power-of-two axis for the wave kernels - above all a large Paley block taken over the whole
 // dimension (1544 = 1543 + 1, the 1536 + 8 expansion of section 5.2.2), also p * 2^k with k < 7.
 // Here the rotation really is a dense contraction, y = H_n x with n multiply-adds per output
 // (sections 2.3.3, 4.2), so it runs on the matrix cores as a GEMM: D[a'][row] = sum_a H[a'][a]
-// X[row][a], v_mfma_f32_16x16x32_bf16 with
+// X[row][a], v_mfma_f32_16x16x32_bf16 (or _f16) with
 //   B operand  16 rows x 32 inputs as they are in memory: lane (g, r) takes the 16 bytes
-//              X[row0 + r][32 kk + 8 g ..] (exact bf16, no conversion), staged through LDS so that the
+//              X[row0 + r][32 kk + 8 g ..] (exact, no conversion), staged through LDS so that the
 //              loads from memory are coalesced (see the loader role in the kernel);
-//   A operand  a 16 x 32 tile of +-1 (bf16), made in registers from one sign bit per entry: the handle
+//   A operand  a 16 x 32 tile of +-1 (in the rows' format), made in registers from one sign bit per entry: the handle
 //              holds the matrix as n^2 / 8 bytes of signs, a lane's 8 signs of a tile sit in a 32-bit word
 //              (four tiles per word) at the positions where one rotation of the word brings two of them
 //              to bits 15 and 31, so an operand register costs a rotate and an and-or:
@@ -33,7 +33,7 @@ constexpr int dense_words(int mtw) { return mtw <= 16 ? 4 : 8; }
 
 // Operand register d (entries 2 d, 2 d + 1 of the lane's eight) of the tile in slot jj of a sign word:
 // the rotation by 4 jj + d brings their signs to bits 15 and 31.  `mask` (0x80008000) and `one`
-// (0x3F803F80) are passed in registers so that the and-or is one instruction.
+// (0x3F803F80, fp16 0x3C003C00) are passed in registers so that the and-or is one instruction.
 template <int RHO>
 __device__ __forceinline__ uint32_t sign_pair(uint32_t word, uint32_t mask, uint32_t one) {
     const uint32_t x = RHO ? __builtin_amdgcn_alignbit(word, word, RHO) : word;
@@ -51,7 +51,7 @@ __device__ __forceinline__ u32x4 sign_tile(uint32_t word, uint32_t mask, uint32_
 constexpr int kDenseGroup = 4;
 constexpr int dense_steps_padded(int n) { return (((n + 31) / 32 + kDenseGroup - 1) / kDenseGroup + 1) * kDenseGroup; }
 
-template <int MTW, int NT, int BITS>
+template <int MTW, int NT, int BITS, bool F16>
 __global__ __launch_bounds__(64 * kDenseWaves) void k_dense_block(WaveArgs a, int n) {
     constexpr int RB = 16 * NT;                          // rows per workgroup
     constexpr int QV = dense_words(MTW) / 4;             // 16-byte sign loads per lane and step
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(64 * kDenseWaves) void k_dense_block(WaveArgs a, in
     bool row_ok[NT];
 #pragma unroll
     for (int q = 0; q < NT; ++q) row_ok[q] = row0 + 16 * q + r < a.rows;
-    uint32_t kmask = 0x80008000u, kone = 0x3F803F80u;
+    uint32_t kmask = 0x80008000u, kone = F16 ? 0x3C003C00u : 0x3F803F80u;
     asm volatile("" : "+v"(kmask), "+v"(kone));          // kept in registers, see sign_pair
     const u32x4* const signs = a.tiles + ((size_t)wave * 64 + lane) * QV;     // + kk * 8 * 64 * QV
 
@@ -116,8 +116,7 @@ __global__ __launch_bounds__(64 * kDenseWaves) void k_dense_block(WaveArgs a, in
                                            : sign_tile<3>(word, kmask, kone);
 #pragma unroll
             for (int q = 0; q < NT; ++q)
-                acc[j][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, t),
-                                                                    __builtin_bit_cast(bf16x8, x[q]), acc[j][q], 0, 0, 0);
+                acc[j][q] = mfma_pm1<F16>(t, x[q], acc[j][q]);
         }
         // issue order: the 8 vector instructions that make tile j + 1 go between the matrix-core instructions
         // of tile j (into other registers than tile j's, which those are still reading)
@@ -271,10 +270,12 @@ int launch_dense(const WaveArgs& a, int n, int bits, hipStream_t s) {
     if (groups > 0x7fffffffLL) return RQ_ERR_ARG;
     const size_t rows_lds = (size_t)16 * NT * n * bits / 8, stage_lds = (size_t)2 * 16 * NT * (64 * kDenseGroup + 16);
     const size_t lds = rows_lds > stage_lds ? rows_lds : stage_lds;
-    if (bits == 4)
-        launch_kernel((k_dense_block<MTW, NT, 4>), dim3((unsigned)groups), dim3(64 * kDenseWaves), lds, s, a, n);
-    else
-        launch_kernel((k_dense_block<MTW, NT, 3>), dim3((unsigned)groups), dim3(64 * kDenseWaves), lds, s, a, n);
+    auto go = [&](auto kernel) { launch_kernel(kernel, dim3((unsigned)groups), dim3(64 * kDenseWaves), lds, s, a, n); };
+    if (a.f16) {
+        if (bits == 4) go(k_dense_block<MTW, NT, 4, true>); else go(k_dense_block<MTW, NT, 3, true>);
+    } else {
+        if (bits == 4) go(k_dense_block<MTW, NT, 4, false>); else go(k_dense_block<MTW, NT, 3, false>);
+    }
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }
 
@@ -308,7 +309,7 @@ std::vector<uint32_t> dense_block_tiles(const std::vector<int8_t>& hm, int n) {
 }
 
 bool dense_block_supports(const rq_hadamard* h, const RowArgs& a) {
-    if (h->device < 0 || !h->d_tiles || !h->dense_ok || a.dtype != RQ_BF16) return false;
+    if (h->device < 0 || !h->d_tiles || !h->dense_ok || a.dtype == RQ_F32) return false;
     if ((reinterpret_cast<uintptr_t>(a.X) & 15) != 0 || (a.ld & 7) != 0 || (a.d & 7) != 0) return false;
     return true;
 }
@@ -319,11 +320,12 @@ int dense_block_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float cl
     WaveArgs w{static_cast<const uint16_t*>(a.X), a.rows, a.d, a.ld,
                static_cast<const u32x4*>(h->d_tiles), codes, scales,
                lvl / (double)clip, (double)clip / (std::sqrt((double)a.n) * lvl)};
+    w.f16 = a.dtype == RQ_F16;
     const int mtw = ((a.n + 15) / 16 + kDenseWaves - 1) / kDenseWaves;
-    // 32 rows per workgroup: every operand tile made in registers then serves two groups of rows; used when
-    // that still leaves a workgroup for every CU and the accumulators fit the register budget (two waves
-    // per SIMD; 64 rows need 208 accumulator registers per wave and spill)
-    const bool two = a.rows >= (int64_t)32 * h->num_cu;
+    // 32 rows per workgroup: every operand tile made in registers then serves two groups of rows; used from where 16 rows
+    // would give some compute unit a second workgroup (4200 rows of 1544: 56 -> 41 us) and the accumulators fit the
+    // register budget (two waves per SIMD; 64 rows need 208 accumulator registers per wave and spill)
+    const bool two = a.rows > (int64_t)16 * h->num_cu;
 #define RQ_DENSE_CASE(M) \
     if (mtw <= M) return two ? launch_dense<M, 2>(w, a.n, a.bits, s) : launch_dense<M, 1>(w, a.n, a.bits, s)
     RQ_DENSE_CASE(4);
