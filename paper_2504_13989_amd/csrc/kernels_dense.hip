@@ -230,8 +230,9 @@ __global__ __launch_bounds__(64 * kDenseWaves) void k_dense_block(WaveArgs a, in
                 for (int e = 3; e >= 0; --e) {
                     float u = fmaf(acc[j][q][e], s[q], Quant<BITS>::kBias);
                     u = __builtin_amdgcn_fmed3f(u, Quant<BITS>::kLo, Quant<BITS>::kHi);
-                    w = (w << BITS) | ((__float_as_uint(u) ^ (1u << (BITS - 1))) & ((1u << BITS) - 1u));
+                    w = e == 3 ? __float_as_uint(u) : Quant<BITS>::chain(w, u);
                 }
+                w = (w ^ Quant<BITS>::msb()) & ((1u << 4 * BITS) - 1u);   // four codes (their exponents lie above)
                 const int o = 16 * mt + 4 * g;           // first output of this lane
                 if (BITS == 4) {
                     if (o < n) *reinterpret_cast<uint16_t*>(srow + o / 2) = (uint16_t)w;

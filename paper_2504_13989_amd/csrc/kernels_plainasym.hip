@@ -165,11 +165,7 @@ __global__ __launch_bounds__(64) void k_plain_asym(const void* X, int64_t n_grou
                     if (!(__builtin_fabsf(e[k]) <= thr))
                         v[k] = Quant<BITS>::kMagic + (float)fmin(fmax(rint(((double)x[u][k] - lo64) / delta64), 0.0), kL);
             }
-            uint32_t w = 0;
-#pragma unroll
-            for (int k = 7; k >= 0; --k)
-                w = (w << BITS) + __float_as_uint(__builtin_amdgcn_fmed3f(v[k], Quant<BITS>::kLo, Quant<BITS>::kHi));
-            w -= Quant<BITS>::csum();
+            const uint32_t w = Quant<BITS>::join(v);
             if (BITS == 4) {
                 if (live) store_codes(out0 + u * (16 * BITS), w);
             } else {
@@ -262,11 +258,7 @@ __global__ __launch_bounds__(64) void k_plain_short(const void* X, int64_t rows,
                     if (!(__builtin_fabsf(e[k]) <= thr))
                         v[k] = Quant<BITS>::kBias + fminf(fmaxf((float)rint((double)x[u][k] / delta64), kQmin), kQmax);
             }
-            uint32_t w = 0;
-#pragma unroll
-            for (int k = 7; k >= 0; --k)
-                w = (w << BITS) + __float_as_uint(__builtin_amdgcn_fmed3f(v[k], Quant<BITS>::kLo, Quant<BITS>::kHi));
-            w = (w - Quant<BITS>::csum()) ^ Quant<BITS>::msb();
+            const uint32_t w = Quant<BITS>::join(v) ^ Quant<BITS>::msb();
             uint32_t* out = codes + row * (int64_t)row_dwords;
             if (BITS == 4) {
                 if (live) store_codes(out + c, w);

@@ -255,11 +255,7 @@ __device__ __forceinline__ uint32_t pack8_plain(const float (&x)[8], float cen, 
         for (int k = 0; k < 8; ++k)
             if (!(__builtin_fabsf(e[k]) <= thr)) v[k] = exact(x[k]);
     }
-    uint32_t w = 0;
-#pragma unroll
-    for (int k = 7; k >= 0; --k)
-        w = (w << BITS) + __float_as_uint(__builtin_amdgcn_fmed3f(v[k], Quant<BITS>::kLo, Quant<BITS>::kHi));
-    return (w - Quant<BITS>::csum()) ^ tail_xor;
+    return Quant<BITS>::join(v) ^ tail_xor;
 }
 
 template <int CB, int BITS, int U, bool GUARD, bool ASYM, bool F16, bool PLAIN = false>
@@ -925,9 +921,9 @@ __global__ __launch_bounds__(64 * W) void k_plain_wave(PlainArgs a) {
                 // quotient decides, for this value only
                 if (__builtin_fabsf(e) > 0.49998f && m > 0.0f)
                     u = Quant<BITS>::kBias + fminf(fmaxf((float)rint((double)x[r] / delta), kQmin), kQmax);
-                w = (w << BITS) + __float_as_uint(u);
+                w = r == 7 ? __float_as_uint(u) : Quant<BITS>::chain(w, u);
             }
-            w = (w - Quant<BITS>::csum()) ^ Quant<BITS>::msb();
+            w = Quant<BITS>::chained(w) ^ Quant<BITS>::msb();
             if (BITS == 4) {
                 if (idx < nchunks) store_codes(out + idx, w);
             } else {

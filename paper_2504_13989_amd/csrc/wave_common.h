@@ -267,17 +267,21 @@ struct WaveArgs {
 
 // Quantizer constants for b-bit codes (section 2.1 with the clip ratio of section 3.1).
 // u = fma(y, s, kBias) rounds y*s + 2^(b-1) to the nearest-even integer on the fp32 lattice
-// above 1.5 * 2^23; v_med3 clamps it to [kLo, kHi]; the code (offset binary) is the low
-// mantissa bits.  Eight codes are chained with shift-adds, the accumulated exponent bits
-// (kCsum) are subtracted once and one xor (kMsb) turns offset binary into two's complement.
+// above 2^23 (below it, where the lattice is finer, every value is clamped to code 0 anyway); v_med3
+// clamps it to [kLo, kHi]; the code (offset binary) is the low mantissa bits.  Eight codes are
+// chained with shift-adds, one instruction each (written as such: left to itself the compiler turns the
+// chain into a sum of shifted values, two instructions longer).  The exponent field, 0x4B000000,
+// of the eight values falls outside the 24 bits of eight 3-bit codes, whose users take those 24 bits
+// only; for 4-bit codes what it adds to the top byte is subtracted once (csum).  One xor (msb) turns
+// offset binary into two's complement.
 template <int BITS>
 struct Quant {
-    static constexpr float kMagic = 12582912.0f;   // 1.5 * 2^23
+    static constexpr float kMagic = 8388608.0f;    // 2^23
     static constexpr float kLo = kMagic, kHi = kMagic + (float)((1 << BITS) - 1);
     static constexpr float kBias = kMagic + (float)(1 << (BITS - 1));
     static constexpr uint32_t csum() {
         uint32_t c = 0;
-        for (int r = 0; r < 8; ++r) c += 0x4B400000u << (BITS * r);
+        for (int r = 0; r < 8; ++r) c += 0x4B000000u << (BITS * r);
         return c;
     }
     static constexpr uint32_t msb() {
@@ -285,36 +289,46 @@ struct Quant {
         for (int r = 0; r < 8; ++r) m |= 1u << (BITS * r + BITS - 1);
         return m;
     }
+    // the next code of the chain: w 2^b + u
+    static __device__ __forceinline__ uint32_t chain(uint32_t w, float u) {
+        uint32_t r;
+        asm("v_lshl_add_u32 %0, %1, %2, %3" : "=v"(r) : "v"(w), "n"(BITS), "v"(u));
+        return r;
+    }
+    // end of the chain: eight codes, for b = 3 in the low 24 bits (the rest undefined)
+    static __device__ __forceinline__ uint32_t chained(uint32_t w) {
+        static_assert(BITS == 4 || (csum() & 0xffffffu) == 0, "the exponents must stay clear of the codes");
+        return BITS == 3 ? w : w - csum();
+    }
+    // clamps and chains u7 .. u0 (u0 in the low bits)
+    static __device__ __forceinline__ uint32_t join(const float (&u)[8]) {
+        uint32_t w = __float_as_uint(__builtin_amdgcn_fmed3f(u[7], kLo, kHi));
+#pragma unroll
+        for (int r = 6; r >= 0; --r) w = chain(w, __builtin_amdgcn_fmed3f(u[r], kLo, kHi));
+        return chained(w);
+    }
     // packs codes of y0..y7 (y0 in the low bits) into 8*BITS bits
     static __device__ __forceinline__ uint32_t pack8(float y0, float y1, float y2, float y3, float y4,
                                                      float y5, float y6, float y7, float s) {
         const float y[8] = {y0, y1, y2, y3, y4, y5, y6, y7};
-        uint32_t w = 0;
+        float u[8];
 #pragma unroll
-        for (int r = 7; r >= 0; --r) {
-            float u = fmaf(y[r], s, kBias);
-            u = __builtin_amdgcn_fmed3f(u, kLo, kHi);
-            w = (w << BITS) + __float_as_uint(u);
-        }
-        return (w - csum()) ^ msb();
+        for (int r = 0; r < 8; ++r) u[r] = fmaf(y[r], s, kBias);
+        return join(u) ^ msb();
     }
     // Unsigned codes 0 .. 2^b - 1 of (y - cen) * s + bias - kMagic: the asymmetric group
     // quantizer, centred on the value `cen` that maps to the middle code so that the fp32
     // products stay as small as in the symmetric case.
     static __device__ __forceinline__ uint32_t pack8u(const float (&y)[8], float cen, float s, float bias) {
-        uint32_t w = 0;
+        float u[8];
 #pragma unroll
-        for (int r = 7; r >= 0; --r) {
-            float u = fmaf(y[r] - cen, s, bias);
-            u = __builtin_amdgcn_fmed3f(u, kLo, kHi);
-            w = (w << BITS) + __float_as_uint(u);
-        }
-        return w - csum();
+        for (int r = 0; r < 8; ++r) u[r] = fmaf(y[r] - cen, s, bias);
+        return join(u);
     }
 };
 
-// b = 3: a lane's 24 bits and those of the lane holding the next 8 columns (lane + 1, or
-// lane - 1 in mirrored quads) make the dword for quad position qpos (0..2).
+// b = 3: a lane's 24 bits (the low ones of w) and those of the lane holding the next 8 columns (lane + 1, or
+// lane - 1 in mirrored quads) make the dword for quad position qpos (0..2): bytes qpos .. qpos + 3 of the six.
 template <bool MIRROR>
 __device__ __forceinline__ uint32_t merge24(uint32_t w, int qpos) {
     uint32_t nxt;
@@ -324,7 +338,8 @@ __device__ __forceinline__ uint32_t merge24(uint32_t w, int qpos) {
     } else {
         nxt = dpp_u<kDppNext>(w);
     }
-    return (w >> (8 * qpos)) | (nxt << (24 - 8 * qpos));
+    // (selector bytes 0 - 2 take bytes of w, 4 - 6 of nxt)
+    return __builtin_amdgcn_perm(nxt, w, qpos == 0 ? 0x04020100u : qpos == 1 ? 0x05040201u : 0x06050402u);
 }
 
 // b = 3 output path.  A lane holds 24 bits per group of 8 columns, which is not a whole dword;
