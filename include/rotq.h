@@ -336,8 +336,8 @@ size_t rq_gbs_workspace(int64_t rows);
  * are rotated once and searched in one launch, other tensors take a few launches enqueued together.
  * The call waits for the result: a calibration call, not a hot-path call (not for a stream under
  * capture).  A search uses about 260 KB of device memory and 2 KB of pinned host memory that the
- * library allocates and keeps for the next one, as many sets per device as searches ever ran at the
- * same time; nothing else is allocated.  Searches may run on any number of threads and streams; one at
+ * library allocates and keeps for the next one: up to four sets per device, given back when the last
+ * handle on the device is freed; nothing else is allocated.  Searches may run on any number of threads and streams; one at
  * a time per device takes the single-launch form.
  *   eps          [in]  bracket width to stop at, > 0
  *   max_evals    [in]  1 .. 256

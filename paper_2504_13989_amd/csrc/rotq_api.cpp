@@ -64,6 +64,133 @@ struct TableSet {
     }
 };
 
+// What a search needs besides the caller's workspace: its state on the device and the results in host memory the device
+// writes.
+struct SearchMem {
+    int device;
+    uint32_t epoch;           // first step number that is not in `exchange`
+    uint64_t* exchange;       // of the resident form: two buffers, taken in turn
+    rq::GbsDev* state;
+    rq::GbsOut* out;          // pinned, mapped
+    rq::GbsOut* out_dev;
+};
+
+// The devices that handles live on.  A few sets are kept for the next search there and given back with the device's last
+// handle; nothing below allocates host memory once a handle exists.
+struct SearchDevice {
+    static constexpr int kKeep = 4;
+    int device;
+    int handles;
+    bool resident;            // a resident search is under way: one at a time, since two of them could each keep the
+                              // other's workgroups from running (a second one takes the batched form)
+    int kept;
+    SearchMem mem[kKeep];
+};
+std::mutex g_search_lock;
+std::vector<SearchDevice>& search_devices() {
+    static std::vector<SearchDevice>* devices = new std::vector<SearchDevice>;   // not torn down before the runtime is
+    return *devices;
+}
+// (g_search_lock held)
+SearchDevice* search_device(int device) {
+    for (SearchDevice& d : search_devices())
+        if (d.device == device) return &d;
+    return nullptr;
+}
+
+void free_search_mem(const SearchMem& m) {
+    (void)hipFree(m.exchange);                            // waits for a search that is still leaving the device
+    (void)hipHostFree(m.out);
+    (void)hipGetLastError();
+}
+
+bool add_handle(int device) {
+    std::lock_guard<std::mutex> hold(g_search_lock);
+    SearchDevice* d = search_device(device);
+    if (!d) {
+        try {
+            search_devices().push_back(SearchDevice{device, 0, false, 0, {}});
+        } catch (const std::bad_alloc&) {
+            return false;
+        }
+        d = &search_devices().back();
+    }
+    ++d->handles;
+    return true;
+}
+
+void remove_handle(int device) {
+    SearchMem mem[SearchDevice::kKeep];
+    int n = 0;
+    {
+        std::lock_guard<std::mutex> hold(g_search_lock);
+        SearchDevice* d = search_device(device);
+        if (!d || --d->handles > 0) return;
+        n = d->kept;
+        std::copy(d->mem, d->mem + n, mem);
+        d->kept = 0;
+    }
+    for (int i = 0; i < n; ++i) free_search_mem(mem[i]);
+}
+
+// The turn of the resident form on a device (negative: none is wanted).
+class ResidentTurn {
+    int device_;
+    bool mine_ = false;
+public:
+    explicit ResidentTurn(int device) : device_(device) {
+        if (device < 0) return;
+        std::lock_guard<std::mutex> hold(g_search_lock);
+        SearchDevice* d = search_device(device);
+        if (d && !d->resident) mine_ = d->resident = true;
+    }
+    ~ResidentTurn() {
+        if (!mine_) return;
+        std::lock_guard<std::mutex> hold(g_search_lock);
+        search_device(device_)->resident = false;         // (entries stay for good)
+    }
+    ResidentTurn(const ResidentTurn&) = delete;
+    ResidentTurn& operator=(const ResidentTurn&) = delete;
+    explicit operator bool() const { return mine_; }
+};
+
+int take_search_mem(int device, SearchMem* m) {
+    {
+        std::lock_guard<std::mutex> hold(g_search_lock);
+        SearchDevice* d = search_device(device);
+        if (d && d->kept > 0) {
+            *m = d->mem[--d->kept];
+            return RQ_OK;
+        }
+    }
+    int cur = -1;
+    void *state = nullptr, *out = nullptr, *out_dev = nullptr;
+    const size_t ex = 2 * rq::gbs_exchange_bytes();       // (the state follows it in the same allocation)
+    if (hipGetDevice(&cur) == hipSuccess && cur == device && hipMalloc(&state, ex + rq::gbs_state_bytes()) == hipSuccess &&
+        hipMemset(state, 0, ex) == hipSuccess && hipDeviceSynchronize() == hipSuccess &&
+        hipHostMalloc(&out, sizeof(rq::GbsOut), hipHostMallocMapped) == hipSuccess &&
+        hipHostGetDevicePointer(&out_dev, out, 0) == hipSuccess && out_dev) {
+        *m = SearchMem{device, 1u, static_cast<uint64_t*>(state),
+                       reinterpret_cast<rq::GbsDev*>(static_cast<char*>(state) + ex), static_cast<rq::GbsOut*>(out), static_cast<rq::GbsOut*>(out_dev)};
+        return RQ_OK;
+    }
+    if (state) (void)hipFree(state);
+    if (out) (void)hipHostFree(out);
+    (void)hipGetLastError();
+    return RQ_ERR_HIP;
+}
+
+void give_search_mem(const SearchMem& m) {
+    {
+        std::lock_guard<std::mutex> hold(g_search_lock);
+        SearchDevice* d = search_device(m.device);
+        if (d && d->handles > 0 && d->kept < SearchDevice::kKeep) {
+            d->mem[d->kept++] = m;
+            return;
+        }
+    }
+    free_search_mem(m);
+}
 }  // namespace
 
 extern "C" {
@@ -167,6 +294,11 @@ int rq_hadamard_build(int n, rq_hadamard_t** out) {
         delete h;
         return RQ_ERR_HIP;
     }
+    if (!add_handle(dev)) {
+        (void)hipFree(h->d_tables);
+        delete h;
+        return RQ_ERR_NOMEM;
+    }
     h->d_block = static_cast<int8_t*>(d_block);
     h->device = dev;
     h->generic_ok = rq::generic_prepare(h);
@@ -180,6 +312,7 @@ int rq_hadamard_build(int n, rq_hadamard_t** out) {
 
 void rq_hadamard_free(rq_hadamard_t* h) {
     if (!h) return;
+    if (h->device >= 0) remove_handle(h->device);
     if (h->d_tables) (void)hipFree(h->d_tables);
     delete h;
 }
@@ -514,83 +647,6 @@ int gbs_most_steps(double eps, int limit) {
     return steps;
 }
 
-// What a search needs besides the caller's workspace: its state on the device and the results in host memory the device
-// writes.  Sets are kept for the next search on the same device, as many as ever ran at one time.
-struct SearchMem {
-    int device;
-    uint32_t epoch;           // first step number that is not in `exchange`
-    uint64_t* exchange;       // of the resident form: two buffers, taken in turn
-    rq::GbsDev* state;
-    rq::GbsOut* out;          // pinned, mapped
-    rq::GbsOut* out_dev;
-};
-// Devices on which a resident search is under way: one at a time, since two of them could each keep the other's
-// workgroups from running (a second one takes the batched form).
-std::mutex g_search_lock;
-std::vector<int>& resident_on() {
-    static std::vector<int>* devices = new std::vector<int>;
-    return *devices;
-}
-class ResidentTurn {
-    int device_;
-    bool mine_ = false;
-public:
-    explicit ResidentTurn(int device) : device_(device) {       // (negative: none is wanted)
-        if (device < 0) return;
-        std::lock_guard<std::mutex> hold(g_search_lock);
-        std::vector<int>& on = resident_on();
-        if (std::find(on.begin(), on.end(), device) == on.end()) {
-            on.push_back(device);
-            mine_ = true;
-        }
-    }
-    ~ResidentTurn() {
-        if (!mine_) return;
-        std::lock_guard<std::mutex> hold(g_search_lock);
-        std::vector<int>& on = resident_on();
-        on.erase(std::find(on.begin(), on.end(), device_));
-    }
-    ResidentTurn(const ResidentTurn&) = delete;
-    ResidentTurn& operator=(const ResidentTurn&) = delete;
-    explicit operator bool() const { return mine_; }
-};
-std::vector<SearchMem>& search_pool() {
-    static std::vector<SearchMem>* pool = new std::vector<SearchMem>;     // not torn down before the runtime is
-    return *pool;
-}
-
-int take_search_mem(int device, SearchMem* m) {
-    {
-        std::lock_guard<std::mutex> hold(g_search_lock);
-        std::vector<SearchMem>& pool = search_pool();
-        for (size_t i = 0; i < pool.size(); ++i)
-            if (pool[i].device == device) {
-                *m = pool[i];
-                pool.erase(pool.begin() + (std::ptrdiff_t)i);
-                return RQ_OK;
-            }
-    }
-    int cur = -1;
-    void *state = nullptr, *out = nullptr, *out_dev = nullptr;
-    const size_t ex = 2 * rq::gbs_exchange_bytes();       // (the state follows it in the same allocation)
-    if (hipGetDevice(&cur) == hipSuccess && cur == device && hipMalloc(&state, ex + rq::gbs_state_bytes()) == hipSuccess &&
-        hipMemset(state, 0, ex) == hipSuccess && hipDeviceSynchronize() == hipSuccess &&
-        hipHostMalloc(&out, sizeof(rq::GbsOut), hipHostMallocMapped) == hipSuccess &&
-        hipHostGetDevicePointer(&out_dev, out, 0) == hipSuccess && out_dev) {
-        *m = SearchMem{device, 1u, static_cast<uint64_t*>(state),
-                       reinterpret_cast<rq::GbsDev*>(static_cast<char*>(state) + ex), static_cast<rq::GbsOut*>(out), static_cast<rq::GbsOut*>(out_dev)};
-        return RQ_OK;
-    }
-    if (state) (void)hipFree(state);
-    if (out) (void)hipHostFree(out);
-    (void)hipGetLastError();
-    return RQ_ERR_HIP;
-}
-
-void give_search_mem(const SearchMem& m) {
-    std::lock_guard<std::mutex> hold(g_search_lock);
-    search_pool().push_back(m);
-}
 }  // namespace
 
 size_t rq_gbs_workspace(int64_t rows) {

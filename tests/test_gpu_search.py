@@ -58,3 +58,24 @@ def test_searches_of_several_threads_and_streams():
         for c, m, tr in got[i]:
             assert c == clip and [p for p, _ in tr] == [p for p, _ in trace]
             assert np.allclose([v for _, v in tr], [v for _, v in trace], rtol=2e-6, atol=0.0)
+
+
+def test_search_memory_after_the_last_handle():
+    """More searches at once than sets are kept, then none of the handles left: the next search starts afresh."""
+    import gc
+    import threading
+    rng = np.random.default_rng(6)
+    x = parity.to_device(wl.f32_to_bf16_bits(rng.standard_normal((64, 1024)).astype(np.float32)))
+    got = []
+    for _ in range(2):
+        h = binding.hadamard_build(1024)
+        threads = [threading.Thread(target=lambda h=h: got.append(binding.gbs_search(h, x, 4, 1.0 / 64))) for _ in range(6)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        del threads, h
+        gc.collect()
+    assert len(got) == 12
+    for clip, _, trace in got:
+        assert clip == got[0][0] and [p for p, _ in trace] == [p for p, _ in got[0][2]]
