@@ -67,3 +67,14 @@ def test_errors():
     h.close()
     with pytest.raises(binding.RotqError):
         binding.rotate_quantize(h, x, 4, 0.9)
+
+
+@pytest.mark.parametrize("rows", [16, 4096])
+def test_results_share_memory_only_while_small(rows):
+    """codes of 16 x 2048 bytes and their scales come from one allocation, codes of 8 MB stand alone"""
+    h = binding.hadamard_build(4096)
+    codes, scales = binding.rotate_quantize(h, _rows(rows, 4096), 4, 0.9)
+    shared = codes.untyped_storage().data_ptr() == scales.untyped_storage().data_ptr()
+    assert shared == (rows == 16)
+    assert scales.untyped_storage().nbytes() <= (1 << 20)
+    assert codes.shape == (rows, 2048) and scales.shape == (rows,) and codes.is_contiguous() and scales.is_contiguous()
