@@ -273,5 +273,5 @@ def gbs_search(h: Hadamard, x, bits: int, eps: float, max_evals: int = 64, works
                asym: bool = False):
     """rq_gbs_search (rq_gbs_search_asym with asym=True) on a CUDA tensor x [..., d]; returns
     (clip, mse, trace) with trace a list of (probe, objective) pairs in the algorithm's order.
-    Synchronises the stream once per batch of probes."""
+    Waits for the result; not for a stream under capture."""
     return (_nat or _native()).gbs_search(h._p, x, bits, eps, max_evals, workspace, stream, asym)
