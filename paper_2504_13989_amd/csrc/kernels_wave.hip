@@ -523,9 +523,11 @@ struct BlockRotArgs {
     void* Y;
     int d_out;
     int64_t ld_out;
-    float inv;            // 1 / sqrt(n)
+    double inv;           // 1 / sqrt(n)
 };
 
+// (fp32 results from codes: the sums are exact integers and the scale is applied in fp64, so that a result is rounded
+// once; a product in fp32 has 1.5 times the error, scale and factor being rounded on their own)
 template <bool FULL, int NV, bool F16, int OUT, int SRC = 0>
 __global__ __launch_bounds__(64) void k_wave_block_rotate(WaveArgs a, int pb, BlockRotArgs o) {
     const int lane = threadIdx.x;
@@ -536,12 +538,14 @@ __global__ __launch_bounds__(64) void k_wave_block_rotate(WaveArgs a, int pb, Bl
     float sf[4];
 #pragma unroll
     for (int b = 0; b < 4; ++b) sf[b] = ((c >> b) & 1) ? -1.0f : 1.0f;
-    const float k0 = ((__builtin_popcount(c) & 1) ? -1.0f : 1.0f) * o.inv;
+    const float flip = (__builtin_popcount(c) & 1) ? -1.0f : 1.0f;
+    const float k0 = flip * (float)o.inv;
     const int base_g = 8 * g < pb - 8 ? 8 * g : pb - 8;
     const int e_base = base_g * 128 + c * 8;
     for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
         float y[8][NV];
         const float k = SRC ? k0 * a.scales[row] : k0;
+        [[maybe_unused]] const double kd = SRC ? (double)(flip * a.scales[row]) * o.inv : 0.0;
         (void)block_rotate_row<FULL, NV, F16, SRC>(a, row, e_base, A0, A1, sf, y);
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
@@ -551,10 +555,18 @@ __global__ __launch_bounds__(64) void k_wave_block_rotate(WaveArgs a, int pb, Bl
             if constexpr (OUT == 1) {
                 // block rows 4 j .. 4 j + 3 are one block of 64 chunks: block row g, chunk c
                 float* const yr = static_cast<float*>(o.Y) + row * o.ld_out + 4 * j * 128;
-                store_block_f32(lds_out, g * 16 + c, lane, v8, k, 0.0f, [&](int e, const u32x4& unit) {
+                auto put = [&](int e, const u32x4& unit) {
                     if (4 * j + (e >> 7) < pb && 4 * j * 128 + e < o.d_out)
                         __builtin_nontemporal_store(unit, reinterpret_cast<u32x4*>(yr + e));
-                });
+                };
+                if constexpr (SRC != 0) {
+                    float r8[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) r8[i] = (float)((double)v8[i] * kd);
+                    store_block_f32(lds_out, g * 16 + c, lane, r8, put);
+                } else {
+                    store_block_f32(lds_out, g * 16 + c, lane, v8, k, 0.0f, put);
+                }
             } else if (ao < pb && col < o.d_out) {
                 store8<OUT>(o.Y, row * o.ld_out + col, v8, k);
             }
@@ -1183,7 +1195,7 @@ static void launch_block_rotate_nv(int src, bool full, bool f16, int out, unsign
 }
 
 static int launch_block_rotate(int src, const RowArgs& a, const WaveArgs& w, const OutArgs& o, hipStream_t s) {
-    const BlockRotArgs bo{o.Y, o.d_out, o.ld_out, (float)(1.0 / std::sqrt((double)a.n))};
+    const BlockRotArgs bo{o.Y, o.d_out, o.ld_out, 1.0 / std::sqrt((double)a.n)};
     const int out = o.dtype == RQ_BF16 ? 0 : o.dtype == RQ_F32 ? 1 : 2;
     const int pb = a.p << (a.log2m - 7);
     const int64_t cap = 1 << 24;

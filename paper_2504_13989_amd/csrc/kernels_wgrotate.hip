@@ -12,22 +12,22 @@ namespace {
 template <int KK>
 size_t rot_lds_bytes(int out) { return wg_ops_bytes<KK>() + (out == 1 ? (size_t)KK * 2 * 2048 : 0); }
 
-template <int KK, bool F16, int SRC>
+template <int KK, bool F16, int SRC, bool WIDE>
 WgKernel<kWgRotate> pick_shape(int cb) {
     if (cb == 4) {
-        if constexpr (KK >= 2) return k_wg_block<KK, 4, false, kWgRotate, 4, F16, SRC>;
+        if constexpr (KK >= 2) return k_wg_block<KK, 4, false, kWgRotate, 4, F16, SRC, WIDE>;
         return nullptr;
     }
-    if (cb == 3) return k_wg_block<KK, 4, false, kWgRotate, 3, F16, SRC>;
-    return cb == 2 ? k_wg_block<KK, 4, false, kWgRotate, 2, F16, SRC> : nullptr;
+    if (cb == 3) return k_wg_block<KK, 4, false, kWgRotate, 3, F16, SRC, WIDE>;
+    return cb == 2 ? k_wg_block<KK, 4, false, kWgRotate, 2, F16, SRC, WIDE> : nullptr;
 }
 
 // src: 0 rows of X, 3 / 4 packed codes of that width.
-template <int KK>
+template <int KK, bool WIDE>
 WgKernel<kWgRotate> pick_kernel(int src, int cb, bool f16) {
-    if (src == 4) return pick_shape<KK, true, 4>(cb);
-    if (src == 3) return pick_shape<KK, true, 3>(cb);
-    return f16 ? pick_shape<KK, true, 0>(cb) : pick_shape<KK, false, 0>(cb);
+    if (src == 4) return pick_shape<KK, true, 4, WIDE>(cb);
+    if (src == 3) return pick_shape<KK, true, 3, WIDE>(cb);
+    return f16 ? pick_shape<KK, true, 0, WIDE>(cb) : pick_shape<KK, false, 0, WIDE>(cb);
 }
 
 template <int KK>
@@ -36,19 +36,20 @@ bool prepare_kk() {
     for (int src : {0, 3, 4})
         for (int cb = 2; cb <= 4; ++cb)
             for (int f16 = 0; f16 < 2; ++f16) {
-                WgKernel<kWgRotate> fn = pick_kernel<KK>(src, cb, f16 != 0);
-                if (fn && hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                              (int)rot_lds_bytes<KK>(1)) != hipSuccess)
-                    return false;
+                for (WgKernel<kWgRotate> fn : {pick_kernel<KK, false>(src, cb, f16 != 0), pick_kernel<KK, true>(src, cb, f16 != 0)})
+                    if (fn && hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                  (int)rot_lds_bytes<KK>(1)) != hipSuccess)
+                        return false;
             }
     return true;
 }
 
 template <int KK>
 int launch_kk(const rq_hadamard* h, const WaveArgs& w, int src, int pb, int cb, const WgRotArgs& o, hipStream_t s) {
-    WgKernel<kWgRotate> fn = pick_kernel<KK>(src, cb, w.f16);
+    const bool wide = o.out == 1;
+    WgKernel<kWgRotate> fn = wide ? pick_kernel<KK, true>(src, cb, w.f16) : pick_kernel<KK, false>(src, cb, w.f16);
     if (!fn) return RQ_ERR_NO_ORDER;
-    return wg_launch<KK, kWgRotate>(h, fn, w, pb, cb, rot_lds_bytes<KK>(o.out), o, s);
+    return wg_launch<KK, kWgRotate>(h, fn, w, pb, cb, rot_lds_bytes<KK>(o.out), o, s, wg_waves_per_simd<KK>(wide));
 }
 
 int launch(const rq_hadamard* h, const WaveArgs& w, int src, int pb, int cb, const WgRotArgs& o, hipStream_t s) {
@@ -66,7 +67,7 @@ int launch(const rq_hadamard* h, const WaveArgs& w, int src, int pb, int cb, con
 }
 
 WgRotArgs rot_args(const RowArgs& a, const OutArgs& o) {
-    return WgRotArgs{o.Y, o.d_out, o.ld_out, (float)(1.0 / std::sqrt((double)a.n)),
+    return WgRotArgs{o.Y, o.d_out, o.ld_out, 1.0 / std::sqrt((double)a.n),
                      o.dtype == RQ_BF16 ? 0 : o.dtype == RQ_F32 ? 1 : 2};
 }
 

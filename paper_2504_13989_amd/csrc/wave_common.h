@@ -36,6 +36,12 @@ __device__ __forceinline__ float dpp_f(float v) {
         float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
 }
 template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+    const uint2 u = __builtin_bit_cast(uint2, v);
+    return __builtin_bit_cast(double, make_uint2((uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.x, CTRL, 0xf, 0xf, true),
+                                                 (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.y, CTRL, 0xf, 0xf, true)));
+}
+template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_u(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
 }
@@ -524,12 +530,7 @@ __device__ __forceinline__ void store8(void* Y, int64_t idx, const float (&v)[8]
 // 16-byte unit of values e .. e + 3 of the block where it belongs (and decides whether it exists).  Every lane of the
 // wave must be active.
 template <typename Put>
-__device__ __forceinline__ void store_block_f32(float* lds, int pos, int lane, const float (&v)[8], float k, float add0,
-                                                Put put) {
-    float o[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) o[i] = v[i] * k;
-    o[0] += add0;
+__device__ __forceinline__ void store_block_f32(float* lds, int pos, int lane, const float (&o)[8], Put put) {
     u32x4* const w = reinterpret_cast<u32x4*>(lds) + 2 * pos;
     w[0] = u32x4{__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])};
     w[1] = u32x4{__float_as_uint(o[4]), __float_as_uint(o[5]), __float_as_uint(o[6]), __float_as_uint(o[7])};
@@ -542,6 +543,15 @@ __device__ __forceinline__ void store_block_f32(float* lds, int pos, int lane, c
     __builtin_amdgcn_wave_barrier();
     put(4 * lane, lo);
     put(256 + 4 * lane, hi);
+}
+template <typename Put>
+__device__ __forceinline__ void store_block_f32(float* lds, int pos, int lane, const float (&v)[8], float k, float add0,
+                                                Put put) {
+    float o[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) o[i] = v[i] * k;
+    o[0] += add0;
+    store_block_f32(lds, pos, lane, o, put);
 }
 
 // Eight consecutive signed b-bit codes (the low 8 b bits of `w`) as exact fp16 integers: a code in offset binary, u,

@@ -59,7 +59,7 @@ constexpr size_t wg_lds_bytes() { return wg_ops_bytes<KK>() + (size_t)KK * 32 * 
 // loads: measured slower.  (Touching one byte per 128 of the next row a pass ahead, to bring it into
 // the L2 cache, measured no better than the plain loads either.)
 template <int KK>
-constexpr int wg_waves_per_simd() { return (KK <= 3 || KK == 5) ? 6 : 4; }
+constexpr int wg_waves_per_simd(bool wide = false) { return !wide && (KK <= 3 || KK == 5) ? 6 : 4; }
 
 // What the kernel does with the rotated row (phase 4), and the arguments that takes beyond WaveArgs:
 //   kWgQuantize  codes and scale of rq_rotate_quantize;
@@ -76,7 +76,7 @@ struct WgRotArgs {
     void* Y;
     int d_out;
     int64_t ld_out;
-    float inv;            // 1 / sqrt(n)
+    double inv;           // 1 / sqrt(n)
     int out;              // 0 bf16, 1 fp32, 2 fp16
 };
 template <int SINK>
@@ -95,15 +95,16 @@ __device__ __forceinline__ void wg_lane(int lane, int& g, int& cl, int& rsub) {
 // SRC: 0 = 16-bit rows of X, 3 / 4 = packed signed codes of that width (kWgRotate only): the lane's eight codes of
 // a block row become fp16 integers (codes_f16), the matrix cores contract them exactly, and the
 // row's scale multiplies once at the end.
-template <int KK, int BITS, bool FULL, int SINK, int CB = 4, bool F16 = false, int SRC = 0>
-__global__ __launch_bounds__(128 * KK) __attribute__((amdgpu_waves_per_eu(wg_waves_per_simd<KK>())))
+// WIDE: fp32 results (kWgRotate only), see phase 3; the doubles take 128 registers, 80 spill up to 37 of them.
+template <int KK, int BITS, bool FULL, int SINK, int CB = 4, bool F16 = false, int SRC = 0, bool WIDE = false>
+__global__ __launch_bounds__(128 * KK) __attribute__((amdgpu_waves_per_eu(wg_waves_per_simd<KK>(WIDE))))
 void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
     static_assert(CB >= 2 && CB <= 4 && (CB == 4 || !FULL), "unsupported shape");
     static_assert(SRC == 0 || (SINK == kWgRotate && F16 && !FULL), "packed codes: rotation only, fp16 operands");
     constexpr bool QE = SINK == kWgError;
     constexpr int RPW = 16 >> CB;                        // rows of X per pass
     constexpr int SEG = 8 << CB;                         // columns of one block row (2^k)
-    constexpr bool PF = wg_waves_per_simd<KK>() == 4;    // loads run one pass ahead
+    constexpr bool PF = !WIDE && wg_waves_per_simd<KK>() == 4;   // loads run one pass ahead
     __shared__ float esum[QE ? 16 : 1][QE ? RPW : 1][QE ? RQ_MAX_CLIPS : 1];   // [wave][row of the pass][clip]
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
     uint8_t* const ops = lds_raw;                        // [column tile][contraction step] x 1 KB, see wg_ops_bytes
@@ -253,6 +254,53 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
         }
         // ---- phase 3
         if constexpr (SINK != kWgRotate) __builtin_amdgcn_s_setprio(1);
+        if constexpr (WIDE && SRC == 0) {
+            // fp32 results of rows: the Sylvester stages and the factor in fp64, one register of the accumulators at a
+            // time, so that seven stages do not each add a rounding.  Relative error against 64 bits on 18944-wide rows:
+            // 6.1e-8 with fp32 stages, 2.6e-8 so (the general kernel, with fp64 block sums, 3.6e-8).  fp64 additions run at
+            // the fp32 rate; the launch stays bound by its traffic (4.2 - 5.4 TB/s on 2^26 values).
+            __syncthreads();                            // the operand buffer is free from here on
+            int gq, cq, rq;
+            wg_lane<CB>(lane, gq, cq, rq);
+            const int64_t row0 = pass * RPW, left = a.rows - row0;
+            const int live_rows = left < RPW ? (int)left : RPW;
+            const auto ys = __builtin_amdgcn_make_buffer_rsrc(static_cast<char*>(sa.Y) + row0 * sa.ld_out * 4, 0,
+                                                              (int)(((live_rows - 1) * sa.ld_out + sa.d_out) * 4), 0x00020000);
+            auto sign = [&](int b) { return __builtin_bit_cast(double, make_uint2(0u, 0x3FF00000u | ((uint32_t)(cq >> b) << 31))); };
+#pragma unroll
+            for (int ip = 0; ip < 4; ++ip) {
+                double v[8];
+#pragma unroll
+                for (int nt = 0; nt < 8; ++nt) v[nt] = (double)acc[nt][ip];
+#pragma unroll
+                for (int s = 1; s < 8; s <<= 1)
+#pragma unroll
+                    for (int nt = 0; nt < 8; ++nt)
+                        if (!(nt & s)) {
+                            const double u = v[nt], w = v[nt | s];
+                            v[nt] = u + w;
+                            v[nt | s] = u - w;
+                        }
+                float o[8];
+#pragma unroll
+                for (int nt = 0; nt < 8; ++nt) {
+                    double x = v[nt];
+                    x = fma(x, sign(0), dpp_d<kDppXor1>(x));
+                    x = fma(x, sign(1), dpp_d<kDppXor2>(x));
+                    if constexpr (CB >= 3) x = fma(x, sign(2), dpp_d<kDppHalfMirror>(x));
+                    if constexpr (CB >= 4) x = fma(x, sign(3), dpp_d<kDppRor8>(x));
+                    o[nt] = (float)(x * sa.inv);
+                }
+                const int ao0 = 16 * wave + 4 * ip;
+                store_block_f32(reinterpret_cast<float*>(stage) + wave * 512, ((rq * 4 + gq) << CB) + cq, lane, o,
+                                [&](int e, const u32x4& unit) {
+                    const int rs = CB == 4 ? 0 : e / (4 * SEG), col = ao0 * SEG + (CB == 4 ? e : e % (4 * SEG));
+                    const uint32_t off = CB == 4 || col < sa.d_out ? (uint32_t)(rs * (int)sa.ld_out + col) * 4u : 0x80000000u;
+                    __builtin_amdgcn_raw_buffer_store_b128(unit, ys, off, 0, 2);
+                });
+            }
+            continue;
+        }
 #pragma unroll
         for (int s = 1; s < 8; s <<= 1)
 #pragma unroll
@@ -289,10 +337,11 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
             // row per pass the columns from d_out on) is not stored
             int gq, cq, rq;
             wg_lane<CB>(lane, gq, cq, rq);
-            const float k = ((__builtin_popcount(CB == 4 ? cq : cq >> 1) & 1) ? -sa.inv : sa.inv) * rscale;
+            const float sgn = (__builtin_popcount(CB == 4 ? cq : cq >> 1) & 1) ? -1.0f : 1.0f;
+            const float k = sgn * (float)sa.inv * rscale;
             const int64_t row0 = pass * RPW, left = a.rows - row0;
             const int live_rows = left < RPW ? (int)left : RPW;
-            const int esz = sa.out == 1 ? 4 : 2;
+            constexpr int esz = WIDE ? 4 : 2;
             const auto ys = __builtin_amdgcn_make_buffer_rsrc(static_cast<char*>(sa.Y) + row0 * sa.ld_out * esz, 0,
                                                               (int)(((live_rows - 1) * sa.ld_out + sa.d_out) * esz), 0x00020000);
 #pragma unroll
@@ -301,9 +350,13 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
                 float o[8];
 #pragma unroll
                 for (int nt = 0; nt < 8; ++nt) o[nt] = acc[nt][ip];
-                if (sa.out == 1) {
+                if constexpr (WIDE) {
+                    // (exact integers times the scale: one rounding)
+                    const double kd = (double)(sgn * rscale) * sa.inv;
+#pragma unroll
+                    for (int nt = 0; nt < 8; ++nt) o[nt] = (float)((double)o[nt] * kd);
                     // block rows ao0 .. ao0 + 3 of each row of the pass are 4 SEG consecutive values
-                    store_block_f32(reinterpret_cast<float*>(stage) + wave * 512, ((rq * 4 + gq) << CB) + cq, lane, o, k, 0.0f,
+                    store_block_f32(reinterpret_cast<float*>(stage) + wave * 512, ((rq * 4 + gq) << CB) + cq, lane, o,
                                     [&](int e, const u32x4& unit) {
                         const int rs = CB == 4 ? 0 : e / (4 * SEG), col = ao0 * SEG + (CB == 4 ? e : e % (4 * SEG));
                         const uint32_t off = CB == 4 || col < sa.d_out ? (uint32_t)(rs * (int)sa.ld_out + col) * 4u : 0x80000000u;
@@ -424,10 +477,10 @@ using WgKernel = void (*)(WaveArgs, int, WgArgs<SINK>);
 // One launch: as many workgroups as fit the chip (registers, LDS), each looping over rows.
 template <int KK, int SINK>
 int wg_launch(const rq_hadamard* h, WgKernel<SINK> fn, const WaveArgs& a, int pb, int cb, size_t lds, const WgArgs<SINK>& sa,
-              hipStream_t s) {
+              hipStream_t s, int waves_per_simd = wg_waves_per_simd<KK>()) {
     const int nw = (pb + 15) / 16;
     int per_cu = (int)((size_t)h->max_lds / (lds + 128));
-    const int by_waves = 4 * wg_waves_per_simd<KK>() / nw;   // see the register budget note at the kernel
+    const int by_waves = 4 * waves_per_simd / nw;   // see the register budget note at the kernel
     if (per_cu > by_waves) per_cu = by_waves;
     if (per_cu < 1) per_cu = 1;
     const int64_t cap = (int64_t)h->num_cu * per_cu;

@@ -72,3 +72,27 @@ def test_dequantize_rotate(n, d, d_out, rows, kernel, b):
             assert h.last_kernel == f"{kernel}_dequant_rotate"
             _close(buf[:rows, :d_out], want[:, :d_out], out_dtype, f"n={n} b={b} ->{out_dtype} transpose={transpose}")
             assert bool((buf[:, d_out:] == 7.0).all()) and bool((buf[rows:] == 7.0).all())
+
+
+@pytest.mark.parametrize("n", [896, 3584, 4864, 5120, 8960, 16384, 18944, 28672])
+def test_fp32_results_are_rounded_once(n):
+    """Error of fp32 results against 64 bits, 2-norm.  One rounding to nearest is uniform within 2^-24 of a value at most:
+    2^-24 / sqrt(3).  From codes the sums are exact integers; from 16-bit rows the partial sums of a block stay within 24
+    bits but for rare small terms.  With fp32 stages behind the block, rows have 3.7e-8 (896) to 7.4e-8 (13824)."""
+    import torch
+    rng = np.random.default_rng(n)
+    h = binding.hadamard_build(n)
+    bound = 2.0 ** -24 / 3 ** 0.5
+
+    def rel(got, want):
+        return np.linalg.norm(got.double().cpu().numpy() - want) / np.linalg.norm(want)
+
+    q = rng.integers(-4, 4, size=(16, n))
+    scales = rng.uniform(0.5, 2.0, size=16).astype(np.float32)
+    got = binding.dequantize_rotate(h, torch.from_numpy(oracle.pack_codes(q, 3)).cuda(), torch.from_numpy(scales).cuda(), 3)
+    assert rel(got, oracle.rotate_back(oracle.dequantize(q, scales.astype(np.float64)), n)) <= bound
+    if n != 3584:                                       # (one-wave kernel: fp32 stages)
+        x = rng.standard_normal((16, n)).astype(np.float16)
+        for transpose in (False, True):
+            want = oracle.rotate_back(oracle.as_f64(x), n) if transpose else oracle.rotate(x, n)
+            assert rel(binding.rotate(h, parity.to_device(x), transpose=transpose), want) <= bound
