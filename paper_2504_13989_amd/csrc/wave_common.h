@@ -411,14 +411,17 @@ __device__ __forceinline__ float rows_sum(float v) {
 // so the reduction runs on unsigned integers (one DPP-fused v_max_u32 per step).  ROW_BITS of
 // the four DPP row patterns are used (lanes that share a row differ in those bits), then the two
 // cross-row steps.
-template <int ROW_BITS = 4>
-__device__ __forceinline__ float wave_absmax(float mf) {
-    uint32_t m = __float_as_uint(mf);
+template <int ROW_BITS>
+__device__ __forceinline__ uint32_t lanes_max_u32(uint32_t m) {
     m = max(m, dpp_u<kDppXor1>(m));
     m = max(m, dpp_u<kDppXor2>(m));
     if (ROW_BITS >= 3) m = max(m, dpp_u<kDppHalfMirror>(m));
     if (ROW_BITS >= 4) m = max(m, dpp_u<kDppRor8>(m));
-    return __uint_as_float(rows_max_u32(m));
+    return m;
+}
+template <int ROW_BITS = 4>
+__device__ __forceinline__ float wave_absmax(float mf) {
+    return __uint_as_float(rows_max_u32(lanes_max_u32<ROW_BITS>(__float_as_uint(mf))));
 }
 
 // Min / max of eight floats as three-operand instructions.  Written in assembly because the

@@ -92,6 +92,13 @@ __device__ __forceinline__ void wg_lane(int lane, int& g, int& cl, int& rsub) {
     rsub = CB == 4 ? 0 : c >> CB;
 }
 
+// The sign a lane's values carry after the column transform (CB < 4: the first lane stage is the plain one, the fused
+// ones start at the second bit).
+template <int CB>
+__device__ __forceinline__ float wg_flip(int cl) {
+    return (__builtin_popcount(CB == 4 ? cl : cl >> 1) & 1) ? -1.0f : 1.0f;
+}
+
 // SRC: 0 = 16-bit rows of X, 3 / 4 = packed signed codes of that width (kWgRotate only): the lane's eight codes of
 // a block row become fp16 integers (codes_f16), the matrix cores contract them exactly, and the
 // row's scale multiplies once at the end.
@@ -121,9 +128,10 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
     u32x4 A[KK];
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) A[kk] = a.tiles[(wave * KK + kk) * 64 + lane];
-    const float c1h = (float)a.c1, c1l = (float)(a.c1 - (double)c1h);
-    // CB < 4: the first lane stage is the plain one, the fused ones start at the second bit
-    const float flip = (__builtin_popcount(CB == 4 ? c : cl >> 1) & 1) ? -1.0f : 1.0f;
+    // (uniform, but computed by vector instructions: moved to scalar registers)
+    auto uniform = [](float x) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x))); };
+    const float c1h = uniform((float)a.c1), c1l = uniform((float)(a.c1 - (double)c1h));
+    const float flip = wg_flip<CB>(cl);
     const uint32_t sg0 = (c & 1) ? 0x80000000u : 0u;
 
     // phase-1 geometry: lane (g, c) loads block rows 16 wave + 4 g + t, t = 0..3, at constant
@@ -202,8 +210,6 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
     };
     if (PF && (int64_t)blockIdx.x < n_pass) load_pass(blockIdx.x);
     for (int64_t pass = blockIdx.x; pass < n_pass; pass += gridDim.x) {
-        const int64_t row = pass * RPW + rsub;
-        const bool live = CB == 4 || row < a.rows;
         if (!PF) load_pass(pass);
         if constexpr (SRC != 0) {
 #pragma unroll
@@ -226,8 +232,9 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
         if (PF && pass + gridDim.x < n_pass) load_pass(pass + gridDim.x);
         // ---- phase 2
         // Waves of another workgroup that are in their vector phases go first: a wave in here mostly waits for its
-        // operand reads or for the matrix cores (18944-wide rows: 56.3 -> 54.9 us; the rotation, bound by its memory
-        // traffic, gains nothing)
+        // operand reads or for the matrix cores (4096 rows of 18944, b = 3: 52.8 -> 51.8 us; 512 MiB of 8960-wide rows,
+        // b = 4 204 -> 196; 14336, 28672 and 4864 wide: no difference; the rotation, bound by its memory traffic, gains
+        // nothing)
         if constexpr (SINK != kWgRotate) __builtin_amdgcn_s_setprio(0);
         f32x4 acc[8];
 #pragma unroll
@@ -337,7 +344,7 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
             // row per pass the columns from d_out on) is not stored
             int gq, cq, rq;
             wg_lane<CB>(lane, gq, cq, rq);
-            const float sgn = (__builtin_popcount(CB == 4 ? cq : cq >> 1) & 1) ? -1.0f : 1.0f;
+            const float sgn = wg_flip<CB>(cq);
             const float k = sgn * (float)sa.inv * rscale;
             const int64_t row0 = pass * RPW, left = a.rows - row0;
             const int live_rows = left < RPW ? (int)left : RPW;
@@ -379,16 +386,30 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
         if (g == 0 && cl == 0) wmax[rsub * 16 + wave] = m;
         __syncthreads();    // also: every wave is done reading this row's operands from LDS
         {
-            // all waves' maxima with a few 16-byte reads in flight together: one read per wave, each waiting for the
-            // one before it, took nw LDS latencies at the point where every wave of the workgroup waits for them
-            // (18944-wide rows, ten waves: 57.2 -> 56.3 us for 4096 rows)
-            constexpr int NQ = (2 * KK + 3) / 4;
-            f32x4 q[NQ];
+            // All waves' maxima with one LDS latency (a read per wave, each waiting for the one before it, takes nw of
+            // them while the whole workgroup waits: 14336-wide rows, b = 4, 512 MiB 154 -> 145 us).  Up to four 16-byte
+            // reads in flight, or, where their registers spill (KK = 5 with several rows per pass: 80 registers for 32
+            // values and 20 of operand tiles; 8960-wide rows 196 -> 165 us), one read: the lane of chunk cl takes RPW of the
+            // row's 16 slots and the lanes that share the row do the rest.  (Elsewhere the reads are the faster: 4864-wide
+            // rows 148 against 151 us.)
+            int gq, cq, rq;
+            wg_lane<CB>(lane, gq, cq, rq);
+            if constexpr (KK == 5 && CB < 4) {
+                uint32_t u[RPW];
+                __builtin_memcpy(u, &wmax[rq * 16 + cq * RPW], sizeof u);
+                uint32_t mu = u[0];
 #pragma unroll
-            for (int i = 0; i < NQ; ++i) q[i] = *reinterpret_cast<const f32x4*>(&wmax[rsub * 16 + 4 * i]);
-            m = 0.0f;
+                for (int i = 1; i < RPW; ++i) mu = max(mu, u[i]);
+                m = __uint_as_float(lanes_max_u32<CB>(mu));
+            } else {
+                constexpr int NQ = (2 * KK + 3) / 4;
+                f32x4 q[NQ];
 #pragma unroll
-            for (int i = 0; i < NQ; ++i) m = absmax4(m, q[i]);
+                for (int i = 0; i < NQ; ++i) q[i] = *reinterpret_cast<const f32x4*>(&wmax[rq * 16 + 4 * i]);
+                m = 0.0f;
+#pragma unroll
+                for (int i = 0; i < NQ; ++i) m = absmax4(m, q[i]);
+            }
         }
         // ---- phase 4
         if constexpr (QE) {
@@ -416,16 +437,29 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
             }
             continue;
         }
+        // Where registers are tight (several rows per pass; b = 4 at 80 registers) the lane's place is worked out again
+        // here, so that nothing of it is held through the phases before (512 MiB of rows: 8960 wide, b = 4 229 -> 196 us;
+        // 18944 wide, b = 4 182 -> 175).  Elsewhere holding it is the faster: 14336 wide, b = 4 145 against 150, 18944 wide,
+        // b = 3 169 against 173, 1792 wide (KK = 1) 132 against 134.
+        constexpr bool AGAIN = KK > 1 && (CB < 4 || (BITS == 4 && wg_waves_per_simd<KK>() == 6));
+        int gq = g, cq = cl, rq = rsub, lq = lane;
+        if constexpr (AGAIN) {
+            wg_lane<CB>(lane, gq, cq, rq);
+            asm volatile("" : "+v"(lq));
+        }
+        const int64_t row = pass * RPW + rq;
+        const bool live = CB == 4 || row < a.rows;
+        const float fl = AGAIN ? wg_flip<CB>(cq) : flip;
         // (2^b - 1) / (clip m) from a float pair of the constant: reciprocal, Newton step, correction
-        const float s = m > 0.0f ? flip * div_pair(c1h, c1l, m) : 0.0f;
+        const float s = m > 0.0f ? fl * div_pair(c1h, c1l, m) : 0.0f;
         uint32_t* out = a.codes + row * (int64_t)(SEG * BITS / 32) * pb;   // used by live lanes only
 #pragma unroll
         for (int ip = 0; ip < 4; ++ip) {
-            const int ao = 16 * wave + 4 * ip + g;      // output block row of this register
+            const int ao = 16 * wave + 4 * ip + gq;      // output block row of this register
             const uint32_t w = Quant<BITS>::pack8(acc[0][ip], acc[1][ip], acc[2][ip], acc[3][ip],
                                                   acc[4][ip], acc[5][ip], acc[6][ip], acc[7][ip], s);
             if constexpr (CB == 4) {
-                const int word = ao * 16 + c;
+                const int word = ao * 16 + cq;
                 if (BITS == 4) {
                     if (ao < pb) store_codes(out + word, w);
                 } else {
@@ -434,9 +468,9 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
             } else if (ao < pb) {
                 // the pass's rows are staged one after the other, each pb * 2^CB groups of 8 codes
                 if (BITS == 4) {
-                    if (live) store_codes(out + (ao << CB) + cl, w);
+                    if (live) store_codes(out + (ao << CB) + cq, w);
                 } else {
-                    stage24(stage, ((rsub * pb + ao) << CB) + cl, w);
+                    stage24(stage, ((rq * pb + ao) << CB) + cq, w);
                 }
             }
         }
@@ -446,10 +480,10 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             constexpr int UPR = 3 << CB;
-            const int rs = lane / UPR;
-            const int unit = UPR * wave + lane % UPR;   // the row has pb * UPR / 16 units
+            const int rs = lq / UPR;
+            const int unit = UPR * wave + lq % UPR;   // the row has pb * UPR / 16 units
             const int64_t orow = pass * RPW + rs;
-            if (lane < 48 && unit * 16 < pb * UPR && orow < a.rows)
+            if (lq < 48 && unit * 16 < pb * UPR && orow < a.rows)
                 __builtin_nontemporal_store(
                     *reinterpret_cast<const u32x4*>(stage + (size_t)rs * pb * UPR + unit * 16),
                     reinterpret_cast<u32x4*>(a.codes + orow * (int64_t)(SEG * 3 / 32) * pb) + unit);
@@ -460,12 +494,12 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const int unit = 48 * wave + lane;          // 16-byte units; the row has 3 pb of them
-            if (lane < 48 && unit < 3 * pb)
+            const int unit = 48 * wave + lq;          // 16-byte units; the row has 3 pb of them
+            if (lq < 48 && unit < 3 * pb)
                 __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(stage + unit * 16),
                                             reinterpret_cast<u32x4*>(out) + unit);
         }
-        if (wave == 0 && g == 0 && cl == 0 && live) a.scales[row] = (float)(a.c2 * (double)m);
+        if (wave == 0 && gq == 0 && cq == 0 && live) a.scales[row] = (float)(a.c2 * (double)m);
         }
     }
 }
