@@ -164,38 +164,15 @@ struct Out {
     }
 };
 
-// The results of a quantizing call: codes [rows, row_bytes], then one or two float tensors of `size`.  Small results that
-// the caller does not give are cut from one allocation: taking and returning a block of the allocator is most of what a
-// result costs the host (16 x 4096 rows 4.6 -> 4.0 us a call).  Tensors cut from one allocation keep each other's memory
-// alive and are saved together, so this stops at kShared bytes; the kernels of larger results outlast the host's work
-// (2048 x 4096 rows, 4 MB: 5.6 us either way).
+// The results of a quantizing call: codes [rows, row_bytes], then one or two float tensors of `size`.  Each has a storage
+// of its own: torch does not save tensors of different types that share one, and a result that is resized must not
+// grow into another.  (One allocation for all of them would save the host 0.5 us a call.)
 void make_results(c10::Device device, int64_t rows, int64_t row_bytes, at::IntArrayRef size, std::initializer_list<PyObject*> given,
                   std::initializer_list<Out*> outs) {
     PyObject* const* g = given.begin();
     Out* const* o = outs.begin();
-    const size_t k = outs.size();
-    int64_t count = 1;
-    for (int64_t n : size) count *= n;
-    constexpr int64_t kStep = 512;                       // the allocator's own granularity
-    constexpr int64_t kShared = 1 << 20;
-    const int64_t code_step = (rows * row_bytes + kStep - 1) / kStep * kStep, float_step = (count * 4 + kStep - 1) / kStep * kStep;
-    bool together = code_step + (int64_t)(k - 1) * float_step <= kShared;
-    for (size_t i = 0; i < k; ++i) together = together && g[i] == Py_None;
-    if (!together) {
-        o[0]->make(g[0], {rows, row_bytes}, at::kByte, device);
-        for (size_t i = 1; i < k; ++i) o[i]->make(g[i], size, at::kFloat, device);
-        return;
-    }
-    at::Tensor codes(at::detail::empty_cuda({code_step + (int64_t)(k - 1) * float_step}, at::kByte, device, std::nullopt));
-    for (size_t i = 1; i < k; ++i) {
-        auto impl = c10::make_intrusive<c10::TensorImpl>(c10::Storage(codes.storage()), codes.key_set(),
-                                                         c10::scalarTypeToTypeMeta(at::kFloat));
-        impl->set_storage_offset((code_step + (int64_t)(i - 1) * float_step) / 4);
-        impl->set_sizes_contiguous(size);
-        o[i]->adopt(at::Tensor(std::move(impl)));
-    }
-    codes.unsafeGetTensorImpl()->set_sizes_contiguous({rows, row_bytes});
-    o[0]->adopt(std::move(codes));
+    o[0]->make(g[0], {rows, row_bytes}, at::kByte, device);
+    for (size_t i = 1; i < outs.size(); ++i) o[i]->make(g[i], size, at::kFloat, device);
 }
 
 template <typename F>

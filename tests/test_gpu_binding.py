@@ -70,11 +70,18 @@ def test_errors():
 
 
 @pytest.mark.parametrize("rows", [16, 4096])
-def test_results_share_memory_only_while_small(rows):
-    """codes of 16 x 2048 bytes and their scales come from one allocation, codes of 8 MB stand alone"""
-    h = binding.hadamard_build(4096)
-    codes, scales = binding.rotate_quantize(h, _rows(rows, 4096), 4, 0.9)
-    shared = codes.untyped_storage().data_ptr() == scales.untyped_storage().data_ptr()
-    assert shared == (rows == 16)
-    assert scales.untyped_storage().nbytes() <= (1 << 20)
-    assert codes.shape == (rows, 2048) and scales.shape == (rows,) and codes.is_contiguous() and scales.is_contiguous()
+@pytest.mark.parametrize("call", ["rotate_quantize", "rotate_quantize_asym", "quantize", "quantize_asym"])
+def test_results_are_saved_together_and_resized_apart(tmp_path, call, rows):
+    """every result has a storage of its own, of its own size: torch.save takes them in one file, and resizing one
+    leaves the others alone"""
+    x = _rows(rows, 256)
+    fn = getattr(binding, call)
+    results = fn(binding.hadamard_build(256), x, 4, 0.9) if call.startswith("rotate") else fn(x, 4, 0.9)
+    assert [r.untyped_storage().nbytes() for r in results] == [r.numel() * r.element_size() for r in results]
+    assert len({r.untyped_storage().data_ptr() for r in results}) == len(results)
+    torch.save(results, tmp_path / "results.pt")
+    back = torch.load(tmp_path / "results.pt", weights_only=True)
+    assert all(torch.equal(a, b) for a, b in zip(results, back))
+    kept = [r.clone() for r in results[1:]]
+    results[0].resize_(rows + 8, 128).fill_(255)
+    assert all(torch.equal(a, b) for a, b in zip(results[1:], kept))
