@@ -640,8 +640,10 @@ namespace {
 constexpr int64_t kGbsSmall = (int64_t)1 << 22;              // rows * n up to which 5 steps are taken
 int gbs_depth(int64_t rows, int n) { return (double)rows * (double)n <= (double)kGbsSmall ? 5 : 3; }
 
-// Most steps a search down to a bracket of eps can take: two steps halve the bracket (from 1, by way of 3/4).
+// Most steps a search down to a bracket of eps can take: two steps halve the bracket (from 1, by way of 3/4).  That
+// holds while the midpoints are exact; a bracket of a few ulps stops shrinking and the search goes on to its limit.
 int gbs_most_steps(double eps, int limit) {
+    if (eps < 0x1p-50) return limit;
     int steps = 0;
     for (double w = 1.0; w > eps && steps < limit; ++steps) w = steps % 2 == 0 ? w * 0.75 : w / 1.5;
     return steps;

@@ -33,6 +33,22 @@ def test_search_takes_the_steps_of_algorithm_1(n, d, rows, dtype):
         assert short == trace[:4]
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("eps", [1e-15, 1e-16, 1e-30])
+def test_a_bracket_that_stops_shrinking(dtype, eps):
+    """Below an ulp of the clip ratio the bracket no longer shrinks: the search ends at its limit of evaluations, in the
+    batched form (fp32 rows) as in the resident one."""
+    rng = np.random.default_rng(8)
+    xf = rng.standard_normal((16, 1024)).astype(np.float32)
+    x = parity.to_device(xf if dtype == "f32" else wl.f32_to_bf16_bits(xf))
+    for limit in (128, 256):
+        clip, mse, trace = binding.gbs_search(binding.hadamard_build(1024), x, 3, eps, max_evals=limit)
+        seen = dict(trace)
+        m, fm, otrace = oracle.gbs_search(lambda c: seen[np.float32(c)], float(np.float32(eps)), max_evals=limit)
+        assert [np.float32(c) for c, _ in otrace] == [np.float32(c) for c, _ in trace]
+        assert clip == np.float32(m) and mse == fm
+
+
 def test_searches_of_several_threads_and_streams():
     import threading
     import torch
