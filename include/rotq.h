@@ -335,10 +335,11 @@ size_t rq_gbs_workspace(int64_t rows);
  * comparisons give), and the comparisons are taken on the device: rows the chip can hold in registers
  * are rotated once and searched in one launch, other tensors take a few launches enqueued together.
  * The call waits for the result: a calibration call, not a hot-path call (not for a stream under
- * capture).  A search uses about 260 KB of device memory and 2 KB of pinned host memory that the
- * library allocates and keeps for the next one: up to four sets per device, given back when the last
- * handle on the device is freed; nothing else is allocated.  Searches may run on any number of threads and streams; one at
- * a time per device takes the single-launch form.
+ * capture).  Besides the workspace a search uses static device memory (as rq_quant_error_noalloc does) and 256 KB of
+ * device and 33 KB of pinned host memory that the first search on a device allocates and that stay until the process
+ * ends; where the pinned memory cannot be had the results are copied back on `stream` instead, and more than 16 searches
+ * at once on a device allocate a few KB for the call.  Searches may run on any number of threads and streams; one at a
+ * time per device takes the single-launch form.
  *   eps          [in]  bracket width to stop at, > 0
  *   max_evals    [in]  1 .. 256
  *   workspace    [in]  DEVICE, >= rq_gbs_workspace(rows) bytes, 8-byte aligned, scratch
@@ -365,7 +366,7 @@ int rq_gbs_search_asym(const rq_hadamard_t* h, const void* X, int dtype, int64_t
  * Select the kernel family for subsequent hot-path calls on this handle (testing /
  * measurement): 0 = automatic (fastest available), 1 = the general LDS kernel; for long
  * power-of-two rows 2 = one wave per row at any row count, 3 / 4 = a row split over 2 / 4 waves
- * at any row count (automatic picks by the number of rows).
+ * at any row count (automatic picks by the number of rows); automatic but for the searches: 7 = no pinned memory.
  * Errors: RQ_ERR_ARG.
  */
 int rq_hadamard_set_variant(rq_hadamard_t* h, int variant);

@@ -8,6 +8,8 @@
 // The probes are taken in the listing's order, but evaluated ahead of time in batches: where a probe lies depends only
 // on the outcomes of the comparisons before it, so one batch covers every probe the next `depth` steps can ask for, a
 // binary tree over those outcomes.  The sequence of probes is that of the one-at-a-time loop.
+#include <mutex>
+
 #include "row_rotation.h"
 
 namespace rq {
@@ -143,6 +145,7 @@ __global__ __launch_bounds__(kStepThreads) void k_gbs_step(GbsDev* state, GbsOut
         state->fm = fm;
         state->evals = evals;
         state->done = finished;
+        if (first && !finished) out->done = 0;
         if (finished) {
             state->clips.n = 0;
             out->clip = (float)st.best;
@@ -463,6 +466,26 @@ int gbs_resident(const rq_hadamard* h, const RowArgs& a, GbsOut* out, uint64_t* 
 }
 
 size_t gbs_state_bytes() { return sizeof(GbsDev); }
+GbsDev* gbs_state_at(GbsDev* base, int slot) { return base + slot; }
+
+static __device__ GbsDev g_states[kSearchSlots];
+static __device__ GbsOut g_outs[kSearchSlots];
+
+SearchMemory search_memory(int dev) {
+    constexpr int kMaxDevices = 64;
+    static std::mutex lock;
+    static SearchMemory found[kMaxDevices];
+    if (dev < 0 || dev >= kMaxDevices) return SearchMemory{};
+    std::lock_guard<std::mutex> hold(lock);
+    if (found[dev].state) return found[dev];
+    int cur = -1;
+    void *state = nullptr, *out = nullptr;
+    if (hipGetDevice(&cur) == hipSuccess && cur == dev && hipGetSymbolAddress(&state, HIP_SYMBOL(g_states)) == hipSuccess &&
+        hipGetSymbolAddress(&out, HIP_SYMBOL(g_outs)) == hipSuccess)
+        found[dev] = SearchMemory{static_cast<GbsDev*>(state), static_cast<GbsOut*>(out)};
+    (void)hipGetLastError();
+    return found[dev];
+}
 const ClipList* gbs_state_clips(const GbsDev* state) { return &state->clips; }
 
 void gbs_first_batch(double eps, int depth, int bits, ClipList* out) {

@@ -27,6 +27,8 @@ int check_rows(const rq_hadamard_t* h, const void* X, int dtype, int64_t rows, i
 
 bool clip_ok(float c) { return c > 0.0f && c <= 1.0f; }   // false for NaN
 
+constexpr int kSearchUnpinned = 7;       // variants that only searches know, see rq_hadamard_set_variant
+
 // records which kernel family a call chose (diagnostic; the handle's only field written after build)
 void note(const rq_hadamard_t* h, const char* name) { h->last_kernel.store(name, std::memory_order_relaxed); }
 
@@ -64,132 +66,109 @@ struct TableSet {
     }
 };
 
-// What a search needs besides the caller's workspace: its state on the device and the results in host memory the device
-// writes.
+// What a search needs besides the caller's workspace: its state on the device, and its results in pinned host memory the
+// device writes (`out`) or, where there is none, in device memory (`out` is null) from where they are copied.
 struct SearchMem {
-    int device;
-    uint32_t epoch;           // first step number that is not in `exchange`
-    uint64_t* exchange;       // of the resident form: two buffers, taken in turn
+    int slot;                 // of the device's static memory; negative: `own` holds the state and the results
     rq::GbsDev* state;
-    rq::GbsOut* out;          // pinned, mapped
+    rq::GbsOut* out;
     rq::GbsOut* out_dev;
+    void* own;
 };
 
-// The devices that handles live on.  A few sets are kept for the next search there and given back with the device's last
-// handle; nothing below allocates host memory once a handle exists.
+// Searches under way on a device.  The states and the results' device copies are static device arrays, as the scratch of
+// rq_quant_error_noalloc is; the pinned memory (33 KB) and the resident form's exchange buffers (256 KB) are allocated by
+// the first search on a device that wants them and, like the arrays, stay until the process ends: a handle built for one
+// search pays for neither.  (Exchange buffers in a static array cost a search of 512 x 4096 rows 48.6 us instead of
+// 45.5.)  Constant-initialised, so there is nothing to construct.
+constexpr int kMaxDevices = 64;
 struct SearchDevice {
-    static constexpr int kKeep = 4;
-    int device;
-    int handles;
+    uint32_t used;            // slots in use, one bit each
     bool resident;            // a resident search is under way: one at a time, since two of them could each keep the
                               // other's workgroups from running (a second one takes the batched form)
-    int kept;
-    SearchMem mem[kKeep];
+    uint64_t* exchange;       // of the resident form: two buffers, taken in turn
+    uint32_t epoch;           // first step number that is not in them
+    rq::GbsOut *out, *out_dev;
 };
+static_assert(rq::kSearchSlots <= 32, "one bit each");
 std::mutex g_search_lock;
-std::vector<SearchDevice>& search_devices() {
-    static std::vector<SearchDevice>* devices = new std::vector<SearchDevice>;   // not torn down before the runtime is
-    return *devices;
-}
-// (g_search_lock held)
-SearchDevice* search_device(int device) {
-    for (SearchDevice& d : search_devices())
-        if (d.device == device) return &d;
-    return nullptr;
-}
+SearchDevice g_search[kMaxDevices];
 
-void free_search_mem(const SearchMem& m) {
-    (void)hipFree(m.exchange);                            // waits for a search that is still leaving the device
-    (void)hipHostFree(m.out);
-    (void)hipGetLastError();
-}
-
-bool add_handle(int device) {
-    std::lock_guard<std::mutex> hold(g_search_lock);
-    SearchDevice* d = search_device(device);
-    if (!d) {
-        try {
-            search_devices().push_back(SearchDevice{device, 0, false, 0, {}});
-        } catch (const std::bad_alloc&) {
-            return false;
-        }
-        d = &search_devices().back();
-    }
-    ++d->handles;
-    return true;
-}
-
-void remove_handle(int device) {
-    SearchMem mem[SearchDevice::kKeep];
-    int n = 0;
-    {
-        std::lock_guard<std::mutex> hold(g_search_lock);
-        SearchDevice* d = search_device(device);
-        if (!d || --d->handles > 0) return;
-        n = d->kept;
-        std::copy(d->mem, d->mem + n, mem);
-        d->kept = 0;
-    }
-    for (int i = 0; i < n; ++i) free_search_mem(mem[i]);
-}
-
-// The turn of the resident form on a device (negative: none is wanted).
+// The turn of the resident form on a device, where it is wanted and its buffers can be had.
 class ResidentTurn {
-    int device_;
-    bool mine_ = false;
+    SearchDevice* mine_ = nullptr;
 public:
-    explicit ResidentTurn(int device) : device_(device) {
-        if (device < 0) return;
+    ResidentTurn(int device, bool wanted) {
+        if (!wanted || device >= kMaxDevices) return;
         std::lock_guard<std::mutex> hold(g_search_lock);
-        SearchDevice* d = search_device(device);
-        if (d && !d->resident) mine_ = d->resident = true;
+        SearchDevice& d = g_search[device];
+        if (d.resident) return;
+        if (!d.exchange) {
+            void* p = nullptr;
+            int cur = -1;
+            if (hipGetDevice(&cur) != hipSuccess || cur != device || hipMalloc(&p, 2 * rq::gbs_exchange_bytes()) != hipSuccess) {
+                (void)hipGetLastError();
+                return;
+            }
+            d.exchange = static_cast<uint64_t*>(p);
+        }
+        mine_ = &d;
+        mine_->resident = true;
     }
     ~ResidentTurn() {
         if (!mine_) return;
         std::lock_guard<std::mutex> hold(g_search_lock);
-        search_device(device_)->resident = false;         // (entries stay for good)
+        mine_->resident = false;
     }
     ResidentTurn(const ResidentTurn&) = delete;
     ResidentTurn& operator=(const ResidentTurn&) = delete;
     explicit operator bool() const { return mine_; }
+    SearchDevice* operator->() const { return mine_; }    // (exchange, epoch: only the turn's holder touches them)
 };
 
-int take_search_mem(int device, SearchMem* m) {
+int take_search_mem(int device, bool pinned, SearchMem* m) {
+    const rq::SearchMemory st = rq::search_memory(device);
+    if (!st.state) return RQ_ERR_HIP;
+    int slot = -1;
+    rq::GbsOut *out = nullptr, *out_dev = nullptr;
     {
         std::lock_guard<std::mutex> hold(g_search_lock);
-        SearchDevice* d = search_device(device);
-        if (d && d->kept > 0) {
-            *m = d->mem[--d->kept];
-            return RQ_OK;
+        SearchDevice& d = g_search[device];
+        for (int i = 0; i < rq::kSearchSlots && slot < 0; ++i)
+            if (!(d.used >> i & 1u)) slot = i;
+        if (slot >= 0) d.used |= 1u << slot;
+        if (slot >= 0 && pinned && !d.out) {
+            void *host = nullptr, *dev = nullptr;
+            if (hipHostMalloc(&host, rq::kSearchSlots * sizeof(rq::GbsOut), hipHostMallocMapped | hipHostMallocPortable) == hipSuccess &&
+                hipHostGetDevicePointer(&dev, host, 0) == hipSuccess && dev) {
+                d.out = static_cast<rq::GbsOut*>(host);
+                d.out_dev = static_cast<rq::GbsOut*>(dev);
+            } else {
+                if (host) (void)hipHostFree(host);
+                (void)hipGetLastError();
+            }
         }
+        if (pinned) out = d.out, out_dev = d.out_dev;
     }
-    int cur = -1;
-    void *state = nullptr, *out = nullptr, *out_dev = nullptr;
-    const size_t ex = 2 * rq::gbs_exchange_bytes();       // (the state follows it in the same allocation)
-    if (hipGetDevice(&cur) == hipSuccess && cur == device && hipMalloc(&state, ex + rq::gbs_state_bytes()) == hipSuccess &&
-        hipMemset(state, 0, ex) == hipSuccess && hipDeviceSynchronize() == hipSuccess &&
-        hipHostMalloc(&out, sizeof(rq::GbsOut), hipHostMallocMapped) == hipSuccess &&
-        hipHostGetDevicePointer(&out_dev, out, 0) == hipSuccess && out_dev) {
-        *m = SearchMem{device, 1u, static_cast<uint64_t*>(state),
-                       reinterpret_cast<rq::GbsDev*>(static_cast<char*>(state) + ex), static_cast<rq::GbsOut*>(out), static_cast<rq::GbsOut*>(out_dev)};
+    if (slot >= 0) {
+        *m = SearchMem{slot, rq::gbs_state_at(st.state, slot), out ? out + slot : nullptr, out ? out_dev + slot : st.out + slot, nullptr};
         return RQ_OK;
     }
-    if (state) (void)hipFree(state);
-    if (out) (void)hipHostFree(out);
-    (void)hipGetLastError();
-    return RQ_ERR_HIP;
+    void* own = nullptr;                                  // more searches at once than there are slots
+    if (hipMalloc(&own, rq::gbs_state_bytes() + sizeof(rq::GbsOut)) != hipSuccess) {
+        (void)hipGetLastError();
+        return RQ_ERR_HIP;
+    }
+    *m = SearchMem{-1, static_cast<rq::GbsDev*>(own), nullptr,
+                   reinterpret_cast<rq::GbsOut*>(static_cast<char*>(own) + rq::gbs_state_bytes()), own};
+    return RQ_OK;
 }
 
-void give_search_mem(const SearchMem& m) {
-    {
-        std::lock_guard<std::mutex> hold(g_search_lock);
-        SearchDevice* d = search_device(m.device);
-        if (d && d->handles > 0 && d->kept < SearchDevice::kKeep) {
-            d->mem[d->kept++] = m;
-            return;
-        }
-    }
-    free_search_mem(m);
+void give_search_mem(int device, const SearchMem& m) {
+    if (m.own) (void)hipFree(m.own);
+    if (m.slot < 0) return;
+    std::lock_guard<std::mutex> hold(g_search_lock);
+    g_search[device].used &= ~(1u << m.slot);
 }
 }  // namespace
 
@@ -294,25 +273,20 @@ int rq_hadamard_build(int n, rq_hadamard_t** out) {
         delete h;
         return RQ_ERR_HIP;
     }
-    if (!add_handle(dev)) {
-        (void)hipFree(h->d_tables);
-        delete h;
-        return RQ_ERR_NOMEM;
-    }
     h->d_block = static_cast<int8_t*>(d_block);
     h->device = dev;
     h->generic_ok = rq::generic_prepare(h);
     h->f64_ok = h->generic_f64_ok && rq::f64_prepare(h);
-    // set-up time is when the static scratch array's address on this device is asked for; a failure
-    // only makes rq_quant_error_noalloc return RQ_ERR_HIP
+    // set-up time is when the addresses of the static arrays on this device are asked for; a failure only makes
+    // rq_quant_error_noalloc or the searches return RQ_ERR_HIP
     (void)rq::static_scratch(dev);
+    (void)rq::search_memory(dev);
     *out = h;
     return RQ_OK;
 }
 
 void rq_hadamard_free(rq_hadamard_t* h) {
     if (!h) return;
-    if (h->device >= 0) remove_handle(h->device);
     if (h->d_tables) (void)hipFree(h->d_tables);
     delete h;
 }
@@ -350,8 +324,9 @@ int rq_next_order(int d, int* n_out) {
 }
 
 int rq_hadamard_set_variant(rq_hadamard_t* h, int variant) {
-    if (!h || variant < 0 || variant > 4) return RQ_ERR_ARG;
+    if (!h || variant < 0 || (variant > 4 && variant != kSearchUnpinned)) return RQ_ERR_ARG;
     h->variant = variant == 1 ? 1 : 0;
+    h->search = variant > 4 ? variant : 0;
     h->split = variant == 2 ? -1 : variant == 3 ? 2 : variant == 4 ? 4 : 0;
     return RQ_OK;
 }
@@ -674,37 +649,38 @@ static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t ro
     hipStream_t s = static_cast<hipStream_t>(stream);
     const rq::RowArgs a = row_args(h, X, dtype, rows, d, ld, bits);
     SearchMem mem;
-    rc = take_search_mem(h->device, &mem);
+    rc = take_search_mem(h->device, h->search != kSearchUnpinned, &mem);
     if (rc != RQ_OK) return rc;
-    mem.out->done = 0;
-    const volatile int* done = &mem.out->done;
-    auto finish = [&](int code) {
+    auto finish = [&](int code, const rq::GbsOut* o) {
         if (code == RQ_OK) {
-            const rq::GbsOut& o = *mem.out;
-            *clip_out = o.clip;
-            *mse_out = o.mse;
-            if (trace_clips) std::memcpy(trace_clips, o.trace_clips, sizeof(float) * (size_t)o.evals);
-            if (trace_mse) std::memcpy(trace_mse, o.trace_mse, sizeof(float) * (size_t)o.evals);
-            if (n_evals) *n_evals = o.evals;
+            *clip_out = o->clip;
+            *mse_out = o->mse;
+            if (trace_clips) std::memcpy(trace_clips, o->trace_clips, sizeof(float) * (size_t)o->evals);
+            if (trace_mse) std::memcpy(trace_mse, o->trace_mse, sizeof(float) * (size_t)o->evals);
+            if (n_evals) *n_evals = o->evals;
         }
-        give_search_mem(mem);
+        give_search_mem(h->device, mem);
         return code;
     };
-    const bool can_stay = !asym && h->variant == 0 && rq::gbs_resident_supports(h, a);
-    if (const ResidentTurn turn{can_stay ? h->device : -1}; can_stay && turn) {
+    if (mem.out) mem.out->done = 0;
+    const volatile int* done = mem.out ? &mem.out->done : nullptr;
+    // (without pinned memory there is no result to look for while the stream is busy: the batched form)
+    const bool can_stay = !asym && h->variant == 0 && mem.out && rq::gbs_resident_supports(h, a);
+    if (const ResidentTurn turn{h->device, can_stay}) {
         note(h, "wave_quant_error");
-        // step numbers have 16 bits: when they are used up, the buffers are cleared and they start again
+        // step numbers have 16 bits: when they are used up, the buffers are cleared and they start again (as after the
+        // first allocation: 0 is no step's number)
         constexpr uint32_t kSteps = 512;                     // more than the steps of any search
-        if (mem.epoch + kSteps > 0xffffu) {
-            if (hipMemsetAsync(mem.exchange, 0, 2 * rq::gbs_exchange_bytes(), s) != hipSuccess) return finish(RQ_ERR_HIP);
-            mem.epoch = 1;
+        if (turn->epoch == 0 || turn->epoch + kSteps > 0xffffu) {
+            if (hipMemsetAsync(turn->exchange, 0, 2 * rq::gbs_exchange_bytes(), s) != hipSuccess) return finish(RQ_ERR_HIP, nullptr);
+            turn->epoch = 1;
         }
         // (searches take the buffers in turn: the host goes on when the result has arrived, and a workgroup of this
         // search may then still be reading the last step's words)
-        uint64_t* const buf = mem.exchange + (mem.epoch / kSteps & 1) * (rq::gbs_exchange_bytes() / sizeof(uint64_t));
-        rc = rq::gbs_resident(h, a, mem.out_dev, buf, mem.epoch, (double)eps, max_evals, s);
-        mem.epoch += kSteps;
-        if (rc != RQ_OK) return finish(rc);
+        uint64_t* const buf = turn->exchange + (turn->epoch / kSteps & 1) * (rq::gbs_exchange_bytes() / sizeof(uint64_t));
+        rc = rq::gbs_resident(h, a, mem.out_dev, buf, turn->epoch, (double)eps, max_evals, s);
+        turn->epoch += kSteps;
+        if (rc != RQ_OK) return finish(rc, nullptr);
         // The result arrives in host memory before the runtime reports the stream done: worth about 5 us to look there.
         const auto began = std::chrono::steady_clock::now();
         for (int spin = 1; !*done; ++spin) {
@@ -712,9 +688,9 @@ static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t ro
             if (spin % 256 == 0 && std::chrono::steady_clock::now() - began > std::chrono::milliseconds(5)) break;
         }
         std::atomic_thread_fence(std::memory_order_acquire);
-        if (*done) return finish(RQ_OK);
-        if (hipStreamSynchronize(s) != hipSuccess) return finish(RQ_ERR_HIP);
-        if (*done) return finish(RQ_OK);
+        if (*done) return finish(RQ_OK, mem.out);
+        if (hipStreamSynchronize(s) != hipSuccess) return finish(RQ_ERR_HIP, nullptr);
+        if (*done) return finish(RQ_OK, mem.out);
         // other work kept part of the search from running: the batched form needs no two workgroups at one time
     }
     // as few batches as the depth allows, each no deeper than that number needs (16 steps: four batches of four, 61
@@ -727,7 +703,7 @@ static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t ro
     rq::ClipArg cl;
     std::memset(&cl, 0, sizeof cl);
     rq::gbs_first_batch((double)eps, depth, bits, &cl.list);
-    for (int b = 0; b < batches && rc == RQ_OK && !*done; ++b) {
+    for (int b = 0; b < batches && rc == RQ_OK && !(done && *done); ++b) {
         const bool first = b == 0;
         if (!first) cl.dev = rq::gbs_state_clips(mem.state);
         int64_t count = 0, stride = 0;
@@ -736,8 +712,14 @@ static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t ro
         if (rc == RQ_OK)
             rc = rq::gbs_step(mem.state, mem.out_dev, first, (double)eps, depth, max_evals, bits, partial, rows, count, stride, s);
     }
+    rq::GbsOut copied;
+    const rq::GbsOut* result = mem.out;
+    if (rc == RQ_OK && !mem.out) {
+        result = &copied;
+        if (hipMemcpyAsync(&copied, mem.out_dev, sizeof copied, hipMemcpyDeviceToHost, s) != hipSuccess) rc = RQ_ERR_HIP;
+    }
     if (hipStreamSynchronize(s) != hipSuccess && rc == RQ_OK) rc = RQ_ERR_HIP;
-    return finish(rc == RQ_OK && !*done ? RQ_ERR_HIP : rc);
+    return finish(rc == RQ_OK && !result->done ? RQ_ERR_HIP : rc, result);
 }
 
 int rq_gbs_search(const rq_hadamard_t* h, const void* X, int dtype, int64_t rows, int d, int64_t ld,

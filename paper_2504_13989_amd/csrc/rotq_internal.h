@@ -35,6 +35,7 @@ struct rq_hadamard {
     // thread reads a whole value
     std::atomic<int> variant{0};     // 0 auto, 1 general LDS kernel
     std::atomic<int> split{0};       // long Sylvester rows: 0 auto, 2 / 4 waves per row, -1 never split
+    std::atomic<int> search{0};      // variants of the searches only: 0 auto, 7 no pinned memory
     // diagnostic only: name of the kernel family the most recent hot-path call chose.  The hot-path
     // calls take the handle as const and may run on several host threads at once, hence atomic.
     mutable std::atomic<const char*> last_kernel{""};
@@ -221,6 +222,15 @@ struct GbsOut {               // host memory the device writes (pinned, mapped)
     float trace_clips[256], trace_mse[256];
 };
 size_t gbs_state_bytes();
+GbsDev* gbs_state_at(GbsDev* base, int slot);
+// The static device memory of the searches on device `dev` (null pointers when it cannot be resolved; as
+// static_scratch, to be asked for first with that device current): kSearchSlots states and results.
+constexpr int kSearchSlots = 16;
+struct SearchMemory {
+    GbsDev* state;
+    GbsOut* out;
+};
+SearchMemory search_memory(int dev);
 const ClipList* gbs_state_clips(const GbsDev* state);
 // The first batch of a search, `depth` steps ahead: the starting point and every probe those steps can ask for.
 void gbs_first_batch(double eps, int depth, int bits, ClipList* out);
