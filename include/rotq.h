@@ -333,7 +333,9 @@ size_t rq_gbs_workspace(int64_t rows);
  * max_evals evaluations of f.  The probes and their values are those of that loop taken one at a
  * time; they are evaluated ahead in batches (every probe the next few steps can ask for, whatever the
  * comparisons give), and the comparisons are taken on the device: rows the chip can hold in registers
- * are rotated once and searched in one launch, other tensors take a few launches enqueued together.
+ * are rotated once and searched in one launch (or with a launch per few steps, to the same values bit for bit, where other
+ * work keeps that one from running), other tensors take a few launches enqueued together.  f is summed in an order of
+ * the search's own: it agrees with rq_quant_error to 2e-6, not to the last bit.  The same call gives the same result.
  * The call waits for the result: a calibration call, not a hot-path call (not for a stream under
  * capture).  Besides the workspace a search uses static device memory (as rq_quant_error_noalloc does) and 256 KB of
  * device and 33 KB of pinned host memory that the first search on a device allocates and that stay until the process
@@ -366,7 +368,9 @@ int rq_gbs_search_asym(const rq_hadamard_t* h, const void* X, int dtype, int64_t
  * Select the kernel family for subsequent hot-path calls on this handle (testing /
  * measurement): 0 = automatic (fastest available), 1 = the general LDS kernel; for long
  * power-of-two rows 2 = one wave per row at any row count, 3 / 4 = a row split over 2 / 4 waves
- * at any row count (automatic picks by the number of rows); automatic but for the searches: 7 = no pinned memory.
+ * at any row count (automatic picks by the number of rows); automatic but for the searches that fit the
+ * chip's registers: 5 = a launch per step ("gbs_stepped"), 6 = one launch ("gbs_resident") whose workgroups do not wait for each
+ * other, so that it gives up and the former takes over, and for all searches 7 = no pinned memory.
  * Errors: RQ_ERR_ARG.
  */
 int rq_hadamard_set_variant(rq_hadamard_t* h, int variant);

@@ -1,9 +1,12 @@
-// The clip-ratio search of Algorithm 1 (section 4.1) on the device, in two forms.
+// The clip-ratio search of Algorithm 1 (section 4.1) on the device, in three forms.
 //
 // Batches (any tensor): between the batches of objective values a search
 // needs (one quant_error pass each), a kernel of one workgroup averages the batch, walks the search with it and writes
 // the clip ratios of the next batch to device memory, where the next pass reads them.  The host enqueues all of it and
 // waits once; a trip to the host between the batches cost about 8 us each, as much as a pass on a small tensor.
+// Resident (tensors that fit the chip's registers): one launch.  Stepped: the resident form's steps as a launch each,
+// where that cannot run; which of the two a call takes depends on what else the device is doing, so they compute the same
+// values bit for bit.
 //
 // The probes are taken in the listing's order, but evaluated ahead of time in batches: where a probe lies depends only
 // on the outcomes of the comparisons before it, so one batch covers every probe the next `depth` steps can ask for, a
@@ -47,7 +50,16 @@ __host__ __device__ inline bool gbs_node(GbsState st, double eps, int depth, int
     return live;
 }
 
+// What one launch of the stepped form hands to the next.
+struct GbsCarry {
+    GbsState st;
+    float fm;             // objective at the best point
+    int evals;
+    int done;
+};
+
 struct GbsDev {
+    GbsCarry carry[2];    // stepped form; the rest: batched form
     ClipList clips;       // the next batch
     GbsState st;
     float fm;             // objective at the best point
@@ -179,22 +191,30 @@ __global__ __launch_bounds__(kStepThreads) void k_gbs_step(GbsDev* state, GbsOut
 // exchange between the workgroups (about 3 us, whence three probes a step); the batched form pays two launches and a
 // repeated rotation for four steps.
 //
-// Exchange: a sum travels in one 64-bit word, the upper 48 bits of the fp64 value and the number of the step below them,
-// so that a word is its own flag; two sets of words alternate, which is enough, because a workgroup that is two steps
-// ahead has seen every other one publish the step between.  At most one workgroup per compute unit is launched, so
-// all are resident together unless other work holds the chip; a workgroup that waits longer than kWaitTicks gives the
-// search up (everyone does in the end), and the host takes the batched form.
+// Exchange: a sum travels in one 64-bit word, the upper 48 bits of the fp64 value (rounded to nearest: 37 significant
+// bits, where the fp32 sums of the waves it is made of have 24) and the number of the step below them, so that a word is
+// its own flag.  (Whole values in two words are twice the traffic: 512 x 4096 46 -> 57 us.)  Two sets of words
+// alternate, which is enough, because a workgroup that is two steps ahead has seen every other one publish the step
+// between.  At most one workgroup per compute unit is launched, so all are resident together unless other work holds
+// the chip; a workgroup that waits longer than wait_ticks gives the search up (everyone does in the end), and the host
+// takes the stepped form: the same kernel, which leaves its sums in the workspace and returns after each step; the next
+// launch picks them up (512 x 4096: 65 us).
 constexpr int kMaxGroups = 1024;
-constexpr uint64_t kWaitTicks = 1000000;                  // of the 100 MHz clock: 10 ms
+constexpr uint64_t kWaitTicks = 30000;                    // of the 100 MHz clock: 300 us, a hundred times a step
 constexpr int kAhead = 3, kSlots = 1 << kAhead;           // probes a step looks ahead, clip ratios of a step
 
 struct ResidentArgs {
     GbsOut* out;
     uint64_t* exchange;       // [2][kMaxGroups][kSlots]
-    uint32_t epoch;           // 16-bit number of the first step; no word in the buffer has it or one of the next 511
+    uint32_t epoch;           // 16-bit number of the first step; no word in the buffer has it or one of the next 255
     double eps, levels;
     int max_evals;
     int rows_per_group;
+    uint64_t wait_ticks;
+    // stepped form
+    GbsCarry* carry;          // [2], taken in turn
+    double* sums;             // [2][workgroups][kSlots]
+    uint32_t step;
 };
 
 // A Sylvester row of 512 T values over W waves, T / W register sets each.
@@ -238,14 +258,14 @@ struct BlockRows {
     }
 };
 
-template <typename Rows, int BITS>
+template <typename Rows, int BITS, bool STEPPED>
 __global__ __launch_bounds__(1024) void k_gbs_resident(WaveArgs a, int pb, double inv_norm, ResidentArgs r) {
     constexpr int W = Rows::W, NVAL = Rows::NVAL;
     __shared__ float wmax[16];
     __shared__ __attribute__((aligned(16))) float esum[kSlots][16];      // [slot][wave], zero beyond the waves there are
     __shared__ __attribute__((aligned(16))) double gsum[kSlots][16];
     __shared__ int gave_up;
-    __shared__ float trace_clips[256], trace_mse[256];    // (kept by the first workgroup)
+    __shared__ float trace_clips[STEPPED ? 1 : 256], trace_mse[STEPPED ? 1 : 256];    // (kept by the first workgroup)
     const int tid = threadIdx.x, lane = tid & 63, nt = (int)blockDim.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rsub = wave / W, seg = wave - rsub * W;
@@ -271,15 +291,17 @@ __global__ __launch_bounds__(1024) void k_gbs_resident(WaveArgs a, int pb, doubl
     const double inv_m = m > 0.0f ? 1.0 / (double)m : 0.0, inv_rows = 1.0 / (double)a.rows;
     const double m_over_levels = (double)m / r.levels;
     const int words = (int)gridDim.x * kSlots;
+    auto put = [](auto* to, auto x) { __hip_atomic_store(to, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); };
 
     GbsState st = gbs_start();
     float fm = 0.0f;
     int evals = 0;
-    for (uint32_t step = 0;; ++step) {
+
+    // The sums of this workgroup's rows at the clip ratios of a step, one thread a ratio: returned to the first kSlots.
+    auto evaluate = [&](bool first) -> uint64_t {
         // the step's clip ratios, one lane a slot (first step: the starting point, then nodes 1 .. 7; later nodes 1 .. 7); a
         // slot the search cannot reach repeats the best point
-        const int lead = step == 0 ? 1 : 0;
-        const int node = (lane & (kSlots - 1)) + 1 - lead;
+        const int node = (lane & (kSlots - 1)) + (first ? 0 : 1);
         double x = st.best;
         bool reach = node == 0;
         if (node >= 1 && node < kSlots) {
@@ -325,46 +347,31 @@ __global__ __launch_bounds__(1024) void k_gbs_resident(WaveArgs a, int pb, doubl
             }
         }
         __syncthreads();
-        const uint64_t tag = (r.epoch + step) & 0xffffu;
-        uint64_t* const set = r.exchange + (size_t)(step & 1) * kMaxGroups * kSlots;
+        double t = 0.0;
         if (tid < kSlots) {
-            double t = 0.0;
 #pragma unroll
             for (int w = 0; w < 16; ++w) t += (double)esum[tid][w];
-            const uint64_t bits = (uint64_t)__double_as_longlong(t * inv_norm);
-            __hip_atomic_store(set + (size_t)blockIdx.x * kSlots + tid, (bits & ~0xffffull) | tag, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
         }
-        // everyone's sums, in a fixed order: consecutive lanes read consecutive words (reading a workgroup's words one after
-        // the other in a lane multiplied the traffic by eight: 7 us a step)
+        // the bits a sum has in the exchange, in both forms
+        return ((uint64_t)__double_as_longlong(t * inv_norm) + 0x8000u) & ~0xffffull;
+    };
+    // Everyone's sums, in a fixed order: fetch(i0, value) gives the thread the sums i0, i0 + nt, i0 + 2 nt, i0 + 3 nt (those
+    // there are) or returns false.  Consecutive lanes read consecutive sums (reading a workgroup's sums one after the
+    // other in a lane multiplied the traffic by eight: 7 us a step).  Then the search takes the step's decisions.
+    auto decide = [&](bool first, auto fetch) {
         double f = 0.0;
-        const uint64_t began = wall_clock64();
         bool lost = false;
         for (int i0 = tid; i0 < words && !lost; i0 += 4 * nt) {
-            uint64_t w[4];
-            for (;;) {
-                bool ready = true;
+            double value[4];
+            lost = !fetch(i0, value);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int i = i0 + u * nt;
-                    w[u] = __hip_atomic_load(set + (i < words ? i : i0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) ready = ready && (w[u] & 0xffffull) == tag;
-                if (ready) break;
-                if (wall_clock64() - began > kWaitTicks) {
-                    lost = true;
-                    break;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) f += i0 + u * nt < words ? __longlong_as_double((long long)(w[u] & ~0xffffull)) : 0.0;
+            for (int u = 0; u < 4; ++u) f += i0 + u * nt < words ? value[u] : 0.0;
         }
         if (lost) gave_up = 1;
         for (int sh = kSlots; sh < 64; sh <<= 1) f += __shfl_xor(f, sh, 64);
         if (lane < kSlots) gsum[lane][wave] = f;
         __syncthreads();
-        if (gave_up) return;                              // the whole workgroup; the others run into the same limit
+        if (gave_up) return false;                        // the whole workgroup; the others run into the same limit
         double t = 0.0;
 #pragma unroll
         for (int w = 0; w < 16; ++w) t += gsum[lane & (kSlots - 1)][w];
@@ -374,12 +381,18 @@ __global__ __launch_bounds__(1024) void k_gbs_resident(WaveArgs a, int pb, doubl
         };
         auto record = [&](float c, float f1) {
             if (blockIdx.x == 0 && tid == 0) {
-                trace_clips[evals] = c;
-                trace_mse[evals] = f1;
+                if constexpr (STEPPED) {
+                    put(&r.out->trace_clips[evals], c);
+                    put(&r.out->trace_mse[evals], f1);
+                } else {
+                    trace_clips[evals] = c;
+                    trace_mse[evals] = f1;
+                }
             }
             ++evals;
         };
-        if (lead) {
+        const int lead = first ? 1 : 0;
+        if (first) {
             fm = value(0);
             record((float)st.best, fm);
         }
@@ -393,15 +406,17 @@ __global__ __launch_bounds__(1024) void k_gbs_resident(WaveArgs a, int pb, doubl
             st.next(p, better);
             at = 2 * at + (better ? 0 : 1);
         }
-        if (st.width() <= r.eps || evals >= r.max_evals) break;
-    }
-    if (blockIdx.x == 0 && wave == 0) {
-        // results to host memory by one wave, the flag when they have arrived there
-        auto put = [](auto* to, auto x) { __hip_atomic_store(to, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); };
-        for (int i = lane; i < evals; i += 64) {
-            put(&r.out->trace_clips[i], trace_clips[i]);
-            put(&r.out->trace_mse[i], trace_mse[i]);
-        }
+        return true;
+    };
+    auto over = [&] { return st.width() <= r.eps || evals >= r.max_evals; };
+    // Results to host memory by one wave, the flag when they have arrived there.
+    auto finish = [&] {
+        if (blockIdx.x != 0 || wave != 0) return;
+        if constexpr (!STEPPED)
+            for (int i = lane; i < evals; i += 64) {
+                put(&r.out->trace_clips[i], trace_clips[i]);
+                put(&r.out->trace_mse[i], trace_mse[i]);
+            }
         if (lane == 0) {
             put(&r.out->clip, (float)st.best);
             put(&r.out->mse, fm);
@@ -409,6 +424,64 @@ __global__ __launch_bounds__(1024) void k_gbs_resident(WaveArgs a, int pb, doubl
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (lane == 0) put(&r.out->done, 1);
+    };
+
+    if constexpr (STEPPED) {
+        const uint32_t step = r.step;
+        const bool keeps = blockIdx.x == 0 && tid == 0;
+        GbsCarry* const next = r.carry + (step & 1);
+        if (step > 0) {
+            const GbsCarry last = r.carry[(step - 1) & 1];
+            bool done = last.done;                        // (a launch enqueued beyond the end of the search)
+            if (!done) {
+                st = last.st;
+                fm = last.fm;
+                evals = last.evals;
+                const double* const from = r.sums + (size_t)((step - 1) & 1) * words;
+                decide(step == 1, [&](int i0, double (&value)[4]) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) value[u] = from[i0 + u * nt < words ? i0 + u * nt : i0];
+                    return true;
+                });
+                done = over();
+                if (done) finish();
+            }
+            if (done) {
+                if (keeps) next->done = 1;
+                return;
+            }
+        } else if (keeps) {
+            put(&r.out->done, 0);
+        }
+        if (keeps) *next = GbsCarry{st, fm, evals, 0};
+        const uint64_t sum = evaluate(step == 0);
+        if (tid < kSlots) r.sums[(size_t)(step & 1) * words + blockIdx.x * kSlots + tid] = __longlong_as_double((long long)sum);
+    } else {
+        for (uint32_t step = 0;; ++step) {
+            const uint64_t sum = evaluate(step == 0), tag = (r.epoch + step) & 0xffffu;
+            uint64_t* const set = r.exchange + (size_t)(step & 1) * kMaxGroups * kSlots;
+            if (tid < kSlots)
+                __hip_atomic_store(set + (size_t)blockIdx.x * kSlots + tid, sum | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t began = wall_clock64();
+            const bool met = decide(step == 0, [&](int i0, double (&value)[4]) {
+                for (;;) {
+                    uint64_t w[4];
+                    bool ready = true;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        w[u] = __hip_atomic_load(set + (i0 + u * nt < words ? i0 + u * nt : i0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) ready = ready && (w[u] & 0xffffull) == tag;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) value[u] = __longlong_as_double((long long)(w[u] & ~0xffffull));
+                    if (ready) return true;
+                    if (wall_clock64() - began > r.wait_ticks) return false;
+                }
+            });
+            if (!met) return;
+            if (over()) break;
+        }
+        finish();
     }
 }
 
@@ -418,22 +491,43 @@ int resident_waves(const RowArgs& a) {
     return (a.p << (a.log2m - 7)) <= 16 ? 1 : 2;
 }
 
-template <int BITS, bool F16>
+template <int BITS, bool F16, bool STEPPED>
 int launch_resident(const RowArgs& a, const WaveArgs& w, double inv_norm, const ResidentArgs& r, dim3 grid, dim3 block, hipStream_t s) {
     const int pb = a.p > 1 ? a.p << (a.log2m - 7) : 0;
     auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, w, pb, inv_norm, r); };
     if (a.p > 1) {
-        if (pb <= 16) go(k_gbs_resident<BlockRows<1, F16>, BITS>); else go(k_gbs_resident<BlockRows<2, F16>, BITS>);
+        if (pb <= 16) go(k_gbs_resident<BlockRows<1, F16>, BITS, STEPPED>); else go(k_gbs_resident<BlockRows<2, F16>, BITS, STEPPED>);
     } else {
         switch (a.log2m) {
-            case 10: go(k_gbs_resident<SylvesterRows<2, 1, F16>, BITS>); break;
-            case 11: go(k_gbs_resident<SylvesterRows<4, 2, F16>, BITS>); break;
-            case 12: go(k_gbs_resident<SylvesterRows<8, 4, F16>, BITS>); break;
-            case 13: go(k_gbs_resident<SylvesterRows<16, 4, F16>, BITS>); break;
+            case 10: go(k_gbs_resident<SylvesterRows<2, 1, F16>, BITS, STEPPED>); break;
+            case 11: go(k_gbs_resident<SylvesterRows<4, 2, F16>, BITS, STEPPED>); break;
+            case 12: go(k_gbs_resident<SylvesterRows<8, 4, F16>, BITS, STEPPED>); break;
+            case 13: go(k_gbs_resident<SylvesterRows<16, 4, F16>, BITS, STEPPED>); break;
             default: return RQ_ERR_NO_ORDER;
         }
     }
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+}
+
+// Grid, block and what both forms share of the arguments.
+template <bool STEPPED>
+int resident_launch(const rq_hadamard* h, const RowArgs& a, ResidentArgs r, hipStream_t s) {
+    const int w = resident_waves(a);
+    const int groups = h->num_cu < kMaxGroups ? h->num_cu : kMaxGroups;
+    const int per = (int)((a.rows + groups - 1) / groups);
+    const bool f16 = a.dtype == RQ_F16;
+    WaveArgs wa{static_cast<const uint16_t*>(a.X), a.rows, a.d, a.ld,
+                static_cast<const u32x4*>(f16 ? h->d_tiles_f16 : h->d_tiles), nullptr, nullptr, 0.0, 0.0};
+    wa.f16 = f16;
+    r.levels = (double)((1 << a.bits) - 1);
+    r.rows_per_group = per;
+    const double inv_norm = 1.0 / ((double)a.n * (double)a.n);
+    const dim3 grid((unsigned)((a.rows + per - 1) / per)), block((unsigned)(64 * per * w));
+    if (f16)
+        return a.bits == 4 ? launch_resident<4, true, STEPPED>(a, wa, inv_norm, r, grid, block, s)
+                           : launch_resident<3, true, STEPPED>(a, wa, inv_norm, r, grid, block, s);
+    return a.bits == 4 ? launch_resident<4, false, STEPPED>(a, wa, inv_norm, r, grid, block, s)
+                       : launch_resident<3, false, STEPPED>(a, wa, inv_norm, r, grid, block, s);
 }
 
 }  // namespace
@@ -449,20 +543,35 @@ bool gbs_resident_supports(const rq_hadamard* h, const RowArgs& a) {
 size_t gbs_exchange_bytes() { return (size_t)2 * kMaxGroups * kSlots * sizeof(uint64_t); }
 
 int gbs_resident(const rq_hadamard* h, const RowArgs& a, GbsOut* out, uint64_t* exchange, uint32_t epoch, double eps, int max_evals,
-                 hipStream_t s) {
-    const int w = resident_waves(a);
-    const int groups = h->num_cu < kMaxGroups ? h->num_cu : kMaxGroups;
-    const int per = (int)((a.rows + groups - 1) / groups);
-    const bool f16 = a.dtype == RQ_F16;
-    WaveArgs wa{static_cast<const uint16_t*>(a.X), a.rows, a.d, a.ld,
-                static_cast<const u32x4*>(f16 ? h->d_tiles_f16 : h->d_tiles), nullptr, nullptr, 0.0, 0.0};
-    wa.f16 = f16;
-    const ResidentArgs r{out, exchange, epoch, eps, (double)((1 << a.bits) - 1), max_evals, per};
-    const double inv_norm = 1.0 / ((double)a.n * (double)a.n);
-    const dim3 grid((unsigned)((a.rows + per - 1) / per)), block((unsigned)(64 * per * w));
-    if (f16)
-        return a.bits == 4 ? launch_resident<4, true>(a, wa, inv_norm, r, grid, block, s) : launch_resident<3, true>(a, wa, inv_norm, r, grid, block, s);
-    return a.bits == 4 ? launch_resident<4, false>(a, wa, inv_norm, r, grid, block, s) : launch_resident<3, false>(a, wa, inv_norm, r, grid, block, s);
+                 bool wait, hipStream_t s) {
+    ResidentArgs r{};
+    r.out = out;
+    r.exchange = exchange;
+    r.epoch = epoch;
+    r.eps = eps;
+    r.max_evals = max_evals;
+    r.wait_ticks = wait ? kWaitTicks : 0;
+    return resident_launch<false>(h, a, r, s);
+}
+
+// (a workgroup has a row at least, and the workspace of a search 8 values a row or more: room for two sets of kSlots sums
+// needs 16, which it has wherever the resident form applies)
+int gbs_stepped(const rq_hadamard* h, const RowArgs& a, GbsDev* state, GbsOut* out, double* sums, double eps, int max_evals, int steps,
+                hipStream_t s) {
+    ResidentArgs r{};
+    r.out = out;
+    r.eps = eps;
+    r.max_evals = max_evals;
+    r.carry = state->carry;
+    r.sums = sums;
+    // a launch for every kAhead steps of the search, and one that takes the last decisions
+    const int launches = (steps > 0 ? (steps + kAhead - 1) / kAhead : 1) + 1;
+    int rc = RQ_OK;
+    for (int i = 0; i < launches && rc == RQ_OK; ++i) {
+        r.step = (uint32_t)i;
+        rc = resident_launch<true>(h, a, r, s);
+    }
+    return rc;
 }
 
 size_t gbs_state_bytes() { return sizeof(GbsDev); }

@@ -27,7 +27,8 @@ int check_rows(const rq_hadamard_t* h, const void* X, int dtype, int64_t rows, i
 
 bool clip_ok(float c) { return c > 0.0f && c <= 1.0f; }   // false for NaN
 
-constexpr int kSearchUnpinned = 7;       // variants that only searches know, see rq_hadamard_set_variant
+// variants that only searches know, see rq_hadamard_set_variant
+constexpr int kSearchStepped = 5, kSearchNoWait = 6, kSearchUnpinned = 7;
 
 // records which kernel family a call chose (diagnostic; the handle's only field written after build)
 void note(const rq_hadamard_t* h, const char* name) { h->last_kernel.store(name, std::memory_order_relaxed); }
@@ -88,11 +89,16 @@ struct SearchDevice {
                               // other's workgroups from running (a second one takes the batched form)
     uint64_t* exchange;       // of the resident form: two buffers, taken in turn
     uint32_t epoch;           // first step number that is not in them
+    int turn;                 // buffer of the next search
+    int unclear;              // buffers to be cleared before use, one bit each
     rq::GbsOut *out, *out_dev;
 };
 static_assert(rq::kSearchSlots <= 32, "one bit each");
 std::mutex g_search_lock;
 SearchDevice g_search[kMaxDevices];
+
+// Numbers a search takes for its steps, as many as the most steps of any search.  They have 16 bits.
+constexpr uint32_t kSteps = 256, kStepNumbers = 1u << 16;
 
 // The turn of the resident form on a device, where it is wanted and its buffers can be had.
 class ResidentTurn {
@@ -111,6 +117,8 @@ public:
                 return;
             }
             d.exchange = static_cast<uint64_t*>(p);
+            d.epoch = 1;                                  // (0 is what a cleared buffer holds)
+            d.unclear = 3;
         }
         mine_ = &d;
         mine_->resident = true;
@@ -123,7 +131,7 @@ public:
     ResidentTurn(const ResidentTurn&) = delete;
     ResidentTurn& operator=(const ResidentTurn&) = delete;
     explicit operator bool() const { return mine_; }
-    SearchDevice* operator->() const { return mine_; }    // (exchange, epoch: only the turn's holder touches them)
+    SearchDevice* operator->() const { return mine_; }    // (only the turn's holder touches the exchange)
 };
 
 int take_search_mem(int device, bool pinned, SearchMem* m) {
@@ -324,7 +332,7 @@ int rq_next_order(int d, int* n_out) {
 }
 
 int rq_hadamard_set_variant(rq_hadamard_t* h, int variant) {
-    if (!h || variant < 0 || (variant > 4 && variant != kSearchUnpinned)) return RQ_ERR_ARG;
+    if (!h || variant < 0 || variant > 7) return RQ_ERR_ARG;
     h->variant = variant == 1 ? 1 : 0;
     h->search = variant > 4 ? variant : 0;
     h->split = variant == 2 ? -1 : variant == 3 ? 2 : variant == 4 ? 4 : 0;
@@ -664,38 +672,58 @@ static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t ro
     };
     if (mem.out) mem.out->done = 0;
     const volatile int* done = mem.out ? &mem.out->done : nullptr;
-    // (without pinned memory there is no result to look for while the stream is busy: the batched form)
-    const bool can_stay = !asym && h->variant == 0 && mem.out && rq::gbs_resident_supports(h, a);
-    if (const ResidentTurn turn{h->device, can_stay}) {
-        note(h, "wave_quant_error");
-        // step numbers have 16 bits: when they are used up, the buffers are cleared and they start again (as after the
-        // first allocation: 0 is no step's number)
-        constexpr uint32_t kSteps = 512;                     // more than the steps of any search
-        if (turn->epoch == 0 || turn->epoch + kSteps > 0xffffu) {
-            if (hipMemsetAsync(turn->exchange, 0, 2 * rq::gbs_exchange_bytes(), s) != hipSuccess) return finish(RQ_ERR_HIP, nullptr);
+    const int steps = gbs_most_steps((double)eps, max_evals - 1);
+    const bool in_registers = !asym && h->variant == 0 && rq::gbs_resident_supports(h, a);
+    // (without pinned memory there is no result to look for while the stream is busy: the stepped form)
+    const int form = h->search;
+    if (const ResidentTurn turn{h->device, in_registers && mem.out && form != kSearchStepped}) {
+        if (turn->epoch + kSteps > kStepNumbers) {           // the numbers start again
             turn->epoch = 1;
+            turn->unclear = 3;
         }
-        // (searches take the buffers in turn: the host goes on when the result has arrived, and a workgroup of this
-        // search may then still be reading the last step's words)
-        uint64_t* const buf = turn->exchange + (turn->epoch / kSteps & 1) * (rq::gbs_exchange_bytes() / sizeof(uint64_t));
-        rc = rq::gbs_resident(h, a, mem.out_dev, buf, turn->epoch, (double)eps, max_evals, s);
+        // Searches take the buffers in turn: the host goes on when the result has arrived, and a workgroup of this
+        // search may then still be reading the last step's words.  A buffer is cleared when its own turn has come.
+        const int b = turn->turn;
+        uint64_t* const buf = turn->exchange + b * (rq::gbs_exchange_bytes() / sizeof(uint64_t));
+        if (turn->unclear >> b & 1) {
+            if (hipMemsetAsync(buf, 0, rq::gbs_exchange_bytes(), s) != hipSuccess) return finish(RQ_ERR_HIP, nullptr);
+            turn->unclear &= ~(1 << b);
+        }
+        rc = rq::gbs_resident(h, a, mem.out_dev, buf, turn->epoch, (double)eps, max_evals, form != kSearchNoWait, s);
         turn->epoch += kSteps;
+        turn->turn ^= 1;
         if (rc != RQ_OK) return finish(rc, nullptr);
         // The result arrives in host memory before the runtime reports the stream done: worth about 5 us to look there.
         const auto began = std::chrono::steady_clock::now();
         for (int spin = 1; !*done; ++spin) {
             __builtin_ia32_pause();
-            if (spin % 256 == 0 && std::chrono::steady_clock::now() - began > std::chrono::milliseconds(5)) break;
+            if (spin % 256 == 0 && std::chrono::steady_clock::now() - began > std::chrono::microseconds(500)) break;
         }
+        if (!*done && hipStreamSynchronize(s) != hipSuccess) return finish(RQ_ERR_HIP, nullptr);
         std::atomic_thread_fence(std::memory_order_acquire);
-        if (*done) return finish(RQ_OK, mem.out);
-        if (hipStreamSynchronize(s) != hipSuccess) return finish(RQ_ERR_HIP, nullptr);
-        if (*done) return finish(RQ_OK, mem.out);
-        // other work kept part of the search from running: the batched form needs no two workgroups at one time
+        if (*done) {
+            note(h, "gbs_resident");
+            return finish(RQ_OK, mem.out);
+        }
+        // other work kept part of the search from running: the stepped form needs no two workgroups at one time
+    }
+    // after the last launch: the results, copied back where they are in device memory
+    auto collect = [&](int code) {
+        rq::GbsOut copied;
+        const rq::GbsOut* result = mem.out;
+        if (code == RQ_OK && !mem.out) {
+            result = &copied;
+            if (hipMemcpyAsync(&copied, mem.out_dev, sizeof copied, hipMemcpyDeviceToHost, s) != hipSuccess) code = RQ_ERR_HIP;
+        }
+        if (hipStreamSynchronize(s) != hipSuccess && code == RQ_OK) code = RQ_ERR_HIP;
+        return finish(code == RQ_OK && !result->done ? RQ_ERR_HIP : code, result);
+    };
+    if (in_registers) {
+        note(h, "gbs_stepped");
+        return collect(rq::gbs_stepped(h, a, mem.state, mem.out_dev, partial, (double)eps, max_evals, steps, s));
     }
     // as few batches as the depth allows, each no deeper than that number needs (16 steps: four batches of four, 61
     // candidates, where batches of five would evaluate 95)
-    const int steps = gbs_most_steps((double)eps, max_evals - 1);
     const int deepest = gbs_depth(rows, h->f.n);
     const int batches = steps > 0 ? (steps + deepest - 1) / deepest : 1;
     const int depth = steps > 0 ? (steps + batches - 1) / batches : 1;
@@ -712,14 +740,7 @@ static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t ro
         if (rc == RQ_OK)
             rc = rq::gbs_step(mem.state, mem.out_dev, first, (double)eps, depth, max_evals, bits, partial, rows, count, stride, s);
     }
-    rq::GbsOut copied;
-    const rq::GbsOut* result = mem.out;
-    if (rc == RQ_OK && !mem.out) {
-        result = &copied;
-        if (hipMemcpyAsync(&copied, mem.out_dev, sizeof copied, hipMemcpyDeviceToHost, s) != hipSuccess) rc = RQ_ERR_HIP;
-    }
-    if (hipStreamSynchronize(s) != hipSuccess && rc == RQ_OK) rc = RQ_ERR_HIP;
-    return finish(rc == RQ_OK && !result->done ? RQ_ERR_HIP : rc, result);
+    return collect(rc);
 }
 
 int rq_gbs_search(const rq_hadamard_t* h, const void* X, int dtype, int64_t rows, int d, int64_t ld,

@@ -35,7 +35,7 @@ struct rq_hadamard {
     // thread reads a whole value
     std::atomic<int> variant{0};     // 0 auto, 1 general LDS kernel
     std::atomic<int> split{0};       // long Sylvester rows: 0 auto, 2 / 4 waves per row, -1 never split
-    std::atomic<int> search{0};      // variants of the searches only: 0 auto, 7 no pinned memory
+    std::atomic<int> search{0};      // variants of the searches only: 0 auto, 5 .. 7 see rq_hadamard_set_variant
     // diagnostic only: name of the kernel family the most recent hot-path call chose.  The hot-path
     // calls take the handle as const and may run on several host threads at once, hence atomic.
     mutable std::atomic<const char*> last_kernel{""};
@@ -234,11 +234,15 @@ SearchMemory search_memory(int dev);
 const ClipList* gbs_state_clips(const GbsDev* state);
 // The first batch of a search, `depth` steps ahead: the starting point and every probe those steps can ask for.
 void gbs_first_batch(double eps, int depth, int bits, ClipList* out);
-// The whole search in one launch, for rows the chip holds in registers all at once; false where it does not.
+// The whole search in one launch, for rows the chip holds in registers all at once; false where it does not.  (`wait`
+// false: a workgroup that finds another's sums missing gives the search up at once, for tests.)
 bool gbs_resident_supports(const rq_hadamard* h, const RowArgs& a);
 size_t gbs_exchange_bytes();
 int gbs_resident(const rq_hadamard* h, const RowArgs& a, GbsOut* out, uint64_t* exchange, uint32_t epoch, double eps, int max_evals,
-                 hipStream_t s);
+                 bool wait, hipStream_t s);
+// The same steps, a launch each, for searches of up to `steps` steps after the starting point; `sums` is the workspace.
+int gbs_stepped(const rq_hadamard* h, const RowArgs& a, GbsDev* state, GbsOut* out, double* sums, double eps, int max_evals, int steps,
+                hipStream_t s);
 int gbs_step(GbsDev* state, GbsOut* out, bool first, double eps, int depth, int max_evals, int bits, const double* partial,
              int64_t rows, int64_t count, int64_t stride, hipStream_t s);
 

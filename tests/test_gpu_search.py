@@ -1,5 +1,6 @@
-"""GPU: the resident form of the clip search (one launch) against the batched form and Algorithm 1 run on quant_error's own
-values: every waves-per-row form, one row to the most rows a chip holds, ragged last workgroup, an evaluation limit."""
+"""GPU: the clip search against Algorithm 1 run on its own values and against quant_error, in its resident form (one launch),
+its stepped form (the same values bit for bit) and its batched form: every waves-per-row form, one row to the most rows a
+chip holds, ragged last workgroup, an evaluation limit; its memory, numbers and threads."""
 import numpy as np
 import pytest
 
@@ -19,8 +20,10 @@ def test_search_takes_the_steps_of_algorithm_1(n, d, rows, dtype):
     xf[rows // 2] *= 20.0
     x = parity.to_device(wl.f32_to_bf16_bits(xf) if dtype == "bf16" else xf.astype(np.float16))
     h = binding.hadamard_build(n)
+    most = {1024: 4096, 1536: 4096, 2048: 2048, 3072: 2048, 3584: 2048, 4096: 1024, 8192: 1024}[n]     # 256 compute units
     for b in (3, 4):
         clip, mse, trace = binding.gbs_search(h, x, b, 1.0 / 100)
+        assert (h.last_kernel == "gbs_resident") == (rows <= most), h.last_kernel
         # Algorithm 1 with the values of the trace as its objective asks for the trace's probes, in its order
         seen = dict(trace)
         m, fm, otrace = oracle.gbs_search(lambda c: seen[np.float32(c)], 1.0 / 100)
@@ -31,6 +34,43 @@ def test_search_takes_the_steps_of_algorithm_1(n, d, rows, dtype):
         assert np.allclose([v for _, v in trace], want, rtol=2e-6, atol=0.0)
         _, _, short = binding.gbs_search(h, x, b, 1.0 / 100, max_evals=4)
         assert short == trace[:4]
+
+
+@pytest.mark.parametrize("n,d,rows", [(1024, 1024, 4096), (2048, 2000, 515), (4096, 4096, 1), (4096, 4096, 1023), (8192, 8192, 300),
+                                      (1536, 1536, 257), (3584, 3584, 700), (3072, 3000, 2048)])
+def test_the_stepped_form_gives_the_resident_forms_bits(n, d, rows):
+    """a launch per step (variant 5), and the resident form given up because nobody waits (variant 6)"""
+    rng = np.random.default_rng(n + rows)
+    x = parity.to_device(wl.f32_to_bf16_bits((rng.standard_normal((rows, d)) * 3).astype(np.float32)))
+    h = binding.hadamard_build(n)
+    for b, eps, limit in ((3, 1.0 / 256, 64), (4, 1.0 / 64, 64), (4, 1e-30, 256), (3, 1.0 / 256, 1), (3, 1.0 / 256, 2), (4, 0.9, 64)):
+        h.set_variant(0)
+        want = binding.gbs_search(h, x, b, eps, max_evals=limit)
+        assert h.last_kernel == "gbs_resident"
+        for variant in (5, 6, 7):
+            h.set_variant(variant)
+            for _ in range(2):
+                assert binding.gbs_search(h, x, b, eps, max_evals=limit) == want, (b, eps, limit, variant)
+                if variant != 6:
+                    assert h.last_kernel == "gbs_stepped"
+                elif rows > 16:
+                    assert h.last_kernel in ("gbs_stepped", "gbs_resident")
+    h.set_variant(0)
+
+
+def test_step_numbers_that_wrap():
+    """the resident form's step numbers start again after 255 searches; two streams in turn, so that nothing but the
+    exchange buffers orders the searches"""
+    import torch
+    rng = np.random.default_rng(10)
+    xs = [parity.to_device(wl.f32_to_bf16_bits(rng.standard_normal((r, 4096)).astype(np.float32))) for r in (900, 33)]
+    h = binding.hadamard_build(4096)
+    want = [binding.gbs_search(h, x, 3, 1.0 / 256) for x in xs]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    for i in range(600):
+        assert binding.gbs_search(h, xs[i % 2], 3, 1.0 / 256, stream=streams[i % 3 % 2]) == want[i % 2], i
+        assert h.last_kernel == "gbs_resident", i
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -72,8 +112,7 @@ def test_searches_of_several_threads_and_streams():
     for i, (clip, mse, trace) in enumerate(want):
         assert len(got[i]) == 10
         for c, m, tr in got[i]:
-            assert c == clip and [p for p, _ in tr] == [p for p, _ in trace]
-            assert np.allclose([v for _, v in tr], [v for _, v in trace], rtol=2e-6, atol=0.0)
+            assert (c, m, tr) == (clip, mse, trace)
 
 
 def test_more_searches_at_once_than_slots_and_no_handle_left():
@@ -102,8 +141,7 @@ def test_more_searches_at_once_than_slots_and_no_handle_left():
         del threads, work, h
         gc.collect()
     assert len(got) == 2 * 24 * 4
-    for clip, _, trace in got:
-        assert clip == got[0][0] and [p for p, _ in trace] == [p for p, _ in got[0][2]]
+    assert all(g == got[0] for g in got)
 
 
 def test_results_without_pinned_memory():
@@ -116,9 +154,7 @@ def test_results_without_pinned_memory():
             want = binding.gbs_search(h, x, 3, 1.0 / 256, max_evals=n_evals, asym=asym)
             h.set_variant(7)
             for _ in range(3):
-                clip, mse, trace = binding.gbs_search(h, x, 3, 1.0 / 256, max_evals=n_evals, asym=asym)
-                assert clip == want[0] and [p for p, _ in trace] == [p for p, _ in want[2]]
-                assert np.allclose([v for _, v in trace], [v for _, v in want[2]], rtol=2e-6, atol=0.0)
+                assert binding.gbs_search(h, x, 3, 1.0 / 256, max_evals=n_evals, asym=asym) == want
 
 
 def test_a_search_on_a_new_handle_allocates_nothing():
