@@ -64,7 +64,8 @@ __global__ __launch_bounds__(1024) void k_f64_rows(F64Args a) {
     __shared__ unsigned long long smax[RW];
     const int tid = threadIdx.x, nt = blockDim.x;
     const int n = BLOCK ? a.p * M : M;
-    const int64_t row0 = (int64_t)blockIdx.x * RW;
+    const int64_t row0 = group_index() * RW;
+    if (row0 >= a.rows) return;                           // whole workgroup
     if (tid < RW) smax[tid] = 0ull;
     // the sign masks of this wave's part, one lane an input block row, on their way while the row comes in
     constexpr int LOG2C = K < 6 ? 6 : K;                  // columns of the workgroup (a wave has one part)
@@ -281,7 +282,7 @@ int f64_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float clip, uint
     const F64Args f{static_cast<const float*>(a.X), a.rows, a.d, a.ld, a.p, static_cast<const uint32_t*>(h->d_signs), codes,
                     scales, (double)clip,
                     1.0 / (std::sqrt((double)a.n) * (double)((1 << a.bits) - 1))};
-    launch_kernel(pick(a.log2m, a.p > 1, a.bits), dim3((unsigned)groups), dim3(sh.threads), sh.lds, s, f);
+    launch_kernel(pick(a.log2m, a.p > 1, a.bits), group_grid(groups, sh.threads), dim3(sh.threads), sh.lds, s, f);
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
 }
 

@@ -650,7 +650,7 @@ __global__ __launch_bounds__(64) void k_wave_quant_error(WaveArgs a, ClipArg ca,
 
 // Few rows: a row split over the S waves of a workgroup as in k_wave_sylvester_split, every wave with all clip ratios
 // of the workgroup's share on its T / S register sets; the rotation is not repeated for each share of the ratios as
-// it is where whole rows are given to several waves (512 x 4096, 15 ratios: see qe_split).
+// it is where whole rows are given to several waves (launch_qe has the rule and its figures).
 template <int T, int BITS, int S, bool F16>
 __global__ __launch_bounds__(64 * S) void k_wave_quant_error_split(WaveArgs a, ClipArg ca, int ksplit, double* partial) {
     constexpr int N = 512 * T, TS = T / S;
@@ -660,9 +660,9 @@ __global__ __launch_bounds__(64 * S) void k_wave_quant_error_split(WaveArgs a, C
     const int seg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, cphys = lane & 15;
     const int c = (cphys & 4) ? (cphys ^ 3) : cphys;
-    const int64_t row = blockIdx.x / ksplit;
-    if (row >= a.rows) return;
-    const int part = (int)(blockIdx.x - row * ksplit);
+    const int64_t item = group_index(), row = item / ksplit;
+    if (row >= a.rows) return;                           // whole workgroup
+    const int part = (int)(item - row * ksplit);
     const int per = (clips.n + ksplit - 1) / ksplit;
     const int k0 = part * per, k1 = k0 + per < clips.n ? k0 + per : clips.n;
     const u32x4 A0 = a.tiles[lane], A1 = a.tiles[64 + lane];
@@ -950,7 +950,7 @@ __global__ __launch_bounds__(64 * W) void k_plain_wave(PlainArgs a) {
 
 template <int T, int W = 1>
 int launch_plain(const PlainArgs& a, int bits, hipStream_t s) {
-    const int64_t cap = 1 << 24;
+    const int64_t cap = (1 << 24) / W;                   // (2^30 threads; the kernel loops over rows)
     const dim3 grid((unsigned)(a.rows < cap ? a.rows : cap)), block(64 * W);
     auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, a); };
     if (a.f16) {
@@ -1284,8 +1284,9 @@ static int launch_qe(const rq_hadamard* h, const WaveArgs& w, const ClipArg& cli
         int64_t ksplit = 2 * simds / (w.rows * split);
         ksplit = ksplit < 1 ? 1 : ksplit > 8 ? 8 : ksplit;
         if (ksplit > n_clips) ksplit = n_clips;
-        const dim3 grid((unsigned)(w.rows * ksplit));         // (rows * 8 ratios of a workspace: far below 2^31)
-        auto go = [&](auto kernel, int S) { launch_kernel(kernel, grid, dim3(64 * S), 0, s, w, clips, (int)ksplit, partial); };
+        auto go = [&](auto kernel, int S) {
+            launch_kernel(kernel, group_grid(w.rows * ksplit, 64 * S), dim3(64 * S), 0, s, w, clips, (int)ksplit, partial);
+        };
         auto pick = [&](auto s_c) {
             constexpr int S = decltype(s_c)::value;
             if (w.f16) {
