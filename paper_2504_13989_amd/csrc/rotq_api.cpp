@@ -212,17 +212,13 @@ int rq_hadamard_build(int n, rq_hadamard_t** out) {
     h->num_cu = prop.multiProcessorCount;
     // every table goes to the device in one allocation and one copy; a slot may share another's table
     TableSet tables;
-    std::vector<uint32_t> block_words((h->block.size() + 3) / 4);
-    std::memcpy(block_words.data(), h->block.data(), h->block.size());
     void* d_block = nullptr;
-    tables.add(&d_block, block_words);
     const bool sylv = f.p == 1 && f.log2m >= 7 && f.log2m <= 13;
     // block orders of the block kernels; the Sylvester orders 2^14, 2^15 ride along with p = 1
     const bool blk = (f.p > 1 && f.log2m >= 7 && (f.p << (f.log2m - 7)) <= 256) ||
                      (f.p == 1 && (f.log2m == 14 || f.log2m == 15));
     const bool blk_short = f.p > 1 && (f.log2m == 5 || f.log2m == 6) && f.p <= 256;   // block rows of 32 / 64
     const bool dense = !sylv && !blk && !blk_short && n <= 4096;
-    if (f.p > 1 && f.log2m >= 5 && f.p <= rq::kMaxPaleyOrder) tables.add(&h->d_signs, rq::f64_block_signs(h->block, f.p));
     // tiles of a block in both 16-bit encodings, and those of its transpose (Paley I blocks are not symmetric)
     auto add_block = [&](const std::vector<int8_t>& bm, int pb, std::vector<uint32_t> (*make)(const std::vector<int8_t>&, int)) {
         const std::vector<uint32_t> tiles = make(bm, pb);
@@ -241,6 +237,10 @@ int rq_hadamard_build(int n, rq_hadamard_t** out) {
         }
     };
     try {
+        std::vector<uint32_t> block_words((h->block.size() + 3) / 4);
+        std::memcpy(block_words.data(), h->block.data(), h->block.size());
+        tables.add(&d_block, block_words);
+        if (f.p > 1 && f.log2m >= 5 && f.p <= rq::kMaxPaleyOrder) tables.add(&h->d_signs, rq::f64_block_signs(h->block, f.p));
         if (sylv) {
             const std::vector<uint32_t> tiles = rq::wave_sylvester_tiles();
             tables.add(&h->d_tiles, tiles);

@@ -54,13 +54,13 @@ inline void launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, size_t ld
     }, values);
 }
 
-// Grid of `groups` workgroups (fewer than 2^35) of a kernel that takes one item each, numbered by group_index(): a
-// dimension holds fewer than 2^32 threads (beyond that the launch keeps the remainder, without an error).
+// Grid of `groups` workgroups (fewer than 2^35) of a kernel that takes one item each, numbered by group_index()
+// (wave_common.h): a dimension holds fewer than 2^32 threads (beyond that the launch keeps the remainder, without
+// an error).
 inline dim3 group_grid(int64_t groups, int threads) {
     const int64_t most = ((int64_t)1 << 31) / threads;
     return groups <= most ? dim3((unsigned)groups) : dim3((unsigned)most, (unsigned)((groups + most - 1) / most));
 }
-__device__ inline int64_t group_index() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
 
 struct RowArgs {
     const void* X;

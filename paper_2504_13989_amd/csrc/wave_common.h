@@ -23,6 +23,9 @@ mfma_pm1(const u32x4& a, const u32x4& b, const float __attribute__((ext_vector_t
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// The workgroup's number in a grid of group_grid().
+__device__ __forceinline__ int64_t group_index() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 constexpr int kDppXor1 = 0xB1;         // quad_perm:[1,0,3,2]
 constexpr int kDppXor2 = 0x4E;         // quad_perm:[2,3,0,1]
 constexpr int kDppHalfMirror = 0x141;  // row_half_mirror: lane i <-> 7 - i
