@@ -1,6 +1,8 @@
-"""Build librotq.so (HIP kernels + C ABI) for gfx950 and _pyrotq.so (its Python side) in-tree with hipcc."""
+"""Build librotq.so (HIP kernels + C ABI) for gfx950 and _pyrotq.so (its Python side) in-tree with hipcc.  The library
+itself needs no torch; where torch is not installed the Python side is left out."""
 from __future__ import annotations
 
+import importlib.util
 import os
 import shutil
 import subprocess
@@ -62,17 +64,22 @@ def build_library(verbose: bool = False, extra_flags=()) -> str:
     """Compile every source to an object (a few at a time), then link the library and the Python side."""
     hipcc = hipcc_path()
     compile_flags = [f for f in FLAGS if f != "-shared"]
+    python_side = importlib.util.find_spec("torch") is not None
     with tempfile.TemporaryDirectory(prefix="rotq_build_") as tmpdir:
         objs = [os.path.join(tmpdir, os.path.splitext(s)[0] + ".o") for s in SOURCES]
         jobs = [[hipcc, *compile_flags, *extra_flags, "-c", "-x", "hip", os.path.join(CSRC, s), "-o", o]
                 for s, o in zip(SOURCES, objs)]
         pyobj = os.path.join(tmpdir, "pyrotq.o")
-        jobs.append(_native_compile(hipcc, pyobj))
-        with ThreadPoolExecutor(max_workers=min(len(jobs), 6)) as pool:
+        with ThreadPoolExecutor(max_workers=min(len(jobs) + 1, 6)) as pool:
+            native = pool.submit(lambda: _run(_native_compile(hipcc, pyobj), verbose)) if python_side else None
             list(pool.map(lambda c: _run(c, verbose), jobs))
         tmp = LIB_PATH + ".tmp"
         _run([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", *objs, "-o", tmp], verbose)
         os.replace(tmp, LIB_PATH)
+        if native is None:
+            print("torch is not installed: librotq.so built, its Python side (_pyrotq.so) left out")
+            return LIB_PATH
+        native.result()
         tmp = NATIVE_PATH + ".tmp"
         _run(_native_link(hipcc, pyobj, tmp), verbose)
         os.replace(tmp, NATIVE_PATH)
