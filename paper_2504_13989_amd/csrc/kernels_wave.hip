@@ -539,13 +539,12 @@ __global__ __launch_bounds__(64) void k_wave_block_rotate(WaveArgs a, int pb, Bl
 #pragma unroll
     for (int b = 0; b < 4; ++b) sf[b] = ((c >> b) & 1) ? -1.0f : 1.0f;
     const float flip = (__builtin_popcount(c) & 1) ? -1.0f : 1.0f;
-    const float k0 = flip * (float)o.inv;
     const int base_g = 8 * g < pb - 8 ? 8 * g : pb - 8;
     const int e_base = base_g * 128 + c * 8;
     for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
         float y[8][NV];
-        const float k = SRC ? k0 * a.scales[row] : k0;
-        [[maybe_unused]] const double kd = SRC ? (double)(flip * a.scales[row]) * o.inv : 0.0;
+        const double kd = (double)(SRC ? flip * a.scales[row] : flip) * o.inv;
+        const float k = (float)kd;                        // (rounded once)
         (void)block_rotate_row<FULL, NV, F16, SRC>(a, row, e_base, A0, A1, sf, y);
 #pragma unroll
         for (int j = 0; j < NV; ++j) {

@@ -102,7 +102,10 @@ __device__ __forceinline__ float wg_flip(int cl) {
 // SRC: 0 = 16-bit rows of X, 3 / 4 = packed signed codes of that width (kWgRotate only): the lane's eight codes of
 // a block row become fp16 integers (codes_f16), the matrix cores contract them exactly, and the
 // row's scale multiplies once at the end.
-// WIDE: fp32 results (kWgRotate only), see phase 3; the doubles take 128 registers, 80 spill up to 37 of them.
+// WIDE: fp32 results (kWgRotate only), see phase 3; the doubles take 128 registers, 80 spill up to 37 of them (KK = 8
+// spills 21 - 32 at 128).  16-bit results keep fp32 stages: the type's own rounding is all of their error (18944 wide, rows to
+// bf16 1.659369867e-3 against 64 bits, 1.659369866e-3 on the general kernel with its fp64 block sums; fp16 2.0731412e-4 and
+// 2.0731411e-4), and fp64 stages cost 3584 x 18944 to bf16 51 -> 81 us.
 template <int KK, int BITS, bool FULL, int SINK, int CB = 4, bool F16 = false, int SRC = 0, bool WIDE = false>
 __global__ __launch_bounds__(128 * KK) __attribute__((amdgpu_waves_per_eu(wg_waves_per_simd<KK>(WIDE))))
 void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
@@ -345,7 +348,9 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
             int gq, cq, rq;
             wg_lane<CB>(lane, gq, cq, rq);
             const float sgn = wg_flip<CB>(cq);
-            const float k = sgn * (float)sa.inv * rscale;
+            // (the factor is rounded once; from codes the sums are exact integers)
+            const double kd = SRC ? (double)(sgn * rscale) * sa.inv : (double)sgn * sa.inv;
+            const float k = (float)kd;
             const int64_t row0 = pass * RPW, left = a.rows - row0;
             const int live_rows = left < RPW ? (int)left : RPW;
             constexpr int esz = WIDE ? 4 : 2;
@@ -359,7 +364,6 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
                 for (int nt = 0; nt < 8; ++nt) o[nt] = acc[nt][ip];
                 if constexpr (WIDE) {
                     // (exact integers times the scale: one rounding)
-                    const double kd = (double)(sgn * rscale) * sa.inv;
 #pragma unroll
                     for (int nt = 0; nt < 8; ++nt) o[nt] = (float)((double)o[nt] * kd);
                     // block rows ao0 .. ao0 + 3 of each row of the pass are 4 SEG consecutive values

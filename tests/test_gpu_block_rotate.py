@@ -3,6 +3,7 @@ the oracle: every number of contraction steps, symmetric and unsymmetric blocks,
 ragged end, zero-padded input, narrowed output, every input / output type, both directions."""
 import numpy as np
 import pytest
+import torch
 
 import parity
 import rotq_oracle as oracle
@@ -96,3 +97,24 @@ def test_fp32_results_are_rounded_once(n):
         for transpose in (False, True):
             want = oracle.rotate_back(oracle.as_f64(x), n) if transpose else oracle.rotate(x, n)
             assert rel(binding.rotate(h, parity.to_device(x), transpose=transpose), want) <= bound
+
+
+@pytest.mark.parametrize("n", [3584, 4864, 18944])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_16_bit_results_of_codes_take_their_factor_rounded_once(n, dtype):
+    """scale / sqrt(n) is formed in fp64 and rounded once.  Rows of a single code 1 have that factor as every result; the
+    scales are ones for which 1 / sqrt(n) in fp32 times the scale in fp32 falls to the other side of a rounding boundary of
+    the 16-bit type (a few in a million)"""
+    inv = 1.0 / np.sqrt(np.float64(n))
+    scales = torch.rand(1 << 24, generator=torch.Generator().manual_seed(n), dtype=torch.float32) + 0.5
+    once = (scales.double() * inv).to(torch.float32).to(dtype)
+    twice = (scales * torch.tensor(inv, dtype=torch.float32)).to(dtype)
+    scales, want = scales[once != twice][:64], once[once != twice][:64]
+    assert len(scales) >= 3
+    h = binding.hadamard_build(n)
+    for b in (3, 4):
+        codes = torch.zeros((len(scales), n * b // 8), dtype=torch.uint8, device="cuda")
+        codes[:, 0] = 1
+        y = binding.dequantize_rotate(h, codes, scales.cuda(), b, out_dtype=dtype)
+        assert h.last_kernel in ("wave_block_dequant_rotate", "wg_block_dequant_rotate")
+        assert torch.equal(y.abs().cpu(), want[:, None].expand(-1, n))
