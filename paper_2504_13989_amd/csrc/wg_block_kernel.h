@@ -198,7 +198,9 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const int e = (br + t) * SEG + cq * 8;
-                const uint32_t off = CB == 4 || e < a.d ? (uint32_t)(base + e) * 2u : 0x80000000u;
+                // (block rows that do not exist read as zero: any other value's product with a zero column of B would do as
+                // well, but not that of an infinity)
+                const uint32_t off = b0 < pb && (CB == 4 || e < a.d) ? (uint32_t)(base + e) * 2u : 0x80000000u;
                 R[t] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 2));
             }
         }

@@ -118,3 +118,22 @@ def test_16_bit_results_of_codes_take_their_factor_rounded_once(n, dtype):
         y = binding.dequantize_rotate(h, codes, scales.cuda(), b, out_dtype=dtype)
         assert h.last_kernel in ("wave_block_dequant_rotate", "wg_block_dequant_rotate")
         assert torch.equal(y.abs().cpu(), want[:, None].expand(-1, n))
+
+
+@pytest.mark.parametrize("n", [896, 4864, 8960, 11264, 13824, 18944])
+@pytest.mark.parametrize("out", [torch.float32, torch.bfloat16])
+def test_infinities_of_the_last_block_rows(n, out):
+    """one infinity in a row makes every result an infinity of its own sign, as on the general kernel; NaN makes every
+    result NaN"""
+    h = binding.hadamard_build(n)
+    x = torch.randn((6, n), generator=torch.Generator().manual_seed(n)).to(torch.bfloat16)
+    for i, at in enumerate((0, n // 2, n - 1, n - 130, n - 520)):
+        x[i, at] = float("inf") if i % 2 else -float("inf")
+    x[5, n - 1] = float("nan")
+    x = x.cuda()
+    y = binding.rotate(h, x, out_dtype=out)
+    assert h.last_kernel == "wg_block_rotate"
+    h.set_variant(1)
+    want = binding.rotate(h, x, out_dtype=out)
+    assert torch.isinf(want[:5]).all() and torch.isnan(y[5]).all()
+    assert torch.equal(y[:5], want[:5])
