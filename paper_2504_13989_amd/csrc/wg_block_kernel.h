@@ -103,7 +103,7 @@ __device__ __forceinline__ float wg_flip(int cl) {
 // a block row become fp16 integers (codes_f16), the matrix cores contract them exactly, and the
 // row's scale multiplies once at the end.
 // WIDE: fp32 results (kWgRotate only), see phase 3; the doubles take 128 registers, 80 spill up to 37 of them (KK = 8
-// spills 21 - 32 at 128).  16-bit results keep fp32 stages: the type's own rounding is all of their error (18944 wide, rows to
+// spills 20 - 24 at 128).  16-bit results keep fp32 stages: the type's own rounding is all of their error (18944 wide, rows to
 // bf16 1.659369867e-3 against 64 bits, 1.659369866e-3 on the general kernel with its fp64 block sums; fp16 2.0731412e-4 and
 // 2.0731411e-4), and fp64 stages cost 3584 x 18944 to bf16 51 -> 81 us.
 template <int KK, int BITS, bool FULL, int SINK, int CB = 4, bool F16 = false, int SRC = 0, bool WIDE = false>
@@ -177,7 +177,9 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
         const int live_rows = left < RPW ? (int)left : RPW;
         int gq, cq, rq;
         wg_lane<CB>(lane, gq, cq, rq);
-        const int b0 = 16 * wave + 4 * gq, br = b0 < pb ? b0 : pb - 4;
+        // block rows that do not exist: of X they lie beyond d and read as zero (their products with zero columns of B
+        // would not, for infinities of real rows); of codes the last four real ones are read
+        const int b0 = 16 * wave + 4 * gq, br = SRC == 0 || b0 < pb ? b0 : pb - 4;
         if constexpr (SRC != 0) {
             const int row_bytes = (SEG * SRC / 8) * pb;
             const auto rs = __builtin_amdgcn_make_buffer_rsrc(a.codes + row0 * (row_bytes / 4), 0, live_rows * row_bytes, 0x00020000);
@@ -198,9 +200,7 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const int e = (br + t) * SEG + cq * 8;
-                // (block rows that do not exist read as zero: any other value's product with a zero column of B would do as
-                // well, but not that of an infinity)
-                const uint32_t off = b0 < pb && (CB == 4 || e < a.d) ? (uint32_t)(base + e) * 2u : 0x80000000u;
+                const uint32_t off = CB == 4 || e < a.d ? (uint32_t)(base + e) * 2u : 0x80000000u;
                 R[t] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 2));
             }
         }
