@@ -74,7 +74,7 @@ struct RowArgs {
 };
 
 struct OutArgs {
-    void* Y;          // rows x d_out results, fp32 or bf16
+    void* Y;          // rows x d_out results, fp32, bf16 or fp16
     int dtype;
     int d_out;
     int64_t ld_out;
@@ -118,7 +118,7 @@ int generic_dequant_rotate(const rq_hadamard* h, const RowArgs& a, const uint32_
 // Rotation-free per-token quantizer (any d that is a multiple of 32).
 int plain_quantize(const void* X, int dtype, int64_t rows, int d, int64_t ld, int bits, float clip,
                    uint32_t* codes, float* scales, hipStream_t s);
-// The same on the wave path: bf16 rows up to 20480 wide, 16-byte aligned.
+// The same on the wave path: bf16 / fp16 rows up to 20480 wide, 16-byte aligned.
 bool plain_wave_supports(const void* X, int dtype, int d, int64_t ld);
 int plain_wave_quantize(const void* X, int dtype, int64_t rows, int d, int64_t ld, int bits, float clip,
                         uint32_t* codes, float* scales, hipStream_t s);
@@ -130,14 +130,14 @@ int plain_wave_short_quantize(const void* X, int dtype, int64_t rows, int d, int
 bool generic_supports(const rq_hadamard* h);
 bool generic_prepare(rq_hadamard* h);
 
-// Wave-per-row kernels (bf16 rows, Sylvester orders 128 .. 8192, 16-byte aligned rows).
+// Wave-per-row kernels (bf16 / fp16 rows, Sylvester orders 128 .. 8192, 16-byte aligned rows).
 std::vector<uint32_t> wave_sylvester_tiles();
 // The +-1 entries of a bf16 operand table re-encoded as IEEE fp16.
 std::vector<uint32_t> tiles_to_f16(const std::vector<uint32_t>& bf16_tiles);
 bool wave_supports(const rq_hadamard* h, const RowArgs& a);
 int wave_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float clip, uint32_t* codes,
                          float* scales, hipStream_t s);
-// Asymmetric group-128 variant on the wave path: bf16 rows of order 128 (one group per row).
+// Asymmetric group-128 variant on the wave path: bf16 / fp16 rows of order 128 (one group per row).
 bool wave_asym_supports(const rq_hadamard* h, const RowArgs& a);
 int wave_rotate_quantize_asym(const rq_hadamard* h, const RowArgs& a, float clip, uint32_t* codes,
                               float* scales, float* mins, hipStream_t s);
@@ -151,7 +151,7 @@ int reduce_partials(double* partial, int64_t rows, int n_clips, float* mse, hipS
 // First level of that reduction for many rows: sums over chunks of rows, each left in the chunk's own first row of
 // `partial`.  Returns the number of sums per clip ratio and their distance in rows; RQ_OK or an error.
 int reduce_chunks(double* partial, int64_t rows, int n_clips, const ClipList* dev, int64_t* count, int64_t* stride, hipStream_t s);
-// Block kernel: bf16 rows, n = pb * 128 with a +-1 block of order pb <= 32 (Paley (x) small
+// Block kernel: bf16 / fp16 rows, n = pb * 128 with a +-1 block of order pb <= 32 (Paley (x) small
 // Sylvester) on the matrix cores.
 std::vector<uint32_t> wave_block_tiles(const std::vector<int8_t>& bm, int pb);
 bool wave_block_supports(const rq_hadamard* h, const RowArgs& a);
@@ -188,7 +188,7 @@ bool wave_dequant_rotate_supports(const rq_hadamard* h, const RowArgs& a, const 
 int wave_dequant_rotate(const rq_hadamard* h, const RowArgs& a, const uint32_t* codes, const float* scales,
                         const float* mins, const OutArgs& o, hipStream_t s);
 
-// Dense-block kernel: bf16 rows, any order n <= 4096 that the wave kernels do not serve (the whole
+// Dense-block kernel: bf16 / fp16 rows, any order n <= 4096 that the wave kernels do not serve (the whole
 // matrix on the matrix cores), e.g. 1544 as one Paley block.
 std::vector<uint32_t> dense_block_tiles(const std::vector<int8_t>& hm, int n);
 bool dense_block_supports(const rq_hadamard* h, const RowArgs& a);
@@ -202,7 +202,7 @@ bool f64_rows_supports(const rq_hadamard* h, const RowArgs& a);
 int f64_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float clip, uint32_t* codes, float* scales, hipStream_t s);
 
 // Workgroup block kernel: bf16 or fp16 rows, n = pb * 128 with 32 < pb <= 256 (e.g. 18944 = 148 * 128),
-// or n = p * 64 / p * 32 with 4 <= p <= 256 (several rows per pass); quant_error: the former, bf16.
+// or n = p * 64 / p * 32 with 4 <= p <= 256 (several rows per pass).
 std::vector<uint32_t> wg_block_tiles(const std::vector<int8_t>& bm, int pb);
 bool wg_block_prepare(int pb);
 // Shape of a launch of that kernel: block order and lane bits of the column transform; false when it does not serve the order.

@@ -298,8 +298,10 @@ struct Quant {
         for (int r = 0; r < 8; ++r) m |= 1u << (BITS * r + BITS - 1);
         return m;
     }
-    // the next code of the chain: w 2^b + u
+    // the next code of the chain: w 2^b + u (FREE: left to the compiler)
+    template <bool FREE = false>
     static __device__ __forceinline__ uint32_t chain(uint32_t w, float u) {
+        if constexpr (FREE) return (w << BITS) + __float_as_uint(u);
         uint32_t r;
         asm("v_lshl_add_u32 %0, %1, %2, %3" : "=v"(r) : "v"(w), "n"(BITS), "v"(u));
         return r;
@@ -310,20 +312,22 @@ struct Quant {
         return BITS == 3 ? w : w - csum();
     }
     // clamps and chains u7 .. u0 (u0 in the low bits)
+    template <bool FREE = false>
     static __device__ __forceinline__ uint32_t join(const float (&u)[8]) {
         uint32_t w = __float_as_uint(__builtin_amdgcn_fmed3f(u[7], kLo, kHi));
 #pragma unroll
-        for (int r = 6; r >= 0; --r) w = chain(w, __builtin_amdgcn_fmed3f(u[r], kLo, kHi));
+        for (int r = 6; r >= 0; --r) w = chain<FREE>(w, __builtin_amdgcn_fmed3f(u[r], kLo, kHi));
         return chained(w);
     }
     // packs codes of y0..y7 (y0 in the low bits) into 8*BITS bits
+    template <bool FREE = false>
     static __device__ __forceinline__ uint32_t pack8(float y0, float y1, float y2, float y3, float y4,
                                                      float y5, float y6, float y7, float s) {
         const float y[8] = {y0, y1, y2, y3, y4, y5, y6, y7};
         float u[8];
 #pragma unroll
         for (int r = 0; r < 8; ++r) u[r] = fmaf(y[r], s, kBias);
-        return join(u) ^ msb();
+        return join<FREE>(u) ^ msb();
     }
     // Unsigned codes 0 .. 2^b - 1 of (y - cen) * s + bias - kMagic: the asymmetric group
     // quantizer, centred on the value `cen` that maps to the middle code so that the fp32

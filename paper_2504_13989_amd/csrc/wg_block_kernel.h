@@ -1,4 +1,4 @@
-// Workgroup block kernel: bf16 rows of order n = pb * 128 with a +-1 block of order
+// Workgroup block kernel: bf16 / fp16 rows of order n = pb * 128 with a +-1 block of order
 // 32 < pb <= 256 along the strided axis (H_n = B (x) H_128, B = H_p (x) H_{2^(k-7)}; sections
 // 2.3.2, 2.3.3) - e.g. 18944 = 148 * 128 with the order-148 Paley II block; also the Sylvester
 // orders 2^14 and 2^15, which are too long for one wave (B = H_128, H_256).
@@ -394,13 +394,13 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
         {
             // All waves' maxima with one LDS latency (a read per wave, each waiting for the one before it, takes nw of
             // them while the whole workgroup waits: 14336-wide rows, b = 4, 512 MiB 154 -> 145 us).  Up to four 16-byte
-            // reads in flight, or, where their registers spill (KK = 5 with several rows per pass: 80 registers for 32
-            // values and 20 of operand tiles; 8960-wide rows 196 -> 165 us), one read: the lane of chunk cl takes RPW of the
-            // row's 16 slots and the lanes that share the row do the rest.  (Elsewhere the reads are the faster: 4864-wide
-            // rows 148 against 151 us.)
+            // reads in flight, or, where their registers spill (KK = 5 with several rows per pass or b = 4: 80 registers for
+            // 32 values and 20 of operand tiles; 8960-wide rows 196 -> 165 us), one read: the lane of chunk cl takes RPW of
+            // the row's 16 slots and the lanes that share the row do the rest.  (Elsewhere the reads are the faster:
+            // 4864-wide rows 148 against 151 us.)
             int gq, cq, rq;
             wg_lane<CB>(lane, gq, cq, rq);
-            if constexpr (KK == 5 && CB < 4) {
+            if constexpr (KK == 5 && (CB < 4 || BITS == 4)) {
                 uint32_t u[RPW];
                 __builtin_memcpy(u, &wmax[rq * 16 + cq * RPW], sizeof u);
                 uint32_t mu = u[0];
@@ -443,11 +443,11 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
             }
             continue;
         }
-        // Where registers are tight (several rows per pass; b = 4 at 80 registers) the lane's place is worked out again
-        // here, so that nothing of it is held through the phases before (512 MiB of rows: 8960 wide, b = 4 229 -> 196 us;
-        // 18944 wide, b = 4 182 -> 175).  Elsewhere holding it is the faster: 14336 wide, b = 4 145 against 150, 18944 wide,
-        // b = 3 169 against 173, 1792 wide (KK = 1) 132 against 134.
-        constexpr bool AGAIN = KK > 1 && (CB < 4 || (BITS == 4 && wg_waves_per_simd<KK>() == 6));
+        // Where registers are tight (several rows per pass; b = 4 at KK = 2, 3) the lane's place is worked out again here, so
+        // that nothing of it is held through the phases before (512 MiB of rows, b = 4: 8960 wide 229 -> 196 us, 11008 wide
+        // 161 -> 151).  Elsewhere holding it is the faster: 14336 wide, b = 4 145 against 150, 18944 wide, b = 3 169 against
+        // 173, 1792 wide (KK = 1) 132 against 134.
+        constexpr bool AGAIN = KK > 1 && (CB < 4 || (BITS == 4 && KK <= 3));
         int gq = g, cq = cl, rq = rsub, lq = lane;
         if constexpr (AGAIN) {
             wg_lane<CB>(lane, gq, cq, rq);
@@ -456,14 +456,17 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
         const int64_t row = pass * RPW + rq;
         const bool live = CB == 4 || row < a.rows;
         const float fl = AGAIN ? wg_flip<CB>(cq) : flip;
+        // (18944 wide, b = 4: the compiler's own order of the shift-adds needs fewer registers: 4096 rows 53 -> 51.5 us; other
+        // forms are the faster with the chain, 8960 wide 170 against 179)
+        constexpr bool FREE = KK == 5 && CB == 4 && BITS == 4;
         // (2^b - 1) / (clip m) from a float pair of the constant: reciprocal, Newton step, correction
         const float s = m > 0.0f ? fl * div_pair(c1h, c1l, m) : 0.0f;
         uint32_t* out = a.codes + row * (int64_t)(SEG * BITS / 32) * pb;   // used by live lanes only
 #pragma unroll
         for (int ip = 0; ip < 4; ++ip) {
             const int ao = 16 * wave + 4 * ip + gq;      // output block row of this register
-            const uint32_t w = Quant<BITS>::pack8(acc[0][ip], acc[1][ip], acc[2][ip], acc[3][ip],
-                                                  acc[4][ip], acc[5][ip], acc[6][ip], acc[7][ip], s);
+            const uint32_t w = Quant<BITS>::template pack8<FREE>(acc[0][ip], acc[1][ip], acc[2][ip], acc[3][ip], acc[4][ip],
+                                                                 acc[5][ip], acc[6][ip], acc[7][ip], s);
             if constexpr (CB == 4) {
                 const int word = ao * 16 + cq;
                 if (BITS == 4) {
@@ -529,7 +532,7 @@ int wg_launch(const rq_hadamard* h, WgKernel<SINK> fn, const WaveArgs& a, int pb
     unsigned shares = 1;
     if constexpr (SINK == kWgError) {
         // few rows: the clip ratios of a pass over as many workgroups as make about ten waves per compute unit (32 x 8960, 32
-        // ratios: 31.9 -> 12.8 us; beyond that the repeated rotations cost more than the idle units: 512 x 5120 with four
+        // ratios: 31.9 -> 12.3 us; beyond that the repeated rotations cost more than the idle units: 512 x 5120 with four
         // shares 16.4 -> 20.4)
         const int64_t want = (int64_t)h->num_cu * 10 / (passes * nw);
         shares = (unsigned)(want < 1 ? 1 : want > sa.max_shares ? sa.max_shares : want);
