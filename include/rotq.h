@@ -16,11 +16,12 @@
  *     exist for one p the first is used.  n must be a multiple of 8 and at least 32 (packed rows are
  *     whole bytes); where no block of at most 256 exists a Paley block of up to 4096 is taken.  The
  *     fast kernels serve 16-bit rows of the orders rq_next_order returns (2^k >= 32, block <= 256);
- *     every other case (fp32 rows, unaligned rows, other orders) runs on a general kernel that
- *     keeps the row in the 160 KB of LDS, which bounds n: 2^15 for Sylvester orders and 20448 for
- *     block orders; fp32 rows are quantized from an fp64 copy of the row and stop at n = 2^14
- *     (Sylvester) and 9728 (block orders).  A row call on an order beyond what its kernels can hold
- *     returns RQ_ERR_NO_ORDER.
+ *     fp32 rows to be quantized per token on orders with 2^k <= 512 (Sylvester: up to 2^14) have an fp64
+ *     kernel of their own; every other case (other calls on fp32 rows, unaligned rows, other orders) runs
+ *     on a general kernel that keeps the row in the 160 KB of LDS, which bounds n: 2^15 for Sylvester
+ *     orders and 20448 for block orders; fp32 rows are quantized from an fp64 copy of the row and stop at
+ *     n = 2^14 (Sylvester) and 9728 (block orders).  A row call on an order beyond what its kernels can
+ *     hold returns RQ_ERR_NO_ORDER.
  *   - H_n = H_p (x) H_{2^k}: flat index j = a * 2^k + c (a < p, c < 2^k),
  *     H_n[i, j] = H_p[i / 2^k, j / 2^k] * (-1)^popcount((i % 2^k) & (j % 2^k)).
  *   - Rotated row: y = H_n pad(x) / sqrt(n), pad() appends n - d zeros.
@@ -333,9 +334,10 @@ size_t rq_gbs_workspace(int64_t rows);
  * max_evals evaluations of f.  The probes and their values are those of that loop taken one at a
  * time; they are evaluated ahead in batches (every probe the next few steps can ask for, whatever the
  * comparisons give), and the comparisons are taken on the device: rows the chip can hold in registers
- * are rotated once and searched in one launch (or with a launch per few steps, to the same values bit for bit, where other
- * work keeps that one from running), other tensors take a few launches enqueued together.  f is summed in an order of
- * the search's own: it agrees with rq_quant_error to 2e-6, not to the last bit.  The same call gives the same result.
+ * are rotated once and searched in one launch (or, to the same values bit for bit, with a launch for every
+ * three steps where other work keeps that one from running), other tensors take a few launches enqueued
+ * together.  f is summed in an order of the search's own: it agrees with rq_quant_error to 2e-6 (relative), not
+ * to the last bit.  The same call gives the same result.
  * The call waits for the result: a calibration call, not a hot-path call (not for a stream under
  * capture).  Besides the workspace a search uses static device memory (as rq_quant_error_noalloc does) and 256 KB of
  * device and 33 KB of pinned host memory that the first search on a device allocates and that stay until the process
@@ -368,9 +370,10 @@ int rq_gbs_search_asym(const rq_hadamard_t* h, const void* X, int dtype, int64_t
  * Select the kernel family for subsequent hot-path calls on this handle (testing /
  * measurement): 0 = automatic (fastest available), 1 = the general LDS kernel; for long
  * power-of-two rows 2 = one wave per row at any row count, 3 / 4 = a row split over 2 / 4 waves
- * at any row count (automatic picks by the number of rows); automatic but for the searches that fit the
- * chip's registers: 5 = a launch per step ("gbs_stepped"), 6 = one launch ("gbs_resident") whose workgroups do not wait for each
- * other, so that it gives up and the former takes over, and for all searches 7 = no pinned memory.
+ * at any row count (automatic picks by the number of rows); 5 .. 7 are automatic but for
+ * the searches: for tensors that fit the chip's registers 5 = a launch for every three steps ("gbs_stepped"),
+ * 6 = one launch ("gbs_resident") whose workgroups do not wait for each other, so that it gives up and the
+ * former takes over; 7 = no pinned memory (the former form again, for every tensor the results copied back).
  * Errors: RQ_ERR_ARG.
  */
 int rq_hadamard_set_variant(rq_hadamard_t* h, int variant);
