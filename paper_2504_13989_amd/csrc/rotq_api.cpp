@@ -682,13 +682,12 @@ static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t ro
             turn->unclear = 3;
         }
         // Searches take the buffers in turn: the host goes on when the result has arrived, and a workgroup of this
-        // search may then still be reading the last step's words.  A buffer is cleared when its own turn has come.
+        // search may then still be reading the last step's words.  A buffer is cleared when its own turn has come, and counts
+        // as cleared once a search has come through on it (on a stream under capture nothing has run).
         const int b = turn->turn;
         uint64_t* const buf = turn->exchange + b * (rq::gbs_exchange_bytes() / sizeof(uint64_t));
-        if (turn->unclear >> b & 1) {
-            if (hipMemsetAsync(buf, 0, rq::gbs_exchange_bytes(), s) != hipSuccess) return finish(RQ_ERR_HIP, nullptr);
-            turn->unclear &= ~(1 << b);
-        }
+        if ((turn->unclear >> b & 1) && hipMemsetAsync(buf, 0, rq::gbs_exchange_bytes(), s) != hipSuccess)
+            return finish(RQ_ERR_HIP, nullptr);
         rc = rq::gbs_resident(h, a, mem.out_dev, buf, turn->epoch, (double)eps, max_evals, form != kSearchNoWait, s);
         turn->epoch += kSteps;
         turn->turn ^= 1;
@@ -702,6 +701,7 @@ static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t ro
         if (!*done && hipStreamSynchronize(s) != hipSuccess) return finish(RQ_ERR_HIP, nullptr);
         std::atomic_thread_fence(std::memory_order_acquire);
         if (*done) {
+            turn->unclear &= ~(1 << b);
             note(h, "gbs_resident");
             return finish(RQ_OK, mem.out);
         }
