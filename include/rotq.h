@@ -332,18 +332,19 @@ size_t rq_gbs_workspace(int64_t rows);
  * f(x) < f(m) becomes the new middle and the far bracket end moves to the old middle, otherwise
  * the bracket end on the probe's side moves to the probe; stops when b - a <= eps or after
  * max_evals evaluations of f.  The probes and their values are those of that loop taken one at a
- * time; they are evaluated ahead in batches (every probe the next few steps can ask for, whatever the
- * comparisons give), and the comparisons are taken on the device: rows the chip can hold in registers
- * are rotated once and searched in one launch (or, to the same values bit for bit, with a launch for every
- * three steps where other work keeps that one from running), other tensors take a few launches enqueued
- * together.  f is summed in an order of the search's own: it agrees with rq_quant_error to 2e-6 (relative), not
+ * time; they are evaluated ahead, and the comparisons are taken on the device: for eps >= 1 / 256 every
+ * probe there can be is a multiple of 1 / 512, and 16-bit rows are passed over once with all of these evaluated at
+ * once; for a smaller eps rows the chip can hold in registers are rotated once and searched in one launch (or,
+ * to the same values bit for bit, with a launch for every three steps where other work keeps that one from
+ * running); other tensors take a few launches enqueued together, each of which evaluates every probe the next few
+ * steps can ask for.  f is summed in an order of the search's own: it agrees with rq_quant_error to 2e-6 (relative), not
  * to the last bit.  The same call gives the same result.
  * The call waits for the result: a calibration call, not a hot-path call (not for a stream under
  * capture).  Besides the workspace a search uses static device memory (as rq_quant_error_noalloc does) and 256 KB of
  * device and 33 KB of pinned host memory that the first search on a device allocates and that stay until the process
  * ends; where the pinned memory cannot be had the results are copied back on `stream` instead, and more than 16 searches
- * at once on a device allocate a few KB for the call.  Searches may run on any number of threads and streams; one at a
- * time per device takes the single-launch form.
+ * at once on a device allocate 1 MB for the call.  Searches may run on any number of threads and streams; one at a
+ * time per device takes the form whose one launch walks the whole search.
  *   eps          [in]  bracket width to stop at, > 0
  *   max_evals    [in]  1 .. 256
  *   workspace    [in]  DEVICE, >= rq_gbs_workspace(rows) bytes, 8-byte aligned, scratch
@@ -374,6 +375,8 @@ int rq_gbs_search_asym(const rq_hadamard_t* h, const void* X, int dtype, int64_t
  * the searches: for tensors that fit the chip's registers 5 = a launch for every three steps ("gbs_stepped"),
  * 6 = one launch ("gbs_resident") whose workgroups do not wait for each other, so that it gives up and the
  * former takes over; 7 = no pinned memory (the former form again, for every tensor the results copied back).
+ * Where all probes are evaluated at once (eps >= 1 / 256) 5 and 7 wait for the stream instead of looking for the result,
+ * under the same two names.
  * Errors: RQ_ERR_ARG.
  */
 int rq_hadamard_set_variant(rq_hadamard_t* h, int variant);

@@ -1,0 +1,199 @@
+// The clip-ratio search of Algorithm 1 (section 4.1) in its grid form: every probe of a search down to a bracket of 1 / 256
+// is a multiple of 1 / 512 (a probe halves the wider of the two gaps beside the best point, so no gap gets to a quarter of
+// the bracket or below), and the error of a row at all 511 ratios costs little more than the rotation (error_grid.h).  One
+// kernel passes over the rows once and leaves each workgroup's sums, a second adds them up and walks the search; nothing
+// is evaluated twice and no step waits for another.
+// Bound: latency.  512 x 4096, b = 3: 13 us in the first kernel (launch and cold rows 4, rotation 1.5, the additions of two
+// rows a compute unit 2.3, about 20 cycles of LDS each, the passes over the histogram 3), 6 in the second (launch, 1 MB
+// of sums, the walk, results over the bus).  A search, us a call, resident or batched form before -> now: 512 x 4096 46 ->
+// 25, 1024 x 8192 90 -> 41, 78 x 5120 48 -> 26, 960 x 14336 199 -> 64, 512 x 18944 164 -> 42 - 51.
+#include "error_grid.h"
+#include "row_rotation.h"
+
+namespace rq {
+namespace {
+
+// Rows held in registers, eight waves a row, `conc` rows (one or two) a workgroup at a time, each with a histogram of its
+// own.  Where a row is rotated by fewer waves, W, all eight repeat the rotation and share the values: the additions and
+// the passes over the histogram take longer than the rotation, and LDS (57 KB a row for b = 4) leaves no room for more
+// rows in their place (one row a wave: 2048 x 1024, b = 4 65 us a search, 512 x 4096 on four waves a row 26.7).
+template <typename Rows, int BITS>
+__global__ __launch_bounds__(1024) void k_grid_rows(WaveArgs a, int pb, int conc, double inv_norm, GbsDev* dev) {
+    using Grid = ErrorGrid<BITS>;
+    constexpr int W = Rows::W, NVAL = Rows::NVAL, NT = 512, SHARES = NT / 64 / W;
+    static_assert(NT >= kGridRatios - 1, "a ratio a thread");
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    __shared__ float wmax[16];
+    __shared__ uint64_t tot[2][3][16];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rsub = wave >> 3, seg = wave % W, share = (wave & 7) / W, t = tid - rsub * NT;
+    uint64_t* const hist = reinterpret_cast<uint64_t*>(lds) + (size_t)rsub * Grid::WORDS;
+    if (blockIdx.x == 0 && tid == 0) dev->grid_ticket = 0;
+    double sum = 0.0;
+    for (int64_t row0 = (int64_t)blockIdx.x * conc; row0 < a.rows; row0 += (int64_t)gridDim.x * conc) {
+        for (int i = t; i < Grid::WORDS / 2; i += NT) reinterpret_cast<u32x4*>(hist)[i] = u32x4{0u, 0u, 0u, 0u};
+        const int64_t row = row0 + rsub;
+        const bool live = row < a.rows;
+        float v[NVAL], flip = 1.0f, m = 0.0f;
+        if (live) {
+            m = Rows::rotate(a, pb, row, seg, lane, v, &flip);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NVAL; ++i) v[i] = 0.0f;
+        }
+        if (lane == 0) wmax[wave] = m;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < W; ++w) m = __builtin_fmaxf(m, wmax[rsub * 8 + w]);
+        const typename Grid::Scale sc = Grid::scale(m, inv_norm);
+        // a row with an infinity or a NaN has one in every value, or its maximum is infinite: its error is NaN
+        double q2 = !(__builtin_fabsf(v[0]) < __builtin_inff()) || !(m < __builtin_inff()) ? __builtin_nan("") : 0.0;
+#pragma unroll
+        for (int i = 0; i < NVAL; ++i)
+            if (i % SHARES == share) Grid::add(hist, v[i] * flip, sc.s, q2);
+        __syncthreads();
+        q2 = Grid::finish(hist, q2, t, NT, tot[rsub]);
+        if (t > 0 && t < kGridRatios) sum += Grid::error(hist, t, q2, sc);
+        __syncthreads();
+    }
+    // the rows a workgroup took side by side
+    double* const part = reinterpret_cast<double*>(lds);
+    if (rsub == 1) part[t] = sum;
+    __syncthreads();
+    if (rsub == 0) dev->grid_sums[blockIdx.x][t] = conc > 1 ? sum + part[t] : sum;
+}
+
+// Totals over the workgroups, eight ratios a workgroup, then, in the workgroup that is last, the search.
+constexpr int kWalkThreads = 256, kWalkRatios = 8;
+__global__ __launch_bounds__(kWalkThreads) void k_grid_walk(GbsDev* dev, GbsOut* out, int groups, int64_t rows, double eps, int max_evals) {
+    __shared__ double part[kWalkThreads];
+    __shared__ float mean[kGridRatios];
+    __shared__ float trace_clips[256], trace_mse[256];
+    __shared__ uint32_t came;
+    __shared__ int n_evals;
+    const int tid = threadIdx.x, c = blockIdx.x * kWalkRatios + (tid & (kWalkRatios - 1));
+    constexpr int LANES = kWalkThreads / kWalkRatios, U = kGridGroups / LANES;
+    double v[U], s = 0.0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int g = tid / kWalkRatios + u * LANES;
+        v[u] = dev->grid_sums[g < groups ? g : 0][c];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) s += tid / kWalkRatios + u * LANES < groups ? v[u] : 0.0;
+    part[tid] = s;
+    for (int h = kWalkThreads / 2; h >= kWalkRatios; h >>= 1) {
+        __syncthreads();
+        if (tid < h) part[tid] += part[tid + h];
+    }
+    // Totals go past the L2 (agent scope), are there before the workgroup counts itself, and are read past it by the last
+    // one: no fence, which would write the L2 back.
+    if (tid < 64) {
+        if (tid < kWalkRatios) __hip_atomic_store(&dev->grid_totals[c], part[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (tid == 0) came = __hip_atomic_fetch_add(&dev->grid_ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (came != gridDim.x - 1) return;
+    for (int i = tid; i < kGridRatios; i += kWalkThreads)
+        mean[i] = (float)(__hip_atomic_load(&dev->grid_totals[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) / (double)rows);
+    __syncthreads();
+    auto put = [](auto* to, auto x) { __hip_atomic_store(to, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); };
+    if (tid == 0) {
+        // GbsState in units of 1 / kGridRatios
+        int left = 0, right = kGridRatios, best = kGridRatios / 2, side = 0, evals = 0;
+        constexpr float unit = 1.0f / kGridRatios;
+        auto value = [&](int x) {
+            const float f = mean[x];
+            trace_clips[evals] = (float)x * unit;
+            trace_mse[evals++] = f;
+            return f;
+        };
+        const int most = (int)fmin(eps * kGridRatios, (double)kGridRatios);      // brackets of at most so many units end the search
+        float fm = value(best);
+        while (right - left > most && evals < max_evals) {
+            const int x = ((side ? right : left) + best) >> 1;
+            const float fx = value(x);
+            const bool better = fx < fm, to_left = better ? side == 1 : side == 0;
+            const int bound = better ? best : x;
+            left = to_left ? bound : left;
+            right = to_left ? right : bound;
+            best = better ? x : best;
+            fm = better ? fx : fm;
+            side ^= 1;
+        }
+        put(&out->clip, (float)best * unit);
+        put(&out->mse, fm);
+        put(&out->evals, evals);
+        n_evals = evals;
+    }
+    __syncthreads();
+    if (tid >= 64) return;
+    for (int i = tid; i < n_evals; i += 64) {
+        put(&out->trace_clips[i], trace_clips[i]);
+        put(&out->trace_mse[i], trace_mse[i]);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the flag when the results have arrived
+    if (tid == 0) put(&out->done, 1);
+}
+
+template <typename Rows, int BITS>
+int launch_rows(const rq_hadamard* h, const RowArgs& a, const WaveArgs& w, int pb, int* groups, GbsDev* dev, hipStream_t s) {
+    using Grid = ErrorGrid<BITS>;
+    static_assert(Grid::WORDS % 2 == 0, "cleared by 16 bytes");
+    const int cus = h->num_cu < kGridGroups ? h->num_cu : kGridGroups;
+    const int conc = a.rows > cus && (size_t)h->max_lds >= 2 * Grid::bytes() + 1024 ? 2 : 1;
+    const int64_t passes = (a.rows + conc - 1) / conc;
+    *groups = (int)(passes < cus ? passes : cus);
+    void (*const fn)(WaveArgs, int, int, double, GbsDev*) = k_grid_rows<Rows, BITS>;
+    const size_t lds = (size_t)conc * Grid::bytes();
+    launch_kernel(fn, dim3((unsigned)*groups), dim3((unsigned)(512 * conc)), lds, s, w, pb, conc,
+                  1.0 / ((double)a.n * (double)a.n), dev);
+    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+}
+
+template <int BITS, bool F16>
+int rows_pass(const rq_hadamard* h, const RowArgs& a, const WaveArgs& w, int* groups, GbsDev* dev, hipStream_t s) {
+    const int pb = a.p > 1 ? a.p << (a.log2m - 7) : 0;
+    if (a.p > 1) return pb <= 16 ? launch_rows<BlockRows<1, F16>, BITS>(h, a, w, pb, groups, dev, s)
+                                 : launch_rows<BlockRows<2, F16>, BITS>(h, a, w, pb, groups, dev, s);
+    switch (a.log2m) {
+        case 10: return launch_rows<SylvesterRows<2, 1, F16>, BITS>(h, a, w, pb, groups, dev, s);
+        case 11: return launch_rows<SylvesterRows<4, 2, F16>, BITS>(h, a, w, pb, groups, dev, s);
+        case 12: return launch_rows<SylvesterRows<8, 4, F16>, BITS>(h, a, w, pb, groups, dev, s);
+        case 13: return launch_rows<SylvesterRows<16, 4, F16>, BITS>(h, a, w, pb, groups, dev, s);
+        default: return RQ_ERR_NO_ORDER;
+    }
+}
+
+}  // namespace
+
+// Brackets down to 2 / kGridRatios, see above.  Short rows leave a pass of the grid form (two rows a compute unit, and on the
+// workgroup block kernel one, for a histogram's LDS) less to do than a quant_error pass over many rows: orders below 2048
+// take it up to 8192 rows (1024 wide, b = 4: 8192 rows 134 us against 146 in batches, 32768 about 480 against 344), those of
+// the workgroup block kernel up to one pass a compute unit (896 wide, b = 4: 1024 rows 58 against 70, 2048 rows 98
+// against 84).  Longer rows are faster at every number (2048 wide, 8192 rows 138 against 217; 18944 wide, 512 rows 42
+// against 165, 8192 rows 377 against 1453).
+bool gbs_grid_supports(const rq_hadamard* h, const RowArgs& a, double eps) {
+    if (eps < 2.0 / kGridRatios) return false;
+    if (gbs_in_registers(h, a)) return a.n >= 2048 || a.rows <= 8192;
+    int pb, cb;
+    if (wave_quant_error_supports(h, a) || !wg_block_supports(h, a, true) || !wg_shape(a, &pb, &cb)) return false;
+    return a.n >= 2048 || a.rows <= (int64_t)h->num_cu * (16 >> cb);
+}
+
+int gbs_grid(const rq_hadamard* h, const RowArgs& a, GbsDev* dev, GbsOut* out, double eps, int max_evals, hipStream_t s) {
+    const bool f16 = a.dtype == RQ_F16;
+    WaveArgs w{static_cast<const uint16_t*>(a.X), a.rows, a.d, a.ld,
+               static_cast<const u32x4*>(f16 ? h->d_tiles_f16 : h->d_tiles), nullptr, nullptr, 0.0, 0.0};
+    w.f16 = f16;
+    int groups = 0;
+    const int rc = !gbs_in_registers(h, a) ? wg_grid_rows(h, a, dev, &groups, s) : a.bits == 4 ? (f16 ? rows_pass<4, true>(h, a, w, &groups, dev, s) : rows_pass<4, false>(h, a, w, &groups, dev, s))
+                               : (f16 ? rows_pass<3, true>(h, a, w, &groups, dev, s) : rows_pass<3, false>(h, a, w, &groups, dev, s));
+    if (rc != RQ_OK) return rc;
+    launch_kernel(k_grid_walk, dim3(kGridRatios / kWalkRatios), dim3(kWalkThreads), 0, s, dev, out, groups, a.rows, eps, max_evals);
+    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+}
+
+}  // namespace rq

@@ -1,4 +1,5 @@
-// The clip-ratio search of Algorithm 1 (section 4.1) on the device, in three forms.
+// The clip-ratio search of Algorithm 1 (section 4.1) on the device, in the three forms that serve what the grid form
+// (kernels_gridsearch.hip) does not: brackets below 1 / 256, other row formats and orders, many short rows.
 //
 // Batches (any tensor): between the batches of objective values a search
 // needs (one quant_error pass each), a kernel of one workgroup averages the batch, walks the search with it and writes
@@ -14,28 +15,9 @@
 #include <mutex>
 
 #include "row_rotation.h"
+#include "search_state.h"
 
 namespace rq {
-
-// Search state: the best point so far and the nearest evaluated point on either side of it; probes go to the midpoint
-// towards the left and the right neighbour in turn.
-struct GbsState {
-    double left, right;   // nearest evaluated points left and right of the best
-    double best;
-    int side;             // neighbour the next probe goes towards: 0 left, 1 right
-    __host__ __device__ double width() const { return right - left; }
-    __host__ __device__ double probe() const { return 0.5 * ((side ? right : left) + best); }
-    // after probing x = probe(): `better` = the probe beat the best point, which then bounds the far side
-    __host__ __device__ void next(double x, bool better) {
-        const bool to_left = better ? side == 1 : side == 0;
-        const double bound = better ? best : x;
-        left = to_left ? bound : left;
-        right = to_left ? right : bound;
-        best = better ? x : best;
-        side = 1 - side;
-    }
-};
-__host__ __device__ inline GbsState gbs_start() { return GbsState{0.0, 1.0, 0.5, 0}; }
 
 // Probe of node i (1 .. 2^depth - 1) of the tree below `st`, in heap order (children 2 i for "better", 2 i + 1 for "not
 // better"); false where the search ends before it gets there.
@@ -49,24 +31,6 @@ __host__ __device__ inline bool gbs_node(GbsState st, double eps, int depth, int
     *x = st.probe();
     return live;
 }
-
-// What one launch of the stepped form hands to the next.
-struct GbsCarry {
-    GbsState st;
-    float fm;             // objective at the best point
-    int evals;
-    int done;
-};
-
-struct GbsDev {
-    GbsCarry carry[2];    // stepped form; the rest: batched form
-    ClipList clips;       // the next batch
-    GbsState st;
-    float fm;             // objective at the best point
-    int evals;
-    int done;
-    float trace_clips[256], trace_mse[256];
-};
 
 namespace {
 
@@ -215,47 +179,6 @@ struct ResidentArgs {
     GbsCarry* carry;          // [2], taken in turn
     double* sums;             // [2][workgroups][kSlots]
     uint32_t step;
-};
-
-// A Sylvester row of 512 T values over W waves, T / W register sets each.
-template <int T, int W_, bool F16>
-struct SylvesterRows {
-    static constexpr int W = W_, NVAL = T / W * 8;
-    static __device__ __forceinline__ float rotate(const WaveArgs& a, int, int64_t row, int seg, int lane, float (&v)[NVAL], float* flip) {
-        const int g = lane >> 4, cphys = lane & 15, c = (cphys & 4) ? (cphys ^ 3) : cphys;
-        const u32x4 A0 = a.tiles[lane], A1 = a.tiles[64 + lane];
-        f32x4 acc[T / W][2];
-        const float m = split_rotate_row<T, false, W, F16>(a, row, seg, c, (g << 4) + c, A0, A1, acc);
-#pragma unroll
-        for (int t = 0; t < T / W; ++t)
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[(t * 2 + h) * 4 + i] = acc[t][h][i];
-        *flip = split_flip<T, W>(c);
-        return wave_absmax<4>(m);
-    }
-};
-// A row of a block order, pb <= 32: W waves with 16 output block rows each.
-template <int W_, bool F16>
-struct BlockRows {
-    static constexpr int W = W_, NVAL = 32;
-    static __device__ __forceinline__ float rotate(const WaveArgs& a, int pb, int64_t row, int seg, int lane, float (&v)[NVAL], float* flip) {
-        const int g = lane >> 4, cphys = lane & 15, c = (cphys & 4) ? (cphys ^ 3) : cphys;
-        const u32x4 A = a.tiles[seg * 64 + lane];
-        float sf[4];
-#pragma unroll
-        for (int b = 0; b < 4; ++b) sf[b] = ((c >> b) & 1) ? -1.0f : 1.0f;
-        const int base_g = 8 * g < pb - 8 ? 8 * g : pb - 8;
-        float y[8][4];
-        const float m = block_rotate_row<false, 4, F16>(a, row, base_g * 128 + c * 8, A, A, sf, y);
-#pragma unroll
-        for (int ic = 0; ic < 8; ++ic)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[ic * 4 + j] = y[ic][j];
-        *flip = (__builtin_popcount(c) & 1) ? -1.0f : 1.0f;
-        return m;
-    }
 };
 
 template <typename Rows, int BITS, bool STEPPED>
@@ -532,10 +455,11 @@ int resident_launch(const rq_hadamard* h, const RowArgs& a, ResidentArgs r, hipS
 
 }  // namespace
 
+bool gbs_in_registers(const rq_hadamard* h, const RowArgs& a) { return wave_quant_error_supports(h, a) && resident_waves(a) > 0; }
+
 bool gbs_resident_supports(const rq_hadamard* h, const RowArgs& a) {
-    if (!wave_quant_error_supports(h, a)) return false;
+    if (!gbs_in_registers(h, a)) return false;
     const int w = resident_waves(a);
-    if (w == 0) return false;
     const int groups = h->num_cu < kMaxGroups ? h->num_cu : kMaxGroups;
     return a.rows <= (int64_t)groups * (16 / w);          // 16 waves per compute unit
 }

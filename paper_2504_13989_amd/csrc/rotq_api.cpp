@@ -674,8 +674,38 @@ static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t ro
     const volatile int* done = mem.out ? &mem.out->done : nullptr;
     const int steps = gbs_most_steps((double)eps, max_evals - 1);
     const bool in_registers = !asym && h->variant == 0 && rq::gbs_resident_supports(h, a);
+    // after the last launch: the results, copied back where they are in device memory
+    auto collect = [&](int code) {
+        rq::GbsOut copied;
+        const rq::GbsOut* result = mem.out;
+        if (code == RQ_OK && !mem.out) {
+            result = &copied;
+            if (hipMemcpyAsync(&copied, mem.out_dev, sizeof copied, hipMemcpyDeviceToHost, s) != hipSuccess) code = RQ_ERR_HIP;
+        }
+        if (hipStreamSynchronize(s) != hipSuccess && code == RQ_OK) code = RQ_ERR_HIP;
+        return finish(code == RQ_OK && !result->done ? RQ_ERR_HIP : code, result);
+    };
+    // The result arrives in host memory before the runtime reports the stream done: worth about 5 us to look there.
+    auto watch = [&] {
+        const auto began = std::chrono::steady_clock::now();
+        for (int spin = 1; !*done; ++spin) {
+            __builtin_ia32_pause();
+            if (spin % 256 == 0 && std::chrono::steady_clock::now() - began > std::chrono::microseconds(500)) break;
+        }
+        if (!*done && hipStreamSynchronize(s) != hipSuccess) return false;
+        std::atomic_thread_fence(std::memory_order_acquire);
+        return true;
+    };
     // (without pinned memory there is no result to look for while the stream is busy: the stepped form)
     const int form = h->search;
+    if (!asym && h->variant == 0 && rq::gbs_grid_supports(h, a, (double)eps)) {
+        const bool look = mem.out && form != kSearchStepped;
+        note(h, !in_registers ? "grid_search" : look ? "gbs_resident" : "gbs_stepped");
+        rc = rq::gbs_grid(h, a, mem.state, mem.out_dev, (double)eps, max_evals, s);
+        if (rc == RQ_OK && look && !watch()) rc = RQ_ERR_HIP;
+        if (rc == RQ_OK && look && *done) return finish(RQ_OK, mem.out);
+        return collect(rc);
+    }
     if (const ResidentTurn turn{h->device, in_registers && mem.out && form != kSearchStepped}) {
         if (turn->epoch + kSteps > kStepNumbers) {           // the numbers start again
             turn->epoch = 1;
@@ -692,14 +722,7 @@ static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t ro
         turn->epoch += kSteps;
         turn->turn ^= 1;
         if (rc != RQ_OK) return finish(rc, nullptr);
-        // The result arrives in host memory before the runtime reports the stream done: worth about 5 us to look there.
-        const auto began = std::chrono::steady_clock::now();
-        for (int spin = 1; !*done; ++spin) {
-            __builtin_ia32_pause();
-            if (spin % 256 == 0 && std::chrono::steady_clock::now() - began > std::chrono::microseconds(500)) break;
-        }
-        if (!*done && hipStreamSynchronize(s) != hipSuccess) return finish(RQ_ERR_HIP, nullptr);
-        std::atomic_thread_fence(std::memory_order_acquire);
+        if (!watch()) return finish(RQ_ERR_HIP, nullptr);
         if (*done) {
             turn->unclear &= ~(1 << b);
             note(h, "gbs_resident");
@@ -707,17 +730,6 @@ static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t ro
         }
         // other work kept part of the search from running: the stepped form needs no two workgroups at one time
     }
-    // after the last launch: the results, copied back where they are in device memory
-    auto collect = [&](int code) {
-        rq::GbsOut copied;
-        const rq::GbsOut* result = mem.out;
-        if (code == RQ_OK && !mem.out) {
-            result = &copied;
-            if (hipMemcpyAsync(&copied, mem.out_dev, sizeof copied, hipMemcpyDeviceToHost, s) != hipSuccess) code = RQ_ERR_HIP;
-        }
-        if (hipStreamSynchronize(s) != hipSuccess && code == RQ_OK) code = RQ_ERR_HIP;
-        return finish(code == RQ_OK && !result->done ? RQ_ERR_HIP : code, result);
-    };
     if (in_registers) {
         note(h, "gbs_stepped");
         return collect(rq::gbs_stepped(h, a, mem.state, mem.out_dev, partial, (double)eps, max_evals, steps, s));

@@ -244,6 +244,7 @@ const ClipList* gbs_state_clips(const GbsDev* state);
 void gbs_first_batch(double eps, int depth, int bits, ClipList* out);
 // The whole search in one launch, for rows the chip holds in registers all at once; false where it does not.  (`wait`
 // false: a workgroup that finds another's sums missing gives the search up at once, for tests.)
+bool gbs_in_registers(const rq_hadamard* h, const RowArgs& a);
 bool gbs_resident_supports(const rq_hadamard* h, const RowArgs& a);
 size_t gbs_exchange_bytes();
 int gbs_resident(const rq_hadamard* h, const RowArgs& a, GbsOut* out, uint64_t* exchange, uint32_t epoch, double eps, int max_evals,
@@ -251,6 +252,10 @@ int gbs_resident(const rq_hadamard* h, const RowArgs& a, GbsOut* out, uint64_t* 
 // The same steps, a launch each, for searches of up to `steps` steps after the starting point; `sums` is the workspace.
 int gbs_stepped(const rq_hadamard* h, const RowArgs& a, GbsDev* state, GbsOut* out, double* sums, double eps, int max_evals, int steps,
                 hipStream_t s);
+// The grid form: any number of those rows or of the workgroup block kernel's, brackets down to 1 / 256; rows of the latter.
+bool gbs_grid_supports(const rq_hadamard* h, const RowArgs& a, double eps);
+int gbs_grid(const rq_hadamard* h, const RowArgs& a, GbsDev* dev, GbsOut* out, double eps, int max_evals, hipStream_t s);
+int wg_grid_rows(const rq_hadamard* h, const RowArgs& a, GbsDev* dev, int* groups, hipStream_t s);
 int gbs_step(GbsDev* state, GbsOut* out, bool first, double eps, int depth, int max_evals, int bits, const double* partial,
              int64_t rows, int64_t count, int64_t stride, hipStream_t s);
 

@@ -154,5 +154,46 @@ __device__ __forceinline__ float block_rotate_row(const WaveArgs& a, int64_t row
     return wave_absmax<4>(m);
 }
 
+// A Sylvester row of 512 T values over W waves, T / W register sets each.
+template <int T, int W_, bool F16>
+struct SylvesterRows {
+    static constexpr int W = W_, NVAL = T / W * 8;
+    static __device__ __forceinline__ float rotate(const WaveArgs& a, int, int64_t row, int seg, int lane, float (&v)[NVAL], float* flip) {
+        const int g = lane >> 4, cphys = lane & 15, c = (cphys & 4) ? (cphys ^ 3) : cphys;
+        const u32x4 A0 = a.tiles[lane], A1 = a.tiles[64 + lane];
+        f32x4 acc[T / W][2];
+        const float m = split_rotate_row<T, false, W, F16>(a, row, seg, c, (g << 4) + c, A0, A1, acc);
+#pragma unroll
+        for (int t = 0; t < T / W; ++t)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[(t * 2 + h) * 4 + i] = acc[t][h][i];
+        *flip = split_flip<T, W>(c);
+        return wave_absmax<4>(m);
+    }
+};
+// A row of a block order, pb <= 32: W waves with 16 output block rows each.
+template <int W_, bool F16>
+struct BlockRows {
+    static constexpr int W = W_, NVAL = 32;
+    static __device__ __forceinline__ float rotate(const WaveArgs& a, int pb, int64_t row, int seg, int lane, float (&v)[NVAL], float* flip) {
+        const int g = lane >> 4, cphys = lane & 15, c = (cphys & 4) ? (cphys ^ 3) : cphys;
+        const u32x4 A = a.tiles[seg * 64 + lane];
+        float sf[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) sf[b] = ((c >> b) & 1) ? -1.0f : 1.0f;
+        const int base_g = 8 * g < pb - 8 ? 8 * g : pb - 8;
+        float y[8][4];
+        const float m = block_rotate_row<false, 4, F16>(a, row, base_g * 128 + c * 8, A, A, sf, y);
+#pragma unroll
+        for (int ic = 0; ic < 8; ++ic)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[ic * 4 + j] = y[ic][j];
+        *flip = (__builtin_popcount(c) & 1) ? -1.0f : 1.0f;
+        return m;
+    }
+};
+
 }  // namespace
 }  // namespace rq

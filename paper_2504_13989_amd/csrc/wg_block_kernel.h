@@ -29,6 +29,7 @@
 // and the output rows are per row of the pass.  Here the block is H_p itself, of any order
 // 4 <= p <= 256.
 #pragma once
+#include "error_grid.h"
 #include "wave_common.h"
 
 namespace rq {
@@ -64,8 +65,9 @@ constexpr int wg_waves_per_simd(bool wide = false) { return !wide && (KK <= 3 ||
 // What the kernel does with the rotated row (phase 4), and the arguments that takes beyond WaveArgs:
 //   kWgQuantize  codes and scale of rq_rotate_quantize;
 //   kWgError     squared quantization error per clip ratio (rq_quant_error);
-//   kWgRotate    the values themselves (rq_rotate; rq_dequantize_rotate, whose rows come from packed codes).
-enum WgSink { kWgQuantize, kWgError, kWgRotate };
+//   kWgRotate    the values themselves (rq_rotate; rq_dequantize_rotate, whose rows come from packed codes);
+//   kWgGrid      squared quantization error at every clip ratio of a search's grid (error_grid.h), summed over the rows.
+enum WgSink { kWgQuantize, kWgError, kWgRotate, kWgGrid };
 struct WgNone {};
 struct QeArgs {
     ClipArg clips;
@@ -79,8 +81,13 @@ struct WgRotArgs {
     double inv;           // 1 / sqrt(n)
     int out;              // 0 bf16, 1 fp32, 2 fp16
 };
+struct WgGridArgs {
+    double inv_norm;      // 1 / n^2
+    GbsDev* dev;
+};
 template <int SINK>
-using WgArgs = std::conditional_t<SINK == kWgError, QeArgs, std::conditional_t<SINK == kWgRotate, WgRotArgs, WgNone>>;
+using WgArgs = std::conditional_t<SINK == kWgError, QeArgs, std::conditional_t<SINK == kWgRotate, WgRotArgs,
+                                  std::conditional_t<SINK == kWgGrid, WgGridArgs, WgNone>>>;
 
 // DPP row, 8-column chunk and row of the pass of a lane, as values the compiler does not keep across the phases.
 template <int CB>
@@ -107,14 +114,14 @@ __device__ __forceinline__ float wg_flip(int cl) {
 // bf16 1.659369867e-3 against 64 bits, 1.659369866e-3 on the general kernel with its fp64 block sums; fp16 2.0731412e-4 and
 // 2.0731411e-4), and fp64 stages cost 3584 x 18944 to bf16 51 -> 81 us.
 template <int KK, int BITS, bool FULL, int SINK, int CB = 4, bool F16 = false, int SRC = 0, bool WIDE = false>
-__global__ __launch_bounds__(128 * KK) __attribute__((amdgpu_waves_per_eu(wg_waves_per_simd<KK>(WIDE))))
+__global__ __launch_bounds__(128 * KK) __attribute__((amdgpu_waves_per_eu(wg_waves_per_simd<KK>(WIDE || SINK == kWgGrid))))
 void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
     static_assert(CB >= 2 && CB <= 4 && (CB == 4 || !FULL), "unsupported shape");
     static_assert(SRC == 0 || (SINK == kWgRotate && F16 && !FULL), "packed codes: rotation only, fp16 operands");
     constexpr bool QE = SINK == kWgError;
     constexpr int RPW = 16 >> CB;                        // rows of X per pass
     constexpr int SEG = 8 << CB;                         // columns of one block row (2^k)
-    constexpr bool PF = !WIDE && wg_waves_per_simd<KK>() == 4;   // loads run one pass ahead
+    constexpr bool PF = !WIDE && SINK != kWgGrid && wg_waves_per_simd<KK>() == 4;   // loads run one pass ahead
     __shared__ float esum[QE ? 16 : 1][QE ? RPW : 1][QE ? RQ_MAX_CLIPS : 1];   // [wave][row of the pass][clip]
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
     uint8_t* const ops = lds_raw;                        // [column tile][contraction step] x 1 KB, see wg_ops_bytes
@@ -205,6 +212,15 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
             }
         }
     };
+    using Grid = ErrorGrid<BITS>;
+    constexpr int SUMS = SINK == kWgGrid ? (kGridRatios - 1 + 64 * (2 * KK - 1) - 1) / (64 * (2 * KK - 1)) : 1;   // ratios of a thread
+    [[maybe_unused]] double sum[SUMS];
+    __shared__ uint64_t tot[SINK == kWgGrid ? 3 : 1][16];
+    if constexpr (SINK == kWgGrid) {
+#pragma unroll
+        for (int k = 0; k < SUMS; ++k) sum[k] = 0.0;
+        if (blockIdx.x == 0 && threadIdx.x == 0) sa.dev->grid_ticket = 0;
+    }
     const int64_t n_pass = (a.rows + RPW - 1) / RPW;
     // CB == 4: one row per pass, uniform over the workgroup; otherwise the lane's own row, the
     // last row standing in (loads only) for rows beyond the end
@@ -418,6 +434,41 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
             }
         }
         // ---- phase 4
+        if constexpr (SINK == kWgGrid) {
+            // one histogram: the rows of a pass one after the other
+            uint64_t* const hist = reinterpret_cast<uint64_t*>(stage);
+            const int NT = (int)blockDim.x, t = (int)threadIdx.x;
+            for (int rs = 0; rs < RPW && pass * RPW + rs < a.rows; ++rs) {
+                for (int i = t; i < Grid::WORDS / 2; i += NT) reinterpret_cast<u32x4*>(hist)[i] = u32x4{0u, 0u, 0u, 0u};
+                float mr = m;
+                if constexpr (RPW > 1) {
+                    mr = 0.0f;
+                    for (int w = 0; w < nw; ++w) mr = __builtin_fmaxf(mr, wmax[rs * 16 + w]);
+                }
+                const typename Grid::Scale sc = Grid::scale(mr, sa.inv_norm);
+                __syncthreads();
+                double q2 = 0.0;
+                float fl = flip;
+                asm volatile("" : "+v"(fl));             // (or the signed values are kept from row to row)
+                if (RPW == 1 || rsub == rs) {
+                    // (a row with an infinity or a NaN has one in every value, or its maximum is infinite: its error is NaN)
+                    if (!(__builtin_fabsf(acc[0][0]) < __builtin_inff()) || !(mr < __builtin_inff())) q2 = __builtin_nan("");
+#pragma unroll
+                    for (int nt = 0; nt < 8; ++nt)
+#pragma unroll
+                        for (int ip = 0; ip < 4; ++ip) Grid::add(hist, acc[nt][ip] * fl, sc.s, q2);
+                }
+                __syncthreads();
+                q2 = Grid::finish(hist, q2, t, NT, tot);
+#pragma unroll
+                for (int k = 0; k < SUMS; ++k) {
+                    const int c1 = 1 + t + k * NT;
+                    if (c1 < kGridRatios) sum[k] += Grid::error(hist, c1, q2, sc);
+                }
+                __syncthreads();
+            }
+            continue;
+        }
         if constexpr (QE) {
             const ClipView clips = clip_view(sa.clips);
             const int per = (clips.n + (int)gridDim.y - 1) / (int)gridDim.y, k0 = (int)blockIdx.y * per, k1 = k0 + per < clips.n ? k0 + per : clips.n;
@@ -509,6 +560,13 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
                                             reinterpret_cast<u32x4*>(out) + unit);
         }
         if (wave == 0 && gq == 0 && cq == 0 && live) a.scales[row] = (float)(a.c2 * (double)m);
+        }
+    }
+    if constexpr (SINK == kWgGrid) {
+#pragma unroll
+        for (int k = 0; k < SUMS; ++k) {
+            const int c1 = 1 + (int)threadIdx.x + k * (int)blockDim.x;
+            if (c1 < kGridRatios) sa.dev->grid_sums[blockIdx.x][c1] = sum[k];
         }
     }
 }

@@ -1,0 +1,94 @@
+"""GPU: the grid form of the clip search (every probe down to a bracket of 1 / 256 evaluated at once, from a histogram of each
+row): its values against quant_error's and its steps against Algorithm 1 run on them, on every rotation it has; the ends of
+its range; rows that are not finite, zero or tiny.  And the resident form's step numbers, which searches down to 1 / 256
+no longer reach."""
+import numpy as np
+import pytest
+
+import parity
+import rotq_oracle as oracle
+from paper_2504_13989_amd import binding, workloads as wl
+
+pytestmark = pytest.mark.gpu
+GRID = ("gbs_resident", "gbs_stepped", "grid_search")
+
+
+def _check(h, x, b, eps, result):
+    clip, mse, trace = result
+    seen = dict(trace)
+    m, fm, otrace = oracle.gbs_search(lambda c: seen[np.float32(c)], eps)
+    assert [np.float32(c) for c, _ in otrace] == [np.float32(c) for c, _ in trace]
+    assert clip == np.float32(m) and mse == fm
+    # both are sums of fp32 squares or better: a few 1e-7 apart
+    want = binding.quant_error(h, x, b, [c for c, _ in trace]).cpu().numpy()
+    assert np.allclose([v for _, v in trace], want, rtol=2e-6, atol=0.0)
+
+
+# one wave a row, two, four, blocks of one and two waves; the workgroup block kernel's block rows of 128, 64 and 32 columns,
+# one wave to sixteen; padded rows; one row, one more than the compute units, one more than two of each
+@pytest.mark.parametrize("n,d,rows", [(1024, 1000, 257), (2048, 2048, 513), (4096, 4096, 1), (8192, 8192, 300), (1536, 1536, 70),
+                                      (3584, 3584, 513), (3072, 3000, 31), (5120, 5120, 258), (18944, 18944, 3), (28672, 28672, 2),
+                                      (8960, 8960, 515), (4864, 4864, 5), (896, 896, 1023), (896, 896, 1), (11264, 11008, 40),
+                                      (384, 384, 9), (32768, 32768, 1)])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_grid_search_takes_the_steps_of_algorithm_1(n, d, rows, dtype):
+    rng = np.random.default_rng(n + rows)
+    xf = rng.standard_normal((rows, d)).astype(np.float32)
+    xf[rows // 2] *= 20.0
+    x = parity.to_device(wl.f32_to_bf16_bits(xf) if dtype == "bf16" else xf.astype(np.float16))
+    h = binding.hadamard_build(n)
+    for b in (3, 4):
+        for eps in (1.0 / 256, 1.0 / 100):
+            got = binding.gbs_search(h, x, b, eps)
+            assert h.last_kernel in GRID
+            _check(h, x, b, float(np.float32(eps)), got)
+            assert binding.gbs_search(h, x, b, eps) == got
+        short = binding.gbs_search(h, x, b, 1.0 / 256, max_evals=3)
+        assert short[2] == binding.gbs_search(h, x, b, 1.0 / 256)[2][:3]
+
+
+def test_ends_of_the_grids_range():
+    rng = np.random.default_rng(3)
+    x = parity.to_device(wl.f32_to_bf16_bits(rng.standard_normal((300, 5120)).astype(np.float32)))
+    h = binding.hadamard_build(5120)
+    for eps, grid in ((1.0 / 256, True), (np.nextafter(np.float32(1.0 / 256), np.float32(0)), False), (0.9, True), (2.0, True), (1e-6, False)):
+        got = binding.gbs_search(h, x, 3, float(eps))
+        assert (h.last_kernel == "grid_search") == grid
+        _check(h, x, 3, float(eps), got)
+
+
+@pytest.mark.parametrize("n", [4096, 1536, 5120, 896])
+def test_rows_that_are_not_finite_zero_or_tiny(n):
+    rng = np.random.default_rng(n)
+    xf = rng.standard_normal((9, n)).astype(np.float32)
+    h = binding.hadamard_build(n)
+    base = xf.copy()
+    for what in ("zero", "tiny", "inf", "nan"):
+        xf = base.copy()
+        xf[4] = {"zero": 0.0, "tiny": xf[4] * np.float32(1e-36), "inf": xf[4], "nan": xf[4]}[what]
+        if what in ("inf", "nan"):
+            xf[4, 7] = np.inf if what == "inf" else np.nan
+        x = parity.to_device(wl.f32_to_bf16_bits(xf))
+        clip, mse, trace = got = binding.gbs_search(h, x, 4, 1.0 / 256)
+        assert h.last_kernel in GRID
+        if what in ("zero", "tiny"):
+            _check(h, x, 4, 1.0 / 256, got)
+        else:
+            want = binding.quant_error(h, x, 4, [c for c, _ in trace]).cpu().numpy()
+            assert np.isnan(mse) and all(np.isnan(v) for _, v in trace) and np.isnan(want).all() and clip == 0.5
+
+
+def test_step_numbers_of_the_resident_form_that_wrap():
+    """255 searches use the numbers up; two streams in turn, so that nothing but the exchange buffers orders the searches"""
+    import torch
+    rng = np.random.default_rng(10)
+    xs = [parity.to_device(wl.f32_to_bf16_bits(rng.standard_normal((r, 4096)).astype(np.float32))) for r in (900, 33)]
+    h = binding.hadamard_build(4096)
+    want = [binding.gbs_search(h, x, 3, 1.0 / 300) for x in xs]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    resident = 0
+    for i in range(600):
+        assert binding.gbs_search(h, xs[i % 2], 3, 1.0 / 300, stream=streams[i % 3 % 2]) == want[i % 2], i
+        resident += h.last_kernel == "gbs_resident"
+    assert resident > 540
