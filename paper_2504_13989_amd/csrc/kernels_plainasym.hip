@@ -13,67 +13,82 @@
 namespace rq {
 namespace {
 
-// DT: 0 bf16, 1 fp32, 2 fp16.  ALIGNED: 16-byte loads (X 16-byte aligned, ld a multiple of 8 / 4).
+// Eight values as they are stored.  DT: 0 bf16, 1 fp32, 2 fp16.  ALIGNED: 16-byte loads (X 16-byte aligned, ld a multiple of
+// 8 / 4).
+template <int DT>
+struct Raw8 { uint32_t w[DT == 1 ? 8 : 4]; };
 template <int DT, bool ALIGNED>
-__device__ __forceinline__ void load8(const void* X, int64_t idx, float (&x)[8]) {
-    if constexpr (DT == 1) {
-        const float* p = static_cast<const float*>(X) + idx;
-        if constexpr (ALIGNED) {
-            const u32x4 a = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
-            const u32x4 b = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p) + 1);
+__device__ __forceinline__ Raw8<DT> load_raw8(const void* X, int64_t idx) {
+    Raw8<DT> r;
+    if constexpr (ALIGNED) {
+        const u32x4* p = reinterpret_cast<const u32x4*>(static_cast<const char*>(X) + idx * (DT == 1 ? 4 : 2));
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                x[i] = __uint_as_float(a[i]);
-                x[4 + i] = __uint_as_float(b[i]);
-            }
-        } else {
+        for (int h = 0; h < (DT == 1 ? 2 : 1); ++h) {
+            const u32x4 a = __builtin_nontemporal_load(p + h);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) x[i] = p[i];
+            for (int i = 0; i < 4; ++i) r.w[4 * h + i] = a[i];
         }
+    } else if constexpr (DT == 1) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) r.w[i] = static_cast<const uint32_t*>(X)[idx + i];
     } else {
         const uint16_t* p = static_cast<const uint16_t*>(X) + idx;
-        uint32_t w[4];
-        if constexpr (ALIGNED) {
-            const u32x4 a = load16(p);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) w[i] = a[i];
-        } else {
+        for (int i = 0; i < 4; ++i) r.w[i] = (uint32_t)p[2 * i] | ((uint32_t)p[2 * i + 1] << 16);
+    }
+    return r;
+}
+template <int DT>
+__device__ __forceinline__ void to_float8(const Raw8<DT>& r, float (&x)[8]) {
+    if constexpr (DT == 1) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) w[i] = (uint32_t)p[2 * i] | ((uint32_t)p[2 * i + 1] << 16);
-        }
+        for (int i = 0; i < 8; ++i) x[i] = __uint_as_float(r.w[i]);
+    } else {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if constexpr (DT == 2) {
-                x[2 * i] = (float)__builtin_bit_cast(_Float16, (uint16_t)w[i]);
-                x[2 * i + 1] = (float)__builtin_bit_cast(_Float16, (uint16_t)(w[i] >> 16));
+                x[2 * i] = (float)__builtin_bit_cast(_Float16, (uint16_t)r.w[i]);
+                x[2 * i + 1] = (float)__builtin_bit_cast(_Float16, (uint16_t)(r.w[i] >> 16));
             } else {
-                x[2 * i] = __uint_as_float(w[i] << 16);
-                x[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+                x[2 * i] = __uint_as_float(r.w[i] << 16);
+                x[2 * i + 1] = __uint_as_float(r.w[i] & 0xffff0000u);
             }
         }
     }
 }
 
-// Minimum of mn and maximum of mx over the 16 lanes of a DPP row, every lane ending with both: four
-// butterfly steps, each one instruction with a DPP operand (assembly: the compiler does not fold a DPP
-// operand into a float min / max, and first passes each operand through a canonicalizing max).  The
-// s_nop keep two wait states between a vector write of a register and a DPP read of it.
-__device__ __forceinline__ void row_min_max(float& mn, float& mx) {
+// Minima and maxima of four passes over the 16 lanes of a DPP row: lane c of the row ends with those of pass c mod 4.  The first
+// two steps merge passes two and two while they cross the lane bits that name them.  (Assembly: the compiler does not fold a
+// DPP operand into a float min / max, and first passes each operand through a canonicalizing max.  The s_nop keep two wait
+// states between a vector write of a register and a DPP read of it.)
+__device__ __forceinline__ void row_min_max4(const float (&mn)[4], const float (&mx)[4], int lane, float& lo, float& hi) {
+    const bool b0 = lane & 1, b1 = lane & 2;
+    float n0 = b0 ? mn[1] : mn[0], n1 = b0 ? mn[3] : mn[2], x0 = b0 ? mx[1] : mx[0], x1 = b0 ? mx[3] : mx[2];
     asm("s_nop 1\n\t"
-        "v_min_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-        "v_max_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_min_f32_dpp %0, %4, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_min_f32_dpp %1, %5, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %2, %6, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %3, %7, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+        : "+v"(n0), "+v"(n1), "+v"(x0), "+v"(x1)
+        : "v"(b0 ? mn[0] : mn[1]), "v"(b0 ? mn[2] : mn[3]), "v"(b0 ? mx[0] : mx[1]), "v"(b0 ? mx[2] : mx[3]));
+    lo = b1 ? n1 : n0;
+    hi = b1 ? x1 : x0;
+    asm("s_nop 1\n\t"
+        "v_min_f32_dpp %0, %2, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %3, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
         "s_nop 0\n\t"
-        "v_min_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-        "v_max_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_min_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-        "v_max_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_min_f32_dpp %0, %0, %0 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
         "s_nop 0\n\t"
         "v_min_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
         "v_max_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
         "s_nop 1"
-        : "+v"(mn), "+v"(mx));
+        : "+v"(lo), "+v"(hi)
+        : "v"(b1 ? n0 : n1), "v"(b1 ? x0 : x1));
 }
+// Lane u of each quad to all four.
+template <int U>
+__device__ __forceinline__ float quad_lane(float x) { return __uint_as_float(dpp_u<0x55 * U>(__float_as_uint(x))); }
 
 // max |y_k| of eight floats as three-operand instructions with magnitude operands
 __device__ __forceinline__ float absmax8(const float (&y)[8]) {
@@ -87,9 +102,15 @@ __device__ __forceinline__ float absmax8(const float (&y)[8]) {
     return m;
 }
 
-template <int BITS, int DT, bool ALIGNED, int U>
+// Bound: vector issue.  A wave takes four passes of four groups; extremes, multiplier, centre, tie window and results of its
+// sixteen groups are worked out once, lane c of a DPP row for pass c mod 4, and go back to the lanes of a pass with one quad
+// permutation each; sixteen groups that lie one behind the other (ld = d) are read from one address.  bf16, b = 3, before (all of
+// it once a pass and by every lane, a 64-bit address for each load) -> now: 262 016 groups 18.8 -> 16.9 us, 1 048 576 63.3 ->
+// 55.7 (5.2 -> 5.9 TB/s); b = 4, 2 097 152 groups 125 -> 110.
+template <int BITS, int DT, bool ALIGNED>
 __global__ __launch_bounds__(64) void k_plain_asym(const void* X, int64_t n_groups, int gpr, int gpr_shift, uint32_t gpr_magic, int64_t ld, double clip,
                                                    uint32_t* codes, float* scales, float* mins) {
+    constexpr int U = 4;
     constexpr double kL = (double)((1 << BITS) - 1);
     constexpr double kMid = (double)(1 << (BITS - 1)) / kL;     // centre of the code range
     const int lane = threadIdx.x;
@@ -98,74 +119,108 @@ __global__ __launch_bounds__(64) void k_plain_asym(const void* X, int64_t n_grou
     const float c1f = (float)(kL / clip), clipf = (float)clip;
     // a wave takes U passes of four groups per iteration, all loads issued before the first is used
     for (int64_t g0 = (int64_t)blockIdx.x * (4 * U); g0 < n_groups; g0 += (int64_t)gridDim.x * (4 * U)) {
-        float x[U][8];
-        // uniform over the wave, so scalar work - but a 64-bit scalar division is a hundred instructions:
-        // a shift where gpr is a power of two (the usual widths), else a 32-bit division if that will do
-        int64_t row0;
-        if (gpr_shift >= 0) row0 = g0 >> gpr_shift;
-        else if (n_groups <= 0xffffffffll) row0 = (uint32_t)g0 / (uint32_t)gpr;
-        else row0 = g0 / gpr;
-        const uint32_t rem0 = (uint32_t)(g0 - row0 * gpr);
-        // outputs of the iteration: a base in scalar registers plus per-lane offsets; lane c of a group
-        // keeps the parameters of pass c, so that the iteration's U * 4 scales and minima leave in one store each
+        Raw8<DT> raw[U];
+        const int left = n_groups - g0 < 4 * U ? (int)(n_groups - g0) : 4 * U;
+        if (left == 4 * U && ld == (int64_t)gpr * 128) {
+            // sixteen consecutive groups: one base, one lane offset
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                raw[u] = load_raw8<DT, ALIGNED>(static_cast<const char*>(X) + g0 * (128 * (DT == 1 ? 4 : 2)), u * 512 + lane * 8);
+        } else {
+            // uniform over the wave, so scalar work - but a 64-bit scalar division is a hundred instructions:
+            // a shift where gpr is a power of two (the usual widths), else a 32-bit division if that will do
+            int64_t row0;
+            if (gpr_shift >= 0) row0 = g0 >> gpr_shift;
+            else if (n_groups <= 0xffffffffll) row0 = (uint32_t)g0 / (uint32_t)gpr;
+            else row0 = g0 / gpr;
+            const uint32_t rem0 = (uint32_t)(g0 - row0 * gpr);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int gi = u * 4 + g;
+                // (row, group of the row) from the iteration's uniform split plus a small offset, whose
+                // quotient by gpr is a multiply-high with ceil(2^32 / gpr): exact while offset * gpr < 2^32
+                const uint32_t off = rem0 + (uint32_t)(gi < left ? gi : left - 1);
+                const uint32_t k = gpr == 1 ? off : __umulhi(off, gpr_magic);
+                const int64_t row = row0 + k;
+                const uint32_t gc = off - k * (uint32_t)gpr;
+                raw[u] = load_raw8<DT, ALIGNED>(X, row * ld + (int64_t)gc * 128 + c * 8);
+            }
+        }
+        // outputs of the iteration: a base in scalar registers plus per-lane offsets
         uint32_t* const cbase = codes + g0 * (4 * BITS);
         const uint32_t code_off = (uint32_t)(g * (4 * BITS) + (BITS == 4 ? c : (c >> 2) * 3 + (c & 3))) * 4u;
         uint32_t* const out0 = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(cbase) + code_off);
-        float keep_d = 0.0f, keep_m = 0.0f;
+        float x[U][8], mn, mx;
+        {
+            float n[U], m[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t gi = g0 + u * 4 + g;
-            const int64_t gl = gi < n_groups ? gi : n_groups - 1;
-            // (row, group of the row) from the iteration's uniform split plus a small offset, whose
-            // quotient by gpr is a multiply-high with ceil(2^32 / gpr): exact while offset * gpr < 2^32
-            const uint32_t off = rem0 + (uint32_t)(gl - g0);
-            const uint32_t k = gpr == 1 ? off : __umulhi(off, gpr_magic);
-            const int64_t row = row0 + k;
-            const uint32_t gc = off - k * (uint32_t)gpr;
-            load8<DT, ALIGNED>(X, row * ld + (int64_t)gc * 128 + c * 8, x[u]);
+            for (int u = 0; u < U; ++u) {
+                to_float8<DT>(raw[u], x[u]);
+                n[u] = min8(x[u]);
+                m[u] = max8(x[u]);
+            }
+            row_min_max4(n, m, lane, mn, mx);
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t gi = g0 + u * 4 + g;
-            const bool live = gi < n_groups;
-            float mn = min8(x[u]), mx = max8(x[u]);
-            row_min_max(mn, mx);
-            // Group parameters in fp32.  What they cost the pre-round value t in accuracy: the range r
-            // and the multiplier s (reciprocal plus one Newton step) about 3e-7 relative, |t - mid| <= 8;
-            // the centre about 2.5 ulp, which in units of t is 3e-7 |cen| s - small for a group that
-            // straddles zero, unbounded for a narrow group far from it.  Both go into the tie window, so
-            // a group whose offset swamps its range is simply taken in fp64 throughout.
-            const float r = mx - mn;
-            const bool flat = !(r > 0.0f);
-            float q = __builtin_amdgcn_rcpf(r);
-            q = fmaf(fmaf(-r, q, 1.0f), q, q);
-            const float s = flat ? 0.0f : c1f * q;
-            const float cen = clipf * fmaf(r, kMidF, mn);
-            // (a range whose reciprocal is subnormal - the reciprocal instruction returns zero for it -
-            // or so small that s overflows leaves no window at all)
-            const float thr = (r < 4e37f && s < 1e30f) ? fmaf(-3e-7f * __builtin_fabsf(cen), s, 0.49998f) : -1.0f;
-            const float bias = flat ? Quant<BITS>::kMagic : Quant<BITS>::kBias;
+        // Group parameters in fp32.  What they cost the pre-round value t in accuracy: the range r
+        // and the multiplier s (reciprocal plus one Newton step) about 3e-7 relative, |t - mid| <= 8;
+        // the centre about 2.5 ulp, which in units of t is 3e-7 |cen| s - small for a group that
+        // straddles zero, unbounded for a narrow group far from it.  Both go into the tie window, so
+        // a group whose offset swamps its range is simply taken in fp64 throughout.
+        const float r = mx - mn;
+        const bool flat = !(r > 0.0f);
+        float q = __builtin_amdgcn_rcpf(r);
+        q = fmaf(fmaf(-r, q, 1.0f), q, q);
+        const float s4 = flat ? 0.0f : c1f * q;
+        const float cen4 = clipf * fmaf(r, kMidF, mn);
+        // (a range whose reciprocal is subnormal - the reciprocal instruction returns zero for it -
+        // or so small that s overflows leaves no window at all, nor does a flat group, which takes code 0)
+        const float thr4 = (r < 4e37f && s4 < 1e30f && !flat) ? fmaf(-3e-7f * __builtin_fabsf(cen4), s4, 0.49998f) : -1.0f;
+        {
+            float delta = clipf * r * (float)(1.0 / kL);            // each factor good to 6e-8
+            if (!(r < 3e38f)) {                                     // max - min beyond fp32
+                float mx_here = mx;
+                asm volatile("" : "+v"(mx_here));
+                delta = (float)((clip * (double)mx_here - clip * (double)mn) * (1.0 / kL));
+            }
+            const int gs = c * 4 + g;                               // lane c < U: group of pass c
+            if (c < U && gs < left) {
+                scales[g0 + gs] = delta;
+                mins[g0 + gs] = clipf * mn;
+            }
+        }
+        auto pass = [&](auto which) {
+            constexpr int u = decltype(which)::value;
+            const float s = quad_lane<u>(s4), cen = quad_lane<u>(cen4), thr = quad_lane<u>(thr4);
             float v[8], e[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const float dx = x[u][k] - cen;
-                v[k] = fmaf(dx, s, bias);
-                e[k] = fmaf(dx, s, bias - v[k]);                   // t - round(t)
+                v[k] = fmaf(dx, s, Quant<BITS>::kBias);
+                e[k] = fmaf(dx, s, Quant<BITS>::kBias - v[k]);     // t - round(t)
             }
             // near a rounding tie: the definition itself, in fp64 and with its two divisions (an exact tie
             // turns on their last bit), for that value only; one test per lane and pass guards the lot
-            const float emax = absmax8(e);
-            if (!(emax <= thr) && !flat) {
-                float mn_here = mn;
-                asm volatile("" : "+v"(mn_here));                  // keeps the fp64 work inside the branch
-                const double lo64 = clip * (double)mn_here, hi64 = clip * (double)mx;
-                const double delta64 = (hi64 - lo64) / kL;
+            const bool near = !(absmax8(e) <= thr);
+            if (__builtin_amdgcn_ballot_w64(near) != 0) {
+                // (the whole wave is here: the extremes come from other lanes)
+                float mn_here = quad_lane<u>(mn), mx_here = quad_lane<u>(mx);
+                asm volatile("" : "+v"(mn_here), "+v"(mx_here));   // keeps the fp64 work inside the branch
+                if (near) {
+                    if (!(mx_here - mn_here > 0.0f)) {
 #pragma unroll
-                for (int k = 0; k < 8; ++k)
-                    if (!(__builtin_fabsf(e[k]) <= thr))
-                        v[k] = Quant<BITS>::kMagic + (float)fmin(fmax(rint(((double)x[u][k] - lo64) / delta64), 0.0), kL);
+                        for (int k = 0; k < 8; ++k) v[k] = Quant<BITS>::kMagic;
+                    } else {
+                        const double lo64 = clip * (double)mn_here, hi64 = clip * (double)mx_here;
+                        const double delta64 = (hi64 - lo64) / kL;
+#pragma unroll
+                        for (int k = 0; k < 8; ++k)
+                            if (!(__builtin_fabsf(e[k]) <= thr))
+                                v[k] = Quant<BITS>::kMagic + (float)fmin(fmax(rint(((double)x[u][k] - lo64) / delta64), 0.0), kL);
+                    }
+                }
             }
             const uint32_t w = Quant<BITS>::join(v);
+            const bool live = u * 4 + g < left;
             if (BITS == 4) {
                 if (live) store_codes(out0 + u * (16 * BITS), w);
             } else {
@@ -173,20 +228,11 @@ __global__ __launch_bounds__(64) void k_plain_asym(const void* X, int64_t n_grou
                 const uint32_t dw = merge24<false>(w, qpos);
                 if (live && qpos < 3) store_codes(out0 + u * (16 * BITS), dw);
             }
-            float delta = clipf * r * (float)(1.0 / kL);            // each factor good to 6e-8
-            if (!(r < 3e38f)) {                                     // max - min beyond fp32
-                float mx_here = mx;
-                asm volatile("" : "+v"(mx_here));
-                delta = (float)((clip * (double)mx_here - clip * (double)mn) * (1.0 / kL));
-            }
-            keep_d = c == u ? delta : keep_d;
-            keep_m = c == u ? clipf * mn : keep_m;
-        }
-        const int64_t gs = g0 + c * 4 + g;                          // lane c < U: group of pass c
-        if (c < U && gs < n_groups) {
-            scales[gs] = keep_d;
-            mins[gs] = keep_m;
-        }
+        };
+        pass(std::integral_constant<int, 0>{});
+        pass(std::integral_constant<int, 1>{});
+        pass(std::integral_constant<int, 2>{});
+        pass(std::integral_constant<int, 3>{});
     }
 }
 
@@ -213,7 +259,7 @@ __global__ __launch_bounds__(64) void k_plain_short(const void* X, int64_t rows,
         for (int u = 0; u < U; ++u) {
             const int64_t row = r0 + u * RPP + sr;
             const int64_t rl = row < rows ? row : rows - 1;
-            if (has) load8<DT, true>(X, rl * ld + c * 8, x[u]);
+            if (has) to_float8<DT>(load_raw8<DT, true>(X, rl * ld + c * 8), x[u]);
             else
 #pragma unroll
                 for (int k = 0; k < 8; ++k) x[u][k] = 0.0f;
@@ -298,9 +344,9 @@ void launch_dt(bool aligned, int bits, unsigned grid, hipStream_t s, const void*
     const uint32_t gpr_magic = (uint32_t)((((uint64_t)1 << 32) + gpr - 1) / gpr);   // gpr >= 2 where it is used
     auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, X, n_groups, gpr, gpr_shift, gpr_magic, ld, clip, codes, scales, mins); };
     if (aligned) {
-        if (bits == 4) go(k_plain_asym<4, DT, true, 4>); else go(k_plain_asym<3, DT, true, 4>);
+        if (bits == 4) go(k_plain_asym<4, DT, true>); else go(k_plain_asym<3, DT, true>);
     } else {
-        if (bits == 4) go(k_plain_asym<4, DT, false, 4>); else go(k_plain_asym<3, DT, false, 4>);
+        if (bits == 4) go(k_plain_asym<4, DT, false>); else go(k_plain_asym<3, DT, false>);
     }
 }
 

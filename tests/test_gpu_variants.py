@@ -412,6 +412,27 @@ def test_plain_quantize_asym(torch, name, rows, b):
                                       f"plain asym {name} view b={b}", rotate=False)
 
 
+@pytest.mark.parametrize("groups", [1, 3])
+@pytest.mark.parametrize("rows", [1, 5, 16, 17, 48, 67])
+def test_plain_quantize_asym_sixteen_groups_a_wave(torch, rows, groups):
+    # a wave takes four passes of four groups, lane c of a group keeping the parameters of pass c mod 4: magnitudes and offsets
+    # of their own in every group, flat ones among them, counts around sixteen, rows one behind the other and rows with a gap
+    rng = np.random.default_rng(rows + groups)
+    d = 128 * groups
+    xf = rng.standard_normal((rows, groups, 128)) * 2.0 ** rng.integers(-9, 9, (rows, groups, 1)) + rng.standard_normal((rows, groups, 1))
+    xf.reshape(-1, 128)[::7] = 1.5
+    xf = xf.reshape(rows, d).astype(np.float32)
+    for x in (wl.f32_to_bf16_bits(xf), xf.astype(np.float16), xf):
+        wide = np.zeros((rows, d + 128), x.dtype)
+        wide[:, :d] = x
+        for b in (3, 4):
+            for xt in (parity.to_device(x), parity.to_device(wide)[:, :d]):
+                codes, scales, mins = binding.quantize_asym(xt, b, 0.9)
+                torch.cuda.synchronize()
+                parity.check_rotate_quantize_asym(x, d, b, 0.9, codes.cpu().numpy(), scales.cpu().numpy(), mins.cpu().numpy(),
+                                                  f"plain asym rows={rows} d={d} {x.dtype} b={b}", rotate=False)
+
+
 @pytest.mark.parametrize("b", [3, 4])
 def test_plain_quantize_asym_groups_far_from_zero(torch, b):
     # groups whose offset is large against their range: fp32 cannot place the centre of such a group
