@@ -154,13 +154,6 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
     uint8_t* const wr0 = ops + ((((wave >> 1) * 4 + 2 * (wave & 1) + (g >> 1)) * 16 + cphys) * 16 + (g & 1) * 8);
     const uint8_t* const rd0 = ops + lane * 16;
 
-    // Units for block rows at or beyond 16 nw are never written by phase 1 but are read by the last
-    // contraction step (against zero columns of B): clear the buffer once so they hold zeros.
-    for (int i = threadIdx.x; i < 8 * KK * 64; i += blockDim.x)
-        reinterpret_cast<u32x4*>(ops)[i] = u32x4{0u, 0u, 0u, 0u};
-    if (threadIdx.x < RPW * 16) wmax[threadIdx.x] = 0.0f;   // (a pass reads the slots of waves that do not exist, too)
-    __syncthreads();
-
     u32x4 R[4];
     [[maybe_unused]] float rscale = 1.0f;               // packed codes: the row's scale
     auto load_row = [&](int64_t row) {
@@ -229,7 +222,15 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
         const int64_t r = ps * RPW + rsub;
         load_row(CB == 4 || r < a.rows ? r : a.rows - 1);
     };
-    if (PF && (int64_t)blockIdx.x < n_pass) load_pass(blockIdx.x);
+    if constexpr (PF) load_pass(blockIdx.x);             // (the grid has no more workgroups than passes)
+    // Units for block rows at or beyond 16 nw (nw odd: the upper half of the last contraction step) are never written by
+    // phase 1 but are read, against zero columns of B: they hold zeros.  A pass reads the maxima of waves that do not exist, too.
+    // The barrier behind the first phase 1 orders both: with the whole buffer cleared and a barrier before the first loads, 500 rows
+    // of 8960 take 7.17 us and not 6.85, 300 of 18944 8.95 and not 8.76, 4096 of 8960 (b = 3) 30.0 and not 29.2.
+    if (nw & 1)
+        for (int i = threadIdx.x; i < 8 * 32; i += blockDim.x)
+            reinterpret_cast<u32x4*>(ops)[((i >> 5) * KK + KK - 1) * 64 + 32 + (i & 31)] = u32x4{0u, 0u, 0u, 0u};
+    if (threadIdx.x < RPW * 16) wmax[threadIdx.x] = 0.0f;
     for (int64_t pass = blockIdx.x; pass < n_pass; pass += gridDim.x) {
         if (!PF) load_pass(pass);
         if constexpr (SRC != 0) {
