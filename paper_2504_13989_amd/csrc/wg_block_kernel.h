@@ -122,6 +122,7 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
     constexpr int RPW = 16 >> CB;                        // rows of X per pass
     constexpr int SEG = 8 << CB;                         // columns of one block row (2^k)
     constexpr bool PF = !WIDE && SINK != kWgGrid && wg_waves_per_simd<KK>() == 4;   // loads run one pass ahead
+    constexpr bool EARLY = SINK == kWgQuantize && KK == 4;   // column stages start beside the block product, see phase 2
     __shared__ float esum[QE ? 16 : 1][QE ? RPW : 1][QE ? RQ_MAX_CLIPS : 1];   // [wave][row of the pass][clip]
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
     uint8_t* const ops = lds_raw;                        // [column tile][contraction step] x 1 KB, see wg_ops_bytes
@@ -266,18 +267,36 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
             // of DEPTH register quads; the contraction step is the outer loop, so that consecutive
             // instructions go to different accumulators and none waits for its predecessor's result.
             // (3 where the 80-register kernels have room for it, 2 in their padded-row and quant_error forms)
+            // EARLY: column tiles 0 - 3 go over all contraction steps first, then 4 - 7, and the first two column stages
+            // of tiles 0 - 3, the same additions as in phase 3, are issued between the matrix-core instructions of the others.
+            // Four accumulators in turn still hide an instruction's latency.  4096 rows, on two cards: 13824 wide,
+            // b = 3 37.0 -> 36.1 and 32.9 -> 32.5 us, 14336 wide, b = 4 38.0 -> 37.4 and 32.9 -> 32.6.  The forms of 80 registers spill on it (18944 wide, b = 4: 2 -> 7 registers, 4096
+            // rows 55.6 -> 57.9 us, 300 rows 8.2 -> 9.3; 4864 wide 27.0 -> 27.3), and one workgroup a compute unit
+            // (KK >= 6) gains nothing (28672 wide 65.3 and 65.5).
             constexpr int DEPTH = KK >= 6 ? 4 : (FULL && !QE) ? 3 : 2, ITEMS = 8 * KK;
-            auto read_item = [&](int i) {                // item i = (contraction step i / 8, column tile i % 8)
-                return *reinterpret_cast<const u32x4*>(rd0 + ((i % 8) * KK + i / 8) * 1024);
-            };
+            auto tile = [](int i) { return EARLY ? i / (4 * KK) * 4 + i % 4 : i % 8; };
+            auto step = [](int i) { return EARLY ? i % (4 * KK) / 4 : i / 8; };
+            auto read_item = [&](int i) { return *reinterpret_cast<const u32x4*>(rd0 + (tile(i) * KK + step(i)) * 1024); };
             u32x4 ring[DEPTH];
 #pragma unroll
             for (int i = 0; i < DEPTH; ++i) ring[i] = read_item(i);
 #pragma unroll
             for (int i = 0; i < ITEMS; ++i) {
                 __builtin_amdgcn_sched_barrier(0);
-                acc[i % 8] = mfma_pm1<F16>(A[i / 8], ring[i % DEPTH], acc[i % 8]);
+                acc[tile(i)] = mfma_pm1<F16>(A[step(i)], ring[i % DEPTH], acc[tile(i)]);
                 if (i + DEPTH < ITEMS) ring[i % DEPTH] = read_item(i + DEPTH);
+                if constexpr (EARLY) {
+                    // additions j of 16: the pairs (0, 1), (2, 3), (0, 2), (1, 3) of four registers each
+                    const int done = i - 4 * KK, of = 4 * KK - 1;
+#pragma unroll
+                    for (int j = 0; j < 16; ++j)
+                        if (done >= 1 && j >= 16 * (done - 1) / of && j < 16 * done / of) {
+                            constexpr int lo[4] = {0, 2, 0, 1}, hi[4] = {1, 3, 2, 3};
+                            const float u = acc[lo[j / 4]][j % 4], v = acc[hi[j / 4]][j % 4];
+                            acc[lo[j / 4]][j % 4] = u + v;
+                            acc[hi[j / 4]][j % 4] = u - v;
+                        }
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -334,7 +353,7 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
         for (int s = 1; s < 8; s <<= 1)
 #pragma unroll
             for (int nt = 0; nt < 8; ++nt)
-                if (!(nt & s)) {
+                if (!(nt & s) && !(EARLY && (nt | s) < 4)) {
                     const f32x4 u = acc[nt], v = acc[nt | s];
                     acc[nt] = u + v;
                     acc[nt | s] = u - v;
