@@ -374,9 +374,8 @@ int rq_gbs_search_asym(const rq_hadamard_t* h, const void* X, int dtype, int64_t
  * at any row count (automatic picks by the number of rows); 5 .. 7 are automatic but for
  * the searches: for tensors that fit the chip's registers 5 = a launch for every three steps ("gbs_stepped"),
  * 6 = one launch ("gbs_resident") whose workgroups do not wait for each other, so that it gives up and the
- * former takes over; 7 = no pinned memory (the former form again, for every tensor the results copied back).
- * Where all probes are evaluated at once (eps >= 1 / 256) 5 and 7 wait for the stream instead of looking for the result,
- * under the same two names.
+ * former takes over; 7 = no pinned memory (for every tensor the results copied back; the former form again where
+ * automatic takes the latter).
  * Errors: RQ_ERR_ARG.
  */
 int rq_hadamard_set_variant(rq_hadamard_t* h, int variant);

@@ -696,16 +696,17 @@ static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t ro
         std::atomic_thread_fence(std::memory_order_acquire);
         return true;
     };
-    // (without pinned memory there is no result to look for while the stream is busy: the stepped form)
     const int form = h->search;
-    if (!asym && h->variant == 0 && rq::gbs_grid_supports(h, a, (double)eps)) {
-        const bool look = mem.out && form != kSearchStepped;
-        note(h, !in_registers ? "grid_search" : look ? "gbs_resident" : "gbs_stepped");
+    // (a variant that names one of the forms below takes it)
+    const bool named = in_registers && (form == kSearchStepped || form == kSearchNoWait);
+    if (!asym && h->variant == 0 && !named && rq::gbs_grid_supports(h, a, (double)eps)) {
+        note(h, "grid_search");
         rc = rq::gbs_grid(h, a, mem.state, mem.out_dev, (double)eps, max_evals, s);
-        if (rc == RQ_OK && look && !watch()) rc = RQ_ERR_HIP;
-        if (rc == RQ_OK && look && *done) return finish(RQ_OK, mem.out);
+        if (rc == RQ_OK && done && !watch()) rc = RQ_ERR_HIP;
+        if (rc == RQ_OK && done && *done) return finish(RQ_OK, mem.out);
         return collect(rc);
     }
+    // (without pinned memory there is no result to look for while the stream is busy: the stepped form)
     if (const ResidentTurn turn{h->device, in_registers && mem.out && form != kSearchStepped}) {
         if (turn->epoch + kSteps > kStepNumbers) {           // the numbers start again
             turn->epoch = 1;

@@ -242,9 +242,10 @@ SearchMemory search_memory(int dev);
 const ClipList* gbs_state_clips(const GbsDev* state);
 // The first batch of a search, `depth` steps ahead: the starting point and every probe those steps can ask for.
 void gbs_first_batch(double eps, int depth, int bits, ClipList* out);
-// The whole search in one launch, for rows the chip holds in registers all at once; false where it does not.  (`wait`
-// false: a workgroup that finds another's sums missing gives the search up at once, for tests.)
+// Rows that a wave or a few hold in registers.
 bool gbs_in_registers(const rq_hadamard* h, const RowArgs& a);
+// The whole search in one launch, for tensors whose rows the chip holds that way all at once; false where it does not.  (`wait`
+// false: a workgroup that finds another's sums missing gives the search up at once, for tests.)
 bool gbs_resident_supports(const rq_hadamard* h, const RowArgs& a);
 size_t gbs_exchange_bytes();
 int gbs_resident(const rq_hadamard* h, const RowArgs& a, GbsOut* out, uint64_t* exchange, uint32_t epoch, double eps, int max_evals,
