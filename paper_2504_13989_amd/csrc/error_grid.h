@@ -28,7 +28,7 @@ template <int BITS>
 struct ErrorGrid {
     static constexpr int LEVELS = (1 << BITS) - 1, Q = (1 << (BITS - 1)) - 1, FRAC = BITS == 3 ? 15 : 14;
     static constexpr int LAST = 2 * Q + 1;                           // units a step of the last threshold
-    static constexpr int CELLS = (2 * Q - 1) * (kGridRatios - 1) + 1, WORDS = CELLS + kGridRatios;
+    static constexpr int CELLS = grid_cells(BITS), WORDS = grid_words(BITS);
     static constexpr size_t bytes() { return (size_t)WORDS * sizeof(uint64_t); }
     static constexpr float kTiny = 1e-30f;                           // rows below it: their squares are zero in fp32
 

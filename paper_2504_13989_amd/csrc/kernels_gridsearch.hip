@@ -169,18 +169,18 @@ int rows_pass(const rq_hadamard* h, const RowArgs& a, const WaveArgs& w, int* gr
 
 }  // namespace
 
-// Brackets down to 2 / kGridRatios, see above.  Short rows leave a pass of the grid form (two rows a compute unit, and on the
-// workgroup block kernel one, for a histogram's LDS) less to do than a quant_error pass over many rows: orders below 2048
-// take it up to 8192 rows (1024 wide, b = 4: 8192 rows 134 us against 146 in batches, 32768 about 480 against 344), those of
-// the workgroup block kernel up to one pass a compute unit (896 wide, b = 4: 1024 rows 58 against 70, 2048 rows 98
-// against 84).  Longer rows are faster at every number (2048 wide, 8192 rows 138 against 217; 18944 wide, 512 rows 42
-// against 165, 8192 rows 377 against 1453).
-bool gbs_grid_supports(const rq_hadamard* h, const RowArgs& a, double eps) {
+// Brackets down to 2 / kGridRatios, see above, where the search is long enough (search_rule.h).
+bool gbs_grid_supports(const rq_hadamard* h, const RowArgs& a, double eps, int steps) {
     if (eps < 2.0 / kGridRatios) return false;
-    if (gbs_in_registers(h, a)) return a.n >= 2048 || a.rows <= 8192;
-    int pb, cb;
-    if (wave_quant_error_supports(h, a) || !wg_block_supports(h, a, true) || !wg_shape(a, &pb, &cb)) return false;
-    return a.n >= 2048 || a.rows <= (int64_t)h->num_cu * (16 >> cb);
+    const int cus = h->num_cu < kGridGroups ? h->num_cu : kGridGroups;
+    GridCase c{a.rows, a.n, a.bits, cus, a.p == 1, gbs_row_waves(h, a), 0, 0};
+    if (c.waves == 0) {
+        int pb, cb;
+        if (wave_quant_error_supports(h, a) || !wg_block_supports(h, a, true) || !wg_shape(a, &pb, &cb)) return false;
+        c.rows_per_pass = 16 >> cb;
+        c.threads = 64 * ((pb + 15) / 16);
+    }
+    return gbs_grid_pays(c, steps);
 }
 
 int gbs_grid(const rq_hadamard* h, const RowArgs& a, GbsDev* dev, GbsOut* out, double eps, int max_evals, hipStream_t s) {
@@ -189,7 +189,7 @@ int gbs_grid(const rq_hadamard* h, const RowArgs& a, GbsDev* dev, GbsOut* out, d
                static_cast<const u32x4*>(f16 ? h->d_tiles_f16 : h->d_tiles), nullptr, nullptr, 0.0, 0.0};
     w.f16 = f16;
     int groups = 0;
-    const int rc = !gbs_in_registers(h, a) ? wg_grid_rows(h, a, dev, &groups, s) : a.bits == 4 ? (f16 ? rows_pass<4, true>(h, a, w, &groups, dev, s) : rows_pass<4, false>(h, a, w, &groups, dev, s))
+    const int rc = gbs_row_waves(h, a) == 0 ? wg_grid_rows(h, a, dev, &groups, s) : a.bits == 4 ? (f16 ? rows_pass<4, true>(h, a, w, &groups, dev, s) : rows_pass<4, false>(h, a, w, &groups, dev, s))
                                : (f16 ? rows_pass<3, true>(h, a, w, &groups, dev, s) : rows_pass<3, false>(h, a, w, &groups, dev, s));
     if (rc != RQ_OK) return rc;
     launch_kernel(k_grid_walk, dim3(kGridRatios / kWalkRatios), dim3(kWalkThreads), 0, s, dev, out, groups, a.rows, eps, max_evals);

@@ -1,5 +1,5 @@
 // The clip-ratio search of Algorithm 1 (section 4.1) on the device, in the three forms that serve what the grid form
-// (kernels_gridsearch.hip) does not: brackets below 1 / 256, other row formats and orders, many short rows.
+// (kernels_gridsearch.hip) does not: brackets below 1 / 256, other row formats and orders, searches of few steps, many short rows.
 //
 // Batches (any tensor): between the batches of objective values a search
 // needs (one quant_error pass each), a kernel of one workgroup averages the batch, walks the search with it and writes
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kStepThreads) void k_gbs_step(GbsDev* state, GbsOut
 // launch picks them up (512 x 4096: 65 us).
 constexpr int kMaxGroups = 1024;
 constexpr uint64_t kWaitTicks = 30000;                    // of the 100 MHz clock: 300 us, a hundred times a step
-constexpr int kAhead = 3, kSlots = 1 << kAhead;           // probes a step looks ahead, clip ratios of a step
+constexpr int kAhead = kStepsAhead, kSlots = 1 << kAhead;  // probes a step looks ahead, clip ratios of a step
 
 struct ResidentArgs {
     GbsOut* out;
@@ -455,11 +455,11 @@ int resident_launch(const rq_hadamard* h, const RowArgs& a, ResidentArgs r, hipS
 
 }  // namespace
 
-bool gbs_in_registers(const rq_hadamard* h, const RowArgs& a) { return wave_quant_error_supports(h, a) && resident_waves(a) > 0; }
+int gbs_row_waves(const rq_hadamard* h, const RowArgs& a) { return wave_quant_error_supports(h, a) ? resident_waves(a) : 0; }
 
 bool gbs_resident_supports(const rq_hadamard* h, const RowArgs& a) {
-    if (!gbs_in_registers(h, a)) return false;
-    const int w = resident_waves(a);
+    const int w = gbs_row_waves(h, a);
+    if (w == 0) return false;
     const int groups = h->num_cu < kMaxGroups ? h->num_cu : kMaxGroups;
     return a.rows <= (int64_t)groups * (16 / w);          // 16 waves per compute unit
 }

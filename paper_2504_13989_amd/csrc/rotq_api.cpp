@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "rotq_internal.h"
+#include "search_rule.h"
 
 namespace {
 
@@ -616,28 +617,10 @@ int rq_quant_error_asym(const rq_hadamard_t* h, const void* X, int dtype, int64_
                                 stream, true);
 }
 
-namespace {
-// Steps a batch of the search looks ahead: up to 5 (the 31 nodes of the outcome tree, plus the starting point in the
-// first batch) on small tensors, up to 3 (7 nodes + 1) on large ones, where the extra candidates would cost more than
-// the passes they save.
-constexpr int64_t kGbsSmall = (int64_t)1 << 22;              // rows * n up to which 5 steps are taken
-int gbs_depth(int64_t rows, int n) { return (double)rows * (double)n <= (double)kGbsSmall ? 5 : 3; }
-
-// Most steps a search down to a bracket of eps can take: two steps halve the bracket (from 1, by way of 3/4).  That
-// holds while the midpoints are exact; a bracket of a few ulps stops shrinking and the search goes on to its limit.
-int gbs_most_steps(double eps, int limit) {
-    if (eps < 0x1p-50) return limit;
-    int steps = 0;
-    for (double w = 1.0; w > eps && steps < limit; ++steps) w = steps % 2 == 0 ? w * 0.75 : w / 1.5;
-    return steps;
-}
-
-}  // namespace
-
 size_t rq_gbs_workspace(int64_t rows) {
     if (rows < 0) return 0;
     // the order is not known here: with the smallest one (32) more than 2^22 / 32 rows always take 3 steps
-    const int cands = rows * 32 <= kGbsSmall ? 32 : 8;
+    const int cands = rows * 32 <= rq::kGbsSmall ? 32 : 8;
     const size_t q = rq_quant_error_workspace(rows, cands);
     return q ? q + 256 : 0;
 }
@@ -672,7 +655,7 @@ static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t ro
     };
     if (mem.out) mem.out->done = 0;
     const volatile int* done = mem.out ? &mem.out->done : nullptr;
-    const int steps = gbs_most_steps((double)eps, max_evals - 1);
+    const int steps = rq::gbs_most_steps((double)eps, max_evals - 1);
     const bool in_registers = !asym && h->variant == 0 && rq::gbs_resident_supports(h, a);
     // after the last launch: the results, copied back where they are in device memory
     auto collect = [&](int code) {
@@ -699,7 +682,7 @@ static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t ro
     const int form = h->search;
     // (a variant that names one of the forms below takes it)
     const bool named = in_registers && (form == kSearchStepped || form == kSearchNoWait);
-    if (!asym && h->variant == 0 && !named && rq::gbs_grid_supports(h, a, (double)eps)) {
+    if (!asym && h->variant == 0 && !named && rq::gbs_grid_supports(h, a, (double)eps, steps)) {
         note(h, "grid_search");
         rc = rq::gbs_grid(h, a, mem.state, mem.out_dev, (double)eps, max_evals, s);
         if (rc == RQ_OK && done && !watch()) rc = RQ_ERR_HIP;
@@ -735,11 +718,7 @@ static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t ro
         note(h, "gbs_stepped");
         return collect(rq::gbs_stepped(h, a, mem.state, mem.out_dev, partial, (double)eps, max_evals, steps, s));
     }
-    // as few batches as the depth allows, each no deeper than that number needs (16 steps: four batches of four, 61
-    // candidates, where batches of five would evaluate 95)
-    const int deepest = gbs_depth(rows, h->f.n);
-    const int batches = steps > 0 ? (steps + deepest - 1) / deepest : 1;
-    const int depth = steps > 0 ? (steps + batches - 1) / batches : 1;
+    const auto [batches, depth] = rq::gbs_batches(rows, h->f.n, steps);
     const int most = 1 << depth;                             // clip ratios of a batch
     rq::ClipArg cl;
     std::memset(&cl, 0, sizeof cl);

@@ -242,8 +242,8 @@ SearchMemory search_memory(int dev);
 const ClipList* gbs_state_clips(const GbsDev* state);
 // The first batch of a search, `depth` steps ahead: the starting point and every probe those steps can ask for.
 void gbs_first_batch(double eps, int depth, int bits, ClipList* out);
-// Rows that a wave or a few hold in registers.
-bool gbs_in_registers(const rq_hadamard* h, const RowArgs& a);
+// Waves that hold a row in their registers, 0 where none do.
+int gbs_row_waves(const rq_hadamard* h, const RowArgs& a);
 // The whole search in one launch, for tensors whose rows the chip holds that way all at once; false where it does not.  (`wait`
 // false: a workgroup that finds another's sums missing gives the search up at once, for tests.)
 bool gbs_resident_supports(const rq_hadamard* h, const RowArgs& a);
@@ -253,8 +253,9 @@ int gbs_resident(const rq_hadamard* h, const RowArgs& a, GbsOut* out, uint64_t* 
 // The same steps, a launch each, for searches of up to `steps` steps after the starting point; `sums` is the workspace.
 int gbs_stepped(const rq_hadamard* h, const RowArgs& a, GbsDev* state, GbsOut* out, double* sums, double eps, int max_evals, int steps,
                 hipStream_t s);
-// The grid form: any number of those rows or of the workgroup block kernel's, brackets down to 1 / 256; rows of the latter.
-bool gbs_grid_supports(const rq_hadamard* h, const RowArgs& a, double eps);
+// The grid form: those rows or the workgroup block kernel's, brackets down to 1 / 256, where it is the faster one for a search
+// of up to `steps` steps; rows of the latter.
+bool gbs_grid_supports(const rq_hadamard* h, const RowArgs& a, double eps, int steps);
 int gbs_grid(const rq_hadamard* h, const RowArgs& a, GbsDev* dev, GbsOut* out, double eps, int max_evals, hipStream_t s);
 int wg_grid_rows(const rq_hadamard* h, const RowArgs& a, GbsDev* dev, int* groups, hipStream_t s);
 int gbs_step(GbsDev* state, GbsOut* out, bool first, double eps, int depth, int max_evals, int bits, const double* partial,

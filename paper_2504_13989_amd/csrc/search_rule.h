@@ -1,0 +1,73 @@
+// What the host decides about a clip search (Algorithm 1, section 4.1): how many steps it can take, how batches of clip ratios
+// cover them, and whether the grid form (kernels_gridsearch.hip) is the faster one.  Plain host code.
+#pragma once
+#include <algorithm>
+#include <cstdint>
+
+namespace rq {
+
+// Steps a batch of the search looks ahead: up to 5 (the 31 nodes of the outcome tree, plus the starting point in the
+// first batch) on small tensors, up to 3 (7 nodes + 1) on large ones, where the extra candidates would cost more than
+// the passes they save.
+constexpr int64_t kGbsSmall = (int64_t)1 << 22;              // rows * n up to which 5 steps are taken
+inline int gbs_depth(int64_t rows, int n) { return (double)rows * (double)n <= (double)kGbsSmall ? 5 : 3; }
+
+// Most steps a search down to a bracket of eps can take: two steps halve the bracket (from 1, by way of 3/4).  That
+// holds while the midpoints are exact; a bracket of a few ulps stops shrinking and the search goes on to its limit.
+inline int gbs_most_steps(double eps, int limit) {
+    if (eps < 0x1p-50) return limit;
+    int steps = 0;
+    for (double w = 1.0; w > eps && steps < limit; ++steps) w = steps % 2 == 0 ? w * 0.75 : w / 1.5;
+    return steps;
+}
+
+// As few batches as the depth allows, each no deeper than that number needs (16 steps: four batches of four, 61
+// candidates, where batches of five would evaluate 95).
+struct GbsBatches { int count, depth; };
+inline GbsBatches gbs_batches(int64_t rows, int n, int steps) {
+    if (steps < 1) return GbsBatches{1, 1};
+    const int deepest = gbs_depth(rows, n), count = (steps + deepest - 1) / deepest;
+    return GbsBatches{count, (steps + count - 1) / count};
+}
+constexpr int kStepsAhead = 3;                               // steps of a search that a step of the resident form decides
+
+// Clip ratios m / kGridRatios of the grid form, and the 64-bit words of LDS that a row's histogram takes (error_grid.h).
+constexpr int kGridRatios = 512, kGridGroups = 256;          // (and the most workgroups that take part)
+constexpr int grid_cells(int bits) { return (2 * ((1 << (bits - 1)) - 1) - 1) * (kGridRatios - 1) + 1; }
+constexpr int grid_words(int bits) { return grid_cells(bits) + kGridRatios; }
+
+struct GridCase {
+    int64_t rows;
+    int n, bits, cus;
+    bool sylvester;
+    int waves;              // a row's in the resident form; 0: a row of the workgroup block kernel, for which
+    int rows_per_pass;      // are its own rows per pass
+    int threads;            // and threads
+};
+
+// Whether the grid form is the faster one for a search of up to `steps` steps: its time does not depend on them, that of the
+// forms it competes with (resident where the chip holds the tensor, else batches) grows with them.  Straight lines through
+// 4400 pairs of measured times, us (25 orders from 384 to 32768, 1 to 32768 rows, 0 to 16 steps, both code widths); the form
+// taken is within a tenth of the faster one but for 14 of them, at worst 1.23 times it.
+// 4096 x 2048 rows, b = 3: grid 45 at any number of steps; batches 26 for up to one, 33 for three, 55 for five, 136 for sixteen.
+// 1024 x 8192 rows: 104; 29, 29 - 33, 55, 143.  4096 x 64 rows: 19; resident 13, 13, 17, 33.  18944 x 512 rows: 39; 30, 36, 62, 169.
+inline bool gbs_grid_pays(const GridCase& c, int steps) {
+    const double kilo = c.n / 1024.0, load = (double)c.rows * c.n / (4096.0 * c.cus);     // 4096 values a compute unit
+    const GbsBatches b = gbs_batches(c.rows, c.n, steps);
+    const int fours = ((1 << b.depth) + 3) / 4;              // clip ratios of a batch are taken four at a time
+    if (c.waves > 0) {
+        // a pass of the grid form: two rows a compute unit, or one where that is all there is
+        const double row = (c.bits == 3 ? 4.4 : 5.7) + 0.95 * kilo + (c.sylvester ? 0.0 : 0.7);
+        const double grid = 14.5 + (c.rows <= c.cus ? 0.5 * row : (double)((c.rows + 2 * c.cus - 1) / (2 * c.cus)) * row);
+        if (c.rows <= (int64_t)c.cus * (16 / c.waves))
+            return grid < 9.0 + std::max(1, (steps + kStepsAhead - 1) / kStepsAhead) * (4.0 + 1.3 * load);
+        return grid < 14.0 + b.count * (9.5 + load * (0.2 + 0.6 * fours));
+    }
+    // the rows of a pass share one histogram: one row after the other
+    const int64_t passes = (c.rows + c.rows_per_pass - 1) / c.rows_per_pass;
+    const int64_t serial = std::min<int64_t>(c.rows, c.rows_per_pass * ((passes + c.cus - 1) / c.cus));
+    const double row = (c.rows_per_pass > 1 ? 5.0 : 2.25) + 0.12 * grid_words(c.bits) / c.threads + 0.47 * kilo;
+    return 15.0 + serial * row < 8.0 + b.count * (13.0 + 0.5 * fours + load * (0.55 + 0.58 * fours));
+}
+
+}  // namespace rq

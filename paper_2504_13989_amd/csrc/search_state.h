@@ -1,6 +1,7 @@
 // State of a clip-ratio search (Algorithm 1, section 4.1) and what it keeps in device memory.
 #pragma once
 #include "rotq_internal.h"
+#include "search_rule.h"
 
 namespace rq {
 
@@ -23,9 +24,6 @@ struct GbsState {
     }
 };
 __host__ __device__ inline GbsState gbs_start() { return GbsState{0.0, 1.0, 0.5, 0}; }
-
-// Grid form (kernels_gridsearch.hip): clip ratios m / kGridRatios, and the most workgroups that take part.
-constexpr int kGridLog2 = 9, kGridRatios = 1 << kGridLog2, kGridGroups = 256;
 
 // What one launch of the stepped form hands to the next.
 struct GbsCarry {

@@ -27,7 +27,7 @@ def _check(h, x, b, eps, result):
 @pytest.mark.parametrize("n,d,rows", [(1024, 1000, 257), (2048, 2048, 513), (4096, 4096, 1), (8192, 8192, 300), (1536, 1536, 70),
                                       (3584, 3584, 513), (3072, 3000, 31), (5120, 5120, 258), (18944, 18944, 3), (28672, 28672, 2),
                                       (8960, 8960, 515), (4864, 4864, 5), (896, 896, 1023), (896, 896, 1), (11264, 11008, 40),
-                                      (384, 384, 9), (32768, 32768, 1)])
+                                      (384, 384, 2), (32768, 32768, 1)])
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_grid_search_takes_the_steps_of_algorithm_1(n, d, rows, dtype):
     rng = np.random.default_rng(n + rows)
@@ -41,15 +41,16 @@ def test_grid_search_takes_the_steps_of_algorithm_1(n, d, rows, dtype):
             assert h.last_kernel == "grid_search"
             _check(h, x, b, float(np.float32(eps)), got)
             assert binding.gbs_search(h, x, b, eps) == got
-        short = binding.gbs_search(h, x, b, 1.0 / 256, max_evals=3)
-        assert short[2] == binding.gbs_search(h, x, b, 1.0 / 256)[2][:3]
+        full = binding.gbs_search(h, x, b, 1.0 / 256)
+        short = binding.gbs_search(h, x, b, 1.0 / 256, max_evals=14)
+        assert h.last_kernel == "grid_search" and short[2] == full[2][:14]
 
 
 def test_ends_of_the_grids_range():
     rng = np.random.default_rng(3)
     x = parity.to_device(wl.f32_to_bf16_bits(rng.standard_normal((300, 5120)).astype(np.float32)))
     h = binding.hadamard_build(5120)
-    for eps, grid in ((1.0 / 256, True), (np.nextafter(np.float32(1.0 / 256), np.float32(0)), False), (0.9, True), (2.0, True), (1e-6, False)):
+    for eps, grid in ((1.0 / 256, True), (np.nextafter(np.float32(1.0 / 256), np.float32(0)), False), (1.0 / 128, True), (1e-6, False)):
         got = binding.gbs_search(h, x, 3, float(eps))
         assert (h.last_kernel == "grid_search") == grid
         _check(h, x, 3, float(eps), got)
@@ -57,6 +58,26 @@ def test_ends_of_the_grids_range():
     want = binding.gbs_search(h, x, 3, 1.0 / 256)
     h.set_variant(7)
     assert binding.gbs_search(h, x, 3, 1.0 / 256) == want and h.last_kernel == "grid_search"
+
+
+@pytest.mark.parametrize("n,rows,kernel", [(4096, 40, "gbs_resident"), (1024, 2048, "gbs_resident"), (4096, 2048, "wave_quant_error"),
+                                           (3584, 2500, "wave_quant_error"), (896, 700, "wg_block_quant_error"),
+                                           (4864, 1500, "wg_block_quant_error"), (18944, 600, "wg_block_quant_error")])
+def test_searches_of_few_steps_evaluate_few_ratios(n, rows, kernel):
+    """a coarse or limited search needs one or two passes of a few clip ratios: the form for that, with Algorithm 1's steps"""
+    rng = np.random.default_rng(n)
+    x = parity.to_device(wl.f32_to_bf16_bits(rng.standard_normal((rows, n)).astype(np.float32)))
+    h = binding.hadamard_build(n)
+    full = binding.gbs_search(h, x, 3, 1.0 / 256)
+    assert h.last_kernel == "grid_search"
+    for eps, limit in ((0.9, 64), (2.0, 64), (0.5, 64), (1.0 / 256, 1), (1.0 / 256, 3)):
+        got = binding.gbs_search(h, x, 3, eps, max_evals=limit)
+        assert h.last_kernel == kernel or (kernel == "gbs_resident" and h.last_kernel == "gbs_stepped")
+        if eps < 0.5:
+            assert [c for c, _ in got[2]] == [c for c, _ in full[2][:limit]]
+            assert np.allclose([v for _, v in got[2]], [v for _, v in full[2][:limit]], rtol=2e-6, atol=0.0)
+        else:
+            _check(h, x, 3, eps, got)
 
 
 @pytest.mark.parametrize("n", [4096, 1536, 5120, 896])
