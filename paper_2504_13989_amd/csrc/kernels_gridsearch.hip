@@ -143,11 +143,12 @@ int launch_rows(const rq_hadamard* h, const RowArgs& a, const WaveArgs& w, int p
     using Grid = ErrorGrid<BITS>;
     static_assert(Grid::WORDS % 2 == 0, "cleared by 16 bytes");
     const int cus = h->num_cu < kGridGroups ? h->num_cu : kGridGroups;
-    const int conc = a.rows > cus && (size_t)h->max_lds >= 2 * Grid::bytes() + 1024 ? 2 : 1;
+    const int conc = a.rows > cus ? grid_rows_beside(BITS, h->max_lds) : 1;
     const int64_t passes = (a.rows + conc - 1) / conc;
     *groups = (int)(passes < cus ? passes : cus);
     void (*const fn)(WaveArgs, int, int, double, GbsDev*) = k_grid_rows<Rows, BITS>;
     const size_t lds = (size_t)conc * Grid::bytes();
+    if (!allow_lds(fn, lds)) return RQ_ERR_NO_ORDER;
     launch_kernel(fn, dim3((unsigned)*groups), dim3((unsigned)(512 * conc)), lds, s, w, pb, conc,
                   1.0 / ((double)a.n * (double)a.n), dev);
     return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
@@ -173,10 +174,11 @@ int rows_pass(const rq_hadamard* h, const RowArgs& a, const WaveArgs& w, int* gr
 bool gbs_grid_supports(const rq_hadamard* h, const RowArgs& a, double eps, int steps) {
     if (eps < 2.0 / kGridRatios) return false;
     const int cus = h->num_cu < kGridGroups ? h->num_cu : kGridGroups;
-    GridCase c{a.rows, a.n, a.bits, cus, a.p == 1, gbs_row_waves(h, a), 0, 0};
+    GridCase c{a.rows, a.n, a.bits, cus, a.p == 1, grid_rows_beside(a.bits, h->max_lds), gbs_row_waves(h, a), 0, 0};
     if (c.waves == 0) {
         int pb, cb;
         if (wave_quant_error_supports(h, a) || !wg_block_supports(h, a, true) || !wg_shape(a, &pb, &cb)) return false;
+        c.beside = grid_rows_beside(a.bits, h->max_lds, (int64_t)wg_grid_ops_bytes(pb));
         c.rows_per_pass = 16 >> cb;
         c.threads = 64 * ((pb + 15) / 16);
     }

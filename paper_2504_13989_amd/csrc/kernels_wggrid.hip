@@ -25,6 +25,7 @@ int launch_kk(const rq_hadamard* h, const WaveArgs& w, int bits, int pb, int cb,
     WgKernel<kWgGrid> fn = pick_kernel<KK>(bits, cb, w.f16);
     if (!fn) return RQ_ERR_NO_ORDER;
     const size_t lds = wg_ops_bytes<KK>() + (bits == 4 ? ErrorGrid<4>::bytes() : ErrorGrid<3>::bytes());
+    if (!allow_lds(fn, lds)) return RQ_ERR_NO_ORDER;
     const int rpw = 16 >> cb, cus = h->num_cu < kGridGroups ? h->num_cu : kGridGroups;
     const int64_t passes = (w.rows + rpw - 1) / rpw;
     *groups = (int)(passes < cus ? passes : cus);
@@ -33,6 +34,8 @@ int launch_kk(const rq_hadamard* h, const WaveArgs& w, int bits, int pb, int cb,
 }
 
 }  // namespace
+
+size_t wg_grid_ops_bytes(int pb) { return (size_t)((pb + 31) / 32) * wg_ops_bytes<1>(); }
 
 int wg_grid_rows(const rq_hadamard* h, const RowArgs& a, GbsDev* dev, int* groups, hipStream_t s) {
     int pb, cb;

@@ -683,11 +683,14 @@ static int gbs_impl(const rq_hadamard_t* h, const void* X, int dtype, int64_t ro
     // (a variant that names one of the forms below takes it)
     const bool named = in_registers && (form == kSearchStepped || form == kSearchNoWait);
     if (!asym && h->variant == 0 && !named && rq::gbs_grid_supports(h, a, (double)eps, steps)) {
-        note(h, "grid_search");
         rc = rq::gbs_grid(h, a, mem.state, mem.out_dev, (double)eps, max_evals, s);
-        if (rc == RQ_OK && done && !watch()) rc = RQ_ERR_HIP;
-        if (rc == RQ_OK && done && *done) return finish(RQ_OK, mem.out);
-        return collect(rc);
+        if (rc != RQ_ERR_NO_ORDER) {                         // (nothing launched: the forms below need less LDS)
+            note(h, "grid_search");
+            if (rc == RQ_OK && done && !watch()) rc = RQ_ERR_HIP;
+            if (rc == RQ_OK && done && *done) return finish(RQ_OK, mem.out);
+            return collect(rc);
+        }
+        rc = RQ_OK;
     }
     // (without pinned memory there is no result to look for while the stream is busy: the stepped form)
     if (const ResidentTurn turn{h->device, in_registers && mem.out && form != kSearchStepped}) {

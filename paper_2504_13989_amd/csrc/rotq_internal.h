@@ -54,6 +54,15 @@ inline void launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, size_t ld
     }, values);
 }
 
+// Leave for a kernel to take that much dynamic LDS; false where the device has none for it.
+template <typename... P>
+inline bool allow_lds(void (*kernel)(P...), size_t lds) {
+    if (lds <= 48 * 1024 || hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                (int)lds) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
 // Grid of `groups` workgroups (fewer than 2^35) of a kernel that takes one item each, numbered by group_index()
 // (wave_common.h): a dimension holds fewer than 2^32 threads (beyond that the launch keeps the remainder, without
 // an error).
@@ -257,7 +266,9 @@ int gbs_stepped(const rq_hadamard* h, const RowArgs& a, GbsDev* state, GbsOut* o
 // of up to `steps` steps; rows of the latter.
 bool gbs_grid_supports(const rq_hadamard* h, const RowArgs& a, double eps, int steps);
 int gbs_grid(const rq_hadamard* h, const RowArgs& a, GbsDev* dev, GbsOut* out, double eps, int max_evals, hipStream_t s);
+// (RQ_ERR_NO_ORDER with nothing launched: the kernels' LDS cannot be had)
 int wg_grid_rows(const rq_hadamard* h, const RowArgs& a, GbsDev* dev, int* groups, hipStream_t s);
+size_t wg_grid_ops_bytes(int pb);                            // LDS of the operand buffer of a block of that order
 int gbs_step(GbsDev* state, GbsOut* out, bool first, double eps, int depth, int max_evals, int bits, const double* partial,
              int64_t rows, int64_t count, int64_t stride, hipStream_t s);
 

@@ -35,11 +35,18 @@ constexpr int kStepsAhead = 3;                               // steps of a searc
 constexpr int kGridRatios = 512, kGridGroups = 256;          // (and the most workgroups that take part)
 constexpr int grid_cells(int bits) { return (2 * ((1 << (bits - 1)) - 1) - 1) * (kGridRatios - 1) + 1; }
 constexpr int grid_words(int bits) { return grid_cells(bits) + kGridRatios; }
+// Rows whose histograms a workgroup can hold side by side: two, one, or none where not even one fits beside `other` bytes of
+// LDS and what the kernels keep in static arrays (up to 832 bytes).
+constexpr int grid_rows_beside(int bits, int64_t max_lds, int64_t other = 0) {
+    const int64_t row = 8 * (int64_t)grid_words(bits), left = max_lds - other - 1024;
+    return left >= 2 * row ? 2 : left >= row ? 1 : 0;
+}
 
 struct GridCase {
     int64_t rows;
     int n, bits, cus;
     bool sylvester;
+    int beside;             // rows that fit a workgroup's LDS, see above
     int waves;              // a row's in the resident form; 0: a row of the workgroup block kernel, for which
     int rows_per_pass;      // are its own rows per pass
     int threads;            // and threads
@@ -52,13 +59,15 @@ struct GridCase {
 // 4096 x 2048 rows, b = 3: grid 45 at any number of steps; batches 26 for up to one, 33 for three, 55 for five, 136 for sixteen.
 // 1024 x 8192 rows: 104; 29, 29 - 33, 55, 143.  4096 x 64 rows: 19; resident 13, 13, 17, 33.  18944 x 512 rows: 39; 30, 36, 62, 169.
 inline bool gbs_grid_pays(const GridCase& c, int steps) {
+    if (c.beside < 1) return false;
     const double kilo = c.n / 1024.0, load = (double)c.rows * c.n / (4096.0 * c.cus);     // 4096 values a compute unit
     const GbsBatches b = gbs_batches(c.rows, c.n, steps);
     const int fours = ((1 << b.depth) + 3) / 4;              // clip ratios of a batch are taken four at a time
     if (c.waves > 0) {
         // a pass of the grid form: two rows a compute unit, or one where that is all there is
         const double row = (c.bits == 3 ? 4.4 : 5.7) + 0.95 * kilo + (c.sylvester ? 0.0 : 0.7);
-        const double grid = 14.5 + (c.rows <= c.cus ? 0.5 * row : (double)((c.rows + 2 * c.cus - 1) / (2 * c.cus)) * row);
+        const int64_t two = 2 * (int64_t)c.cus;
+        const double grid = 14.5 + (c.rows <= c.cus ? 0.5 * row : (double)((c.rows + two - 1) / two) * row * (c.beside > 1 ? 1.0 : 2.0));
         if (c.rows <= (int64_t)c.cus * (16 / c.waves))
             return grid < 9.0 + std::max(1, (steps + kStepsAhead - 1) / kStepsAhead) * (4.0 + 1.3 * load);
         return grid < 14.0 + b.count * (9.5 + load * (0.2 + 0.6 * fours));

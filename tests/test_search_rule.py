@@ -28,24 +28,51 @@ SHAPE = {1024: (1, 1, 0, 0), 2048: (1, 2, 0, 0), 4096: (1, 4, 0, 0), 8192: (1, 4
          896: (0, 0, 4, 128), 4864: (0, 0, 2, 320), 5120: (0, 0, 1, 192), 18944: (0, 0, 1, 640), 28672: (0, 0, 1, 896)}
 
 
-def _host_program(tmp_path, name):
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
     gxx = shutil.which("g++")
     if not gxx:
         pytest.skip("needs g++")
-    exe = str(tmp_path / name)
-    subprocess.run([gxx, "-std=c++17", "-O1", os.path.join(HERE, "host", name + ".cpp"), "-o", exe], check=True, capture_output=True)
+    exe = str(tmp_path_factory.mktemp("rule") / "search_rule")
+    subprocess.run([gxx, "-std=c++17", "-O1", os.path.join(HERE, "host", "search_rule.cpp"), "-o", exe], check=True, capture_output=True)
     return exe
 
 
-def test_a_search_takes_the_faster_form(tmp_path):
-    """coarse or limited searches need one or two passes of a few clip ratios, where the grid form always pays for 511"""
+LDS = 160 * 1024
+
+
+def _taken(threads):                                   # the workgroup block kernel's operand buffer
+    return (threads // 64 + 1) // 2 * 8192
+
+
+def _grid(program, cases, lds=LDS):
     lines = []
-    for n, rows, bits, steps, _, _ in MEASURED:
+    for n, rows, bits, steps in cases:
         sylvester, waves, rpp, threads = SHAPE[n]
-        lines.append(f"{rows} {n} {bits} {sylvester} {waves} {rpp} {threads} {steps}")
-    run = subprocess.run([_host_program(tmp_path, "search_rule")], input="\n".join(lines) + "\n", capture_output=True, text=True, timeout=60)
+        lines.append(f"{rows} {n} {bits} {sylvester} {waves} {rpp} {threads} {steps} {lds} {_taken(threads)}")
+    run = subprocess.run([program], input="\n".join(lines) + "\n", capture_output=True, text=True, timeout=60)
     grid = [int(v) for v in run.stdout.split()]
-    assert run.returncode == 0 and len(grid) == len(MEASURED)
-    for case, g in zip(MEASURED, grid):
+    assert run.returncode == 0 and len(grid) == len(cases)
+    return grid
+
+
+def test_a_search_takes_the_faster_form(program):
+    """coarse or limited searches need one or two passes of a few clip ratios, where the grid form always pays for 511"""
+    for case, g in zip(MEASURED, _grid(program, [c[:4] for c in MEASURED])):
         without, with_grid = case[4:]
         assert (with_grid if g else without) <= 1.1 * min(without, with_grid), (case, g)
+
+
+def test_a_histogram_needs_its_lds(program):
+    """a row's histogram takes 24.5 KB (b = 3) or 57 KB of LDS beside the operand buffer: where it does not fit, the other forms
+    still do"""
+    cases = [(n, 300, bits, 16) for n in (1024, 3584, 5120, 18944, 28672) for bits in (3, 4)]
+    need = {(n, bits): {3: 3068, 4: 7156}[bits] * 8 + _taken(SHAPE[n][3]) + 1024 for n, _, bits, _ in cases}
+    for lds in (32 * 1024, 64 * 1024, 96 * 1024, LDS):
+        fits = [need[n, bits] <= lds for n, _, bits, _ in cases]
+        grid = _grid(program, cases, lds)
+        assert all(f or not g for f, g in zip(fits, grid)), lds
+        if lds == LDS:
+            assert all(grid)
+    for n, bits in need:                               # to the byte
+        assert _grid(program, [(n, 40, bits, 16)], need[n, bits]) == [1] and _grid(program, [(n, 40, bits, 16)], need[n, bits] - 1) == [0]
