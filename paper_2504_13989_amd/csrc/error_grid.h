@@ -47,7 +47,9 @@ struct ErrorGrid {
 
     // One value (y with its sign) into the histogram; q2 accumulates V^2.
     static __device__ __forceinline__ void add(uint64_t* hist, float y, float s, double& q2) {
-        const uint32_t v = (uint32_t)__builtin_rintf(__builtin_fabsf(y) * s);
+        // (the bound holds by itself in a finite row; it is for infinities and NaN, whose conversion is undefined: the minimum of a
+        // NaN and a number is the number)
+        const uint32_t v = (uint32_t)__builtin_rintf(__builtin_fminf(__builtin_fabsf(y) * s, 0x1p28f));
         q2 = fma((double)v, (double)v, q2);
         const uint32_t u = v >> FRAC;
         const unsigned long long word = (1ull << 48) | v;

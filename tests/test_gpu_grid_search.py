@@ -86,9 +86,9 @@ def test_rows_that_are_not_finite_zero_or_tiny(n):
     xf = rng.standard_normal((9, n)).astype(np.float32)
     h = binding.hadamard_build(n)
     base = xf.copy()
-    for what in ("zero", "tiny", "inf", "nan"):
+    for what in ("zero", "tiny", "inf", "nan", "over"):
         xf = base.copy()
-        xf[4] = {"zero": 0.0, "tiny": xf[4] * np.float32(1e-36), "inf": xf[4], "nan": xf[4]}[what]
+        xf[4] = {"zero": 0.0, "tiny": xf[4] * np.float32(1e-36), "inf": xf[4], "nan": xf[4], "over": xf[4] * np.float32(5e37)}[what]
         if what in ("inf", "nan"):
             xf[4, 7] = np.inf if what == "inf" else np.nan
         x = parity.to_device(wl.f32_to_bf16_bits(xf))
