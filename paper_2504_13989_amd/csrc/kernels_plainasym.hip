@@ -69,7 +69,7 @@ __device__ __forceinline__ void row_min_max4(const float (&mn)[4], const float (
         "v_min_f32_dpp %1, %5, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
         "v_max_f32_dpp %2, %6, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
         "v_max_f32_dpp %3, %7, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
-        : "+v"(n0), "+v"(n1), "+v"(x0), "+v"(x1)
+        : "+&v"(n0), "+&v"(n1), "+&v"(x0), "+&v"(x1)
         : "v"(b0 ? mn[0] : mn[1]), "v"(b0 ? mn[2] : mn[3]), "v"(b0 ? mx[0] : mx[1]), "v"(b0 ? mx[2] : mx[3]));
     lo = b1 ? n1 : n0;
     hi = b1 ? x1 : x0;
@@ -83,7 +83,7 @@ __device__ __forceinline__ void row_min_max4(const float (&mn)[4], const float (
         "v_min_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
         "v_max_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
         "s_nop 1"
-        : "+v"(lo), "+v"(hi)
+        : "+&v"(lo), "+&v"(hi)
         : "v"(b1 ? n0 : n1), "v"(b1 ? x0 : x1));
 }
 // Lane u of each quad to all four.

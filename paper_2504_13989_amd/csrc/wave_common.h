@@ -88,7 +88,7 @@ __device__ __forceinline__ void lane_stages_fused(f32x4& v, float s0, float s1, 
         "v_fmac_f32_dpp %1, %1, %7 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f32_dpp %2, %2, %7 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f32_dpp %3, %3, %7 row_ror:8 row_mask:0xf bank_mask:0xf"
-        : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3)
+        : "+&v"(x0), "+&v"(x1), "+&v"(x2), "+&v"(x3)
         : "v"(s0), "v"(s1), "v"(s2), "v"(s3));
     v[0] = x0; v[1] = x1; v[2] = x2; v[3] = x3;
 }
@@ -104,7 +104,7 @@ __device__ __forceinline__ void lane_stages_tail_1(f32x4& v, float s1) {
         "v_fmac_f32_dpp %1, %1, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f32_dpp %2, %2, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f32_dpp %3, %3, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
-        : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3)
+        : "+&v"(x0), "+&v"(x1), "+&v"(x2), "+&v"(x3)
         : "v"(s1));
     v[0] = x0; v[1] = x1; v[2] = x2; v[3] = x3;
 }
@@ -119,7 +119,7 @@ __device__ __forceinline__ void lane_stages_tail_2(f32x4& v, float s1, float s2)
         "v_fmac_f32_dpp %1, %1, %5 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f32_dpp %2, %2, %5 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f32_dpp %3, %3, %5 row_half_mirror row_mask:0xf bank_mask:0xf"
-        : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3)
+        : "+&v"(x0), "+&v"(x1), "+&v"(x2), "+&v"(x3)
         : "v"(s1), "v"(s2));
     v[0] = x0; v[1] = x1; v[2] = x2; v[3] = x3;
 }
@@ -138,7 +138,7 @@ __device__ __forceinline__ void lane_stages_tail_3(f32x4& v, float s1, float s2,
         "v_fmac_f32_dpp %1, %1, %6 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f32_dpp %2, %2, %6 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f32_dpp %3, %3, %6 row_ror:8 row_mask:0xf bank_mask:0xf"
-        : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3)
+        : "+&v"(x0), "+&v"(x1), "+&v"(x2), "+&v"(x3)
         : "v"(s1), "v"(s2), "v"(s3));
     v[0] = x0; v[1] = x1; v[2] = x2; v[3] = x3;
 }
@@ -166,20 +166,20 @@ __device__ __forceinline__ void lane_stages_mfma(f32x4& v, const float (&sf)[4])
     if constexpr (CB == 2)
         asm("s_nop 1\n\t" RQ_ST1("%1") RQ_ST1("%2") RQ_ST1("%3")
             RQ_ST2("%0") RQ_ST2("%1") RQ_ST2("%2") RQ_ST2("%3")
-            : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3)
+            : "+&v"(x0), "+&v"(x1), "+&v"(x2), "+&v"(x3)
             : "v"(sf[0]), "v"(sf[1]), "v"(sf[2]), "v"(sf[3]));
     else if constexpr (CB == 3)
         asm("s_nop 1\n\t" RQ_ST1("%1") RQ_ST1("%2") RQ_ST1("%3")
             RQ_ST2("%0") RQ_ST2("%1") RQ_ST2("%2") RQ_ST2("%3")
             RQ_ST3("%0") RQ_ST3("%1") RQ_ST3("%2") RQ_ST3("%3")
-            : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3)
+            : "+&v"(x0), "+&v"(x1), "+&v"(x2), "+&v"(x3)
             : "v"(sf[0]), "v"(sf[1]), "v"(sf[2]), "v"(sf[3]));
     else
         asm("s_nop 1\n\t" RQ_ST1("%1") RQ_ST1("%2") RQ_ST1("%3")
             RQ_ST2("%0") RQ_ST2("%1") RQ_ST2("%2") RQ_ST2("%3")
             RQ_ST3("%0") RQ_ST3("%1") RQ_ST3("%2") RQ_ST3("%3")
             RQ_ST4("%0") RQ_ST4("%1") RQ_ST4("%2") RQ_ST4("%3")
-            : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3)
+            : "+&v"(x0), "+&v"(x1), "+&v"(x2), "+&v"(x3)
             : "v"(sf[0]), "v"(sf[1]), "v"(sf[2]), "v"(sf[3]));
 #undef RQ_ST1
 #undef RQ_ST2
@@ -199,7 +199,7 @@ __device__ __forceinline__ void lane_stages_fused1(float& x0, float s0, float s1
         "v_fmac_f32_dpp %0, %0, %3 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
         "s_nop 1\n\t"
         "v_fmac_f32_dpp %0, %0, %4 row_ror:8 row_mask:0xf bank_mask:0xf"
-        : "+v"(x0)
+        : "+&v"(x0)
         : "v"(s0), "v"(s1), "v"(s2), "v"(s3));
 }
 __device__ __forceinline__ void lane_stages_fused2(float& x0, float& x1, float s0, float s1, float s2, float s3) {
@@ -215,7 +215,7 @@ __device__ __forceinline__ void lane_stages_fused2(float& x0, float& x1, float s
         "s_nop 0\n\t"
         "v_fmac_f32_dpp %0, %0, %5 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f32_dpp %1, %1, %5 row_ror:8 row_mask:0xf bank_mask:0xf"
-        : "+v"(x0), "+v"(x1)
+        : "+&v"(x0), "+&v"(x1)
         : "v"(s0), "v"(s1), "v"(s2), "v"(s3));
 }
 __device__ __forceinline__ void lane_stages_fused3(float& x0, float& x1, float& x2, float s0, float s1, float s2, float s3) {
@@ -232,7 +232,7 @@ __device__ __forceinline__ void lane_stages_fused3(float& x0, float& x1, float& 
         "v_fmac_f32_dpp %0, %0, %6 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f32_dpp %1, %1, %6 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f32_dpp %2, %2, %6 row_ror:8 row_mask:0xf bank_mask:0xf"
-        : "+v"(x0), "+v"(x1), "+v"(x2)
+        : "+&v"(x0), "+&v"(x1), "+&v"(x2)
         : "v"(s0), "v"(s1), "v"(s2), "v"(s3));
 }
 
