@@ -1,6 +1,6 @@
 """GPU: the grid form of the clip search (every probe down to a bracket of 1 / 256 evaluated at once, from a histogram of each
-row): its values against quant_error's and its steps against Algorithm 1 run on them, on every rotation it has; the ends of
-its range; rows that are not finite, zero or tiny; many searches on two streams."""
+row): its values against quant_error's and against 64 bits, its steps against Algorithm 1 run on them, on every rotation it has;
+the ends of its range; rows that are not finite, zero or tiny; many searches on two streams."""
 import numpy as np
 import pytest
 
@@ -58,6 +58,46 @@ def test_ends_of_the_grids_range():
     want = binding.gbs_search(h, x, 3, 1.0 / 256)
     h.set_variant(7)
     assert binding.gbs_search(h, x, 3, 1.0 / 256) == want and h.last_kernel == "grid_search"
+
+
+def _rows(kind, rows, d, rng):
+    if kind == "constant":                             # one coefficient holds all of the energy
+        return np.full((rows, d), 1.5, np.float32)
+    if kind == "impulse":                              # every coefficient as large as the largest
+        x = np.zeros((rows, d), np.float32)
+        x[np.arange(rows), rng.integers(0, d, rows)] = 3.0
+        return x
+    if kind == "normal":
+        return rng.standard_normal((rows, d)).astype(np.float32)
+    x = rng.standard_t(3, (rows, d))                   # heavy tails, outlier channels, a row that outweighs the others
+    x[:, rng.permutation(d)[:8]] *= 50.0
+    x[rows // 2] *= 500.0
+    return x.astype(np.float32)
+
+
+@pytest.mark.parametrize("n,d,rows", [(1024, 1024, 40), (2048, 2000, 33), (4096, 4096, 300), (8192, 8192, 9), (1536, 1536, 20), (3584, 3584, 40),
+                                      (896, 896, 70), (4864, 4864, 9), (5120, 5120, 20), (18944, 18944, 6)])
+@pytest.mark.parametrize("kind", ["normal", "tails", "constant", "impulse"])
+def test_values_against_64_bits(n, d, rows, kind):
+    rng = np.random.default_rng(n + rows)
+    xf = _rows(kind, rows, d, rng)
+    bits = wl.f32_to_bf16_bits(xf)
+    h = binding.hadamard_build(n)
+    x = parity.to_device(bits)
+    wide = parity.to_device(np.concatenate([bits, bits[:, ::-1], bits], axis=1))       # the middle of a wider tensor
+    wide[:, d:2 * d] = x
+    # log2 n fp32 additions lead to a value, each rounded by up to 2^-25 of it (uniform: over the square root of 3); where one value or
+    # one row sets the error nothing averages that out, and the square doubles it; four standard deviations, and
+    # the fp32 result's own rounding (measured: 4.3e-7 at most over these rows and others, rms 2e-8 - 2.1e-7)
+    tol = 4 * 2 * 2.0 ** -25 * np.sqrt(np.log2(n) / 3) + 2.0 ** -24
+    for b in (3, 4):
+        got = binding.gbs_search(h, x, b, 1.0 / 256)
+        assert h.last_kernel == "grid_search"
+        assert binding.gbs_search(h, wide[:, d:2 * d], b, 1.0 / 256) == got and h.last_kernel == "grid_search"
+        clips = np.array([c for c, _ in got[2]], np.float32)
+        want = oracle.quant_error(bits, n, b, clips)
+        rel = np.array([v for _, v in got[2]], np.float64) / want - 1.0
+        assert np.abs(rel).max() <= tol, (b, np.abs(rel).max())
 
 
 @pytest.mark.parametrize("n,rows,kernel", [(4096, 40, "gbs_resident"), (1024, 2048, "gbs_resident"), (4096, 2048, "wave_quant_error"),

@@ -65,3 +65,15 @@ def test_rotating_workgroup_block_kernels_hold_their_registers(spills):
     for kk, most in ((range(1, 8), 4), (range(8, 9), 24)):
         some = {k: v for k, v in forms.items() if int(re.search(r"k_wg_blockILi(\d+)E", k).group(1)) in kk}
         assert max(some.values()) <= most, sorted(some.items(), key=lambda kv: -kv[1])[:8]
+
+
+def test_grid_search_kernels_hold_their_registers(spills):
+    """The clip search's grid kernels, which keep a row for the passes over its histogram.  Rows held by single waves and the one-row
+    passes of blocks up to 160 spill nothing; larger blocks and several rows per pass are measured as they are."""
+    rows = {k: v for k, v in spills.items() if "k_grid_rows" in k}
+    assert len(rows) == 24 and max(rows.values()) == 0
+    forms = {k: v for k, v in spills.items() if re.search(r"k_wg_blockILi\d+ELi[34]ELb0ELi3E", k)}
+    assert len(forms) == 92
+    for k, v in forms.items():
+        kk, cb = map(int, re.search(r"k_wg_blockILi(\d+)ELi[34]ELb0ELi3ELi(\d)E", k).groups())
+        assert v <= (35 if cb < 4 else 14 if kk >= 6 else 0), (k, v)
