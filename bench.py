@@ -283,7 +283,7 @@ def time_all_configs(torch, binding, wl):
     ms = _graph_ms(torch, lambda: binding.quant_error_noalloc(h, x, 3, clips, mse))
     res["quant_error_noalloc_calib_b3"] = {"rows": w.rows, "n": w.n, "clips": len(clips), "us": ms * 1e3,
                                            "kernel": h.last_kernel, "note": "static device scratch instead of a workspace"}
-    # Algorithm 1 on the calibration tensor with quant_error as the objective (host loop, batched probes)
+    # Algorithm 1 on the calibration tensor with quant_error as the objective
     t0 = time.perf_counter()
     n_search = 20
     for _ in range(n_search):

@@ -332,19 +332,22 @@ size_t rq_gbs_workspace(int64_t rows);
  * f(x) < f(m) becomes the new middle and the far bracket end moves to the old middle, otherwise
  * the bracket end on the probe's side moves to the probe; stops when b - a <= eps or after
  * max_evals evaluations of f.  The probes and their values are those of that loop taken one at a
- * time; they are evaluated ahead, and the comparisons are taken on the device: for eps >= 1 / 256 every
- * probe there can be is a multiple of 1 / 512, and 16-bit rows are passed over once with all of these evaluated at
- * once; for a smaller eps rows the chip can hold in registers are rotated once and searched in one launch (or,
- * to the same values bit for bit, with a launch for every three steps where other work keeps that one from
- * running); other tensors take a few launches enqueued together, each of which evaluates every probe the next few
- * steps can ask for.  f is summed in an order of the search's own: it agrees with rq_quant_error to 2e-6 (relative), not
- * to the last bit.  The same call gives the same result.
+ * time; they are evaluated ahead, and the comparisons are taken on the device.  For eps >= 1 / 256 every
+ * probe there can be is a multiple of 1 / 512: bf16 and fp16 rows of the wave and workgroup kernels (16-byte
+ * aligned, ld and d multiples of 8) are passed over once with all of these evaluated at once, where the search may take
+ * enough steps to be worth it ("grid_search").  Otherwise, rows the chip can hold in registers are rotated once and
+ * searched in one launch ("gbs_resident", or, to the same values bit for bit, with a launch for every three steps where
+ * other work keeps that one from running, "gbs_stepped"); other tensors take a few launches of rq_quant_error's kernels
+ * enqueued together, each of which evaluates every probe the next few steps can ask for.  f is summed in an order
+ * of the search's own: it agrees with rq_quant_error to 2e-6 (relative), not to the last bit (nor do searches that
+ * take different forms).  The same call gives the same result.
  * The call waits for the result: a calibration call, not a hot-path call (not for a stream under
- * capture).  Besides the workspace a search uses static device memory (as rq_quant_error_noalloc does) and 256 KB of
+ * capture).  Besides the workspace a search uses static device memory (as rq_quant_error_noalloc does: 16.9 MB, 1 MB
+ * for each of 16 searches at once, part of the library on every device it is loaded on) and 256 KB of
  * device and 33 KB of pinned host memory that the first search on a device allocates and that stay until the process
  * ends; where the pinned memory cannot be had the results are copied back on `stream` instead, and more than 16 searches
  * at once on a device allocate 1 MB for the call.  Searches may run on any number of threads and streams; one at a
- * time per device takes the form whose one launch walks the whole search.
+ * time per device takes the "gbs_resident" form, where others take its steps one launch at a time.
  *   eps          [in]  bracket width to stop at, > 0
  *   max_evals    [in]  1 .. 256
  *   workspace    [in]  DEVICE, >= rq_gbs_workspace(rows) bytes, 8-byte aligned, scratch

@@ -10,13 +10,14 @@
 // a value costs one LDS addition (two if negative) whatever the number of ratios, where evaluating a ratio costs five
 // vector operations a value.  (At a threshold itself both codes have the same error, so rounding there does not matter.)
 //
-// u is kept in fixed point, V = u 2^FRAC < 2^28, the fp32 product rounded to an integer: sums and counts are exact integers, the
-// result does not depend on the order of the additions, and the three terms, which cancel to 1 / 250 of the first,
-// are formed in fp64 (relative error of a search's values against 64 bits on six shapes 2.5e-8 - 6.5e-8 rms, with fp32 sums of
-// squares 3.2e-8 - 7.3e-8).  A cell is one 64-bit word, the count in the upper 16 bits (at most 2^15 values a row) and the sum of
-// V (below 2^43) under it, so a value is one ds_add_u64.  The last threshold, which only negative values have, has a
-// histogram of its own in cells of 2 Q + 1 units: 24.5 KB in all for b = 3, 57 KB for b = 4, where two signed histograms
-// would take 49 and 114.
+// u is kept in fixed point, V = u 2^FRAC < 2^28, the fp32 product rounded to an integer: sums and counts are exact
+// integers, the result does not depend on the order of the additions, and the three terms, which cancel to 1 / 250 of the
+// first, are formed in fp64 (relative error of a search's values against 64 bits, rms: normal rows 2.2e-8 - 1.1e-7, heavy
+// tails with outliers 2.4e-8 - 2.1e-7, at most 4.3e-7; with fp32 sums of squares 2.2e-8 - 1.3e-7, 2.5e-8 - 2.4e-7 and
+// 6.1e-7; a row whose energy is in one value has that value's rounding, 1.8e-8 - 1.2e-7 and 1.8e-8 - 1.0e-7).  A cell is
+// one 64-bit word, the count in the upper 16 bits (at most 2^15 values a row) and the sum of V (below 2^43) under it, so a
+// value is one ds_add_u64.  The last threshold, which only negative values have, has a histogram of its own in cells of 2 Q
+// + 1 units: 24.5 KB in all for b = 3, 57 KB for b = 4, where two signed histograms would take 49 and 114.
 #pragma once
 #include "search_state.h"
 #include "wave_common.h"

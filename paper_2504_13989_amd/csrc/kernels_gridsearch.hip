@@ -3,10 +3,11 @@
 // the bracket or below), and the error of a row at all 511 ratios costs little more than the rotation (error_grid.h).  One
 // kernel passes over the rows once and leaves each workgroup's sums, a second adds them up and walks the search; nothing
 // is evaluated twice and no step waits for another.
-// Bound: latency.  512 x 4096, b = 3: 13 us in the first kernel (launch and cold rows 4, rotation 1.5, the additions of two
-// rows a compute unit 2.3, about 20 cycles of LDS each, the passes over the histogram 3), 6 in the second (launch, 1 MB
-// of sums, the walk, results over the bus).  A search, us a call, resident or batched form before -> now: 512 x 4096 46 ->
-// 25, 1024 x 8192 90 -> 41, 78 x 5120 48 -> 26, 960 x 14336 199 -> 64, 512 x 18944 164 -> 42 - 51.
+// Bound: latency (vector port 24 - 30 % busy).  512 x 4096, b = 3: 12 us in the first kernel (launch, rotation 1.5, the
+// additions of two rows a compute unit 2.3, about 20 cycles of LDS each, the passes over the histogram 3), 16 on heavy-tailed
+// rows, whose values share fewer cells and LDS banks, 7 in the second (launch, 1 MB of sums, the walk, results over the bus).
+// A search, us a call, resident or batched form before -> now: 512 x 4096 heavy-tailed rows 46.4 -> 28.5; normal rows 47 -> 24,
+// 512 x 8192 61 -> 28, 512 x 3584 45 -> 25, 512 x 5120 94 -> 29, 512 x 14336 135 -> 34, 512 x 18944 169 -> 40, 512 x 896 70 -> 45.
 #include "error_grid.h"
 #include "row_rotation.h"
 
