@@ -137,8 +137,10 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
     const int cl = CB == 4 ? c : c & ((1 << CB) - 1);    // 8-column chunk inside that row
 
     u32x4 A[KK];
+    if constexpr (SINK != kWgGrid) {
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) A[kk] = a.tiles[(wave * KK + kk) * 64 + lane];
+        for (int kk = 0; kk < KK; ++kk) A[kk] = a.tiles[(wave * KK + kk) * 64 + lane];
+    }
     // (uniform, but computed by vector instructions: moved to scalar registers)
     auto uniform = [](float x) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x))); };
     const float c1h = uniform((float)a.c1), c1l = uniform((float)(a.c1 - (double)c1h));
@@ -234,6 +236,15 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
     if (threadIdx.x < RPW * 16) wmax[threadIdx.x] = 0.0f;
     for (int64_t pass = blockIdx.x; pass < n_pass; pass += gridDim.x) {
         if (!PF) load_pass(pass);
+        if constexpr (SINK == kWgGrid) {
+            // Beside the row in every pass: held, the tiles leave too few registers to the histogram's phases (6 - 35 spilled, now 0 - 10
+            // and 24 - 34 for the smallest block).  A search on 512 rows, b = 3, us a call: 8960 wide 46.0 -> 43.5, 18944 43.3 -> 42.3,
+            // 28672 55.2 -> 51.3, 14336 (b = 4) 40.7 -> 40.3, 896 wide unchanged.
+            int l = lane;
+            asm volatile("" : "+v"(l));
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) A[kk] = a.tiles[(wave * KK + kk) * 64 + l];
+        }
         if constexpr (SRC != 0) {
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
