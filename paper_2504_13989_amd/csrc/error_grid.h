@@ -17,7 +17,14 @@
 // 6.1e-7; a row whose energy is in one value has that value's rounding, 1.8e-8 - 1.2e-7 and 1.8e-8 - 1.0e-7).  A cell is
 // one 64-bit word, the count in the upper 16 bits (at most 2^15 values a row) and the sum of V (below 2^43) under it, so a
 // value is one ds_add_u64.  The last threshold, which only negative values have, has a histogram of its own in cells of 2 Q
-// + 1 units: 24.5 KB in all for b = 3, 57 KB for b = 4, where two signed histograms would take 49 and 114.
+// + 1 units: 25.5 KB in all for b = 3, 58 KB for b = 4, where two signed histograms would take 50 and 115.
+//
+// The last cell of either histogram takes whatever lies beyond every threshold: a sixth of a normal row, most of a row that
+// an outlier channel makes bimodal.  Lanes that add to one address are served one after the other, so these two cells have
+// sixteen words each; a suffix sum over them is that of one cell.  A search on heavy-tailed rows, us a call: 512 x 4096
+// 28.6 -> 23.5, 1024 x 3584 38.2 -> 31.9, 300 x 8192 33.9 -> 26.4, 512 x 8960 43.5 -> 36.1, 512 x 14336 (b = 4) 45.3 -> 34.8, 512 x 18944
+// 52.6 -> 37.1; normal rows, 512 x 4096 25.1 -> 23.6.  (The lanes' shares summed in registers and added once a wave: 25.4, 35.1, -, 46,
+// 40.7, 43.3; normal rows 25.4.)
 #pragma once
 #include "search_state.h"
 #include "wave_common.h"
@@ -25,11 +32,14 @@
 namespace rq {
 namespace {
 
-template <int BITS>
+template <int BITS, int SPREAD = kGridSpread>
 struct ErrorGrid {
     static constexpr int LEVELS = (1 << BITS) - 1, Q = (1 << (BITS - 1)) - 1, FRAC = BITS == 3 ? 15 : 14;
     static constexpr int LAST = 2 * Q + 1;                           // units a step of the last threshold
-    static constexpr int CELLS = grid_cells(BITS), WORDS = grid_words(BITS);
+    static constexpr int CELLS = grid_cells(BITS);
+    static constexpr int FINE = CELLS + SPREAD - 1, COARSE = kGridRatios + SPREAD - 1;    // words of the histograms
+    static constexpr int WORDS = FINE + COARSE;
+    static_assert(WORDS == grid_words(BITS) + 2 * (SPREAD - 1) && SPREAD <= kGridSpread && (SPREAD & (SPREAD - 1)) == 0, "see search_rule.h");
     static constexpr size_t bytes() { return (size_t)WORDS * sizeof(uint64_t); }
     static constexpr float kTiny = 1e-30f;                           // rows below it: their squares are zero in fp32
 
@@ -47,18 +57,20 @@ struct ErrorGrid {
     }
 
     // One value (y with its sign) into the histogram; q2 accumulates V^2.
-    static __device__ __forceinline__ void add(uint64_t* hist, float y, float s, double& q2) {
+    static __device__ __forceinline__ void add(uint64_t* hist, float y, float s, double& q2, int lane) {
         // (the bound holds by itself in a finite row; it is for infinities and NaN, whose conversion is undefined: the minimum of a
         // NaN and a number is the number)
         const uint32_t v = (uint32_t)__builtin_rintf(__builtin_fminf(__builtin_fabsf(y) * s, 0x1p28f));
         q2 = fma((double)v, (double)v, q2);
         const uint32_t u = v >> FRAC;
         const unsigned long long word = (1ull << 48) | v;
-        if (u > 0) atomicAdd(reinterpret_cast<unsigned long long*>(hist) + min(u, (uint32_t)CELLS - 1u), word);
+        auto* const h = reinterpret_cast<unsigned long long*>(hist);
+        const uint32_t top = (uint32_t)(CELLS - 1 + (lane & (SPREAD - 1)));      // (any of the last cell's words will do)
+        if (u > 0) atomicAdd(h + min(u, top), word);
         if (y < 0.0f && u >= (uint32_t)LAST) {
-            // u / LAST by multiplication: exact for the u there are (up to 2^(b + 10)); what lies beyond is cut off
+            // u / LAST by multiplication: exact for the u there are (up to 2^(b + 10))
             const uint32_t c = BITS == 3 ? (u * 9363u) >> 16 : (u * 34953u) >> 19;
-            atomicAdd(reinterpret_cast<unsigned long long*>(hist) + CELLS + min(c, (uint32_t)kGridRatios - 1u), word);
+            atomicAdd(h + FINE + min(c, top - (uint32_t)(CELLS - kGridRatios)), word);
         }
     }
 
@@ -116,31 +128,31 @@ struct ErrorGrid {
     }
 
     // The histogram of a row to suffix sums, by the NT threads (whole waves, numbered by t) that share it, and the row's
-    // sum of V^2 from the threads' q2.  `tot`: 3 x 16 words of LDS of the row.  Every thread of the workgroup calls it.
-    static __device__ __forceinline__ double finish(uint64_t* hist, double q2, int t, int NT, uint64_t (*tot)[16]) {
+    // sum of V^2 from the threads' q2.  `tot`: three words of LDS for each wave of the row.  Every thread of the workgroup calls it.
+    static __device__ __forceinline__ double finish(uint64_t* hist, double q2, int t, int NT, uint64_t (*tot)[3]) {
         const int lane = t & 63, wave = t >> 6, nw = NT >> 6;
         // (odd shares: consecutive lanes then start in different banks)
         asm volatile("" : "+v"(t));
-        const int ca = ((CELLS + NT - 1) / NT) | 1, cb = ((kGridRatios + NT - 1) / NT) | 1;
-        const int a0 = min(t * ca, CELLS), a1 = min(a0 + ca, CELLS);
-        const int b0 = min(t * cb, kGridRatios), b1 = min(b0 + cb, kGridRatios);
-        uint64_t* const coarse = hist + CELLS;
+        const int ca = ((FINE + NT - 1) / NT) | 1, cb = ((COARSE + NT - 1) / NT) | 1;
+        const int a0 = min(t * ca, FINE), a1 = min(a0 + ca, FINE);
+        const int b0 = min(t * cb, COARSE), b1 = min(b0 + cb, COARSE);
+        uint64_t* const coarse = hist + FINE;
         const uint64_t sa = chunk_sum(hist, a0, a1), sb = chunk_sum(coarse, b0, b1);
         uint64_t all_a, all_b, xa = lanes_from(sa, lane, all_a) - sa, xb = lanes_from(sb, lane, all_b) - sb;
         q2 = lanes_sum(q2);
         if (lane == 0) {
-            tot[0][wave] = all_a;
-            tot[1][wave] = all_b;
-            tot[2][wave] = (uint64_t)__double_as_longlong(q2);
+            tot[wave][0] = all_a;
+            tot[wave][1] = all_b;
+            tot[wave][2] = (uint64_t)__double_as_longlong(q2);
         }
         __syncthreads();
         q2 = 0.0;
         for (int w = 0; w < nw; ++w) {
             if (w > wave) {
-                xa += tot[0][w];
-                xb += tot[1][w];
+                xa += tot[w][0];
+                xb += tot[w][1];
             }
-            q2 += __longlong_as_double((long long)tot[2][w]);
+            q2 += __longlong_as_double((long long)tot[w][2]);
         }
         chunk_suffix(hist, a0, a1, xa);
         chunk_suffix(coarse, b0, b1, xb);
@@ -152,7 +164,7 @@ struct ErrorGrid {
     static __device__ __forceinline__ double error(const uint64_t* hist, int m, double q2, const Scale& sc) {
         asm volatile("" : "+v"(m));                                  // (or the addresses of all ratios are kept from row to row)
         constexpr uint64_t kSum = (1ull << 48) - 1;
-        uint64_t x = hist[CELLS + m], a = x & kSum;
+        uint64_t x = hist[FINE + m], a = x & kSum;
         uint32_t b = (uint32_t)LAST * (uint32_t)(x >> 48);
 #pragma unroll
         for (int j = 1; j <= Q; ++j) {

@@ -4,10 +4,10 @@
 // kernel passes over the rows once and leaves each workgroup's sums, a second adds them up and walks the search; nothing
 // is evaluated twice and no step waits for another.
 // Bound: latency (vector port 24 - 30 % busy).  512 x 4096, b = 3: 12 us in the first kernel (launch, rotation 1.5, the
-// additions of two rows a compute unit 2.3, about 20 cycles of LDS each, the passes over the histogram 3), 16 on heavy-tailed
-// rows, whose values share fewer cells and LDS banks, 7 in the second (launch, 1 MB of sums, the walk, results over the bus).
-// A search, us a call, resident or batched form before -> now: 512 x 4096 heavy-tailed rows 46.4 -> 28.5; normal rows 47 -> 24,
-// 512 x 8192 61 -> 28, 512 x 3584 45 -> 25, 512 x 5120 94 -> 29, 512 x 14336 135 -> 34, 512 x 18944 169 -> 40, 512 x 896 70 -> 45.
+// additions of two rows a compute unit 2.3, about 20 cycles of LDS each, the passes over the histogram 3), 7 in the second
+// (launch, 1 MB of sums, the walk, results over the bus).
+// A search, us a call, resident or batched form before -> now: 512 x 4096 heavy-tailed rows 46.4 -> 23.5; normal rows 47 -> 23.6,
+// 512 x 8192 61 -> 27, 512 x 3584 45 -> 25, 512 x 5120 94 -> 29, 512 x 14336 135 -> 34, 512 x 18944 169 -> 37, 512 x 896 70 -> 45.
 #include "error_grid.h"
 #include "row_rotation.h"
 
@@ -16,7 +16,7 @@ namespace {
 
 // Rows held in registers, eight waves a row, `conc` rows (one or two) a workgroup at a time, each with a histogram of its
 // own.  Where a row is rotated by fewer waves, W, all eight repeat the rotation and share the values: the additions and
-// the passes over the histogram take longer than the rotation, and LDS (57 KB a row for b = 4) leaves no room for more
+// the passes over the histogram take longer than the rotation, and LDS (58 KB a row for b = 4) leaves no room for more
 // rows in their place (one row a wave: 2048 x 1024, b = 4 65 us a search, 512 x 4096 on four waves a row 26.7).
 template <typename Rows, int BITS>
 __global__ __launch_bounds__(1024) void k_grid_rows(WaveArgs a, int pb, int conc, double inv_norm, GbsDev* dev) {
@@ -25,7 +25,7 @@ __global__ __launch_bounds__(1024) void k_grid_rows(WaveArgs a, int pb, int conc
     static_assert(NT >= kGridRatios - 1, "a ratio a thread");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     __shared__ float wmax[16];
-    __shared__ uint64_t tot[2][3][16];
+    __shared__ uint64_t tot[2][8][3];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rsub = wave >> 3, seg = wave % W, share = (wave & 7) / W, t = tid - rsub * NT;
@@ -37,8 +37,11 @@ __global__ __launch_bounds__(1024) void k_grid_rows(WaveArgs a, int pb, int conc
         const int64_t row = row0 + rsub;
         const bool live = row < a.rows;
         float v[NVAL], flip = 1.0f, m = 0.0f;
+        int l = lane;
+        // (rows of 8192: the operand tiles' address held from row to row is two registers too many)
+        if constexpr (Rows::NVAL == 32 && W == 4) asm volatile("" : "+v"(l));
         if (live) {
-            m = Rows::rotate(a, pb, row, seg, lane, v, &flip);
+            m = Rows::rotate(a, pb, row, seg, l, v, &flip);
         } else {
 #pragma unroll
             for (int i = 0; i < NVAL; ++i) v[i] = 0.0f;
@@ -52,7 +55,7 @@ __global__ __launch_bounds__(1024) void k_grid_rows(WaveArgs a, int pb, int conc
         double q2 = !(__builtin_fabsf(v[0]) < __builtin_inff()) || !(m < __builtin_inff()) ? __builtin_nan("") : 0.0;
 #pragma unroll
         for (int i = 0; i < NVAL; ++i)
-            if (i % SHARES == share) Grid::add(hist, v[i] * flip, sc.s, q2);
+            if (i % SHARES == share) Grid::add(hist, v[i] * flip, sc.s, q2, l);
         __syncthreads();
         q2 = Grid::finish(hist, q2, t, NT, tot[rsub]);
         if (t > 0 && t < kGridRatios) sum += Grid::error(hist, t, q2, sc);

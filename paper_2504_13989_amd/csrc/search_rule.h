@@ -35,8 +35,9 @@ constexpr int kStepsAhead = 3;                               // steps of a searc
 constexpr int kGridRatios = 512, kGridGroups = 256;          // (and the most workgroups that take part)
 constexpr int grid_cells(int bits) { return (2 * ((1 << (bits - 1)) - 1) - 1) * (kGridRatios - 1) + 1; }
 constexpr int grid_words(int bits) { return grid_cells(bits) + kGridRatios; }
+constexpr int kGridSpread = 16;                              // words that share the last cell of either histogram
 // Rows whose histograms a workgroup can hold side by side: two, one, or none where not even one fits beside `other` bytes of
-// LDS and what the kernels keep in static arrays (up to 832 bytes).
+// LDS and 1 KB for what the kernels keep in static arrays (up to 640 bytes) and the last cells' further words (240 a row).
 constexpr int grid_rows_beside(int bits, int64_t max_lds, int64_t other = 0) {
     const int64_t row = 8 * (int64_t)grid_words(bits), left = max_lds - other - 1024;
     return left >= 2 * row ? 2 : left >= row ? 1 : 0;

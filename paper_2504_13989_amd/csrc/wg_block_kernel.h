@@ -208,10 +208,12 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
             }
         }
     };
-    using Grid = ErrorGrid<BITS>;
+    // (two waves a pass, which take its four rows one after the other: a sixteenth of a row's values meet in an instruction, and
+    // the further words cost what they gain; 512 x 896, b = 4 59.0 us a search with them, 58.1 without)
+    using Grid = ErrorGrid<BITS, KK == 1 ? 1 : kGridSpread>;
     constexpr int SUMS = SINK == kWgGrid ? (kGridRatios - 1 + 64 * (2 * KK - 1) - 1) / (64 * (2 * KK - 1)) : 1;   // ratios of a thread
     [[maybe_unused]] double sum[SUMS];
-    __shared__ uint64_t tot[SINK == kWgGrid ? 3 : 1][16];
+    __shared__ uint64_t tot[SINK == kWgGrid ? 16 : 1][3];
     if constexpr (SINK == kWgGrid) {
 #pragma unroll
         for (int k = 0; k < SUMS; ++k) sum[k] = 0.0;
@@ -487,7 +489,7 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
 #pragma unroll
                     for (int nt = 0; nt < 8; ++nt)
 #pragma unroll
-                        for (int ip = 0; ip < 4; ++ip) Grid::add(hist, acc[nt][ip] * fl, sc.s, q2);
+                        for (int ip = 0; ip < 4; ++ip) Grid::add(hist, acc[nt][ip] * fl, sc.s, q2, lane);
                 }
                 __syncthreads();
                 q2 = Grid::finish(hist, q2, t, NT, tot);
