@@ -22,6 +22,8 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # matrix-core results go straight to VGPRs (no AGPR copies in the wave kernels)
     "-mllvm", "-amdgpu-mfma-vgpr-form",
+    # the first plain parameters of a kernel are in scalar registers when a wave starts (see RQ_WAVE_PARAMS)
+    "-mllvm", "-amdgpu-kernarg-preload-count=8",
     "-Wall", "-Wno-unused-command-line-argument", "-Wno-unknown-attributes",
 ]
 

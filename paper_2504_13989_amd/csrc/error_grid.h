@@ -17,7 +17,7 @@
 // 6.1e-7; a row whose energy is in one value has that value's rounding, 1.8e-8 - 1.2e-7 and 1.8e-8 - 1.0e-7).  A cell is
 // one 64-bit word, the count in the upper 16 bits (at most 2^15 values a row) and the sum of V (below 2^43) under it, so a
 // value is one ds_add_u64.  The last threshold, which only negative values have, has a histogram of its own in cells of 2 Q
-// + 1 units: 25.5 KB in all for b = 3, 58 KB for b = 4, where two signed histograms would take 50 and 115.
+// + 1 units: 25 KB in all for b = 3, 57 KB for b = 4, where two signed histograms would take 50 and 115.
 //
 // The last cell of either histogram takes whatever lies beyond every threshold: a sixth of a normal row, most of a row that
 // an outlier channel makes bimodal.  Lanes that add to one address are served one after the other, so these two cells have

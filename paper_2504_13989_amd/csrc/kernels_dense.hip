@@ -277,7 +277,7 @@ int launch_dense(const WaveArgs& a, int n, int bits, hipStream_t s) {
     } else {
         if (bits == 4) go(k_dense_block<MTW, NT, 4, false>); else go(k_dense_block<MTW, NT, 3, false>);
     }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 }  // namespace

@@ -103,7 +103,7 @@ int dequantize_rows(const uint32_t* codes, const float* scales, const float* min
         if (bits == 4) launch_kernel((k_dequantize<4, false>), grid, dim3(kThreads), 0, s, c, scales, mins, rows, n, magic, rows_per_group, Y, y16);
         else launch_kernel((k_dequantize<3, false>), grid, dim3(kThreads), 0, s, c, scales, mins, rows, n, magic, rows_per_group, Y, y16);
     }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 }  // namespace rq

@@ -283,7 +283,7 @@ int f64_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float clip, uint
                     scales, (double)clip,
                     1.0 / (std::sqrt((double)a.n) * (double)((1 << a.bits) - 1))};
     launch_kernel(pick(a.log2m, a.p > 1, a.bits), group_grid(groups, sh.threads), dim3(sh.threads), sh.lds, s, f);
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 }  // namespace rq

@@ -521,7 +521,7 @@ int generic_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float clip, 
         launch_kernel(k_generic_rotate_quantize<float>, dim3((unsigned)a.rows), dim3(kThreads), bytes, s, a,
                            clip, codes, scales);
     }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 int generic_rotate_quantize_asym(const rq_hadamard* h, const RowArgs& a, float clip, uint32_t* codes,
@@ -536,7 +536,7 @@ int generic_rotate_quantize_asym(const rq_hadamard* h, const RowArgs& a, float c
         launch_kernel(k_generic_rotate_quantize_asym<float>, dim3((unsigned)a.rows), dim3(kThreads), bytes,
                            s, a, clip, codes, scales, mins);
     }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 int generic_rotate(const rq_hadamard* h, const RowArgs& a, int transpose, const OutArgs& o,
@@ -544,7 +544,7 @@ int generic_rotate(const rq_hadamard* h, const RowArgs& a, int transpose, const 
     if (a.rows > 0x7fffffffLL) return RQ_ERR_ARG;
     launch_kernel(k_generic_rotate, dim3((unsigned)a.rows), dim3(kThreads), lds_bytes(h), s, a,
                        transpose, o);
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 int generic_dequant_rotate(const rq_hadamard* h, const RowArgs& a, const uint32_t* codes,
@@ -553,7 +553,7 @@ int generic_dequant_rotate(const rq_hadamard* h, const RowArgs& a, const uint32_
     if (a.rows > 0x7fffffffLL) return RQ_ERR_ARG;
     launch_kernel(k_generic_dequant_rotate, dim3((unsigned)a.rows), dim3(kThreads), lds_bytes(h), s,
                        a, codes, scales, mins, transpose, o);
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 int plain_quantize(const void* X, int dtype, int64_t rows, int d, int64_t ld, int bits, float clip,
@@ -561,7 +561,7 @@ int plain_quantize(const void* X, int dtype, int64_t rows, int d, int64_t ld, in
     if (rows > 0x7fffffffLL) return RQ_ERR_ARG;
     launch_kernel(k_plain_quantize, dim3((unsigned)rows), dim3(kThreads), 0, s, X, dtype, d, ld,
                        bits, clip, codes, scales);
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 int reduce_chunks(double* partial, int64_t rows, int n_clips, const ClipList* dev, int64_t* count, int64_t* stride, hipStream_t s) {
@@ -573,7 +573,7 @@ int reduce_chunks(double* partial, int64_t rows, int n_clips, const ClipList* de
     launch_kernel(k_reduce_chunks, dim3((unsigned)chunks), dim3(kThreads), 0, s, partial, rows, n_clips, dev);
     *count = chunks;
     *stride = kChunkRows;
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 int reduce_partials(double* partial, int64_t rows, int n_clips, float* mse, hipStream_t s) {
@@ -581,21 +581,21 @@ int reduce_partials(double* partial, int64_t rows, int n_clips, float* mse, hipS
     const int rc = reduce_chunks(partial, rows, n_clips, nullptr, &count, &stride, s);
     if (rc != RQ_OK) return rc;
     launch_kernel(k_reduce_partials, dim3(n_clips), dim3(kThreads), 0, s, partial, count, stride, rows, n_clips, mse);
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 int generic_quant_error_asym(const rq_hadamard* h, const RowArgs& a, const ClipArg& clips, double* partial, hipStream_t s) {
     if (a.rows > 0x7fffffffLL || a.n % 128 != 0) return RQ_ERR_ARG;
     if (a.rows > 0)
         launch_kernel(k_generic_quant_error_asym, dim3((unsigned)a.rows), dim3(kThreads), lds_bytes(h), s, a, clips, partial);
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 int generic_quant_error(const rq_hadamard* h, const RowArgs& a, const ClipArg& clips, double* partial, hipStream_t s) {
     if (a.rows > 0x7fffffffLL) return RQ_ERR_ARG;
     if (a.rows > 0)
         launch_kernel(k_generic_quant_error, dim3((unsigned)a.rows), dim3(kThreads), lds_bytes(h), s, a, clips, partial);
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 }  // namespace rq

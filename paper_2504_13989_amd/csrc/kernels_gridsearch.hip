@@ -16,7 +16,7 @@ namespace {
 
 // Rows held in registers, eight waves a row, `conc` rows (one or two) a workgroup at a time, each with a histogram of its
 // own.  Where a row is rotated by fewer waves, W, all eight repeat the rotation and share the values: the additions and
-// the passes over the histogram take longer than the rotation, and LDS (58 KB a row for b = 4) leaves no room for more
+// the passes over the histogram take longer than the rotation, and LDS (57 KB a row for b = 4) leaves no room for more
 // rows in their place (one row a wave: 2048 x 1024, b = 4 65 us a search, 512 x 4096 on four waves a row 26.7).
 template <typename Rows, int BITS>
 __global__ __launch_bounds__(1024) void k_grid_rows(WaveArgs a, int pb, int conc, double inv_norm, GbsDev* dev) {
@@ -155,7 +155,7 @@ int launch_rows(const rq_hadamard* h, const RowArgs& a, const WaveArgs& w, int p
     if (!allow_lds(fn, lds)) return RQ_ERR_NO_ORDER;
     launch_kernel(fn, dim3((unsigned)*groups), dim3((unsigned)(512 * conc)), lds, s, w, pb, conc,
                   1.0 / ((double)a.n * (double)a.n), dev);
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 template <int BITS, bool F16>
@@ -199,7 +199,7 @@ int gbs_grid(const rq_hadamard* h, const RowArgs& a, GbsDev* dev, GbsOut* out, d
                                : (f16 ? rows_pass<3, true>(h, a, w, &groups, dev, s) : rows_pass<3, false>(h, a, w, &groups, dev, s));
     if (rc != RQ_OK) return rc;
     launch_kernel(k_grid_walk, dim3(kGridRatios / kWalkRatios), dim3(kWalkThreads), 0, s, dev, out, groups, a.rows, eps, max_evals);
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 }  // namespace rq

@@ -120,7 +120,7 @@ __global__ __launch_bounds__(64) void k_plain_asym(const void* X, int64_t n_grou
     constexpr float kMidF = (float)kMid;
     const float c1f = (float)(kL / clip), clipf = (float)clip;
     // a wave takes U passes of four groups per iteration, all loads issued before the first is used
-    for (int64_t g0 = (int64_t)blockIdx.x * (4 * U); g0 < n_groups; g0 += (int64_t)gridDim.x * (4 * U)) {
+    for (int64_t g0 = (int64_t)blockIdx.x * (4 * U); g0 < n_groups; g0 += (int64_t)kMostGroups * (4 * U)) {
         Raw8<DT> raw[U];
         const int left = n_groups - g0 < 4 * U ? (int)(n_groups - g0) : 4 * U;
         if (left == 4 * U && ld == (int64_t)gpr * 128) {
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(64) void k_plain_short(const void* X, int64_t rows,
     const bool has = c * 8 < d;                                   // d is a multiple of 32: whole quads of lanes
     const int row_dwords = d * BITS / 32;
     const float c1f = (float)(kL / clip), clipf = (float)clip;
-    for (int64_t r0 = (int64_t)blockIdx.x * (RPP * U); r0 < rows; r0 += (int64_t)gridDim.x * (RPP * U)) {
+    for (int64_t r0 = (int64_t)blockIdx.x * (RPP * U); r0 < rows; r0 += (int64_t)kMostGroups * (RPP * U)) {
         float x[U][8];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -325,7 +325,7 @@ void launch_short(int bits, hipStream_t s, const void* X, int64_t rows, int d, i
                   uint32_t* codes, float* scales) {
     constexpr int U = 4;
     const int64_t iters = (rows + (64 / LPR) * U - 1) / ((64 / LPR) * U);
-    const int64_t cap = 1 << 24;
+    const int64_t cap = kMostGroups;
     const unsigned grid = (unsigned)(iters < cap ? iters : cap);
     if (bits == 4) launch_kernel((k_plain_short<4, DT, LPR, U>), dim3(grid), dim3(64), 0, s, X, rows, d, ld, clip, codes, scales);
     else launch_kernel((k_plain_short<3, DT, LPR, U>), dim3(grid), dim3(64), 0, s, X, rows, d, ld, clip, codes, scales);
@@ -359,14 +359,14 @@ int plain_quantize_asym(const void* X, int dtype, int64_t rows, int d, int64_t l
     const int gpr = d / RQ_GROUP;
     const int64_t n_groups = rows * gpr;
     const int64_t passes = (n_groups + 15) / 16;          // 4 groups x 4 passes per wave iteration
-    const int64_t cap = 1 << 24;
+    const int64_t cap = kMostGroups;
     const unsigned grid = (unsigned)(passes < cap ? passes : cap);
     const int esz = dtype == RQ_F32 ? 4 : 2;
     const bool aligned = (reinterpret_cast<uintptr_t>(X) & 15) == 0 && (ld * esz) % 16 == 0;
     if (dtype == RQ_BF16) launch_dt<0>(aligned, bits, grid, s, X, n_groups, gpr, ld, (double)clip, codes, scales, mins);
     else if (dtype == RQ_F32) launch_dt<1>(aligned, bits, grid, s, X, n_groups, gpr, ld, (double)clip, codes, scales, mins);
     else launch_dt<2>(aligned, bits, grid, s, X, n_groups, gpr, ld, (double)clip, codes, scales, mins);
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 bool plain_short_supports(const void* X, int dtype, int d, int64_t ld) {
@@ -379,7 +379,7 @@ int plain_short_quantize(const void* X, int dtype, int64_t rows, int d, int64_t 
     if (dtype == RQ_BF16) launch_short_dt<0>(bits, s, X, rows, d, ld, (double)clip, codes, scales);
     else if (dtype == RQ_F32) launch_short_dt<1>(bits, s, X, rows, d, ld, (double)clip, codes, scales);
     else launch_short_dt<2>(bits, s, X, rows, d, ld, (double)clip, codes, scales);
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 }  // namespace rq

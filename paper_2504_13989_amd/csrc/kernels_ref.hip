@@ -45,7 +45,7 @@ int stream_reference(const void* X, int64_t rows, int n, int64_t ld, int bits, u
     const uint16_t* x = static_cast<const uint16_t*>(X);
     if (bits == 4) launch_kernel(k_stream_reference<4>, grid, block, 0, s, x, rows, n / 512, ld, codes, scales);
     else launch_kernel(k_stream_reference<3>, grid, block, 0, s, x, rows, n / 512, ld, codes, scales);
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 }  // namespace rq

@@ -34,6 +34,23 @@ struct RotArgs {
     const float* mins = nullptr;      // asymmetric group codes, one group per row (n = 128)
     float sqrt_n = 0.0f;
 };
+// The kernels' parameters (see RQ_WAVE_PARAMS): one pointer for the rows or the codes.
+struct RotRest {
+    int64_t ld_out;
+    float inv, sqrt_n;
+    const float* mins;
+};
+#define RQ_ROT_PARAMS u64x4 p0_, u64x2 p1_, uint64_t p2_, RotRest rest_
+#define RQ_ROT_ARGS(a)                                                                                                     \
+    const RotArgs a{global_ptr<const uint16_t>(p0_[0]), (int64_t)p0_[2], (int)(uint32_t)p2_, (int64_t)p0_[3],              \
+                    global_ptr<const u32x4>(p0_[1]), global_ptr<uint8_t>(p1_[1]), (int)(p2_ >> 32), rest_.ld_out, rest_.inv, \
+                    global_ptr<const uint32_t>(p0_[0]), global_ptr<const float>(p1_[0]), rest_.mins, rest_.sqrt_n}
+template <typename K>
+void launch_rot(K kernel, unsigned grid, hipStream_t s, const RotArgs& a) {
+    launch_kernel(kernel, dim3(grid), dim3(64), 0, s,
+                  u64x4{a.codes ? param(a.codes) : param(a.X), param(a.tiles), (uint64_t)a.rows, (uint64_t)a.ld},
+                  u64x2{param(a.scales), param(a.Y)}, param(a.d, a.d_out), RotRest{a.ld_out, a.inv, a.sqrt_n, a.mins});
+}
 
 // The lane's 8 consecutive codes (group idx of the row: codes 8 idx .. 8 idx + 7) as a matrix-core
 // operand: four dwords of two bf16 patterns 0x4300 | u each.  Signed codes are two's complement fields:
@@ -68,7 +85,8 @@ __device__ __forceinline__ u32x4 code_operand(const uint32_t* base, const CodeAt
 
 // n = 512 T: one wave per row.
 template <int T, bool F16, int OUT, int SRC = 0>
-__global__ __launch_bounds__(64) void k_wave_rotate(RotArgs a) {
+__global__ __launch_bounds__(64) void k_wave_rotate(RQ_ROT_PARAMS) {
+    RQ_ROT_ARGS(a);
     const int lane = threadIdx.x;
     const int g = lane >> 4, cphys = lane & 15;
     const int c = (cphys & 4) ? (cphys ^ 3) : cphys;
@@ -84,7 +102,7 @@ __global__ __launch_bounds__(64) void k_wave_rotate(RotArgs a) {
     const float corr = (SRC && chunk == 0) ? -(float)(512 * T) * (float)(128 + (1 << (SRC ? SRC - 1 : 0))) : 0.0f;
     const float sgn = (__builtin_popcount(c) & 1) ? -1.0f : 1.0f;
     const CodeAt cl = code_at<SRC ? SRC : 4>(chunk);
-    for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
+    for (int64_t row = blockIdx.x; row < a.rows; row += kMostGroups) {
         f32x4 acc[T][2];
         u32x4 raw[T];
         if constexpr (SRC == 0) {
@@ -141,7 +159,8 @@ __global__ __launch_bounds__(64) void k_wave_rotate(RotArgs a) {
 
 // n = 32 << CB (128, 256, 512): 16 >> CB rows per wave pass, U passes in flight.
 template <int CB, int U, bool F16, int OUT, int SRC = 0, bool ASYM = false>
-__global__ __launch_bounds__(64) void k_wave_rotate_short(RotArgs a) {
+__global__ __launch_bounds__(64) void k_wave_rotate_short(RQ_ROT_PARAMS) {
+    RQ_ROT_ARGS(a);
     static_assert(!ASYM || (SRC != 0 && CB == 2), "group codes: one group per row");
     constexpr int RPW = 16 >> CB;
     constexpr int ROW_DWORDS = SRC ? (32 << CB) * SRC / 32 : 0;
@@ -163,7 +182,7 @@ __global__ __launch_bounds__(64) void k_wave_rotate_short(RotArgs a) {
     const float corr = (SRC && chunk == 0) ? -(float)(32 << CB) * (float)(128 + (ASYM ? 0 : 1 << (SRC ? SRC - 1 : 0))) : 0.0f;
     const CodeAt cl = code_at<SRC ? SRC : 4>(chunk);
     const int64_t n_super = (a.rows + SUPER - 1) / SUPER;
-    for (int64_t sgi = blockIdx.x; sgi < n_super; sgi += gridDim.x) {
+    for (int64_t sgi = blockIdx.x; sgi < n_super; sgi += kMostGroups) {
         const int64_t row0 = sgi * SUPER;
         u32x4 raw[U];
         float ks[U], add0[U];
@@ -213,7 +232,7 @@ __global__ __launch_bounds__(64) void k_wave_rotate_short(RotArgs a) {
 
 template <int T>
 void launch_long(const RotArgs& a, bool f16, int out, unsigned grid, hipStream_t s) {
-    auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, a); };
+    auto go = [&](auto kernel) { launch_rot(kernel, grid, s, a); };
     if (f16) {
         if (out == 0) go(k_wave_rotate<T, true, 0>); else if (out == 1) go(k_wave_rotate<T, true, 1>); else go(k_wave_rotate<T, true, 2>);
     } else {
@@ -225,9 +244,9 @@ template <int CB>
 void launch_short(const RotArgs& a, bool f16, int out, hipStream_t s) {
     constexpr int U = 4;
     const int64_t items = (a.rows + (16 >> CB) * U - 1) / ((16 >> CB) * U);
-    const int64_t cap = 1 << 24;
+    const int64_t cap = kMostGroups;
     const unsigned grid = (unsigned)(items < cap ? items : cap);
-    auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, a); };
+    auto go = [&](auto kernel) { launch_rot(kernel, grid, s, a); };
     if (f16) {
         if (out == 0) go(k_wave_rotate_short<CB, U, true, 0>); else if (out == 1) go(k_wave_rotate_short<CB, U, true, 1>); else go(k_wave_rotate_short<CB, U, true, 2>);
     } else {
@@ -237,7 +256,7 @@ void launch_short(const RotArgs& a, bool f16, int out, hipStream_t s) {
 
 template <int T>
 void launch_long_codes(const RotArgs& a, int bits, int out, unsigned grid, hipStream_t s) {
-    auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, a); };
+    auto go = [&](auto kernel) { launch_rot(kernel, grid, s, a); };
     if (bits == 4) {
         if (out == 0) go(k_wave_rotate<T, false, 0, 4>); else if (out == 1) go(k_wave_rotate<T, false, 1, 4>); else go(k_wave_rotate<T, false, 2, 4>);
     } else {
@@ -249,9 +268,9 @@ template <int CB, bool ASYM>
 void launch_short_codes(const RotArgs& a, int bits, int out, hipStream_t s) {
     constexpr int U = 4;
     const int64_t items = (a.rows + (16 >> CB) * U - 1) / ((16 >> CB) * U);
-    const int64_t cap = 1 << 24;
+    const int64_t cap = kMostGroups;
     const unsigned grid = (unsigned)(items < cap ? items : cap);
-    auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, a); };
+    auto go = [&](auto kernel) { launch_rot(kernel, grid, s, a); };
     if (bits == 4) {
         if (out == 0) go(k_wave_rotate_short<CB, U, false, 0, 4, ASYM>); else if (out == 1) go(k_wave_rotate_short<CB, U, false, 1, 4, ASYM>); else go(k_wave_rotate_short<CB, U, false, 2, 4, ASYM>);
     } else {
@@ -279,7 +298,7 @@ int wave_dequant_rotate(const rq_hadamard* h, const RowArgs& a, const uint32_t* 
     r.mins = mins;
     r.sqrt_n = (float)std::sqrt((double)a.n);
     const int out = o.dtype == RQ_BF16 ? 0 : o.dtype == RQ_F32 ? 1 : 2;
-    const int64_t cap = 1 << 24;
+    const int64_t cap = kMostGroups;
     const unsigned grid = (unsigned)(a.rows < cap ? a.rows : cap);
     switch (a.log2m) {
         case 7:
@@ -294,7 +313,7 @@ int wave_dequant_rotate(const rq_hadamard* h, const RowArgs& a, const uint32_t* 
         case 13: launch_long_codes<16>(r, a.bits, out, grid, s); break;
         default: return RQ_ERR_NO_ORDER;
     }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 bool wave_rotate_supports(const rq_hadamard* h, const RowArgs& a, const OutArgs& o) {
@@ -311,7 +330,7 @@ int wave_rotate(const rq_hadamard* h, const RowArgs& a, const OutArgs& o, hipStr
                     static_cast<const u32x4*>(f16 ? h->d_tiles_f16 : h->d_tiles), o.Y, o.d_out, o.ld_out,
                     (float)(1.0 / std::sqrt((double)a.n))};
     const int out = o.dtype == RQ_BF16 ? 0 : o.dtype == RQ_F32 ? 1 : 2;
-    const int64_t cap = 1 << 24;
+    const int64_t cap = kMostGroups;
     const unsigned grid = (unsigned)(a.rows < cap ? a.rows : cap);
     switch (a.log2m) {
         case 7: launch_short<2>(r, f16, out, s); break;
@@ -323,7 +342,7 @@ int wave_rotate(const rq_hadamard* h, const RowArgs& a, const OutArgs& o, hipStr
         case 13: launch_long<16>(r, f16, out, grid, s); break;
         default: return RQ_ERR_NO_ORDER;
     }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 }  // namespace rq

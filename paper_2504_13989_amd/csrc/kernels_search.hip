@@ -429,7 +429,7 @@ int launch_resident(const RowArgs& a, const WaveArgs& w, double inv_norm, const 
             default: return RQ_ERR_NO_ORDER;
         }
     }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 // Grid, block and what both forms share of the arguments.
@@ -535,7 +535,7 @@ int gbs_step(GbsDev* state, GbsOut* out, bool first, double eps, int depth, int 
              int64_t rows, int64_t count, int64_t stride, hipStream_t s) {
     launch_kernel(k_gbs_step, dim3(1), dim3(kStepThreads), 0, s, state, out, first ? 1 : 0, eps, depth, max_evals,
                   (double)((1 << bits) - 1), partial, rows, count, stride);
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 }  // namespace rq

@@ -28,7 +28,8 @@ namespace {
 
 // Long rows: n = 512 T (T = 2 .. 16), one wave per row.  FULL: d == n (no zero padding).
 template <int T, int BITS, bool FULL, bool F16 = false>
-__global__ __launch_bounds__(64) void k_wave_sylvester(WaveArgs a) {
+__global__ __launch_bounds__(64) void k_wave_sylvester(RQ_WAVE_PARAMS) {
+    RQ_WAVE_ARGS(a);
     constexpr int ROW_DWORDS = 512 * T * BITS / 32;
     __shared__ __attribute__((aligned(16))) uint8_t stage[BITS == 3 ? ROW_DWORDS * 4 : 16];
     const int lane = threadIdx.x;
@@ -42,7 +43,7 @@ __global__ __launch_bounds__(64) void k_wave_sylvester(WaveArgs a) {
     for (int b = 0; b < 4; ++b) sf[b] = ((c >> b) & 1) ? -1.0f : 1.0f;
     const float flip = (__builtin_popcount(c) & 1) ? -1.0f : 1.0f;
 
-    for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
+    for (int64_t row = blockIdx.x; row < a.rows; row += kMostGroups) {
         const uint16_t* xr = a.X + row * a.ld;
         const RowView xv = row_view(xr, a.d);
         f32x4 acc[T][2];
@@ -400,9 +401,8 @@ __device__ __forceinline__ void short_rows_pass(const WaveArgs& a, const uint16_
 // PLAIN: the same passes on the rows as they are (rq_quantize on head rows that arrive
 // rotated, sections 2.1, 5.1): the matrix cores multiply by the identity - which turns the eight 16-bit
 // values of a lane into fp32 without a vector-ALU instruction - and the butterfly stages are left out.
-template <int CB, int BITS, int U, bool ASYM = false, bool F16 = false, bool PLAIN = false>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(U == 8 && !PLAIN ? 4 : 1)))   // 128 registers
-void k_wave_short(WaveArgs a) {
+template <int CB, int BITS, int U, bool ASYM, bool F16, bool PLAIN>
+__device__ __forceinline__ void short_rows(WaveArgs a) {
     static_assert(!(PLAIN && ASYM), "the rotation-free group quantizer has a kernel of its own");
     static_assert(CB >= 2 && CB <= 4, "unsupported shape");
     constexpr int RPW = 16 >> CB;
@@ -441,7 +441,7 @@ void k_wave_short(WaveArgs a) {
     const bool full_d = a.d == N;
 
     const int64_t n_super = (a.rows + SUPER - 1) / SUPER;
-    for (int64_t sgi = blockIdx.x; sgi < n_super; sgi += gridDim.x) {
+    for (int64_t sgi = blockIdx.x; sgi < n_super; sgi += U == 8 ? gridDim.x : (unsigned)kMostGroups) {
         const int64_t row0 = sgi * SUPER;
         const int64_t left = a.rows - row0;
         const int rem = left < SUPER ? (int)left : SUPER;
@@ -457,6 +457,22 @@ void k_wave_short(WaveArgs a) {
                                                       c1h, c1l, c2h, c2l);
     }
 }
+// (eight passes in flight are for large launches: their arguments come the ordinary way, see RQ_WAVE_PARAMS)
+template <int CB, int BITS, bool ASYM, bool F16, bool PLAIN>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PLAIN ? 1 : 4)))   // 128 registers
+void k_wave_short_deep(WaveArgs a) {
+    short_rows<CB, BITS, 8, ASYM, F16, PLAIN>(a);
+}
+template <int CB, int BITS, bool ASYM, bool F16, bool PLAIN>
+__global__ __launch_bounds__(64) void k_wave_short(RQ_WAVE_PARAMS) {
+    RQ_WAVE_ARGS(a);
+    short_rows<CB, BITS, 4, ASYM, F16, PLAIN>(a);
+}
+template <int CB, int BITS, int U, bool ASYM = false, bool F16 = false, bool PLAIN = false>
+constexpr auto short_kernel() {
+    if constexpr (U == 8) return k_wave_short_deep<CB, BITS, ASYM, F16, PLAIN>;
+    else return k_wave_short<CB, BITS, ASYM, F16, PLAIN>;
+}
 
 // ---------------------------------------------------------------------------------------------
 // Block kernel: n = PB * 128 with a +-1 block of order PB <= 32 along the strided axis
@@ -468,7 +484,8 @@ void k_wave_short(WaveArgs a) {
 // with 8 block rows x 8 consecutive columns per lane; butterflies over i (registers) and c
 // (DPP), quantization and packing then work exactly as in the Sylvester kernel.
 template <int BITS, bool FULL, int NV, bool F16 = false>
-__global__ __launch_bounds__(64) void k_wave_block(WaveArgs a, int pb) {
+__global__ __launch_bounds__(64) void k_wave_block(RQ_WAVE_PARAMS) {
+    RQ_WAVE_ARGS(a);
     constexpr int ROW_DWORDS_PER_A = 128 * BITS / 32;
     __shared__ __attribute__((aligned(16))) uint8_t stage[BITS == 3 ? 32 * 48 : 16];
     const int lane = threadIdx.x;
@@ -485,7 +502,7 @@ __global__ __launch_bounds__(64) void k_wave_block(WaveArgs a, int pb) {
     // block operand has zero columns, so the duplicates contribute nothing.
     const int base_g = 8 * g < pb - 8 ? 8 * g : pb - 8;
     const int e_base = base_g * 128 + c * 8;
-    for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
+    for (int64_t row = blockIdx.x; row < a.rows; row += kMostGroups) {
         float y[8][NV];
         float m = block_rotate_row<FULL, NV, F16>(a, row, e_base, A0, A1, sf, y);
         const float s = m > 0.0f ? flip * (float)(a.c1 / (double)m) : 0.0f;
@@ -866,19 +883,9 @@ __device__ __forceinline__ float half_hi(uint32_t w) {
     else return __uint_as_float(w & 0xffff0000u);
 }
 
-struct PlainArgs {
-    const uint16_t* X;
-    int64_t rows;
-    int d;
-    int64_t ld;
-    uint32_t* codes;
-    float* scales;
-    double clip;
-    bool f16;
-};
-
 template <int T, int W, int BITS, bool F16>
-__global__ __launch_bounds__(64 * W) void k_plain_wave(PlainArgs a) {
+__global__ __launch_bounds__(64 * W) void k_plain_wave(RQ_WAVE_PARAMS) {
+    RQ_WAVE_ARGS(a);
     __shared__ float wmax[W];
     const int lane = threadIdx.x & 63;
     const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -886,7 +893,7 @@ __global__ __launch_bounds__(64 * W) void k_plain_wave(PlainArgs a) {
     const int row_dwords = a.d * BITS / 32;
     constexpr double kLvl = (double)((1 << BITS) - 1);
     constexpr float kQmin = -(float)(1 << (BITS - 1)), kQmax = (float)((1 << (BITS - 1)) - 1);
-    for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
+    for (int64_t row = blockIdx.x; row < a.rows; row += kMostGroups / W) {
         const RowView xv = row_view(a.X + row * a.ld, a.d);
         u32x4 raw[T];
 #pragma unroll
@@ -948,16 +955,16 @@ __global__ __launch_bounds__(64 * W) void k_plain_wave(PlainArgs a) {
 }
 
 template <int T, int W = 1>
-int launch_plain(const PlainArgs& a, int bits, hipStream_t s) {
-    const int64_t cap = (1 << 24) / W;                   // (2^30 threads; the kernel loops over rows)
+int launch_plain(const WaveArgs& a, int bits, hipStream_t s) {
+    const int64_t cap = kMostGroups / W;                 // (2^30 threads; the kernel loops over rows)
     const dim3 grid((unsigned)(a.rows < cap ? a.rows : cap)), block(64 * W);
-    auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, a); };
+    auto go = [&](auto kernel) { launch_wave_kernel(kernel, grid, block, s, a, 0); };
     if (a.f16) {
         if (bits == 4) go(k_plain_wave<T, W, 4, true>); else go(k_plain_wave<T, W, 3, true>);
     } else {
         if (bits == 4) go(k_plain_wave<T, W, 4, false>); else go(k_plain_wave<T, W, 3, false>);
     }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 template <typename K>
@@ -967,17 +974,17 @@ int launch_wave(K kernel, const rq_hadamard* h, const WaveArgs& a, int64_t items
     // than a resident wave looping over rows (measured); the loop only serves huge inputs
     (void)h;
     (void)waves_per_simd;
-    const int64_t cap = 1 << 24;
+    const int64_t cap = kMostGroups;
     const unsigned grid = (unsigned)(items < cap ? items : cap);
-    launch_kernel(kernel, dim3(grid), dim3(64), 0, s, a);
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    launch_wave_kernel(kernel, dim3(grid), dim3(64), s, a, 0);
+    return launch_rc();
 }
 
 template <int T, int S>
 int launch_split(const WaveArgs& a, int bits, hipStream_t s) {
     const bool full = a.d == 512 * T;
     const dim3 grid((unsigned)a.rows), block(64 * S);
-    auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, a); };
+    auto go = [&](auto kernel) { launch_wave_kernel(kernel, grid, block, s, a, 0); };
     if (a.f16) {
         if (bits == 4) { if (full) go(k_wave_sylvester_split<T, 4, true, S, true>); else go(k_wave_sylvester_split<T, 4, false, S, true>); }
         else { if (full) go(k_wave_sylvester_split<T, 3, true, S, true>); else go(k_wave_sylvester_split<T, 3, false, S, true>); }
@@ -985,7 +992,7 @@ int launch_split(const WaveArgs& a, int bits, hipStream_t s) {
         if (bits == 4) { if (full) go(k_wave_sylvester_split<T, 4, true, S, false>); else go(k_wave_sylvester_split<T, 4, false, S, false>); }
         else { if (full) go(k_wave_sylvester_split<T, 3, true, S, false>); else go(k_wave_sylvester_split<T, 3, false, S, false>); }
     }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 template <int T>
@@ -1027,10 +1034,10 @@ int launch_short_u(const rq_hadamard* h, const WaveArgs& a, int bits, hipStream_
     constexpr int SUPER = (16 >> CB) * U;
     const int64_t items = (a.rows + SUPER - 1) / SUPER;
     if (a.f16)
-        return bits == 4 ? launch_wave(k_wave_short<CB, 4, U, false, true>, h, a, items, 8, s)
-                         : launch_wave(k_wave_short<CB, 3, U, false, true>, h, a, items, 8, s);
-    return bits == 4 ? launch_wave(k_wave_short<CB, 4, U>, h, a, items, 8, s)
-                     : launch_wave(k_wave_short<CB, 3, U>, h, a, items, 8, s);
+        return bits == 4 ? launch_wave(short_kernel<CB, 4, U, false, true>(), h, a, items, 8, s)
+                         : launch_wave(short_kernel<CB, 3, U, false, true>(), h, a, items, 8, s);
+    return bits == 4 ? launch_wave(short_kernel<CB, 4, U>(), h, a, items, 8, s)
+                     : launch_wave(short_kernel<CB, 3, U>(), h, a, items, 8, s);
 }
 
 template <int CB>
@@ -1043,10 +1050,10 @@ int launch_short_asym_u(const rq_hadamard* h, const WaveArgs& a, int bits, hipSt
     constexpr int SUPER = 4 * U;
     const int64_t items = (a.rows + SUPER - 1) / SUPER;
     if (a.f16)
-        return bits == 4 ? launch_wave(k_wave_short<2, 4, U, true, true>, h, a, items, 8, s)
-                         : launch_wave(k_wave_short<2, 3, U, true, true>, h, a, items, 8, s);
-    return bits == 4 ? launch_wave(k_wave_short<2, 4, U, true>, h, a, items, 8, s)
-                     : launch_wave(k_wave_short<2, 3, U, true>, h, a, items, 8, s);
+        return bits == 4 ? launch_wave(short_kernel<2, 4, U, true, true>(), h, a, items, 8, s)
+                         : launch_wave(short_kernel<2, 3, U, true, true>(), h, a, items, 8, s);
+    return bits == 4 ? launch_wave(short_kernel<2, 4, U, true>(), h, a, items, 8, s)
+                     : launch_wave(short_kernel<2, 3, U, true>(), h, a, items, 8, s);
 }
 
 int launch_short_asym(const rq_hadamard* h, const WaveArgs& a, int bits, hipStream_t s) {
@@ -1092,20 +1099,20 @@ template <int NV>
 static void launch_block_nv(int bits, bool full, unsigned grid, hipStream_t s, const WaveArgs& w, int pb) {
     if (w.f16) {
         if (bits == 4) {
-            if (full) launch_kernel((k_wave_block<4, true, NV, true>), dim3(grid), dim3(64), 0, s, w, pb);
-            else launch_kernel((k_wave_block<4, false, NV, true>), dim3(grid), dim3(64), 0, s, w, pb);
+            if (full) launch_wave_kernel((k_wave_block<4, true, NV, true>), dim3(grid), dim3(64), s, w, pb);
+            else launch_wave_kernel((k_wave_block<4, false, NV, true>), dim3(grid), dim3(64), s, w, pb);
         } else {
-            if (full) launch_kernel((k_wave_block<3, true, NV, true>), dim3(grid), dim3(64), 0, s, w, pb);
-            else launch_kernel((k_wave_block<3, false, NV, true>), dim3(grid), dim3(64), 0, s, w, pb);
+            if (full) launch_wave_kernel((k_wave_block<3, true, NV, true>), dim3(grid), dim3(64), s, w, pb);
+            else launch_wave_kernel((k_wave_block<3, false, NV, true>), dim3(grid), dim3(64), s, w, pb);
         }
         return;
     }
     if (bits == 4) {
-        if (full) launch_kernel((k_wave_block<4, true, NV>), dim3(grid), dim3(64), 0, s, w, pb);
-        else launch_kernel((k_wave_block<4, false, NV>), dim3(grid), dim3(64), 0, s, w, pb);
+        if (full) launch_wave_kernel((k_wave_block<4, true, NV>), dim3(grid), dim3(64), s, w, pb);
+        else launch_wave_kernel((k_wave_block<4, false, NV>), dim3(grid), dim3(64), s, w, pb);
     } else {
-        if (full) launch_kernel((k_wave_block<3, true, NV>), dim3(grid), dim3(64), 0, s, w, pb);
-        else launch_kernel((k_wave_block<3, false, NV>), dim3(grid), dim3(64), 0, s, w, pb);
+        if (full) launch_wave_kernel((k_wave_block<3, true, NV>), dim3(grid), dim3(64), s, w, pb);
+        else launch_wave_kernel((k_wave_block<3, false, NV>), dim3(grid), dim3(64), s, w, pb);
     }
 }
 
@@ -1153,7 +1160,7 @@ int wave_block_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float cli
         w.tiles = static_cast<const u32x4*>(h->d_tiles_f16);
     }
     const int pb = a.p << (a.log2m - 7);
-    const int64_t cap = 1 << 24;
+    const int64_t cap = kMostGroups;
     const unsigned grid = (unsigned)(a.rows < cap ? a.rows : cap);
     const bool full = a.d == a.n;
     switch ((pb + 3) / 4) {
@@ -1166,7 +1173,7 @@ int wave_block_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float cli
         case 8: launch_block_nv<8>(a.bits, full, grid, s, w, pb); break;
         default: return RQ_ERR_NO_ORDER;
     }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 // src: 0 rows of X, 3 / 4 packed codes of that width (whole rows, fp16 operands).
@@ -1197,7 +1204,7 @@ static int launch_block_rotate(int src, const RowArgs& a, const WaveArgs& w, con
     const BlockRotArgs bo{o.Y, o.d_out, o.ld_out, 1.0 / std::sqrt((double)a.n)};
     const int out = o.dtype == RQ_BF16 ? 0 : o.dtype == RQ_F32 ? 1 : 2;
     const int pb = a.p << (a.log2m - 7);
-    const int64_t cap = 1 << 24;
+    const int64_t cap = kMostGroups;
     const unsigned grid = (unsigned)(a.rows < cap ? a.rows : cap);
     const bool full = a.d == a.n;
     switch ((pb + 3) / 4) {
@@ -1210,7 +1217,7 @@ static int launch_block_rotate(int src, const RowArgs& a, const WaveArgs& w, con
         case 8: launch_block_rotate_nv<8>(src, full, w.f16, out, grid, s, w, pb, bo); break;
         default: return RQ_ERR_NO_ORDER;
     }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 static bool rotate_out_ok(const OutArgs& o) {
@@ -1298,12 +1305,12 @@ static int launch_qe(const rq_hadamard* h, const WaveArgs& w, const ClipArg& cli
             if (split == 4) pick(std::integral_constant<int, 4>{});
         if constexpr (SMAX >= 2 && T != 16)
             if (split == 2) pick(std::integral_constant<int, 2>{});
-        return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+        return launch_rc();
     }
     if constexpr (T < 16) {
         const int ksplit = qe_ksplit(h, w.rows, n_clips);
         const int64_t items = w.rows * ksplit;
-        const int64_t cap = 1 << 24;
+        const int64_t cap = kMostGroups;
         const unsigned grid = (unsigned)(items < cap ? items : cap);
         auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, w, clips, ksplit, partial); };
         if (w.f16) {
@@ -1312,7 +1319,7 @@ static int launch_qe(const rq_hadamard* h, const WaveArgs& w, const ClipArg& cli
             if (bits == 4) go(k_wave_quant_error<T, 4, false>); else go(k_wave_quant_error<T, 3, false>);
         }
     }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 template <int NV>
@@ -1320,7 +1327,7 @@ static int launch_block_qe(const rq_hadamard* h, const WaveArgs& w, int pb, cons
                            int bits, double* partial, hipStream_t s) {
     const int ksplit = qe_ksplit(h, w.rows, n_clips);
     const int64_t items = w.rows * ksplit;
-    const int64_t cap = 1 << 24;
+    const int64_t cap = kMostGroups;
     const dim3 grid((unsigned)(items < cap ? items : cap)), block(64);
     const bool full = w.d == pb * 128;
     auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, w, pb, clips, ksplit, partial); };
@@ -1331,7 +1338,7 @@ static int launch_block_qe(const rq_hadamard* h, const WaveArgs& w, int pb, cons
         if (bits == 4) { if (full) go(k_wave_block_qe<4, true, NV, false>); else go(k_wave_block_qe<4, false, NV, false>); }
         else { if (full) go(k_wave_block_qe<3, true, NV, false>); else go(k_wave_block_qe<3, false, NV, false>); }
     }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 // Short rows: passes of a launch and, with fewer of them than two to a SIMD, workgroups that share a pass's ratios.
@@ -1339,7 +1346,7 @@ static dim3 short_qe_grid(const rq_hadamard* h, int64_t rows, int rpw, int n_cli
     const int64_t passes = (rows + rpw - 1) / rpw, want = (int64_t)h->num_cu * 8 / passes;
     const int most = (n_clips + 3) / 4;
     *ksplit = want < 1 ? 1 : want > most ? most : (int)want;
-    const int64_t items = passes * *ksplit, cap = 1 << 24;
+    const int64_t items = passes * *ksplit, cap = kMostGroups;
     return dim3((unsigned)(items < cap ? items : cap));
 }
 
@@ -1354,7 +1361,7 @@ static int launch_short_qe(const rq_hadamard* h, const WaveArgs& w, const ClipAr
     } else {
         if (bits == 4) go(k_wave_short_qe<CB, 4, false>); else go(k_wave_short_qe<CB, 3, false>);
     }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 int wave_quant_error_asym(const rq_hadamard* h, const RowArgs& a, const ClipArg& clips, int n_clips, double* partial,
@@ -1371,7 +1378,7 @@ int wave_quant_error_asym(const rq_hadamard* h, const RowArgs& a, const ClipArg&
     } else {
         if (a.bits == 4) go(k_wave_short_qe_asym<4, false>); else go(k_wave_short_qe_asym<3, false>);
     }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 int wave_quant_error(const rq_hadamard* h, const RowArgs& a, const ClipArg& clips, int n_clips,
@@ -1433,15 +1440,15 @@ template <int CB, int U>
 static int launch_plain_short_u(const WaveArgs& a, int bits, hipStream_t s) {
     constexpr int SUPER = (16 >> CB) * U;
     const int64_t items = (a.rows + SUPER - 1) / SUPER;
-    const int64_t cap = 1 << 24;
+    const int64_t cap = kMostGroups;
     const dim3 grid((unsigned)(items < cap ? items : cap)), block(64);
-    auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, a); };
+    auto go = [&](auto kernel) { launch_wave_kernel(kernel, grid, block, s, a, 0); };
     if (a.f16) {
-        if (bits == 4) go(k_wave_short<CB, 4, U, false, true, true>); else go(k_wave_short<CB, 3, U, false, true, true>);
+        if (bits == 4) go(short_kernel<CB, 4, U, false, true, true>()); else go(short_kernel<CB, 3, U, false, true, true>());
     } else {
-        if (bits == 4) go(k_wave_short<CB, 4, U, false, false, true>); else go(k_wave_short<CB, 3, U, false, false, true>);
+        if (bits == 4) go(short_kernel<CB, 4, U, false, false, true>()); else go(short_kernel<CB, 3, U, false, false, true>());
     }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 template <int CB>
@@ -1472,7 +1479,9 @@ bool plain_wave_supports(const void* X, int dtype, int d, int64_t ld) {
 
 int plain_wave_quantize(const void* X, int dtype, int64_t rows, int d, int64_t ld, int bits, float clip,
                         uint32_t* codes, float* scales, hipStream_t s) {
-    const PlainArgs a{static_cast<const uint16_t*>(X), rows, d, ld, codes, scales, (double)clip, dtype == RQ_F16};
+    WaveArgs a{static_cast<const uint16_t*>(X), rows, d, ld, nullptr, codes, scales, 0.0, 0.0};
+    a.clip = (double)clip;
+    a.f16 = dtype == RQ_F16;
     const int t = (d + 511) / 512;
     // Waves per row.  One wave with a row of more than 4096 values in its registers leaves two waves per SIMD, so
     // those rows are split over 4 waves, and over 8 beyond 8192 values or where there are few of them (4096 x 18944:

@@ -14,7 +14,8 @@ namespace rq {
 namespace {
 
 template <int BITS, bool FULL, int NV, bool F16>
-__global__ __launch_bounds__(64) void k_wave_block2(WaveArgs a, int pb) {
+__global__ __launch_bounds__(64) void k_wave_block2(RQ_WAVE_PARAMS) {
+    RQ_WAVE_ARGS(a);
     static_assert(NV > 8 && NV <= 16, "blocks of 33 .. 64");
     constexpr int MT = (NV + 3) / 4;                      // output tiles of 16 block rows
     __shared__ __attribute__((aligned(16))) uint8_t stage[BITS == 3 ? 64 * 48 : 16];
@@ -36,7 +37,7 @@ __global__ __launch_bounds__(64) void k_wave_block2(WaveArgs a, int pb) {
     // duplicates this creates)
     const int base1 = 32 + 8 * g < pb - 8 ? 32 + 8 * g : pb - 8;
     const int e0 = 8 * g * 128 + c * 8, e1 = base1 * 128 + c * 8;
-    for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
+    for (int64_t row = blockIdx.x; row < a.rows; row += kMostGroups) {
         const uint16_t* xr = a.X + row * a.ld;
         const RowView xv = row_view(xr, a.d);
         u32x4 R0[8], R1[8];
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(64) void k_wave_block2(WaveArgs a, int pb) {
 
 template <int NV>
 void launch_nv(const WaveArgs& w, int bits, bool full, unsigned grid, int pb, hipStream_t s) {
-    auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, w, pb); };
+    auto go = [&](auto kernel) { launch_wave_kernel(kernel, dim3(grid), dim3(64), s, w, pb); };
     if (w.f16) {
         if (bits == 4) { if (full) go(k_wave_block2<4, true, NV, true>); else go(k_wave_block2<4, false, NV, true>); }
         else { if (full) go(k_wave_block2<3, true, NV, true>); else go(k_wave_block2<3, false, NV, true>); }
@@ -170,7 +171,7 @@ int wave_block2_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float cl
                lvl / (double)clip, (double)clip / (std::sqrt((double)a.n) * lvl)};
     w.f16 = f16;
     const int pb = a.p << (a.log2m - 7);
-    const int64_t cap = 1 << 24;
+    const int64_t cap = kMostGroups;
     const unsigned grid = (unsigned)(a.rows < cap ? a.rows : cap);
     const bool full = a.d == a.n;
     switch ((pb + 3) / 4) {
@@ -184,7 +185,7 @@ int wave_block2_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float cl
         case 16: launch_nv<16>(w, a.bits, full, grid, pb, s); break;
         default: return RQ_ERR_NO_ORDER;
     }
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 }  // namespace rq

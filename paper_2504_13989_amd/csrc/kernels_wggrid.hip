@@ -30,7 +30,7 @@ int launch_kk(const rq_hadamard* h, const WaveArgs& w, int bits, int pb, int cb,
     const int64_t passes = (w.rows + rpw - 1) / rpw;
     *groups = (int)(passes < cus ? passes : cus);
     launch_kernel(fn, dim3((unsigned)*groups), dim3((unsigned)(64 * ((pb + 15) / 16))), lds, s, w, pb, g);
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 }  // namespace

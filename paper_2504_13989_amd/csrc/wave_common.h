@@ -256,6 +256,10 @@ __device__ __forceinline__ u32x4 load_chunk(const RowView& v, int e0) {
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(v.rs, e0 * 2, 0, 2));
 }
 
+// Most workgroups of a launch of one-wave workgroups, each with a row, or a few rows, of its own; beyond that they loop.  (In
+// the kernels as a constant: the grid's size would be one more argument to wait for.)
+constexpr int kMostGroups = 1 << 24;
+
 struct WaveArgs {
     const uint16_t* X;
     int64_t rows;
@@ -273,6 +277,44 @@ struct WaveArgs {
     bool f16 = false;     // X holds IEEE fp16 instead of bf16 (tiles must be the fp16 table then)
 };
 
+// The parameters of a kernel that takes rows.  The first 56 bytes of plain parameters (integers and vectors of them, not
+// members of a structure) are in scalar registers when a wave starts (-amdgpu-kernarg-preload-count), so its first loads
+// wait for no argument: what they need comes first, the rest is read later.  In few parameters, because a launch pays for
+// each (eight cost the host 0.1 us).  us a call, all of them in one structure -> now: orders with a block of 8 .. 32 rows,
+// 1999 x 3000 5.44 -> 5.03, 3636 x 3000 7.21 -> 6.81, 4096 x 3584 8.23 -> 7.98; rotation of 32 x 2595 heads 8.77 -> 8.50;
+// orders 2^k, 2048 x 4096 5.61 -> 5.40; key heads, 64 x 1856 8.94 -> 8.68; group quantizer, 128 x 2047 value heads 16.14 -> 15.77.
+typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+typedef uint64_t u64x4 __attribute__((ext_vector_type(4)));
+struct WaveRest {
+    double c1, c2;
+    float* mins;
+    double clip, c3;
+};
+#define RQ_WAVE_PARAMS u64x4 p0_, u64x2 p1_, uint64_t p2_, WaveRest rest_
+#define RQ_WAVE_ARGS(a)                                                                                                   \
+    const WaveArgs a{global_ptr<const uint16_t>(p0_[0]), (int64_t)p0_[2], (int)(uint32_t)p2_, (int64_t)p0_[3],            \
+                     global_ptr<const u32x4>(p0_[1]), global_ptr<uint32_t>(p1_[0]), global_ptr<float>(p1_[1]), rest_.c1, \
+                     rest_.c2, rest_.mins, rest_.clip, rest_.c3};                                                        \
+    [[maybe_unused]] const int pb = (int)(p2_ >> 32)
+// A pointer that travelled as an integer, which the compiler is told to be one to global memory (or it makes flat loads).
+template <typename T>
+__device__ __forceinline__ T* global_ptr(uint64_t p) {
+    typedef __attribute__((address_space(1))) T G;
+    return (T*)reinterpret_cast<G*>(p);
+}
+inline uint64_t param(const void* p) { return reinterpret_cast<uintptr_t>(p); }
+inline uint64_t param(int lo, int hi) { return (uint64_t)(uint32_t)lo | (uint64_t)(uint32_t)hi << 32; }
+template <typename K>
+inline void launch_wave_kernel(K kernel, dim3 grid, dim3 block, hipStream_t s, const WaveArgs& w, int pb) {
+    launch_kernel(kernel, grid, block, 0, s, u64x4{param(w.X), param(w.tiles), (uint64_t)w.rows, (uint64_t)w.ld},
+                  u64x2{param(w.codes), param(w.scales)}, param(w.d, pb), WaveRest{w.c1, w.c2, w.mins, w.clip, w.c3});
+}
+// Kernels to which the registers set up for each wave cost more than the wait: the rotation of codes for orders with a block
+// (many short waves: 7439 x 1536 8.11 -> 8.47 us), eight passes of short rows a wave (key heads, 512 x 8192 208.8 -> 209.6)
+// and rows split over the waves of a workgroup (16 x 4096 4.59 -> 4.67).
+inline void launch_wave_kernel(void (*kernel)(WaveArgs), dim3 grid, dim3 block, hipStream_t s, const WaveArgs& w, int) {
+    launch_kernel(kernel, grid, block, 0, s, w);
+}
 
 // Quantizer constants for b-bit codes (section 2.1 with the clip ratio of section 3.1).
 // u = fma(y, s, kBias) rounds y*s + 2^(b-1) to the nearest-even integer on the fp32 lattice

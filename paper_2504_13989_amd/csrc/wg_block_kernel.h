@@ -630,7 +630,7 @@ int wg_launch(const rq_hadamard* h, WgKernel<SINK> fn, const WaveArgs& a, int pb
     }
     const unsigned grid = (unsigned)(passes < cap ? passes : cap);
     launch_kernel(fn, dim3(grid, shares), dim3(64 * nw), lds, s, a, pb, sa);
-    return hipGetLastError() == hipSuccess ? RQ_OK : RQ_ERR_HIP;
+    return launch_rc();
 }
 
 }  // namespace
