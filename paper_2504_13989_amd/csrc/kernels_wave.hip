@@ -43,7 +43,7 @@ __global__ __launch_bounds__(64) void k_wave_sylvester(RQ_WAVE_PARAMS) {
     for (int b = 0; b < 4; ++b) sf[b] = ((c >> b) & 1) ? -1.0f : 1.0f;
     const float flip = (__builtin_popcount(c) & 1) ? -1.0f : 1.0f;
 
-    for (int64_t row = blockIdx.x; row < a.rows; row += kMostGroups) {
+    for (int64_t row = blockIdx.x; row < a.rows; row = next_item<true>(row)) {
         const uint16_t* xr = a.X + row * a.ld;
         const RowView xv = row_view(xr, a.d);
         f32x4 acc[T][2];
@@ -502,7 +502,7 @@ __global__ __launch_bounds__(64) void k_wave_block(RQ_WAVE_PARAMS) {
     // block operand has zero columns, so the duplicates contribute nothing.
     const int base_g = 8 * g < pb - 8 ? 8 * g : pb - 8;
     const int e_base = base_g * 128 + c * 8;
-    for (int64_t row = blockIdx.x; row < a.rows; row += kMostGroups) {
+    for (int64_t row = blockIdx.x; row < a.rows; row = next_item(row)) {
         float y[8][NV];
         float m = block_rotate_row<FULL, NV, F16>(a, row, e_base, A0, A1, sf, y);
         const float s = m > 0.0f ? flip * (float)(a.c1 / (double)m) : 0.0f;

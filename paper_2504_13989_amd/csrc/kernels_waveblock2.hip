@@ -37,7 +37,7 @@ __global__ __launch_bounds__(64) void k_wave_block2(RQ_WAVE_PARAMS) {
     // duplicates this creates)
     const int base1 = 32 + 8 * g < pb - 8 ? 32 + 8 * g : pb - 8;
     const int e0 = 8 * g * 128 + c * 8, e1 = base1 * 128 + c * 8;
-    for (int64_t row = blockIdx.x; row < a.rows; row += kMostGroups) {
+    for (int64_t row = blockIdx.x; row < a.rows; row = next_item(row)) {
         const uint16_t* xr = a.X + row * a.ld;
         const RowView xv = row_view(xr, a.d);
         u32x4 R0[8], R1[8];

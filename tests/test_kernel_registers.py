@@ -30,8 +30,8 @@ def _code_objects():
 
 
 @pytest.fixture(scope="module")
-def spills(tmp_path_factory):
-    """kernel symbol -> vector registers spilled"""
+def kernels(tmp_path_factory):
+    """kernel symbol -> vector registers, of them spilled"""
     if not os.path.exists(READELF):
         pytest.skip("llvm-readelf not found")
     binding.lib()
@@ -43,9 +43,27 @@ def spills(tmp_path_factory):
         notes = subprocess.run([READELF, "--notes", path], capture_output=True, text=True, check=True).stdout
         for kernel in re.split(r"\n\s+- \.a", notes):
             name = re.search(r"\.symbol:\s+(\S+)\.kd", kernel)
-            count = re.search(r"\.vgpr_spill_count:\s+(\d+)", kernel)
-            if name and count:
-                found[name.group(1)] = int(count.group(1))
+            count = re.search(r"\.vgpr_count:\s+(\d+)", kernel)
+            spilled = re.search(r"\.vgpr_spill_count:\s+(\d+)", kernel)
+            if name and count and spilled:
+                found[name.group(1)] = int(count.group(1)), int(spilled.group(1))
+    return found
+
+
+@pytest.fixture(scope="module")
+def spills(kernels):
+    """kernel symbol -> vector registers spilled"""
+    return {k: v[1] for k, v in kernels.items()}
+
+
+def _waves(kernels, pattern):
+    """template arguments of the kernels whose symbols match -> waves that a SIMD holds (512 registers a lane, in eights)"""
+    found = {}
+    for k, (count, spilled) in kernels.items():
+        m = re.search(pattern, k)
+        if m:
+            assert spilled == 0, k
+            found[tuple(map(int, m.groups()))] = min(8, 512 // (-(-count // 8) * 8))
     return found
 
 
@@ -77,3 +95,18 @@ def test_grid_search_kernels_hold_their_registers(spills):
     for k, v in forms.items():
         kk, cb = map(int, re.search(r"k_wg_blockILi(\d+)ELi[34]ELb0ELi3ELi(\d)E", k).groups())
         assert v <= (35 if cb < 4 else 14 if kk >= 6 else 0), (k, v)
+
+
+def test_row_kernels_of_block_orders_hold_their_waves(kernels):
+    """One wave a row, so the waves on a SIMD are the rows in flight: with two and not three of them 33600 rows of 5120, b = 4,
+    took 83.6 us and not 76.0, with four and not six 67200 rows of 2560 74.7 and not 69.9."""
+    waves = _waves(kernels, r"k_wave_blockILi([34])ELb([01])ELi(\d+)ELb([01])EE")
+    assert len(waves) == 2 * 2 * 7 * 2
+    for (bits, full, nv, f16), w in waves.items():
+        want = {2: 7, 3: 7, 4: 7, 5: 6, 6: 5 if bits == 3 else 4, 7: 5 if bits == 3 else 4, 8: 4}[nv] if full else \
+            {2: 6, 3: 6, 4: 6, 5: 6, 6: 5, 7: 4, 8: 4}[nv]
+        assert w >= want, (bits, full, nv, f16, w)
+    waves = _waves(kernels, r"k_wave_block2ILi([34])ELb([01])ELi(\d+)ELb([01])EE")
+    assert len(waves) == 2 * 2 * 8 * 2
+    for (bits, full, nv, f16), w in waves.items():
+        assert w >= (3 if full and nv <= 12 else 2), (bits, full, nv, f16, w)
