@@ -120,7 +120,7 @@ __global__ __launch_bounds__(64) void k_plain_asym(const void* X, int64_t n_grou
     constexpr float kMidF = (float)kMid;
     const float c1f = (float)(kL / clip), clipf = (float)clip;
     // a wave takes U passes of four groups per iteration, all loads issued before the first is used
-    for (int64_t g0 = (int64_t)blockIdx.x * (4 * U); g0 < n_groups; g0 += (int64_t)kMostGroups * (4 * U)) {
+    for (int64_t g0 = (int64_t)blockIdx.x * (4 * U); g0 < n_groups; g0 = next_item<false, kMostGroups * 4 * U>(g0)) {
         Raw8<DT> raw[U];
         const int left = n_groups - g0 < 4 * U ? (int)(n_groups - g0) : 4 * U;
         if (left == 4 * U && ld == (int64_t)gpr * 128) {
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(64) void k_plain_short(const void* X, int64_t rows,
     const bool has = c * 8 < d;                                   // d is a multiple of 32: whole quads of lanes
     const int row_dwords = d * BITS / 32;
     const float c1f = (float)(kL / clip), clipf = (float)clip;
-    for (int64_t r0 = (int64_t)blockIdx.x * (RPP * U); r0 < rows; r0 += (int64_t)kMostGroups * (RPP * U)) {
+    for (int64_t r0 = (int64_t)blockIdx.x * (RPP * U); r0 < rows; r0 = next_item<false, kMostGroups * RPP * U>(r0)) {
         float x[U][8];
 #pragma unroll
         for (int u = 0; u < U; ++u) {

@@ -401,7 +401,7 @@ __device__ __forceinline__ void short_rows_pass(const WaveArgs& a, const uint16_
 // PLAIN: the same passes on the rows as they are (rq_quantize on head rows that arrive
 // rotated, sections 2.1, 5.1): the matrix cores multiply by the identity - which turns the eight 16-bit
 // values of a lane into fp32 without a vector-ALU instruction - and the butterfly stages are left out.
-template <int CB, int BITS, int U, bool ASYM, bool F16, bool PLAIN>
+template <int CB, int BITS, int U, bool ASYM, bool F16, bool PLAIN, bool CARRIED>
 __device__ __forceinline__ void short_rows(WaveArgs a) {
     static_assert(!(PLAIN && ASYM), "the rotation-free group quantizer has a kernel of its own");
     static_assert(CB >= 2 && CB <= 4, "unsupported shape");
@@ -441,7 +441,7 @@ __device__ __forceinline__ void short_rows(WaveArgs a) {
     const bool full_d = a.d == N;
 
     const int64_t n_super = (a.rows + SUPER - 1) / SUPER;
-    for (int64_t sgi = blockIdx.x; sgi < n_super; sgi += U == 8 ? gridDim.x : (unsigned)kMostGroups) {
+    for (int64_t sgi = blockIdx.x; sgi < n_super; sgi = U == 8 ? sgi + gridDim.x : next_item<CARRIED>(sgi)) {
         const int64_t row0 = sgi * SUPER;
         const int64_t left = a.rows - row0;
         const int rem = left < SUPER ? (int)left : SUPER;
@@ -461,17 +461,24 @@ __device__ __forceinline__ void short_rows(WaveArgs a) {
 template <int CB, int BITS, bool ASYM, bool F16, bool PLAIN>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PLAIN ? 1 : 4)))   // 128 registers
 void k_wave_short_deep(WaveArgs a) {
-    short_rows<CB, BITS, 8, ASYM, F16, PLAIN>(a);
+    short_rows<CB, BITS, 8, ASYM, F16, PLAIN, false>(a);
 }
-template <int CB, int BITS, bool ASYM, bool F16, bool PLAIN>
+template <int CB, int BITS, bool ASYM, bool F16, bool PLAIN, bool CARRIED>
 __global__ __launch_bounds__(64) void k_wave_short(RQ_WAVE_PARAMS) {
     RQ_WAVE_ARGS(a);
-    short_rows<CB, BITS, 4, ASYM, F16, PLAIN>(a);
+    short_rows<CB, BITS, 4, ASYM, F16, PLAIN, CARRIED>(a);
 }
-template <int CB, int BITS, int U, bool ASYM = false, bool F16 = false, bool PLAIN = false>
+// CARRIED (see next_item): rotated rows of 512, b = 3, and of 256, b = 4, are the faster for it (65536 x 512 16.7 us and 17.3 without,
+// 32768 x 256 6.04 and 6.16), the other forms the slower or the same (us a call, carried -> not: groups of 128, b = 3, 131072 rows 10.77 ->
+// 10.40, 262144 17.16 -> 16.55; 393216 x 256, b = 3 41.4 -> 40.7; without rotation 122880 x 512 29.3 -> 27.8), and of 128, b = 4, it depends
+// on the launch, see launch_short_u.
+template <int CB, int BITS>
+constexpr bool short_carries() { return (CB == 4 && BITS == 3) || (CB == 3 && BITS == 4); }
+template <int CB, int BITS, int U, bool ASYM = false, bool F16 = false, bool PLAIN = false,
+          bool CARRIED = short_carries<CB, BITS>() && !ASYM && !PLAIN>
 constexpr auto short_kernel() {
     if constexpr (U == 8) return k_wave_short_deep<CB, BITS, ASYM, F16, PLAIN>;
-    else return k_wave_short<CB, BITS, ASYM, F16, PLAIN>;
+    else return k_wave_short<CB, BITS, ASYM, F16, PLAIN, CARRIED>;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1033,6 +1040,15 @@ template <int CB, int U>
 int launch_short_u(const rq_hadamard* h, const WaveArgs& a, int bits, hipStream_t s) {
     constexpr int SUPER = (16 >> CB) * U;
     const int64_t items = (a.rows + SUPER - 1) / SUPER;
+    if constexpr (CB == 2 && U == 4) {
+        // Rows of 128, b = 4: with the addresses carried (80 registers, without 83) a SIMD holds six waves and not five, so that all of a
+        // launch of up to 98304 rows run at once; of the waves of longer launches six are slower than five.  us a call, carried and not:
+        // 65536 rows 5.81 and 5.92, 90000 6.92 and 7.84, 98304 7.17 and 8.03, 100500 8.09 and 8.12, 104000 8.33 and 8.24, 131072 9.61 and
+        // 9.58, 491520 27.1 and 26.0, 786432 41.3 and 39.5.
+        if (bits == 4 && items <= (int64_t)h->num_cu * 25)
+            return a.f16 ? launch_wave(short_kernel<CB, 4, U, false, true, false, true>(), h, a, items, 8, s)
+                         : launch_wave(short_kernel<CB, 4, U, false, false, false, true>(), h, a, items, 8, s);
+    }
     if (a.f16)
         return bits == 4 ? launch_wave(short_kernel<CB, 4, U, false, true>(), h, a, items, 8, s)
                          : launch_wave(short_kernel<CB, 3, U, false, true>(), h, a, items, 8, s);

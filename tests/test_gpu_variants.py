@@ -175,6 +175,23 @@ def test_short_rows_large_inputs_ragged_end(torch, n, rows):
                                               ma[idx].cpu().numpy(), f"large short asym b={b}")
 
 
+@pytest.mark.parametrize("dtype", ["bfloat16", "float16"])
+@pytest.mark.parametrize("d", [128, 120])
+def test_rows_of_128_where_the_row_loop_changes_form(torch, d, dtype):
+    # b = 4: up to 25 waves of 16 rows a compute unit in one form of the kernel, from there on in another; both sides of the
+    # border, whole and ragged last waves, against the same rows in calls far below it, bit for bit
+    border = 16 * 25 * torch.cuda.get_device_properties(0).multi_processor_count
+    g = torch.Generator(device="cuda").manual_seed(d)
+    x = torch.randn((border + 19, d), generator=g, device="cuda").to(getattr(torch, dtype))
+    h = handle(128)
+    parts = [binding.rotate_quantize(h, part, 4, 0.9) for part in x.split(30011)]
+    want = torch.cat([p[0] for p in parts]), torch.cat([p[1] for p in parts])
+    for rows in (border - 3, border, border + 1, border + 16, border + 19):
+        say(f"rows of {d}, {dtype}, b=4, {rows} rows")
+        codes, scales = binding.rotate_quantize(h, x[:rows], 4, 0.9)
+        assert torch.equal(codes, want[0][:rows]) and torch.equal(scales, want[1][:rows])
+
+
 @pytest.mark.parametrize("b", [3, 4])
 def test_plain_quantize_general_kernel(torch, b):
     # what neither the short-row nor the wave kernel takes: fp32 rows wider than 512, rows that do not

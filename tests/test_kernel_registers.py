@@ -110,3 +110,15 @@ def test_row_kernels_of_block_orders_hold_their_waves(kernels):
     assert len(waves) == 2 * 2 * 8 * 2
     for (bits, full, nv, f16), w in waves.items():
         assert w >= (3 if full and nv <= 12 else 2), (bits, full, nv, f16, w)
+
+
+def test_short_row_kernels_hold_their_waves(kernels):
+    """Several rows a wave.  655360 unrotated rows of 96 took 40.2 us with five waves a SIMD and 36.1 with six, 122880 of 512
+    29.3 with four and 27.8 with five; of rotated rows of 128, b = 4, short launches have six and long ones five."""
+    waves = _waves(kernels, r"k_plain_shortILi([34])ELi([012])ELi(\d+)ELi4EE")
+    assert len(waves) == 2 * 3 * 3 and min(waves.values()) >= 6, waves
+    waves = _waves(kernels, r"k_wave_shortILi([234])ELi([34])ELb([01])ELb[01]ELb([01])ELb([01])EE")
+    assert len(waves) == 6 + 6 + 2 + 1, waves
+    for (cb, bits, asym, plain, carried), w in waves.items():
+        want = (5 if cb == 4 else 4) if plain else 6 if cb == 4 or (bits == 4 and cb == 2 and carried) else 5
+        assert w >= want, (cb, bits, asym, plain, carried, w)
