@@ -325,10 +325,9 @@ void launch_short(int bits, hipStream_t s, const void* X, int64_t rows, int d, i
                   uint32_t* codes, float* scales) {
     constexpr int U = 4;
     const int64_t iters = (rows + (64 / LPR) * U - 1) / ((64 / LPR) * U);
-    const int64_t cap = kMostGroups;
-    const unsigned grid = (unsigned)(iters < cap ? iters : cap);
-    if (bits == 4) launch_kernel((k_plain_short<4, DT, LPR, U>), dim3(grid), dim3(64), 0, s, X, rows, d, ld, clip, codes, scales);
-    else launch_kernel((k_plain_short<3, DT, LPR, U>), dim3(grid), dim3(64), 0, s, X, rows, d, ld, clip, codes, scales);
+    const dim3 grid = item_groups(iters);
+    if (bits == 4) launch_kernel((k_plain_short<4, DT, LPR, U>), grid, dim3(64), 0, s, X, rows, d, ld, clip, codes, scales);
+    else launch_kernel((k_plain_short<3, DT, LPR, U>), grid, dim3(64), 0, s, X, rows, d, ld, clip, codes, scales);
 }
 
 template <int DT>
@@ -340,11 +339,11 @@ void launch_short_dt(int bits, hipStream_t s, const void* X, int64_t rows, int d
 }
 
 template <int DT>
-void launch_dt(bool aligned, int bits, unsigned grid, hipStream_t s, const void* X, int64_t n_groups, int gpr,
+void launch_dt(bool aligned, int bits, dim3 grid, hipStream_t s, const void* X, int64_t n_groups, int gpr,
                int64_t ld, double clip, uint32_t* codes, float* scales, float* mins) {
     const int gpr_shift = (gpr & (gpr - 1)) == 0 ? __builtin_ctz((unsigned)gpr) : -1;
     const uint32_t gpr_magic = (uint32_t)((((uint64_t)1 << 32) + gpr - 1) / gpr);   // gpr >= 2 where it is used
-    auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, X, n_groups, gpr, gpr_shift, gpr_magic, ld, clip, codes, scales, mins); };
+    auto go = [&](auto kernel) { launch_kernel(kernel, grid, dim3(64), 0, s, X, n_groups, gpr, gpr_shift, gpr_magic, ld, clip, codes, scales, mins); };
     if (aligned) {
         if (bits == 4) go(k_plain_asym<4, DT, true>); else go(k_plain_asym<3, DT, true>);
     } else {
@@ -359,8 +358,7 @@ int plain_quantize_asym(const void* X, int dtype, int64_t rows, int d, int64_t l
     const int gpr = d / RQ_GROUP;
     const int64_t n_groups = rows * gpr;
     const int64_t passes = (n_groups + 15) / 16;          // 4 groups x 4 passes per wave iteration
-    const int64_t cap = kMostGroups;
-    const unsigned grid = (unsigned)(passes < cap ? passes : cap);
+    const dim3 grid = item_groups(passes);
     const int esz = dtype == RQ_F32 ? 4 : 2;
     const bool aligned = (reinterpret_cast<uintptr_t>(X) & 15) == 0 && (ld * esz) % 16 == 0;
     if (dtype == RQ_BF16) launch_dt<0>(aligned, bits, grid, s, X, n_groups, gpr, ld, (double)clip, codes, scales, mins);

@@ -46,8 +46,8 @@ struct RotRest {
                     global_ptr<const u32x4>(p0_[1]), global_ptr<uint8_t>(p1_[1]), (int)(p2_ >> 32), rest_.ld_out, rest_.inv, \
                     global_ptr<const uint32_t>(p0_[0]), global_ptr<const float>(p1_[0]), rest_.mins, rest_.sqrt_n}
 template <typename K>
-void launch_rot(K kernel, unsigned grid, hipStream_t s, const RotArgs& a) {
-    launch_kernel(kernel, dim3(grid), dim3(64), 0, s,
+void launch_rot(K kernel, int64_t items, hipStream_t s, const RotArgs& a) {
+    launch_kernel(kernel, item_groups(items), dim3(64), 0, s,
                   u64x4{a.codes ? param(a.codes) : param(a.X), param(a.tiles), (uint64_t)a.rows, (uint64_t)a.ld},
                   u64x2{param(a.scales), param(a.Y)}, param(a.d, a.d_out), RotRest{a.ld_out, a.inv, a.sqrt_n, a.mins});
 }
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(64) void k_wave_rotate(RQ_ROT_PARAMS) {
     const float corr = (SRC && chunk == 0) ? -(float)(512 * T) * (float)(128 + (1 << (SRC ? SRC - 1 : 0))) : 0.0f;
     const float sgn = (__builtin_popcount(c) & 1) ? -1.0f : 1.0f;
     const CodeAt cl = code_at<SRC ? SRC : 4>(chunk);
-    for (int64_t row = blockIdx.x; row < a.rows; row += kMostGroups) {
+    for (int64_t row = blockIdx.x; row < a.rows; row = next_item<true>(row)) {
         f32x4 acc[T][2];
         u32x4 raw[T];
         if constexpr (SRC == 0) {
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(64) void k_wave_rotate_short(RQ_ROT_PARAMS) {
     const float corr = (SRC && chunk == 0) ? -(float)(32 << CB) * (float)(128 + (ASYM ? 0 : 1 << (SRC ? SRC - 1 : 0))) : 0.0f;
     const CodeAt cl = code_at<SRC ? SRC : 4>(chunk);
     const int64_t n_super = (a.rows + SUPER - 1) / SUPER;
-    for (int64_t sgi = blockIdx.x; sgi < n_super; sgi += kMostGroups) {
+    for (int64_t sgi = blockIdx.x; sgi < n_super; sgi = next_item<true>(sgi)) {
         const int64_t row0 = sgi * SUPER;
         u32x4 raw[U];
         float ks[U], add0[U];
@@ -231,8 +231,8 @@ __global__ __launch_bounds__(64) void k_wave_rotate_short(RQ_ROT_PARAMS) {
 }
 
 template <int T>
-void launch_long(const RotArgs& a, bool f16, int out, unsigned grid, hipStream_t s) {
-    auto go = [&](auto kernel) { launch_rot(kernel, grid, s, a); };
+void launch_long(const RotArgs& a, bool f16, int out, hipStream_t s) {
+    auto go = [&](auto kernel) { launch_rot(kernel, a.rows, s, a); };
     if (f16) {
         if (out == 0) go(k_wave_rotate<T, true, 0>); else if (out == 1) go(k_wave_rotate<T, true, 1>); else go(k_wave_rotate<T, true, 2>);
     } else {
@@ -244,9 +244,7 @@ template <int CB>
 void launch_short(const RotArgs& a, bool f16, int out, hipStream_t s) {
     constexpr int U = 4;
     const int64_t items = (a.rows + (16 >> CB) * U - 1) / ((16 >> CB) * U);
-    const int64_t cap = kMostGroups;
-    const unsigned grid = (unsigned)(items < cap ? items : cap);
-    auto go = [&](auto kernel) { launch_rot(kernel, grid, s, a); };
+    auto go = [&](auto kernel) { launch_rot(kernel, items, s, a); };
     if (f16) {
         if (out == 0) go(k_wave_rotate_short<CB, U, true, 0>); else if (out == 1) go(k_wave_rotate_short<CB, U, true, 1>); else go(k_wave_rotate_short<CB, U, true, 2>);
     } else {
@@ -255,8 +253,8 @@ void launch_short(const RotArgs& a, bool f16, int out, hipStream_t s) {
 }
 
 template <int T>
-void launch_long_codes(const RotArgs& a, int bits, int out, unsigned grid, hipStream_t s) {
-    auto go = [&](auto kernel) { launch_rot(kernel, grid, s, a); };
+void launch_long_codes(const RotArgs& a, int bits, int out, hipStream_t s) {
+    auto go = [&](auto kernel) { launch_rot(kernel, a.rows, s, a); };
     if (bits == 4) {
         if (out == 0) go(k_wave_rotate<T, false, 0, 4>); else if (out == 1) go(k_wave_rotate<T, false, 1, 4>); else go(k_wave_rotate<T, false, 2, 4>);
     } else {
@@ -268,9 +266,7 @@ template <int CB, bool ASYM>
 void launch_short_codes(const RotArgs& a, int bits, int out, hipStream_t s) {
     constexpr int U = 4;
     const int64_t items = (a.rows + (16 >> CB) * U - 1) / ((16 >> CB) * U);
-    const int64_t cap = kMostGroups;
-    const unsigned grid = (unsigned)(items < cap ? items : cap);
-    auto go = [&](auto kernel) { launch_rot(kernel, grid, s, a); };
+    auto go = [&](auto kernel) { launch_rot(kernel, items, s, a); };
     if (bits == 4) {
         if (out == 0) go(k_wave_rotate_short<CB, U, false, 0, 4, ASYM>); else if (out == 1) go(k_wave_rotate_short<CB, U, false, 1, 4, ASYM>); else go(k_wave_rotate_short<CB, U, false, 2, 4, ASYM>);
     } else {
@@ -298,8 +294,6 @@ int wave_dequant_rotate(const rq_hadamard* h, const RowArgs& a, const uint32_t* 
     r.mins = mins;
     r.sqrt_n = (float)std::sqrt((double)a.n);
     const int out = o.dtype == RQ_BF16 ? 0 : o.dtype == RQ_F32 ? 1 : 2;
-    const int64_t cap = kMostGroups;
-    const unsigned grid = (unsigned)(a.rows < cap ? a.rows : cap);
     switch (a.log2m) {
         case 7:
             if (mins) launch_short_codes<2, true>(r, a.bits, out, s);
@@ -307,10 +301,10 @@ int wave_dequant_rotate(const rq_hadamard* h, const RowArgs& a, const uint32_t* 
             break;
         case 8: launch_short_codes<3, false>(r, a.bits, out, s); break;
         case 9: launch_short_codes<4, false>(r, a.bits, out, s); break;
-        case 10: launch_long_codes<2>(r, a.bits, out, grid, s); break;
-        case 11: launch_long_codes<4>(r, a.bits, out, grid, s); break;
-        case 12: launch_long_codes<8>(r, a.bits, out, grid, s); break;
-        case 13: launch_long_codes<16>(r, a.bits, out, grid, s); break;
+        case 10: launch_long_codes<2>(r, a.bits, out, s); break;
+        case 11: launch_long_codes<4>(r, a.bits, out, s); break;
+        case 12: launch_long_codes<8>(r, a.bits, out, s); break;
+        case 13: launch_long_codes<16>(r, a.bits, out, s); break;
         default: return RQ_ERR_NO_ORDER;
     }
     return launch_rc();
@@ -330,16 +324,14 @@ int wave_rotate(const rq_hadamard* h, const RowArgs& a, const OutArgs& o, hipStr
                     static_cast<const u32x4*>(f16 ? h->d_tiles_f16 : h->d_tiles), o.Y, o.d_out, o.ld_out,
                     (float)(1.0 / std::sqrt((double)a.n))};
     const int out = o.dtype == RQ_BF16 ? 0 : o.dtype == RQ_F32 ? 1 : 2;
-    const int64_t cap = kMostGroups;
-    const unsigned grid = (unsigned)(a.rows < cap ? a.rows : cap);
     switch (a.log2m) {
         case 7: launch_short<2>(r, f16, out, s); break;
         case 8: launch_short<3>(r, f16, out, s); break;
         case 9: launch_short<4>(r, f16, out, s); break;
-        case 10: launch_long<2>(r, f16, out, grid, s); break;
-        case 11: launch_long<4>(r, f16, out, grid, s); break;
-        case 12: launch_long<8>(r, f16, out, grid, s); break;
-        case 13: launch_long<16>(r, f16, out, grid, s); break;
+        case 10: launch_long<2>(r, f16, out, s); break;
+        case 11: launch_long<4>(r, f16, out, s); break;
+        case 12: launch_long<8>(r, f16, out, s); break;
+        case 13: launch_long<16>(r, f16, out, s); break;
         default: return RQ_ERR_NO_ORDER;
     }
     return launch_rc();

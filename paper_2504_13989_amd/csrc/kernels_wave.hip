@@ -477,6 +477,7 @@ constexpr bool short_carries() { return (CB == 4 && BITS == 3) || (CB == 3 && BI
 template <int CB, int BITS, int U, bool ASYM = false, bool F16 = false, bool PLAIN = false,
           bool CARRIED = short_carries<CB, BITS>() && !ASYM && !PLAIN>
 constexpr auto short_kernel() {
+    static_assert(U == 4 || U == 8, "passes of the two kernels");
     if constexpr (U == 8) return k_wave_short_deep<CB, BITS, ASYM, F16, PLAIN>;
     else return k_wave_short<CB, BITS, ASYM, F16, PLAIN, CARRIED>;
 }
@@ -900,7 +901,7 @@ __global__ __launch_bounds__(64 * W) void k_plain_wave(RQ_WAVE_PARAMS) {
     const int row_dwords = a.d * BITS / 32;
     constexpr double kLvl = (double)((1 << BITS) - 1);
     constexpr float kQmin = -(float)(1 << (BITS - 1)), kQmax = (float)((1 << (BITS - 1)) - 1);
-    for (int64_t row = blockIdx.x; row < a.rows; row += kMostGroups / W) {
+    for (int64_t row = blockIdx.x; row < a.rows; row = next_item<true, kMostGroups / W>(row)) {
         const RowView xv = row_view(a.X + row * a.ld, a.d);
         u32x4 raw[T];
 #pragma unroll
@@ -963,9 +964,7 @@ __global__ __launch_bounds__(64 * W) void k_plain_wave(RQ_WAVE_PARAMS) {
 
 template <int T, int W = 1>
 int launch_plain(const WaveArgs& a, int bits, hipStream_t s) {
-    const int64_t cap = kMostGroups / W;                 // (2^30 threads; the kernel loops over rows)
-    const dim3 grid((unsigned)(a.rows < cap ? a.rows : cap)), block(64 * W);
-    auto go = [&](auto kernel) { launch_wave_kernel(kernel, grid, block, s, a, 0); };
+    auto go = [&](auto kernel) { launch_wave_kernel(kernel, a.rows, W, s, a, 0); };
     if (a.f16) {
         if (bits == 4) go(k_plain_wave<T, W, 4, true>); else go(k_plain_wave<T, W, 3, true>);
     } else {
@@ -981,9 +980,7 @@ int launch_wave(K kernel, const rq_hadamard* h, const WaveArgs& a, int64_t items
     // than a resident wave looping over rows (measured); the loop only serves huge inputs
     (void)h;
     (void)waves_per_simd;
-    const int64_t cap = kMostGroups;
-    const unsigned grid = (unsigned)(items < cap ? items : cap);
-    launch_wave_kernel(kernel, dim3(grid), dim3(64), s, a, 0);
+    launch_wave_kernel(kernel, items, 1, s, a, 0);
     return launch_rc();
 }
 
@@ -991,7 +988,7 @@ template <int T, int S>
 int launch_split(const WaveArgs& a, int bits, hipStream_t s) {
     const bool full = a.d == 512 * T;
     const dim3 grid((unsigned)a.rows), block(64 * S);
-    auto go = [&](auto kernel) { launch_wave_kernel(kernel, grid, block, s, a, 0); };
+    auto go = [&](auto kernel) { launch_kernel(kernel, grid, block, 0, s, a); };
     if (a.f16) {
         if (bits == 4) { if (full) go(k_wave_sylvester_split<T, 4, true, S, true>); else go(k_wave_sylvester_split<T, 4, false, S, true>); }
         else { if (full) go(k_wave_sylvester_split<T, 3, true, S, true>); else go(k_wave_sylvester_split<T, 3, false, S, true>); }
@@ -1112,23 +1109,23 @@ std::vector<uint32_t> tiles_to_f16(const std::vector<uint32_t>& t) {
 }
 
 template <int NV>
-static void launch_block_nv(int bits, bool full, unsigned grid, hipStream_t s, const WaveArgs& w, int pb) {
+static void launch_block_nv(int bits, bool full, hipStream_t s, const WaveArgs& w, int pb) {
     if (w.f16) {
         if (bits == 4) {
-            if (full) launch_wave_kernel((k_wave_block<4, true, NV, true>), dim3(grid), dim3(64), s, w, pb);
-            else launch_wave_kernel((k_wave_block<4, false, NV, true>), dim3(grid), dim3(64), s, w, pb);
+            if (full) launch_wave_kernel((k_wave_block<4, true, NV, true>), w.rows, 1, s, w, pb);
+            else launch_wave_kernel((k_wave_block<4, false, NV, true>), w.rows, 1, s, w, pb);
         } else {
-            if (full) launch_wave_kernel((k_wave_block<3, true, NV, true>), dim3(grid), dim3(64), s, w, pb);
-            else launch_wave_kernel((k_wave_block<3, false, NV, true>), dim3(grid), dim3(64), s, w, pb);
+            if (full) launch_wave_kernel((k_wave_block<3, true, NV, true>), w.rows, 1, s, w, pb);
+            else launch_wave_kernel((k_wave_block<3, false, NV, true>), w.rows, 1, s, w, pb);
         }
         return;
     }
     if (bits == 4) {
-        if (full) launch_wave_kernel((k_wave_block<4, true, NV>), dim3(grid), dim3(64), s, w, pb);
-        else launch_wave_kernel((k_wave_block<4, false, NV>), dim3(grid), dim3(64), s, w, pb);
+        if (full) launch_wave_kernel((k_wave_block<4, true, NV>), w.rows, 1, s, w, pb);
+        else launch_wave_kernel((k_wave_block<4, false, NV>), w.rows, 1, s, w, pb);
     } else {
-        if (full) launch_wave_kernel((k_wave_block<3, true, NV>), dim3(grid), dim3(64), s, w, pb);
-        else launch_wave_kernel((k_wave_block<3, false, NV>), dim3(grid), dim3(64), s, w, pb);
+        if (full) launch_wave_kernel((k_wave_block<3, true, NV>), w.rows, 1, s, w, pb);
+        else launch_wave_kernel((k_wave_block<3, false, NV>), w.rows, 1, s, w, pb);
     }
 }
 
@@ -1176,17 +1173,15 @@ int wave_block_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float cli
         w.tiles = static_cast<const u32x4*>(h->d_tiles_f16);
     }
     const int pb = a.p << (a.log2m - 7);
-    const int64_t cap = kMostGroups;
-    const unsigned grid = (unsigned)(a.rows < cap ? a.rows : cap);
     const bool full = a.d == a.n;
     switch ((pb + 3) / 4) {
-        case 2: launch_block_nv<2>(a.bits, full, grid, s, w, pb); break;
-        case 3: launch_block_nv<3>(a.bits, full, grid, s, w, pb); break;
-        case 4: launch_block_nv<4>(a.bits, full, grid, s, w, pb); break;
-        case 5: launch_block_nv<5>(a.bits, full, grid, s, w, pb); break;
-        case 6: launch_block_nv<6>(a.bits, full, grid, s, w, pb); break;
-        case 7: launch_block_nv<7>(a.bits, full, grid, s, w, pb); break;
-        case 8: launch_block_nv<8>(a.bits, full, grid, s, w, pb); break;
+        case 2: launch_block_nv<2>(a.bits, full, s, w, pb); break;
+        case 3: launch_block_nv<3>(a.bits, full, s, w, pb); break;
+        case 4: launch_block_nv<4>(a.bits, full, s, w, pb); break;
+        case 5: launch_block_nv<5>(a.bits, full, s, w, pb); break;
+        case 6: launch_block_nv<6>(a.bits, full, s, w, pb); break;
+        case 7: launch_block_nv<7>(a.bits, full, s, w, pb); break;
+        case 8: launch_block_nv<8>(a.bits, full, s, w, pb); break;
         default: return RQ_ERR_NO_ORDER;
     }
     return launch_rc();
@@ -1456,9 +1451,7 @@ template <int CB, int U>
 static int launch_plain_short_u(const WaveArgs& a, int bits, hipStream_t s) {
     constexpr int SUPER = (16 >> CB) * U;
     const int64_t items = (a.rows + SUPER - 1) / SUPER;
-    const int64_t cap = kMostGroups;
-    const dim3 grid((unsigned)(items < cap ? items : cap)), block(64);
-    auto go = [&](auto kernel) { launch_wave_kernel(kernel, grid, block, s, a, 0); };
+    auto go = [&](auto kernel) { launch_wave_kernel(kernel, items, 1, s, a, 0); };
     if (a.f16) {
         if (bits == 4) go(short_kernel<CB, 4, U, false, true, true>()); else go(short_kernel<CB, 3, U, false, true, true>());
     } else {

@@ -117,8 +117,8 @@ __global__ __launch_bounds__(64) void k_wave_block2(RQ_WAVE_PARAMS) {
 }
 
 template <int NV>
-void launch_nv(const WaveArgs& w, int bits, bool full, unsigned grid, int pb, hipStream_t s) {
-    auto go = [&](auto kernel) { launch_wave_kernel(kernel, dim3(grid), dim3(64), s, w, pb); };
+void launch_nv(const WaveArgs& w, int bits, bool full, int pb, hipStream_t s) {
+    auto go = [&](auto kernel) { launch_wave_kernel(kernel, w.rows, 1, s, w, pb); };
     if (w.f16) {
         if (bits == 4) { if (full) go(k_wave_block2<4, true, NV, true>); else go(k_wave_block2<4, false, NV, true>); }
         else { if (full) go(k_wave_block2<3, true, NV, true>); else go(k_wave_block2<3, false, NV, true>); }
@@ -171,18 +171,16 @@ int wave_block2_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float cl
                lvl / (double)clip, (double)clip / (std::sqrt((double)a.n) * lvl)};
     w.f16 = f16;
     const int pb = a.p << (a.log2m - 7);
-    const int64_t cap = kMostGroups;
-    const unsigned grid = (unsigned)(a.rows < cap ? a.rows : cap);
     const bool full = a.d == a.n;
     switch ((pb + 3) / 4) {
-        case 9: launch_nv<9>(w, a.bits, full, grid, pb, s); break;
-        case 10: launch_nv<10>(w, a.bits, full, grid, pb, s); break;
-        case 11: launch_nv<11>(w, a.bits, full, grid, pb, s); break;
-        case 12: launch_nv<12>(w, a.bits, full, grid, pb, s); break;
-        case 13: launch_nv<13>(w, a.bits, full, grid, pb, s); break;
-        case 14: launch_nv<14>(w, a.bits, full, grid, pb, s); break;
-        case 15: launch_nv<15>(w, a.bits, full, grid, pb, s); break;
-        case 16: launch_nv<16>(w, a.bits, full, grid, pb, s); break;
+        case 9: launch_nv<9>(w, a.bits, full, pb, s); break;
+        case 10: launch_nv<10>(w, a.bits, full, pb, s); break;
+        case 11: launch_nv<11>(w, a.bits, full, pb, s); break;
+        case 12: launch_nv<12>(w, a.bits, full, pb, s); break;
+        case 13: launch_nv<13>(w, a.bits, full, pb, s); break;
+        case 14: launch_nv<14>(w, a.bits, full, pb, s); break;
+        case 15: launch_nv<15>(w, a.bits, full, pb, s); break;
+        case 16: launch_nv<16>(w, a.bits, full, pb, s); break;
         default: return RQ_ERR_NO_ORDER;
     }
     return launch_rc();

@@ -271,6 +271,12 @@ __device__ __forceinline__ int64_t next_item(int64_t i) {
     if constexpr (!CARRIED) asm volatile("" : "+s"(step));
     return i + step;
 }
+// The workgroups of a launch of such a kernel: any fewer, and items would be left out, as the loops step over kMostGroups / waves
+// of them.  The launchers below work it out themselves; `waves` a workgroup (a launch holds 2^30 threads).
+inline dim3 item_groups(int64_t items, int waves = 1) {
+    const int64_t most = kMostGroups / waves;
+    return dim3((unsigned)(items < most ? items : most));
+}
 
 struct WaveArgs {
     const uint16_t* X;
@@ -317,15 +323,15 @@ __device__ __forceinline__ T* global_ptr(uint64_t p) {
 inline uint64_t param(const void* p) { return reinterpret_cast<uintptr_t>(p); }
 inline uint64_t param(int lo, int hi) { return (uint64_t)(uint32_t)lo | (uint64_t)(uint32_t)hi << 32; }
 template <typename K>
-inline void launch_wave_kernel(K kernel, dim3 grid, dim3 block, hipStream_t s, const WaveArgs& w, int pb) {
-    launch_kernel(kernel, grid, block, 0, s, u64x4{param(w.X), param(w.tiles), (uint64_t)w.rows, (uint64_t)w.ld},
+inline void launch_wave_kernel(K kernel, int64_t items, int waves, hipStream_t s, const WaveArgs& w, int pb) {
+    launch_kernel(kernel, item_groups(items, waves), dim3(64 * waves), 0, s, u64x4{param(w.X), param(w.tiles), (uint64_t)w.rows, (uint64_t)w.ld},
                   u64x2{param(w.codes), param(w.scales)}, param(w.d, pb), WaveRest{w.c1, w.c2, w.mins, w.clip, w.c3});
 }
 // Kernels to which the registers set up for each wave cost more than the wait: the rotation of codes for orders with a block
 // (many short waves: 7439 x 1536 8.11 -> 8.47 us), eight passes of short rows a wave (key heads, 512 x 8192 208.8 -> 209.6)
 // and rows split over the waves of a workgroup (16 x 4096 4.59 -> 4.67).
-inline void launch_wave_kernel(void (*kernel)(WaveArgs), dim3 grid, dim3 block, hipStream_t s, const WaveArgs& w, int) {
-    launch_kernel(kernel, grid, block, 0, s, w);
+inline void launch_wave_kernel(void (*kernel)(WaveArgs), int64_t items, int waves, hipStream_t s, const WaveArgs& w, int) {
+    launch_kernel(kernel, item_groups(items, waves), dim3(64 * waves), 0, s, w);
 }
 
 // Quantizer constants for b-bit codes (section 2.1 with the clip ratio of section 3.1).

@@ -63,3 +63,59 @@ def test_quant_error_of_rows_split_over_waves():
     assert h.last_kernel == "wave_quant_error"
     want = binding.quant_error(h, alone, 3, clips).cpu().numpy().astype(np.float64) * 5 / rows     # the others are zero
     assert np.allclose(got, want, rtol=1e-6, atol=0.0)
+
+
+def _repeated(call, x, rows):
+    """The sampled rows of a call on x against those of a call on them alone, and rows between them, which are zero."""
+    alone = _rows_alone(x, rows)
+    got = call(x)
+    for g, want in zip(got, call(alone)):
+        assert torch.equal(g[_some(rows)], want)
+    for g in got[:1]:
+        assert not g[2:1000].any() and not g[rows - 1000:rows - 2].any()
+
+
+# Kernels of one-wave workgroups with a row, or a few rows, each: 2^24 workgroups at most, which take a second item from there on.
+MOST = 1 << 24
+
+
+@pytest.mark.parametrize("n,bits,kernel,gigabytes", [(1024, 4, "wave_sylvester", 20), (1536, 3, "wave_block", 25), (5120, 3, "wave_block", 50)],
+                         ids=["orders of 2", "blocks to 32", "blocks to 64"])
+def test_rows_of_one_wave_each(n, bits, kernel, gigabytes):
+    rows = MOST + 5
+    _need(gigabytes)
+    x = torch.zeros((rows, 8), dtype=torch.bfloat16, device="cuda")
+    h = binding.hadamard_build(n)
+    _repeated(lambda v: binding.rotate_quantize(h, v, bits, 0.9), x, rows)
+    assert h.last_kernel == kernel
+    del x
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("n,rows,gigabytes", [(1024, MOST + 5, 50), (128, 16 * MOST + 5, 110)], ids=["one row a wave", "16 rows a wave"])
+def test_rotation_of_rows(n, rows, gigabytes):
+    _need(gigabytes)
+    x = torch.zeros((rows, 8), dtype=torch.bfloat16, device="cuda")
+    h = binding.hadamard_build(n)
+    _repeated(lambda v: (binding.rotate(h, v, out_dtype=torch.bfloat16),), x, rows)
+    assert h.last_kernel == "wave_rotate"
+    del x
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("d,rows,gigabytes", [(544, MOST + 5, 30), (32, 16 * MOST + 5, 30)], ids=["one row a wave", "16 rows a wave"])
+def test_plain_quantizer_of_rows(d, rows, gigabytes):
+    _need(gigabytes)
+    x = torch.zeros((rows, d), dtype=torch.bfloat16, device="cuda")
+    _repeated(lambda v: binding.quantize(v, 3, 0.9), x, rows)
+    del x
+    torch.cuda.empty_cache()
+
+
+def test_plain_group_quantizer_of_rows():
+    rows, d = 16 * MOST + 5, 128
+    _need(110)
+    x = torch.zeros((rows, d), dtype=torch.bfloat16, device="cuda")
+    _repeated(lambda v: binding.quantize_asym(v, 3, 0.9), x, rows)
+    del x
+    torch.cuda.empty_cache()
