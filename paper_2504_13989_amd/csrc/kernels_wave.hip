@@ -494,6 +494,7 @@ constexpr auto short_kernel() {
 template <int BITS, bool FULL, int NV, bool F16 = false>
 __global__ __launch_bounds__(64) void k_wave_block(RQ_WAVE_PARAMS) {
     RQ_WAVE_ARGS(a);
+    RQ_WAVE_BLOCK_ROWS(pb);
     constexpr int ROW_DWORDS_PER_A = 128 * BITS / 32;
     __shared__ __attribute__((aligned(16))) uint8_t stage[BITS == 3 ? 32 * 48 : 16];
     const int lane = threadIdx.x;

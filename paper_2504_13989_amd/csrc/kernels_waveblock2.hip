@@ -16,6 +16,7 @@ namespace {
 template <int BITS, bool FULL, int NV, bool F16>
 __global__ __launch_bounds__(64) void k_wave_block2(RQ_WAVE_PARAMS) {
     RQ_WAVE_ARGS(a);
+    RQ_WAVE_BLOCK_ROWS(pb);
     static_assert(NV > 8 && NV <= 16, "blocks of 33 .. 64");
     constexpr int MT = (NV + 3) / 4;                      // output tiles of 16 block rows
     __shared__ __attribute__((aligned(16))) uint8_t stage[BITS == 3 ? 64 * 48 : 16];

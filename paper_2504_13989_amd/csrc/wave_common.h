@@ -309,16 +309,18 @@ struct WaveRest {
     double clip, c3;
 };
 #define RQ_WAVE_PARAMS u64x4 p0_, u64x2 p1_, uint64_t p2_, WaveRest rest_
-#define RQ_WAVE_ARGS(a)                                                                                                   \
-    const WaveArgs a{global_ptr<const uint16_t>(p0_[0]), (int64_t)p0_[2], (int)(uint32_t)p2_, (int64_t)p0_[3],            \
-                     global_ptr<const u32x4>(p0_[1]), global_ptr<uint32_t>(p1_[0]), global_ptr<float>(p1_[1]), rest_.c1, \
-                     rest_.c2, rest_.mins, rest_.clip, rest_.c3};                                                        \
-    [[maybe_unused]] const int pb = (int)(p2_ >> 32)
+#define RQ_WAVE_ARGS(a) const WaveArgs a = wave_args(p0_, p1_, p2_, rest_)
+#define RQ_WAVE_BLOCK_ROWS(pb) const int pb = (int)(p2_ >> 32)      // launch_wave_kernel's pb
 // A pointer that travelled as an integer, which the compiler is told to be one to global memory (or it makes flat loads).
 template <typename T>
 __device__ __forceinline__ T* global_ptr(uint64_t p) {
     typedef __attribute__((address_space(1))) T G;
     return (T*)reinterpret_cast<G*>(p);
+}
+static_assert(sizeof(WaveArgs) == 13 * 8, "wave_args and launch_wave_kernel carry every member but f16, which kernels have as a template parameter");
+__device__ __forceinline__ WaveArgs wave_args(u64x4 p0, u64x2 p1, uint64_t p2, const WaveRest& rest) {
+    return WaveArgs{global_ptr<const uint16_t>(p0[0]), (int64_t)p0[2], (int)(uint32_t)p2, (int64_t)p0[3], global_ptr<const u32x4>(p0[1]),
+                    global_ptr<uint32_t>(p1[0]), global_ptr<float>(p1[1]), rest.c1, rest.c2, rest.mins, rest.clip, rest.c3};
 }
 inline uint64_t param(const void* p) { return reinterpret_cast<uintptr_t>(p); }
 inline uint64_t param(int lo, int hi) { return (uint64_t)(uint32_t)lo | (uint64_t)(uint32_t)hi << 32; }
@@ -327,9 +329,9 @@ inline void launch_wave_kernel(K kernel, int64_t items, int waves, hipStream_t s
     launch_kernel(kernel, item_groups(items, waves), dim3(64 * waves), 0, s, u64x4{param(w.X), param(w.tiles), (uint64_t)w.rows, (uint64_t)w.ld},
                   u64x2{param(w.codes), param(w.scales)}, param(w.d, pb), WaveRest{w.c1, w.c2, w.mins, w.clip, w.c3});
 }
-// Kernels to which the registers set up for each wave cost more than the wait: the rotation of codes for orders with a block
-// (many short waves: 7439 x 1536 8.11 -> 8.47 us), eight passes of short rows a wave (key heads, 512 x 8192 208.8 -> 209.6)
-// and rows split over the waves of a workgroup (16 x 4096 4.59 -> 4.67).
+// Kernels that keep one structure, because they were slower without it: the rotation of codes for orders with a block
+// (7439 x 1536 8.11 -> 8.47 us), eight passes of short rows a wave (key heads, 512 x 8192 208.8 -> 209.6) and rows split over
+// the waves of a workgroup (16 x 4096 4.59 -> 4.67; launched by themselves).
 inline void launch_wave_kernel(void (*kernel)(WaveArgs), int64_t items, int waves, hipStream_t s, const WaveArgs& w, int) {
     launch_kernel(kernel, item_groups(items, waves), dim3(64 * waves), 0, s, w);
 }
