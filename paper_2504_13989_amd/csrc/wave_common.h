@@ -309,7 +309,10 @@ struct WaveRest {
     double clip, c3;
 };
 #define RQ_WAVE_PARAMS u64x4 p0_, u64x2 p1_, uint64_t p2_, WaveRest rest_
-#define RQ_WAVE_ARGS(a) const WaveArgs a = wave_args(p0_, p1_, p2_, rest_)
+#define RQ_WAVE_ARGS(a)                                                                                                   \
+    const WaveArgs a{global_ptr<const uint16_t>(p0_[0]), (int64_t)p0_[2], (int)(uint32_t)p2_, (int64_t)p0_[3],            \
+                     global_ptr<const u32x4>(p0_[1]), global_ptr<uint32_t>(p1_[0]), global_ptr<float>(p1_[1]), rest_.c1, \
+                     rest_.c2, rest_.mins, rest_.clip, rest_.c3}
 #define RQ_WAVE_BLOCK_ROWS(pb) const int pb = (int)(p2_ >> 32)      // launch_wave_kernel's pb
 // A pointer that travelled as an integer, which the compiler is told to be one to global memory (or it makes flat loads).
 template <typename T>
@@ -317,11 +320,7 @@ __device__ __forceinline__ T* global_ptr(uint64_t p) {
     typedef __attribute__((address_space(1))) T G;
     return (T*)reinterpret_cast<G*>(p);
 }
-static_assert(sizeof(WaveArgs) == 13 * 8, "wave_args and launch_wave_kernel carry every member but f16, which kernels have as a template parameter");
-__device__ __forceinline__ WaveArgs wave_args(u64x4 p0, u64x2 p1, uint64_t p2, const WaveRest& rest) {
-    return WaveArgs{global_ptr<const uint16_t>(p0[0]), (int64_t)p0[2], (int)(uint32_t)p2, (int64_t)p0[3], global_ptr<const u32x4>(p0[1]),
-                    global_ptr<uint32_t>(p1[0]), global_ptr<float>(p1[1]), rest.c1, rest.c2, rest.mins, rest.clip, rest.c3};
-}
+static_assert(sizeof(WaveArgs) == 13 * 8, "RQ_WAVE_ARGS and launch_wave_kernel carry every member but f16, a template parameter of the kernels");
 inline uint64_t param(const void* p) { return reinterpret_cast<uintptr_t>(p); }
 inline uint64_t param(int lo, int hi) { return (uint64_t)(uint32_t)lo | (uint64_t)(uint32_t)hi << 32; }
 template <typename K>
