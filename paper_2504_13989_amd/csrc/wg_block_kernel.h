@@ -239,8 +239,9 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
     for (int64_t pass = blockIdx.x; pass < n_pass; pass += gridDim.x) {
         if (!PF) load_pass(pass);
         if constexpr (SINK == kWgGrid) {
-            // Beside the row in every pass: held, the tiles leave too few registers to the histogram's phases (6 - 35 spilled, now 0 - 10
-            // and 24 - 34 for the smallest block).  A search on 512 rows, b = 3, us a call: 8960 wide 46.0 -> 43.5, 18944 43.3 -> 42.3,
+            // Beside the row in every pass: held, the tiles leave too few registers to the histogram's phases.  Spilled, held -> now: one row per
+            // pass 6 - 14 -> 0 beyond blocks of 160 (0 up to there), several 17 - 35 -> 6 - 10, for blocks up to 32 28 - 32 -> 24 - 28.  A
+            // search on 512 rows, b = 3, us a call: 8960 wide 46.0 -> 43.5, 18944 43.3 -> 42.3,
             // 28672 55.2 -> 51.3, 14336 (b = 4) 40.7 -> 40.3, 896 wide unchanged.
             int l = lane;
             asm volatile("" : "+v"(l));

@@ -86,15 +86,16 @@ def test_rotating_workgroup_block_kernels_hold_their_registers(spills):
 
 
 def test_grid_search_kernels_hold_their_registers(spills):
-    """The clip search's grid kernels, which keep a row for the passes over its histogram.  Rows held by single waves and the one-row
-    passes of blocks up to 160 spill nothing; larger blocks and several rows per pass are measured as they are."""
+    """The clip search's grid kernels, which keep a row for the passes over its histogram.  Rows held by single waves and the passes
+    of one row spill nothing; several rows per pass are measured as they are (with the operand tiles held for the whole launch they spill 17 - 35, and
+    one row per pass 6 - 14 beyond blocks of 160: 512 rows of 28672 then take 55.2 us a search and not 51.3)."""
     rows = {k: v for k, v in spills.items() if "k_grid_rows" in k}
     assert len(rows) == 24 and max(rows.values()) == 0
     forms = {k: v for k, v in spills.items() if re.search(r"k_wg_blockILi\d+ELi[34]ELb0ELi3E", k)}
     assert len(forms) == 92
     for k, v in forms.items():
         kk, cb = map(int, re.search(r"k_wg_blockILi(\d+)ELi[34]ELb0ELi3ELi(\d)E", k).groups())
-        assert v <= (35 if cb < 4 else 14 if kk >= 6 else 0), (k, v)
+        assert v <= (0 if cb == 4 else 28 if kk == 1 else 10), (k, v)
 
 
 def test_row_kernels_of_block_orders_hold_their_waves(kernels):
