@@ -10,18 +10,18 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 
 # (order, rows, bits, steps the search can take, us without the grid form, us with it)
 MEASURED = [
-    (1024, 64, 3, 16, 32.5, 19.1), (1024, 64, 3, 0, 12.4, 17.1), (1024, 2048, 3, 16, 47.1, 38.3), (1024, 2048, 4, 12, 34, 43),
-    (1024, 2048, 3, 3, 15.6, 36.3), (1024, 8192, 3, 16, 143, 107), (1024, 8192, 4, 12, 96, 127), (1024, 8192, 3, 0, 29, 104),
-    (2048, 512, 4, 12, 28.5, 22.9), (2048, 32768, 3, 16, 590, 429), (2048, 32768, 4, 12, 418, 502), (2048, 32768, 3, 0, 75, 427),
-    (4096, 1, 4, 3, 12.1, 18.7), (4096, 512, 3, 16, 46.8, 24.2), (4096, 512, 3, 2, 14, 22), (4096, 2048, 3, 0, 26, 44),
-    (4096, 2048, 3, 7, 76, 45), (4096, 32768, 4, 16, 1034, 593), (4096, 32768, 4, 4, 233, 592), (4096, 32768, 3, 0, 121, 526),
-    (8192, 32768, 3, 16, 2164, 795), (8192, 32768, 3, 3, 391, 796), (8192, 8192, 4, 0, 80, 218),
-    (3584, 64, 4, 16, 37.8, 21.1), (3584, 2048, 4, 3, 24.7, 50.8), (3584, 8192, 3, 16, 301, 148), (3584, 8192, 3, 3, 62, 146),
-    (1536, 2048, 3, 16, 61, 45), (1536, 2048, 3, 6, 28, 44), (896, 1, 3, 16, 61, 24), (896, 64, 4, 12, 44, 56), (896, 512, 4, 3, 22, 55),
-    (896, 512, 3, 16, 70, 45), (896, 2048, 4, 16, 86, 98), (4864, 512, 3, 16, 84, 32), (4864, 32768, 4, 7, 775, 1093),
-    (4864, 32768, 3, 16, 1429, 912), (5120, 512, 3, 16, 94, 29), (5120, 8192, 4, 4, 133, 302), (5120, 32768, 4, 16, 1758, 1174),
-    (18944, 512, 3, 16, 169, 40), (18944, 512, 3, 0, 30.5, 37.5), (18944, 8192, 4, 16, 1447, 371), (18944, 8192, 4, 3, 264, 368),
-    (28672, 8192, 3, 16, 2443, 484), (28672, 8192, 3, 0, 299, 482), (28672, 512, 4, 7, 117, 49),
+    (1024, 64, 3, 16, 32.9, 19.1), (1024, 64, 3, 0, 12.9, 19.1), (1024, 2048, 3, 16, 45.8, 37.2), (1024, 2048, 4, 12, 34.2, 41.7),
+    (1024, 2048, 3, 3, 15.7, 37.2), (1024, 8192, 3, 16, 134, 103), (1024, 8192, 4, 12, 94, 120), (1024, 8192, 3, 0, 29.1, 103),
+    (2048, 512, 4, 12, 28.6, 22.8), (2048, 32768, 3, 16, 576, 393), (2048, 32768, 4, 12, 417, 468), (2048, 32768, 3, 0, 75, 393),
+    (4096, 1, 4, 3, 12.4, 19.7), (4096, 512, 3, 16, 45.3, 23), (4096, 512, 3, 2, 15.9, 23), (4096, 2048, 3, 0, 26.1, 44),
+    (4096, 2048, 3, 7, 75, 44), (4096, 32768, 4, 16, 1030, 546), (4096, 32768, 4, 4, 232, 546), (4096, 32768, 3, 0, 123, 467),
+    (8192, 32768, 3, 16, 2155, 703), (8192, 32768, 3, 3, 412, 703), (8192, 8192, 4, 0, 82, 206), (3584, 64, 4, 16, 38, 21.2),
+    (3584, 2048, 4, 3, 25.8, 51), (3584, 8192, 3, 16, 291, 137), (3584, 8192, 3, 3, 62, 137), (1536, 2048, 3, 16, 58, 44.2),
+    (1536, 2048, 3, 6, 27.3, 44.2), (896, 1, 3, 16, 54, 23.1), (896, 64, 4, 12, 43.1, 58), (896, 512, 4, 3, 21.6, 57),
+    (896, 512, 3, 16, 59, 45.5), (896, 2048, 4, 16, 78, 95), (4864, 512, 3, 16, 75, 30.7), (4864, 32768, 4, 7, 775, 1103),
+    (4864, 32768, 3, 16, 1429, 916), (5120, 512, 3, 16, 81, 27.9), (5120, 8192, 4, 4, 132, 300), (5120, 32768, 4, 16, 1738, 1178),
+    (18944, 512, 3, 16, 153, 35), (18944, 512, 3, 0, 29.5, 35), (18944, 8192, 4, 16, 1459, 365), (18944, 8192, 4, 3, 263, 365),
+    (28672, 8192, 3, 16, 2435, 488), (28672, 8192, 3, 0, 287, 488), (28672, 512, 4, 7, 118, 49),
 ]
 # order: Sylvester or block, waves of a row held in registers; on the workgroup block kernel rows per pass and threads
 SHAPE = {1024: (1, 1, 0, 0), 2048: (1, 2, 0, 0), 4096: (1, 4, 0, 0), 8192: (1, 4, 0, 0), 1536: (0, 1, 0, 0), 3584: (0, 2, 0, 0),
