@@ -3,11 +3,11 @@
 // the bracket or below), and the error of a row at all 511 ratios costs little more than the rotation (error_grid.h).  One
 // kernel passes over the rows once and leaves each workgroup's sums, a second adds them up and walks the search; nothing
 // is evaluated twice and no step waits for another.
-// Bound: latency (vector port 24 - 30 % busy).  512 x 4096, b = 3: 12 us in the first kernel (launch, rotation 1.5, the
+// Bound: latency (vector port 26 - 43 % busy).  512 x 4096, b = 3: 11 us in the first kernel (launch, rotation 1.5, the
 // additions of two rows a compute unit 2.3, about 20 cycles of LDS each, the passes over the histogram 3), 7 in the second
 // (launch, 1 MB of sums, the walk, results over the bus).
-// A search, us a call, resident or batched form before -> now: 512 x 4096 heavy-tailed rows 46.4 -> 23.5; normal rows 47 -> 23.6,
-// 512 x 8192 61 -> 27, 512 x 3584 45 -> 25, 512 x 5120 94 -> 29, 512 x 14336 135 -> 34, 512 x 18944 169 -> 37, 512 x 896 70 -> 45.
+// A search, us a call, resident or batched form -> grid form, normal rows (heavy-tailed ones within 3 %): 512 x 4096 45 -> 23,
+// 512 x 8192 58 -> 26, 512 x 3584 44 -> 24, 512 x 5120 81 -> 28, 512 x 14336 121 -> 30, 512 x 18944 153 -> 35, 512 x 896 59 -> 46.
 #include "error_grid.h"
 #include "row_rotation.h"
 

@@ -107,7 +107,8 @@ __device__ __forceinline__ float absmax8(const float (&y)[8]) {
 // A wave takes four passes of four groups; extremes, multiplier, centre, tie window and results of its
 // sixteen groups are worked out once, lane c of a DPP row for pass c mod 4, and go back to the lanes of a pass with one quad
 // permutation each; sixteen groups that lie one behind the other (ld = d) are read from one address.  bf16, b = 3, before (all of
-// it once a pass and by every lane, a 64-bit address for each load) -> now: 262 016 groups 17.0 -> 16.1 us, 1 048 576 63.3 ->
+// it once a pass and by every lane, a 64-bit address for each load) -> now: 262 016 groups 17.0 -> 16.1 us (15.6 since
+// the arguments come in registers and the loop's step is hidden, see wave_common.h), 1 048 576 63.3 ->
 // 55.7 (5.2 -> 5.9 TB/s); b = 4, 2 097 152 groups 125 -> 110.
 template <int BITS, int DT, bool ALIGNED>
 __global__ __launch_bounds__(64) void k_plain_asym(const void* X, int64_t n_groups, int gpr, int gpr_shift, uint32_t gpr_magic, int64_t ld, double clip,

@@ -55,10 +55,11 @@ struct GridCase {
 
 // Whether the grid form is the faster one for a search of up to `steps` steps: its time does not depend on them, that of the
 // forms it competes with (resident where the chip holds the tensor, else batches) grows with them.  Straight lines through
-// 4400 pairs of measured times, us (25 orders from 384 to 32768, 1 to 32768 rows, 0 to 16 steps, both code widths); the form
-// taken is within a tenth of the faster one but for 14 of them, at worst 1.23 times it.
-// 4096 x 2048 rows, b = 3: grid 45 at any number of steps; batches 26 for up to one, 33 for three, 55 for five, 136 for sixteen.
-// 1024 x 8192 rows: 104; 29, 29 - 33, 55, 143.  4096 x 64 rows: 19; resident 13, 13, 17, 33.  18944 x 512 rows: 39; 30, 36, 62, 169.
+// 4400 pairs of measured times, us (25 orders from 384 to 32768, 1 to 32768 rows, 0 to 16 steps, both code widths), of a grid form
+// up to 14 % slower than the present one.  Of 7488 pairs measured with that (the same orders, 13 row counts, 12 numbers of steps, normal
+// rows) the form taken is within a tenth of the faster one but for 54, at worst 1.27 times it; on heavy-tailed rows but for 57.
+// 4096 x 2048 rows, b = 3: grid 44 at any number of steps; batches 26 for up to one, 33 for three, 54 for five, 135 for sixteen.
+// 1024 x 8192 rows: 103; 29, 33, 55, 134.  4096 x 64 rows: 20; resident 13, 13, 17, 33.  18944 x 512 rows: 35; 30, 36, 61, 153.
 inline bool gbs_grid_pays(const GridCase& c, int steps) {
     if (c.beside < 1) return false;
     const double kilo = c.n / 1024.0, load = (double)c.rows * c.n / (4096.0 * c.cus);     // 4096 values a compute unit
