@@ -259,12 +259,13 @@ __device__ __forceinline__ u32x4 load_chunk(const RowView& v, int e0) {
 // Most workgroups of a launch of one-wave workgroups, each with a row, or a few rows, of its own; beyond that they loop.
 constexpr int kMostGroups = 1 << 24;
 // The next item of a workgroup in such a loop.  The step is a constant, because the grid's size would be one more argument to
-// wait for (with it 14000 x 1536, b = 3 11.7 us and 11.4, 7000 x 2560, b = 4 10.3 and 10.0), and the compiler does not see that it is one: where it does, it carries the addresses of a row over to the next
-// (CARRIED), at up to 28 vector registers a wave, for a loop that hardly ever comes round.  That loses a wave or two a SIMD in
-// many forms, and in launches of several rounds of waves the time with them.  us a call, carried -> not: orders with a block,
-// b = 4, 33600 x 5120 83.6 -> 76.0, 4200 x 5120 14.2 -> 12.9, 67200 x 2560 74.7 -> 69.9, 57344 x 3000 74.2 -> 72.3, b = 3,
-// 56000 x 3072 70.0 -> 68.0, 48000 x 3584 69.1 -> 67.6; up to one round of waves the same within 2 %, or up to 6 % less (1638 x 5120
-// 7.58 -> 7.13).  Kernels to which it costs no wave, or that are slower without it, carry them.
+// wait for (with it 14000 x 1536, b = 3 11.7 us and 11.4, 7000 x 2560, b = 4 10.3 and 10.0), and the compiler does not see
+// that it is one: where it does, it carries the addresses of a row over to the next (CARRIED), at up to 28 vector registers a
+// wave, for a loop that hardly ever comes round.  That loses a wave or two a SIMD in many forms, and in launches of several
+// rounds of waves the time with them.  us a call, carried -> not: orders with a block, b = 4, 33600 x 5120 83.6 -> 76.0, 4200
+// x 5120 14.2 -> 12.9, 67200 x 2560 74.7 -> 69.9, 57344 x 3000 74.2 -> 72.3, b = 3, 56000 x 3072 70.0 -> 68.0, 48000 x 3584
+// 69.1 -> 67.6; up to one round of waves the same within 2 %, or up to 6 % less (1638 x 5120 7.58 -> 7.13).  Kernels to which
+// it costs no wave, or that are slower without it, carry them.
 template <bool CARRIED = false, int STEP = kMostGroups>
 __device__ __forceinline__ int64_t next_item(int64_t i) {
     uint32_t step = STEP;
