@@ -555,7 +555,10 @@ struct BlockRotArgs {
 // (fp32 results from codes: the sums are exact integers and the scale is applied in fp64, so that a result is rounded
 // once; a product in fp32 has 1.5 times the error, scale and factor being rounded on their own)
 template <bool FULL, int NV, bool F16, int OUT, int SRC = 0>
-__global__ __launch_bounds__(64) void k_wave_block_rotate(WaveArgs a, int pb, BlockRotArgs o) {
+__global__ __launch_bounds__(64) void k_wave_block_rotate(u64x4 p0_, u64x2 p1_, uint64_t p2_, BlockRotArgs o) {
+    const WaveRest rest_{};
+    RQ_WAVE_ARGS(a);
+    RQ_WAVE_BLOCK_ROWS(pb);
     const int lane = threadIdx.x;
     const int g = lane >> 4, cphys = lane & 15;
     const int c = (cphys & 4) ? (cphys ^ 3) : cphys;
@@ -567,7 +570,7 @@ __global__ __launch_bounds__(64) void k_wave_block_rotate(WaveArgs a, int pb, Bl
     const float flip = (__builtin_popcount(c) & 1) ? -1.0f : 1.0f;
     const int base_g = 8 * g < pb - 8 ? 8 * g : pb - 8;
     const int e_base = base_g * 128 + c * 8;
-    for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
+    for (int64_t row = blockIdx.x; row < a.rows; row = next_item(row)) {
         float y[8][NV];
         const double kd = (double)(SRC ? flip * a.scales[row] : flip) * o.inv;
         const float k = (float)kd;                        // (rounded once)
@@ -1190,9 +1193,12 @@ int wave_block_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float cli
 
 // src: 0 rows of X, 3 / 4 packed codes of that width (whole rows, fp16 operands).
 template <int NV>
-static void launch_block_rotate_nv(int src, bool full, bool f16, int out, unsigned grid, hipStream_t s, const WaveArgs& w, int pb,
+static void launch_block_rotate_nv(int src, bool full, bool f16, int out, hipStream_t s, const WaveArgs& w, int pb,
                                    const BlockRotArgs& o) {
-    auto go = [&](auto kernel) { launch_kernel(kernel, dim3(grid), dim3(64), 0, s, w, pb, o); };
+    auto go = [&](auto kernel) {
+        launch_kernel(kernel, item_groups(w.rows), dim3(64), 0, s, u64x4{param(w.X), param(w.tiles), (uint64_t)w.rows, (uint64_t)w.ld},
+                      u64x2{param(w.codes), param(w.scales)}, param(w.d, pb), o);
+    };
     auto pick_out = [&](auto full_c, auto f16_c, auto src_c) {
         constexpr bool FL = decltype(full_c)::value, FH = decltype(f16_c)::value;
         constexpr int SRC = decltype(src_c)::value;
@@ -1216,17 +1222,15 @@ static int launch_block_rotate(int src, const RowArgs& a, const WaveArgs& w, con
     const BlockRotArgs bo{o.Y, o.d_out, o.ld_out, 1.0 / std::sqrt((double)a.n)};
     const int out = o.dtype == RQ_BF16 ? 0 : o.dtype == RQ_F32 ? 1 : 2;
     const int pb = a.p << (a.log2m - 7);
-    const int64_t cap = kMostGroups;
-    const unsigned grid = (unsigned)(a.rows < cap ? a.rows : cap);
     const bool full = a.d == a.n;
     switch ((pb + 3) / 4) {
-        case 2: launch_block_rotate_nv<2>(src, full, w.f16, out, grid, s, w, pb, bo); break;
-        case 3: launch_block_rotate_nv<3>(src, full, w.f16, out, grid, s, w, pb, bo); break;
-        case 4: launch_block_rotate_nv<4>(src, full, w.f16, out, grid, s, w, pb, bo); break;
-        case 5: launch_block_rotate_nv<5>(src, full, w.f16, out, grid, s, w, pb, bo); break;
-        case 6: launch_block_rotate_nv<6>(src, full, w.f16, out, grid, s, w, pb, bo); break;
-        case 7: launch_block_rotate_nv<7>(src, full, w.f16, out, grid, s, w, pb, bo); break;
-        case 8: launch_block_rotate_nv<8>(src, full, w.f16, out, grid, s, w, pb, bo); break;
+        case 2: launch_block_rotate_nv<2>(src, full, w.f16, out, s, w, pb, bo); break;
+        case 3: launch_block_rotate_nv<3>(src, full, w.f16, out, s, w, pb, bo); break;
+        case 4: launch_block_rotate_nv<4>(src, full, w.f16, out, s, w, pb, bo); break;
+        case 5: launch_block_rotate_nv<5>(src, full, w.f16, out, s, w, pb, bo); break;
+        case 6: launch_block_rotate_nv<6>(src, full, w.f16, out, s, w, pb, bo); break;
+        case 7: launch_block_rotate_nv<7>(src, full, w.f16, out, s, w, pb, bo); break;
+        case 8: launch_block_rotate_nv<8>(src, full, w.f16, out, s, w, pb, bo); break;
         default: return RQ_ERR_NO_ORDER;
     }
     return launch_rc();

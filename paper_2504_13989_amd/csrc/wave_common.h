@@ -300,7 +300,9 @@ struct WaveArgs {
 // members of a structure) are in scalar registers when a wave starts (-amdgpu-kernarg-preload-count), so its first loads
 // wait for no argument: what they need comes first, the rest is read later.  In few parameters, because a launch pays for
 // each (eight cost the host 0.1 us).  us a call, all of them in one structure -> now: orders with a block of 8 .. 32 rows,
-// 1999 x 3000 5.44 -> 5.03, 3636 x 3000 7.21 -> 6.81, 4096 x 3584 8.23 -> 7.98; rotation of 32 x 2595 heads 8.77 -> 8.50;
+// 1999 x 3000 5.44 -> 5.03, 3636 x 3000 7.21 -> 6.81, 4096 x 3584 8.23 -> 7.98; their rotation (no row step that the compiler
+// sees, see next_item: with it the gain was lost) 2048 x 3584 6.93 -> 6.54, 1067 x 3000 to fp32 5.77 -> 5.22, and from codes, 2048 x
+// 3584 to bf16, 5.88 -> 5.30, 4096 x 3584 7.85 -> 7.57; rotation of 32 x 2595 heads 8.77 -> 8.50;
 // orders 2^k, 2048 x 4096 5.61 -> 5.40; key heads, 64 x 1856 8.94 -> 8.68; group quantizer, 128 x 2047 value heads 16.14 -> 15.77.
 typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 typedef uint64_t u64x4 __attribute__((ext_vector_type(4)));
@@ -329,9 +331,8 @@ inline void launch_wave_kernel(K kernel, int64_t items, int waves, hipStream_t s
     launch_kernel(kernel, item_groups(items, waves), dim3(64 * waves), 0, s, u64x4{param(w.X), param(w.tiles), (uint64_t)w.rows, (uint64_t)w.ld},
                   u64x2{param(w.codes), param(w.scales)}, param(w.d, pb), WaveRest{w.c1, w.c2, w.mins, w.clip, w.c3});
 }
-// Kernels that keep one structure, because they were slower without it: the rotation of codes for orders with a block
-// (7439 x 1536 8.11 -> 8.47 us), eight passes of short rows a wave (key heads, 512 x 8192 208.8 -> 209.6) and rows split over
-// the waves of a workgroup (16 x 4096 4.59 -> 4.67; launched by themselves).
+// Kernels that keep one structure, because they were slower without it: eight passes of short rows a wave (key heads, 512 x
+// 8192 208.8 -> 209.6) and rows split over the waves of a workgroup (16 x 4096 4.59 -> 4.67; launched by themselves).
 inline void launch_wave_kernel(void (*kernel)(WaveArgs), int64_t items, int waves, hipStream_t s, const WaveArgs& w, int) {
     launch_kernel(kernel, item_groups(items, waves), dim3(64 * waves), 0, s, w);
 }

@@ -92,13 +92,15 @@ def test_rows_of_one_wave_each(n, bits, kernel, gigabytes):
     torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("n,rows,gigabytes", [(1024, MOST + 5, 50), (128, 16 * MOST + 5, 110)], ids=["one row a wave", "16 rows a wave"])
-def test_rotation_of_rows(n, rows, gigabytes):
+@pytest.mark.parametrize("n,rows,gigabytes,kernel", [(1024, MOST + 5, 50, "wave_rotate"), (128, 16 * MOST + 5, 110, "wave_rotate"),
+                                                     (1536, MOST + 5, 70, "wave_block_rotate")],
+                         ids=["one row a wave", "16 rows a wave", "block order"])
+def test_rotation_of_rows(n, rows, gigabytes, kernel):
     _need(gigabytes)
     x = torch.zeros((rows, 8), dtype=torch.bfloat16, device="cuda")
     h = binding.hadamard_build(n)
     _repeated(lambda v: (binding.rotate(h, v, out_dtype=torch.bfloat16),), x, rows)
-    assert h.last_kernel == "wave_rotate"
+    assert h.last_kernel == kernel
     del x
     torch.cuda.empty_cache()
 
