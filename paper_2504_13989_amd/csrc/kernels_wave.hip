@@ -574,7 +574,10 @@ __global__ __launch_bounds__(64) void k_wave_block_rotate(u64x4 p0_, u64x2 p1_, 
         float y[8][NV];
         const double kd = (double)(SRC ? flip * a.scales[row] : flip) * o.inv;
         const float k = (float)kd;                        // (rounded once)
-        (void)block_rotate_row<FULL, NV, F16, SRC>(a, row, e_base, A0, A1, sf, y);
+        // 4-bit codes of blocks of up to 16 rows, or to fp32: a launch is bound by its stores as soon as it fills the chip, and is
+        // the slower the sooner all of them come (us a call, spread and through code_operands: 8000 x 1536 7.71 and 8.32, 12000 x
+        // 1536 11.80 and 12.12, 8000 x 2560 to fp32 18.55 and 18.78; 5000 x 1536, not full, 5.66 and 5.45)
+        (void)block_rotate_row<FULL, NV, F16, SRC, SRC == 4 && (NV <= 4 || OUT == 1)>(a, row, e_base, A0, A1, sf, y);
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
             const int ao = 4 * j + g;                      // output block row of this register

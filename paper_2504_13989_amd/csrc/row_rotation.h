@@ -88,12 +88,13 @@ __device__ __forceinline__ float split_flip(int c) {
 // 4 j .. 4 j + 3 (one per DPP row g); only the NV = ceil(pb / 4) registers that hold real block rows
 // are carried.  Values carry the lane's flip sign (see lane_stages_fused).  Returns the row's absmax.
 // SRC = 3, 4: the row comes from packed signed codes of that width (a.codes) as exact fp16 integers.
-template <bool FULL, int NV, bool F16 = false, int SRC = 0>
+// SPREAD (4-bit codes): each row's codes are spread to fp16 first and then transposed like rows, not dealt out by code_operands.
+template <bool FULL, int NV, bool F16 = false, int SRC = 0, bool SPREAD = false>
 __device__ __forceinline__ float block_rotate_row(const WaveArgs& a, int64_t row, int e_base, const u32x4& A0,
                                               const u32x4& A1, const float (&sf)[4], float (&y)[8][NV]) {
     constexpr int NH1 = NV > 4 ? NV - 4 : 0;              // live registers of the second half
     constexpr int NH0 = NV > 4 ? 4 : NV;
-    u32x4 R[8];
+    u32x4 R[8], bm[8];
     if constexpr (SRC != 0) {
         constexpr int STEP = 16 * SRC;                   // bytes of a block row
         const int row_bytes = STEP * (a.d >> 7);
@@ -106,8 +107,16 @@ __device__ __forceinline__ float block_rotate_row(const WaveArgs& a, int64_t row
             if constexpr (SRC == 3) hi[t] = __builtin_amdgcn_raw_buffer_load_b32(rs, at.off1 + t * STEP, 0, 2);
         }
         __builtin_amdgcn_sched_barrier(0);               // every load is issued before the first wait
+        if constexpr (SRC == 3) {
 #pragma unroll
-        for (int t = 0; t < 8; ++t) R[t] = codes_f16<SRC>(SRC == 4 ? lo[t] : __builtin_amdgcn_alignbit(hi[t], lo[t], at.sh));
+            for (int t = 0; t < 8; ++t) lo[t] = __builtin_amdgcn_alignbit(hi[t], lo[t], at.sh);
+        }
+        if constexpr (SPREAD) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) R[t] = codes4_f16(lo[t]);
+        } else {
+            code_operands<SRC, 4>(lo, bm);
+        }
     } else {
         const uint16_t* xr = a.X + row * a.ld + e_base;
         const RowView xv = row_view(a.X + row * a.ld, a.d);
@@ -115,19 +124,23 @@ __device__ __forceinline__ float block_rotate_row(const WaveArgs& a, int64_t row
         for (int t = 0; t < 8; ++t)
             R[t] = FULL ? load16(xr + t * 128) : load_chunk(xv, e_base + t * 128);
     }
+    if constexpr (SRC == 0 || SPREAD) {
+#pragma unroll
+        for (int ic = 0; ic < 8; ++ic) {
+            const uint32_t sel = (ic & 1) ? 0x07060302u : 0x05040100u;
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+                bm[ic][w] = __builtin_amdgcn_perm(R[2 * w + 1][ic >> 1], R[2 * w][ic >> 1], sel);
+        }
+    }
 #pragma unroll
     for (int ic = 0; ic < 8; ++ic) {
-        u32x4 bm;
-        const uint32_t sel = (ic & 1) ? 0x07060302u : 0x05040100u;
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-            bm[w] = __builtin_amdgcn_perm(R[2 * w + 1][ic >> 1], R[2 * w][ic >> 1], sel);
         const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-        const f32x4 d0 = mfma_pm1<F16>(A0, bm, z);
+        const f32x4 d0 = mfma_pm1<F16>(A0, bm[ic], z);
 #pragma unroll
         for (int j = 0; j < NH0; ++j) y[ic][j] = d0[j];
         if constexpr (NH1 > 0) {
-            const f32x4 d1 = mfma_pm1<F16>(A1, bm, z);
+            const f32x4 d1 = mfma_pm1<F16>(A1, bm[ic], z);
 #pragma unroll
             for (int j = 0; j < NH1; ++j) y[ic][4 + j] = d1[j];
         }

@@ -107,7 +107,7 @@ __device__ __forceinline__ float wg_flip(int cl) {
 }
 
 // SRC: 0 = 16-bit rows of X, 3 / 4 = packed signed codes of that width (kWgRotate only): the lane's eight codes of
-// a block row become fp16 integers (codes_f16), the matrix cores contract them exactly, and the
+// a block row become fp16 integers (code_operands), the matrix cores contract them exactly, and the
 // row's scale multiplies once at the end.
 // WIDE: fp32 results (kWgRotate only), see phase 3; the doubles take 128 registers, 80 spill up to 37 of them (KK = 8
 // spills 20 - 24 at 128).  16-bit results keep fp32 stages: the type's own rounding is all of their error (18944 wide, rows to
@@ -248,22 +248,36 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) A[kk] = a.tiles[(wave * KK + kk) * 64 + l];
         }
+        // ---- phase 1
+        // (4-bit codes of several rows a pass, or of blocks up to 64, are spread first and transposed like rows: us a call, so and
+        // through code_operands, 3500 x 8960 23.0 and 25.3, 4000 x 8960 26.5 and 27.9, 3000 x 5120 10.4 and 10.8; the others 2000 x
+        // 14336 18.0 and 17.2, 3000 x 11008 22.0 and 21.4, 2000 x 18944 26.4 and 25.9)
+        constexpr bool DEAL = SRC == 3 || (SRC == 4 && CB == 4 && KK >= 3);
         if constexpr (SRC != 0) {
+            rscale = __uint_as_float(R[0][2]);
+            uint32_t x[4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                if (t == 0) rscale = __uint_as_float(R[0][2]);
-                // (a block row is a whole number of dwords: the field's bit position is that of the chunk in it)
-                R[t] = codes_f16<SRC>(SRC == 4 ? R[t][0] : __builtin_amdgcn_alignbit(R[t][1], R[t][0], (3u * cl & 3u) * 8u));
+            for (int t = 0; t < 4; ++t)   // (a block row is a whole number of dwords: the field's bit position is that of the chunk in it)
+                x[t] = SRC == 4 ? R[t][0] : __builtin_amdgcn_alignbit(R[t][1], R[t][0], (3u * cl & 3u) * 8u);
+            if constexpr (DEAL) {
+                u32x2 v[8];
+                code_operands<SRC, 2>(x, v);
+#pragma unroll
+                for (int ic = 0; ic < 8; ++ic) *reinterpret_cast<u32x2*>(wr0 + ic * (KK * 1024)) = v[ic];
+            } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) R[t] = codes4_f16(x[t]);
             }
         }
-        // ---- phase 1
+        if constexpr (!DEAL) {
 #pragma unroll
-        for (int ic = 0; ic < 8; ++ic) {
-            const uint32_t sel = (ic & 1) ? 0x07060302u : 0x05040100u;
-            uint2 v;
-            v.x = __builtin_amdgcn_perm(R[1][ic >> 1], R[0][ic >> 1], sel);
-            v.y = __builtin_amdgcn_perm(R[3][ic >> 1], R[2][ic >> 1], sel);
-            *reinterpret_cast<uint2*>(wr0 + ic * (KK * 1024)) = v;
+            for (int ic = 0; ic < 8; ++ic) {
+                const uint32_t sel = (ic & 1) ? 0x07060302u : 0x05040100u;
+                uint2 v;
+                v.x = __builtin_amdgcn_perm(R[1][ic >> 1], R[0][ic >> 1], sel);
+                v.y = __builtin_amdgcn_perm(R[3][ic >> 1], R[2][ic >> 1], sel);
+                *reinterpret_cast<uint2*>(wr0 + ic * (KK * 1024)) = v;
+            }
         }
         __syncthreads();
         if (PF && pass + gridDim.x < n_pass) load_pass(pass + gridDim.x);

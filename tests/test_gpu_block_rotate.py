@@ -137,3 +137,30 @@ def test_infinities_of_the_last_block_rows(n, out):
     want = binding.rotate(h, x, out_dtype=out)
     assert torch.isinf(want[:5]).all() and torch.isnan(y[5]).all()
     assert torch.equal(y[:5], want[:5])
+
+
+@pytest.mark.parametrize("b", [3, 4])
+@pytest.mark.parametrize("n", [1536, 2560, 3072, 3584, 8960, 11264, 14336])
+def test_each_code_at_each_place_of_a_chunk(n, b):
+    """Rows with a single code that is not 0, every code at every place of a chunk, in even and odd block rows: each result is
+    code * scale / sqrt(n) up to its sign, with the factor formed in fp64 and rounded once - exactly, since the sums are integers."""
+    columns = 128 if n != 8960 else 64
+    h = binding.hadamard_build(n)
+    places = [(0, 0), (1, 16), (2, 8), (n // columns - 1, columns - 8), (n // columns - 2, 0)]    # block row, first column of a chunk
+    values = [c for c in range(-(2 ** (b - 1)), 2 ** (b - 1)) if c]
+    rows = [(r * columns + c + i, v) for r, c in places for i in range(8) for v in values]
+    q = np.zeros((len(rows), n), dtype=np.int64)
+    for k, (at, v) in enumerate(rows):
+        q[k, at] = v
+    scales = torch.rand(len(rows), generator=torch.Generator().manual_seed(n + b), dtype=torch.float32) + 0.5
+    packed = torch.from_numpy(oracle.pack_codes(q, b)).cuda()
+    code = torch.tensor([v for _, v in rows], dtype=torch.float64)
+    signs = torch.from_numpy(np.sign(oracle.rotate(np.eye(n)[[at for at, _ in rows[::len(values)]]], n))).repeat_interleave(len(values), 0)
+    for dtype in (torch.bfloat16, torch.float16):
+        k = (scales.double() / np.sqrt(np.float64(n))).to(torch.float32)
+        want = (code.to(torch.float32) * k).to(dtype)
+        got = binding.dequantize_rotate(h, packed, scales.cuda(), b, transpose=False, out_dtype=dtype).cpu()
+        assert torch.equal(got, (want[:, None].double() * signs).to(dtype))
+    want = (code * (scales.double() / np.sqrt(np.float64(n)))).to(torch.float32)
+    got = binding.dequantize_rotate(h, packed, scales.cuda(), b, transpose=False, out_dtype=torch.float32).cpu()
+    assert torch.equal(got, (want[:, None].double() * signs).to(torch.float32))
