@@ -29,7 +29,7 @@ int launch_kk(const rq_hadamard* h, const WaveArgs& w, int bits, int pb, int cb,
     const int rpw = 16 >> cb, cus = h->num_cu < kGridGroups ? h->num_cu : kGridGroups;
     const int64_t passes = (w.rows + rpw - 1) / rpw;
     *groups = (int)(passes < cus ? passes : cus);
-    launch_kernel(fn, dim3((unsigned)*groups), dim3((unsigned)(64 * ((pb + 15) / 16))), lds, s, w, pb, g);
+    launch_kernel(fn, dim3((unsigned)*groups), dim3((unsigned)(64 * ((pb + 15) / 16))), lds, s, RQ_WAVE_VALUES(w, pb), g);
     return launch_rc();
 }
 

@@ -327,10 +327,12 @@ __device__ __forceinline__ T* global_ptr(uint64_t p) {
 static_assert(sizeof(WaveArgs) == 13 * 8, "RQ_WAVE_ARGS and launch_wave_kernel carry every member but f16, a template parameter of the kernels");
 inline uint64_t param(const void* p) { return reinterpret_cast<uintptr_t>(p); }
 inline uint64_t param(int lo, int hi) { return (uint64_t)(uint32_t)lo | (uint64_t)(uint32_t)hi << 32; }
+#define RQ_WAVE_VALUES(w, pb)                                                                                          \
+    u64x4{param(w.X), param(w.tiles), (uint64_t)w.rows, (uint64_t)w.ld}, u64x2{param(w.codes), param(w.scales)}, param(w.d, pb), \
+        WaveRest{w.c1, w.c2, w.mins, w.clip, w.c3}
 template <typename K>
 inline void launch_wave_kernel(K kernel, int64_t items, int waves, hipStream_t s, const WaveArgs& w, int pb) {
-    launch_kernel(kernel, item_groups(items, waves), dim3(64 * waves), 0, s, u64x4{param(w.X), param(w.tiles), (uint64_t)w.rows, (uint64_t)w.ld},
-                  u64x2{param(w.codes), param(w.scales)}, param(w.d, pb), WaveRest{w.c1, w.c2, w.mins, w.clip, w.c3});
+    launch_kernel(kernel, item_groups(items, waves), dim3(64 * waves), 0, s, RQ_WAVE_VALUES(w, pb));
 }
 // Kernels that keep one structure, because they were slower without it: eight passes of short rows a wave (key heads, 512 x
 // 8192 208.8 -> 209.6) and rows split over the waves of a workgroup (16 x 4096 4.59 -> 4.67; launched by themselves).

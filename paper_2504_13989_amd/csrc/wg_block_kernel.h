@@ -115,7 +115,9 @@ __device__ __forceinline__ float wg_flip(int cl) {
 // 2.0731411e-4), and fp64 stages cost 3584 x 18944 to bf16 51 -> 81 us.
 template <int KK, int BITS, bool FULL, int SINK, int CB = 4, bool F16 = false, int SRC = 0, bool WIDE = false>
 __global__ __launch_bounds__(128 * KK) __attribute__((amdgpu_waves_per_eu(wg_waves_per_simd<KK>(WIDE || SINK == kWgGrid))))
-void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
+void k_wg_block(RQ_WAVE_PARAMS, WgArgs<SINK> sa) {
+    RQ_WAVE_ARGS(a);
+    RQ_WAVE_BLOCK_ROWS(pb);
     static_assert(CB >= 2 && CB <= 4 && (CB == 4 || !FULL), "unsupported shape");
     static_assert(SRC == 0 || (SINK == kWgRotate && F16 && !FULL), "packed codes: rotation only, fp16 operands");
     constexpr bool QE = SINK == kWgError;
@@ -621,7 +623,7 @@ void k_wg_block(WaveArgs a, int pb, WgArgs<SINK> sa) {
 
 
 template <int SINK>
-using WgKernel = void (*)(WaveArgs, int, WgArgs<SINK>);
+using WgKernel = void (*)(RQ_WAVE_PARAMS, WgArgs<SINK>);
 
 // One launch: as many workgroups as fit the chip (registers, LDS), each looping over rows.
 template <int KK, int SINK>
@@ -644,7 +646,7 @@ int wg_launch(const rq_hadamard* h, WgKernel<SINK> fn, const WaveArgs& a, int pb
         shares = (unsigned)(want < 1 ? 1 : want > sa.max_shares ? sa.max_shares : want);
     }
     const unsigned grid = (unsigned)(passes < cap ? passes : cap);
-    launch_kernel(fn, dim3(grid, shares), dim3(64 * nw), lds, s, a, pb, sa);
+    launch_kernel(fn, dim3(grid, shares), dim3(64 * nw), lds, s, RQ_WAVE_VALUES(a, pb), sa);
     return launch_rc();
 }
 
