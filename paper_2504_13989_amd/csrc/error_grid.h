@@ -32,14 +32,20 @@
 namespace rq {
 namespace {
 
-template <int BITS, int SPREAD = kGridSpread>
+// THREADS: the fewest threads that share a row, where the kernel knows it (finish then keeps a thread's share of the words in
+// registers; FINE and COARSE are whole shares, the words added to them stay zero).
+template <int BITS, int SPREAD = kGridSpread, int THREADS = 0>
 struct ErrorGrid {
     static constexpr int LEVELS = (1 << BITS) - 1, Q = (1 << (BITS - 1)) - 1, FRAC = BITS == 3 ? 15 : 14;
     static constexpr int LAST = 2 * Q + 1;                           // units a step of the last threshold
     static constexpr int CELLS = grid_cells(BITS);
-    static constexpr int FINE = CELLS + SPREAD - 1, COARSE = kGridRatios + SPREAD - 1;    // words of the histograms
-    static constexpr int WORDS = FINE + COARSE;
-    static_assert(WORDS == grid_words(BITS) + 2 * (SPREAD - 1) && SPREAD <= kGridSpread && (SPREAD & (SPREAD - 1)) == 0, "see search_rule.h");
+    // a thread's words of either histogram: odd, so that consecutive lanes start in different banks
+    static constexpr int share(int words) { return THREADS ? ((words + THREADS - 1) / (THREADS ? THREADS : 1)) | 1 : 1; }
+    static constexpr int SHARE_A = share(CELLS + SPREAD - 1), SHARE_B = share(kGridRatios + SPREAD - 1);
+    static constexpr int FINE = (CELLS + SPREAD - 1 + SHARE_A - 1) / SHARE_A * SHARE_A;   // words of the histograms
+    static constexpr int COARSE = (kGridRatios + SPREAD - 1 + SHARE_B - 1) / SHARE_B * SHARE_B;
+    static constexpr int WORDS = (FINE + COARSE + 1) / 2 * 2;        // (cleared by 16 bytes)
+    static_assert(WORDS <= grid_words(BITS) + 2 * (SPREAD - 1) + SHARE_A + SHARE_B && SPREAD <= kGridSpread && (SPREAD & (SPREAD - 1)) == 0, "see search_rule.h");
     static constexpr size_t bytes() { return (size_t)WORDS * sizeof(uint64_t); }
     static constexpr float kTiny = 1e-30f;                           // rows below it: their squares are zero in fp32
 
@@ -130,6 +136,7 @@ struct ErrorGrid {
     // The histogram of a row to suffix sums, by the NT threads (whole waves, numbered by t) that share it, and the row's
     // sum of V^2 from the threads' q2.  `tot`: three words of LDS for each wave of the row.  Every thread of the workgroup calls it.
     static __device__ __forceinline__ double finish(uint64_t* hist, double q2, int t, int NT, uint64_t (*tot)[3]) {
+        if constexpr (THREADS != 0) return finish_known(hist, q2, t, NT >> 6, tot);
         const int lane = t & 63, wave = t >> 6, nw = NT >> 6;
         // (odd shares: consecutive lanes then start in different banks)
         asm volatile("" : "+v"(t));
@@ -156,6 +163,60 @@ struct ErrorGrid {
         }
         chunk_suffix(hist, a0, a1, xa);
         chunk_suffix(coarse, b0, b1, xb);
+        __syncthreads();
+        return q2;
+    }
+
+    // The same where at least THREADS threads, at most 64 more, share the row: a thread's words stay in registers between the two
+    // passes over them, and their number needs no bounds in a loop.  The vector port bounds it (four waves a SIMD): about 200
+    // instructions a wave where the general form has 450; 512 x 4096 2.9 -> 1.7 us of a search's 23.  us a search: 512 x 4096 23.8
+    // -> 22.4, 1000 x 2048 (b = 4) 30.9 -> 27.9, 1000 x 3584 (b = 4) 34.4 -> 31.6, in the workgroup block kernel 512 x 18944 37.3 -> 34.6,
+    // 512 x 8960 36.7 -> 33.5, 200 x 4864 31.4 -> 28.3, 300 x 28672 (b = 4) 48.0 -> 44.0.
+    static __device__ __forceinline__ double finish_known(uint64_t* hist, double q2, int t, int nw, uint64_t (*tot)[3]) {
+        static_assert(THREADS % 64 == 0 && THREADS * SHARE_A >= FINE && THREADS * SHARE_B >= COARSE, "every word is a thread's");
+        const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+        const bool has_a = t < FINE / SHARE_A, has_b = t < COARSE / SHARE_B;
+        uint64_t* const a = hist + t * SHARE_A;
+        uint64_t* const b = hist + FINE + t * SHARE_B;
+        uint64_t x[SHARE_A] = {}, y[SHARE_B] = {};
+        if (has_a) {
+#pragma unroll
+            for (int k = 0; k < SHARE_A; ++k) x[k] = a[k];
+        }
+        if (has_b) {
+#pragma unroll
+            for (int k = 0; k < SHARE_B; ++k) y[k] = b[k];
+        }
+        q2 = lanes_sum(q2);
+#pragma unroll
+        for (int k = SHARE_A - 2; k >= 0; --k) x[k] += x[k + 1];
+#pragma unroll
+        for (int k = SHARE_B - 2; k >= 0; --k) y[k] += y[k + 1];
+        uint64_t all_a, all_b, xa = lanes_from(x[0], lane, all_a) - x[0], xb = lanes_from(y[0], lane, all_b) - y[0];
+        if (lane == 0) {
+            tot[wave][0] = all_a;
+            tot[wave][1] = all_b;
+            tot[wave][2] = (uint64_t)__double_as_longlong(q2);
+        }
+        __syncthreads();
+        q2 = 0.0;
+#pragma unroll
+        for (int w = 0; w <= THREADS / 64; ++w) {
+            if (w >= nw) break;
+            if (w > wave) {
+                xa += tot[w][0];
+                xb += tot[w][1];
+            }
+            q2 += __longlong_as_double((long long)tot[w][2]);
+        }
+        if (has_a) {
+#pragma unroll
+            for (int k = 0; k < SHARE_A; ++k) a[k] = x[k] + xa;
+        }
+        if (has_b) {
+#pragma unroll
+            for (int k = 0; k < SHARE_B; ++k) b[k] = y[k] + xb;
+        }
         __syncthreads();
         return q2;
     }

@@ -3,11 +3,13 @@
 // the bracket or below), and the error of a row at all 511 ratios costs little more than the rotation (error_grid.h).  One
 // kernel passes over the rows once and leaves each workgroup's sums, a second adds them up and walks the search; nothing
 // is evaluated twice and no step waits for another.
-// Bound: latency (vector port 26 - 43 % busy).  512 x 4096, b = 3: 11 us in the first kernel (launch, rotation 1.5, the
-// additions of two rows a compute unit 2.3, about 20 cycles of LDS each, the passes over the histogram 3), 7 in the second
-// (launch, 1 MB of sums, the walk, results over the bus).
-// A search, us a call, resident or batched form -> grid form, normal rows (heavy-tailed ones within 3 %): 512 x 4096 45 -> 23,
-// 512 x 8192 58 -> 26, 512 x 3584 44 -> 24, 512 x 5120 81 -> 28, 512 x 14336 121 -> 30, 512 x 18944 153 -> 35, 512 x 896 59 -> 46.
+// Bound: latency (vector port 26 - 43 % busy).  512 x 4096, b = 3, by time stamps in the kernels: 9 us in the first (a workgroup's
+// rows there and rotated 1.5 after its start, the maximum 1, the additions of two rows a compute unit 1.8, the passes over the
+// histogram 1.7, sums out 0.9; the first workgroup starts 2 before most others, as the chip has been idle), 1.5 between the kernels, 6
+// in the second (1 MB of sums 1.5, the count of the workgroups 1, totals back 0.6, the walk 1.7, results over the bus 0.7).
+// The totals reduced inside the waves and both loads of the means at once: no difference (22.9 and 22.45 - 23.0).
+// A search, us a call, resident or batched form -> grid form, normal rows (heavy-tailed ones within 3 %): 512 x 4096 45 -> 22,
+// 512 x 8192 58 -> 25, 512 x 3584 44 -> 23, 512 x 5120 81 -> 28, 512 x 14336 121 -> 28, 512 x 18944 153 -> 32, 512 x 896 59 -> 46.
 #include "error_grid.h"
 #include "row_rotation.h"
 
@@ -18,10 +20,11 @@ namespace {
 // own.  Where a row is rotated by fewer waves, W, all eight repeat the rotation and share the values: the additions and
 // the passes over the histogram take longer than the rotation, and LDS (57 KB a row for b = 4) leaves no room for more
 // rows in their place (one row a wave: 2048 x 1024, b = 4 65 us a search, 512 x 4096 on four waves a row 26.7).
+constexpr int kRowThreads = 512;
 template <typename Rows, int BITS>
 __global__ __launch_bounds__(1024) void k_grid_rows(WaveArgs a, int pb, int conc, double inv_norm, GbsDev* dev) {
-    using Grid = ErrorGrid<BITS>;
-    constexpr int W = Rows::W, NVAL = Rows::NVAL, NT = 512, SHARES = NT / 64 / W;
+    constexpr int W = Rows::W, NVAL = Rows::NVAL, NT = kRowThreads, SHARES = NT / 64 / W;
+    using Grid = ErrorGrid<BITS, kGridSpread, NT>;
     static_assert(NT >= kGridRatios - 1, "a ratio a thread");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     __shared__ float wmax[16];
@@ -144,8 +147,7 @@ __global__ __launch_bounds__(kWalkThreads) void k_grid_walk(GbsDev* dev, GbsOut*
 
 template <typename Rows, int BITS>
 int launch_rows(const rq_hadamard* h, const RowArgs& a, const WaveArgs& w, int pb, int* groups, GbsDev* dev, hipStream_t s) {
-    using Grid = ErrorGrid<BITS>;
-    static_assert(Grid::WORDS % 2 == 0, "cleared by 16 bytes");
+    using Grid = ErrorGrid<BITS, kGridSpread, kRowThreads>;
     const int cus = h->num_cu < kGridGroups ? h->num_cu : kGridGroups;
     const int conc = a.rows > cus ? grid_rows_beside(BITS, h->max_lds) : 1;
     const int64_t passes = (a.rows + conc - 1) / conc;
@@ -153,7 +155,7 @@ int launch_rows(const rq_hadamard* h, const RowArgs& a, const WaveArgs& w, int p
     void (*const fn)(WaveArgs, int, int, double, GbsDev*) = k_grid_rows<Rows, BITS>;
     const size_t lds = (size_t)conc * Grid::bytes();
     if (!allow_lds(fn, lds)) return RQ_ERR_NO_ORDER;
-    launch_kernel(fn, dim3((unsigned)*groups), dim3((unsigned)(512 * conc)), lds, s, w, pb, conc,
+    launch_kernel(fn, dim3((unsigned)*groups), dim3((unsigned)(kRowThreads * conc)), lds, s, w, pb, conc,
                   1.0 / ((double)a.n * (double)a.n), dev);
     return launch_rc();
 }

@@ -24,7 +24,7 @@ template <int KK>
 int launch_kk(const rq_hadamard* h, const WaveArgs& w, int bits, int pb, int cb, int* groups, const WgGridArgs& g, hipStream_t s) {
     WgKernel<kWgGrid> fn = pick_kernel<KK>(bits, cb, w.f16);
     if (!fn) return RQ_ERR_NO_ORDER;
-    const size_t lds = wg_ops_bytes<KK>() + (bits == 4 ? ErrorGrid<4>::bytes() : ErrorGrid<3>::bytes());
+    const size_t lds = wg_ops_bytes<KK>() + (bits == 4 ? WgGrid<KK, 4>::bytes() : WgGrid<KK, 3>::bytes());
     if (!allow_lds(fn, lds)) return RQ_ERR_NO_ORDER;
     const int rpw = 16 >> cb, cus = h->num_cu < kGridGroups ? h->num_cu : kGridGroups;
     const int64_t passes = (w.rows + rpw - 1) / rpw;

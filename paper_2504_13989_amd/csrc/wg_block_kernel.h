@@ -89,6 +89,12 @@ template <int SINK>
 using WgArgs = std::conditional_t<SINK == kWgError, QeArgs, std::conditional_t<SINK == kWgRotate, WgRotArgs,
                                   std::conditional_t<SINK == kWgGrid, WgGridArgs, WgNone>>>;
 
+// The histogram of the grid sink.  (KK == 1: two waves a pass, which take its four rows one after the other: a sixteenth of a row's
+// values meet in an instruction, and the last cells' further words cost what they gain; 512 x 896, b = 4 59.0 us a search with them, 58.1
+// without.  A thread's words are held in registers where its share is small enough: 21 of them, KK = 3 with b = 4, spill 18.)
+template <int KK, int BITS>
+using WgGrid = ErrorGrid<BITS, KK == 1 ? 1 : kGridSpread, KK < (BITS == 3 ? 3 : 5) ? 0 : 64 * (2 * KK - 1)>;
+
 // DPP row, 8-column chunk and row of the pass of a lane, as values the compiler does not keep across the phases.
 template <int CB>
 __device__ __forceinline__ void wg_lane(int lane, int& g, int& cl, int& rsub) {
@@ -210,9 +216,7 @@ void k_wg_block(RQ_WAVE_PARAMS, WgArgs<SINK> sa) {
             }
         }
     };
-    // (two waves a pass, which take its four rows one after the other: a sixteenth of a row's values meet in an instruction, and
-    // the further words cost what they gain; 512 x 896, b = 4 59.0 us a search with them, 58.1 without)
-    using Grid = ErrorGrid<BITS, KK == 1 ? 1 : kGridSpread>;
+    using Grid = WgGrid<KK, BITS>;
     constexpr int SUMS = SINK == kWgGrid ? (kGridRatios - 1 + 64 * (2 * KK - 1) - 1) / (64 * (2 * KK - 1)) : 1;   // ratios of a thread
     [[maybe_unused]] double sum[SUMS];
     __shared__ uint64_t tot[SINK == kWgGrid ? 16 : 1][3];
