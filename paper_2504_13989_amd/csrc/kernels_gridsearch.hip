@@ -5,8 +5,8 @@
 // is evaluated twice and no step waits for another.
 // Bound: latency (vector port 26 - 43 % busy).  512 x 4096, b = 3, by time stamps in the kernels: 9 us in the first (a workgroup's
 // rows there and rotated 1.5 after its start, the maximum 1, the additions of two rows a compute unit 1.8, the passes over the
-// histogram 1.7, sums out 0.9; the first workgroup starts 2 before most others, as the chip has been idle), 1.5 between the kernels, 6
-// in the second (1 MB of sums 1.5, the count of the workgroups 1, totals back 0.6, the walk 1.7, results over the bus 0.7).
+// histogram 1.7, sums out 0.9; the first workgroup starts 2 before most others, as the chip has been idle), 1.5 between the kernels, 5.5
+// in the second (1 MB of sums 1.5, the count of the workgroups 1, totals back 0.6, the walk 1.2, results over the bus 0.7).
 // The totals reduced inside the waves and both loads of the means at once: no difference (22.9 and 22.45 - 23.0).
 // A search, us a call, resident or batched form -> grid form, normal rows (heavy-tailed ones within 3 %): 512 x 4096 45 -> 22,
 // 512 x 8192 58 -> 25, 512 x 3584 44 -> 23, 512 x 5120 81 -> 28, 512 x 14336 121 -> 28, 512 x 18944 153 -> 32, 512 x 896 59 -> 46.
@@ -109,25 +109,34 @@ __global__ __launch_bounds__(kWalkThreads) void k_grid_walk(GbsDev* dev, GbsOut*
     auto put = [](auto* to, auto x) { __hip_atomic_store(to, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); };
     if (tid == 0) {
         // GbsState in units of 1 / kGridRatios
-        int left = 0, right = kGridRatios, best = kGridRatios / 2, side = 0, evals = 0;
         constexpr float unit = 1.0f / kGridRatios;
-        auto value = [&](int x) {
-            const float f = mean[x];
-            trace_clips[evals] = (float)x * unit;
-            trace_mse[evals++] = f;
-            return f;
-        };
         const int most = (int)fmin(eps * kGridRatios, (double)kGridRatios);      // brackets of at most so many units end the search
-        float fm = value(best);
+        int left = 0, right = kGridRatios, best = kGridRatios / 2, side = 0, evals = 1;
+        float fm = mean[best];
+        trace_clips[0] = (float)best * unit;
+        trace_mse[0] = fm;
+        // The probe to come and the two that may follow it, whose values are read while its own is compared: a step after the
+        // other, each waiting for a value out of LDS, is 1.7 us for 16 steps, this about 1.2 (512 x 3584 23.4 -> 22.9 us a search,
+        // 64 x 2048 20.1 -> 19.5).  Six steps at a time with a path a lane: 2.1, most of it instructions fetched for one use.
+        int x = (left + best) >> 1;
+        float fb = mean[x], fw = fb;
+        bool better = true;                              // which of the two x is
+#pragma unroll 2
         while (right - left > most && evals < max_evals) {
-            const int x = ((side ? right : left) + best) >> 1;
-            const float fx = value(x);
-            const bool better = fx < fm, to_left = better ? side == 1 : side == 0;
-            const int bound = better ? best : x;
-            left = to_left ? bound : left;
-            right = to_left ? right : bound;
+            const int bl = side ? best : left, br = side ? right : best, wl = side ? left : x, wr = side ? x : right;
+            const int xb = ((side ? bl : br) + x) >> 1, xw = ((side ? wl : wr) + best) >> 1;
+            const float nb = mean[xb], nw = mean[xw];
+            const float fx = better ? fb : fw;
+            trace_clips[evals] = (float)x * unit;
+            trace_mse[evals++] = fx;
+            better = fx < fm;
+            left = better ? bl : wl;
+            right = better ? br : wr;
             best = better ? x : best;
             fm = better ? fx : fm;
+            x = better ? xb : xw;
+            fb = nb;
+            fw = nw;
             side ^= 1;
         }
         put(&out->clip, (float)best * unit);
