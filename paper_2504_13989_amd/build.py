@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "librotq.so")
 NATIVE_PATH = os.path.join(HERE, "_pyrotq.so")
 
-SOURCES = ["hadamard.cpp", "rotq_api.cpp", "kernels_generic.hip", "kernels_wave.hip", "kernels_wgblock.hip", "kernels_wgrotate.hip", "kernels_dense.hip", "kernels_ref.hip", "kernels_waveblock2.hip", "kernels_rotate.hip", "kernels_plainasym.hip", "kernels_dequant.hip", "kernels_f64.hip", "kernels_search.hip", "kernels_gridsearch.hip", "kernels_wggrid.hip", "noalloc.hip"]
+SOURCES = ["hadamard.cpp", "rotq_api.cpp", "kernels_generic.hip", "kernels_wave.hip", "kernels_wgblock.hip", "kernels_wgrotate.hip", "kernels_wgpair.hip", "kernels_dense.hip", "kernels_ref.hip", "kernels_waveblock2.hip", "kernels_rotate.hip", "kernels_plainasym.hip", "kernels_dequant.hip", "kernels_f64.hip", "kernels_search.hip", "kernels_gridsearch.hip", "kernels_wggrid.hip", "noalloc.hip"]
 
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",

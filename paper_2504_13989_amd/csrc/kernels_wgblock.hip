@@ -54,7 +54,7 @@ bool prepare_kk() {
 
 // Operand tiles of the zero-padded block `bm` (order pb): [wave][kk][lane] x 16 bytes, wave <
 // ceil(pb/16), kk < ceil(pb/32); operand lane (gA, mm) of (wave, kk) holds block row
-// 16 wave + 4 (mm & 3) + (mm >> 2) at the contraction slots a = 32 kk + 8 gA + i.
+// 16 wave + 4 (mm & 3) + (mm >> 2) at the contraction slots a = 32 kk + 8 gA + i.  Those of the pair form follow.
 std::vector<uint32_t> wg_block_tiles(const std::vector<int8_t>& bm, int pb) {
     const int NW = (pb + 15) / 16, KK = (pb + 31) / 32;
     std::vector<uint32_t> t((size_t)NW * KK * 64 * 4, 0u);
@@ -70,11 +70,13 @@ std::vector<uint32_t> wg_block_tiles(const std::vector<int8_t>& bm, int pb) {
                     t[(((size_t)w * KK + kk) * 64 + lane) * 4 + (i >> 1)] |= v << ((i & 1) * 16);
                 }
             }
+    const std::vector<uint32_t> pairs = wg_pair_tiles(bm, pb);
+    t.insert(t.end(), pairs.begin(), pairs.end());
     return t;
 }
 
 bool wg_block_prepare(int pb) {
-    if (!wg_rotate_prepare(pb)) return false;
+    if (!wg_rotate_prepare(pb) || !wg_pair_prepare(pb)) return false;
     switch ((pb + 31) / 32) {
         case 1: return prepare_kk<1>();
         case 2: return prepare_kk<2>();
@@ -153,6 +155,7 @@ int wg_block_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float clip,
                              float* scales, hipStream_t s) {
     int pb, cb;
     if (!wg_shape(a, &pb, &cb)) return RQ_ERR_NO_ORDER;
+    if (cb == 4 && wg_pair_pays(h, a, pb)) return wg_pair_rotate_quantize(h, a, pb, clip, codes, scales, s);
     const bool f16 = a.dtype == RQ_F16;
     const double lvl = (double)((1 << a.bits) - 1);
     WaveArgs w{static_cast<const uint16_t*>(a.X), a.rows, a.d, a.ld,

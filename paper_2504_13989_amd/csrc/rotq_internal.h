@@ -224,6 +224,13 @@ std::vector<uint32_t> wg_block_tiles(const std::vector<int8_t>& bm, int pb);
 bool wg_block_prepare(int pb);
 // Shape of a launch of that kernel: block order and lane bits of the column transform; false when it does not serve the order.
 bool wg_shape(const RowArgs& a, int* pb, int* cb);
+// Its form for many rows whose block splits into pairs of rows (wg_pair_kernel.h): rq_rotate_quantize only.
+// Its operand tiles lie behind the others' (at wg_pair_tiles_at, in units of 16 bytes) where the block is large enough.
+std::vector<uint32_t> wg_pair_tiles(const std::vector<int8_t>& bm, int pb);
+size_t wg_pair_tiles_at(int pb);
+bool wg_pair_prepare(int pb);
+bool wg_pair_pays(const rq_hadamard* h, const RowArgs& a, int pb);
+int wg_pair_rotate_quantize(const rq_hadamard* h, const RowArgs& a, int pb, float clip, uint32_t* codes, float* scales, hipStream_t s);
 // Rotation alone on it, from rows or from packed per-token codes; with transpose the transposed block's tiles.
 bool wg_rotate_prepare(int pb);
 bool wg_rotate_supports(const rq_hadamard* h, const RowArgs& a, const OutArgs& o);

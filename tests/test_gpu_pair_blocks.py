@@ -1,0 +1,49 @@
+"""GPU: rows of the orders whose block splits into pairs of rows, enough of them for the form of the workgroup block kernel
+that uses it, against the same rows a few at a time (the other form, which the oracle's tests cover) and against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import parity
+from paper_2504_13989_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+# five waves a row with and without a diagonal, six, four, seven with and without, eight
+ORDERS = [148 * 128, 160 * 128, 192 * 128, 112 * 128, 128 * 128, 196 * 128, 204 * 128, 224 * 128, 256 * 128]
+
+
+@pytest.mark.parametrize("bits", [3, 4])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("n", ORDERS)
+def test_many_rows_against_few(n, dtype, bits):
+    # more than two rows a compute unit, in rounds that end unevenly; a padded width and a leading dimension beyond it
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rows, d = 3 * cus + 5, n - 136 if bits == 3 else n
+    gen = torch.Generator(device="cuda").manual_seed(n + bits)
+    wide = torch.randn((rows, d + 40), generator=gen, device="cuda")
+    wide[:, torch.randperm(d, generator=gen, device="cuda")[:5]] *= 40
+    wide[3] = 0
+    wide[rows - 2, d // 2] = float("inf")
+    wide[7, 130] = -float("inf")
+    wide[cus, 5] = float("nan")
+    x = wide.to(dtype)[:, :d]
+    h = binding.hadamard_build(n)
+    codes, scales = binding.rotate_quantize(h, x, bits, 0.9)
+    few = [binding.rotate_quantize(h, x[i:i + cus], bits, 0.9) for i in range(0, rows, cus)]
+    want, wscales = (torch.cat([f[k] for f in few]) for k in (0, 1))
+    odd = torch.tensor([3, 7, cus, rows - 2], device="cuda")
+    assert torch.equal(codes[odd], want[odd]) and torch.equal(scales[odd].view(torch.int32), wscales[odd].view(torch.int32))
+    # each form sums up to 256 values to a maximum of about 256^(1/2) times theirs, and adds for seven stages, in fp32: a few units of
+    # 2^-24 of the largest value, which a code's boundary is as near as in one value of 10^5
+    keep = torch.ones(rows, dtype=torch.bool, device="cuda")
+    keep[odd] = False
+    assert ((scales[keep] / wscales[keep] - 1).abs() < 16 * 2.0 ** -24).all()
+    differ = codes[keep] != want[keep]
+    assert differ.float().mean().item() < 2e-5
+    # the oracle on a few rows
+    some = [0, cus - 1, rows - 1]
+    xs = x[some].contiguous()
+    got = xs.view(torch.int16).cpu().numpy().view(np.uint16) if dtype == torch.bfloat16 else xs.cpu().numpy()
+    if n <= 20480:                                       # (the dense matrix of the wider orders is too large here)
+        parity.check_rotate_quantize(got, n, bits, 0.9, codes[some].cpu().numpy(), scales[some].cpu().numpy(), f"pairs n={n} b={bits}")

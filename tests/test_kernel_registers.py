@@ -75,6 +75,13 @@ def test_quantizing_workgroup_block_kernels_hold_their_registers(spills):
     assert max(forms.values()) <= 3, sorted(forms.items(), key=lambda kv: -kv[1])[:8]
 
 
+def test_pair_form_of_the_workgroup_block_kernel_holds_its_registers(spills):
+    """128 registers with 64 accumulators: 10 to 14 spilled cost 28672-wide rows, b = 4, a twentieth of their time."""
+    forms = {k: v for k, v in spills.items() if "k_wg_pair" in k}
+    assert len(forms) == 7 * 2 * 2
+    assert max(forms.values()) <= 1, sorted(forms.items(), key=lambda kv: -kv[1])[:8]
+
+
 def test_rotating_workgroup_block_kernels_hold_their_registers(spills):
     """29 registers spilled made the rotation of 28672-wide rows to fp32 1.3 times as long.  (Blocks of 225 to 256 with fp32
     results spill 20 to 24, measured as they are.)"""
