@@ -37,9 +37,9 @@ constexpr int grid_cells(int bits) { return (2 * ((1 << (bits - 1)) - 1) - 1) * 
 constexpr int grid_words(int bits) { return grid_cells(bits) + kGridRatios; }
 constexpr int kGridSpread = 16;                              // words that share the last cell of either histogram
 // Rows whose histograms a workgroup can hold side by side: two, one, or none where not even one fits beside `other` bytes of
-// LDS and 1 KB for what the kernels keep in static arrays (up to 640 bytes) and the last cells' further words (240 a row).
+// LDS and 1.5 KB for what the kernels keep in static arrays (up to 640 bytes) and the histograms' further words (up to 400 bytes a row).
 constexpr int grid_rows_beside(int bits, int64_t max_lds, int64_t other = 0) {
-    const int64_t row = 8 * (int64_t)grid_words(bits), left = max_lds - other - 1024;
+    const int64_t row = 8 * (int64_t)grid_words(bits), left = max_lds - other - 1536;
     return left >= 2 * row ? 2 : left >= row ? 1 : 0;
 }
 
@@ -56,7 +56,7 @@ struct GridCase {
 // Whether the grid form is the faster one for a search of up to `steps` steps: its time does not depend on them, that of the
 // forms it competes with (resident where the chip holds the tensor, else batches) grows with them.  Straight lines through
 // 4400 pairs of measured times, us (25 orders from 384 to 32768, 1 to 32768 rows, 0 to 16 steps, both code widths), of a grid form
-// up to 14 % slower than the present one.  Of 7488 pairs measured with that (the same orders, 13 row counts, 12 numbers of steps, normal
+// up to 25 % slower than the present one.  Of 7488 pairs measured with one 5 to 11 % slower than the present (the same orders, 13 row counts, 12 numbers of steps, normal
 // rows) the form taken is within a tenth of the faster one but for 54, at worst 1.27 times it; on heavy-tailed rows but for 57.
 // 4096 x 2048 rows, b = 3: grid 44 at any number of steps; batches 26 for up to one, 33 for three, 54 for five, 135 for sixteen.
 // 1024 x 8192 rows: 103; 29, 33, 55, 134.  4096 x 64 rows: 20; resident 13, 13, 17, 33.  18944 x 512 rows: 35; 30, 36, 61, 153.

@@ -9,14 +9,13 @@
 // a value.  D costs no step: where the last step is half empty (NW odd), its upper lanes read the
 // wave's own 16 rows of the other half, and the operand tile has the diagonal there.
 //
-// A wave holds 16 rows of e and of f, 64 accumulators, and has 128 registers (four waves a SIMD).  A workgroup's waves always
-// start at the same SIMD, so that of five-wave workgroups only two fit a compute unit (4 2 2 2 waves a SIMD; 4096 x 18944 52 us):
-// three rows share a workgroup there (4 4 4 3; 47), and two where a row takes six waves.  Each row's waves meet at a barrier of
-// their own (row_barrier), or the rows would load, contract and quantize in step.  (The other form holds 6 6 4 4 waves with half the
-// accumulators: the fullest SIMD has 30 percent of the work of two rows, here 27 percent of that of three.)
+// A wave holds 16 rows of e and of f, 64 accumulators, and has 128 registers (four waves a SIMD).  Of five-wave workgroups a
+// compute unit takes only two at a time (3 3 2 2 waves a SIMD; a third would fit, 4 4 4 3, and waits; 4096 x 18944 52 us): three
+// rows share a workgroup there (47), and two where a row takes six waves.  Each row's waves meet at a barrier of their own
+// (row_barrier), or the rows would load, contract and quantize in step.
 //
-// What bounds it: vector issue (895 instructions a wave and row, four fifths of the fullest SIMD's cycles at 16384 x 18944) at the 2.1 GHz
-// that the power limit leaves; the matrix cores are busy 17 percent of the time, 27 in the other form.  us a call, other form -> this:
+// What bounds it: vector issue (905 instructions a wave and row, four fifths of the fullest SIMD's cycles at 16384 x 18944) at the
+// clock that the power limit leaves; the matrix cores are busy 16 percent of the time, 24 in the other form.  us a call, other form -> this:
 // 18944 wide, 1024 rows, b = 4 15.8 -> 14.5, 4096 rows, b = 3 51.2 -> 46.7, b = 4 52.7 -> 48.2, 10000 rows, b = 4 125 -> 113; 28672
 // wide, 300 rows 11.9 -> 10.5, 4096 rows, b = 3 77 -> 64, 6000 rows, b = 4 113 -> 98; 2048 rows: 14336, b = 4 18.8 -> 17.8, 16384, b = 4
 // 20.4 -> 19.0, 20480, b = 3 28.2 -> 25.3, 24576, b = 4 32.9 -> 31.8, 25088, b = 4 39.7 -> 34.5, 32768, b = 3 45.4 -> 36.6.
