@@ -93,9 +93,10 @@ bool wg_pair_prepare(int pb) {
 }
 
 // Few rows leave compute units with a row or two, whose latency the longer waves make longer: up to there the workgroup
-// block kernel is the faster.  us a call there and here: two rows a unit (512 rows, b = 3) 14336 wide 6.6 and 7.2, 16384 7.1 and 7.4, 18944 9.5 and 10.0,
-// 20480 10.2 and 10.3; beyond (640 rows, b = 4) 14336 8.10 and 8.13, 16384 8.8 and 8.4, 18944 12.3 and 11.7, 20480 12.7 and 12.3.  From six waves a row on, with one workgroup of the other kernel on a
-// unit: one row a unit, 28672 wide 8.3 and 8.6; beyond (384 rows) 24576 10.7 and 10.1, 28672 14.1 and 11.6, 32768 16.1 and 12.2.
+// block kernel is the faster.  us a call there and here, two rows a unit (512 rows, b = 3): 14336 wide 6.6 and 7.2, 16384 7.1
+// and 7.4, 18944 9.5 and 10.0, 20480 10.2 and 10.3; beyond (640 rows, b = 4): 14336 8.10 and 8.13, 16384 8.8 and 8.4, 18944
+// 12.3 and 11.7, 20480 12.7 and 12.3.  From six waves a row on, where the other kernel has one workgroup on a unit, the line is at
+// one row a unit: 28672 wide 8.3 and 8.6 there; beyond (384 rows) 24576 10.7 and 10.1, 28672 14.1 and 11.6, 32768 16.1 and 12.2.
 bool wg_pair_pays(const rq_hadamard* h, const RowArgs& a, int pb) {
     bool diag;
     if (!in_pairs(h->f, &diag)) return false;
