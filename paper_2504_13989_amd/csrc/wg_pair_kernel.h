@@ -16,9 +16,10 @@
 //
 // What bounds it: vector issue (905 instructions a wave and row, four fifths of the fullest SIMD's cycles at 16384 x 18944) at the
 // clock that the power limit leaves; the matrix cores are busy 16 percent of the time, 24 in the other form.  us a call, other form -> this:
-// 18944 wide, 1024 rows, b = 4 15.8 -> 14.5, 4096 rows, b = 3 51.2 -> 46.7, b = 4 52.7 -> 48.2, 10000 rows, b = 4 125 -> 113; 28672
-// wide, 300 rows 11.9 -> 10.5, 4096 rows, b = 3 77 -> 64, 6000 rows, b = 4 113 -> 98; 2048 rows: 14336, b = 4 18.8 -> 17.8, 16384, b = 4
-// 20.4 -> 19.0, 20480, b = 3 28.2 -> 25.3, 24576, b = 4 32.9 -> 31.8, 25088, b = 4 39.7 -> 34.5, 32768, b = 3 45.4 -> 36.6.
+// 18944 wide, 1024 rows, b = 4 17.2 -> 15.7, 4096 rows, b = 3 52.8 -> 47.2, 10000 rows, b = 4 127.7 -> 111.2; 14336 wide, 700 rows, b = 4 9.8
+// -> 8.6, 3000 rows, b = 4 28.8 -> 27.6, 10000 rows, b = 3 81.6 -> 75.2; 28672 wide, 300 rows, b = 3 13.3 -> 10.7, 1000 rows, b = 4 26.4 -> 22.9,
+// 4096 rows, b = 3 82.4 -> 68.3; 2048 rows: 16384, b = 4 21.3 and 21.3, 20480, b = 3 28.2 -> 25.3, 24576, b = 4 34.2 -> 31.4, 25088, b = 4 39.7 ->
+// 34.5, 32768, b = 3 45.4 -> 36.6.
 // Scales against 64 bits, rms (largest), either form: 18944 wide 4.8 - 5.5e-8 (1.6e-7), 14336 4.6 - 5.4e-8 (1.8e-7).
 // (A row with infinities: 0 inf is NaN where an operand tile has zeros, so with a diagonal the 32 block rows of the infinity's wave are
 // NaN, which the maximum passes over; the scale is infinite as in the other form.)
@@ -129,12 +130,27 @@ void k_wg_pair(RQ_WAVE_PARAMS) {
 #pragma unroll
         for (int nt = 0; nt < 8; ++nt) acc[0][nt] = acc[1][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
         {
-            // reads run DEPTH ahead, sixteen accumulators in turn (three ahead: 1000 x 18944 15.6 and 14.7 us)
-            constexpr int DEPTH = 2, ITEMS = 16 * STEPS;
+            // Column tiles 0 - 3 of both halves go over all steps first, then 4 - 7, and the pairs and first two column stages of
+            // tiles 0 - 3, the same additions as in phase 3, are issued between the matrix-core instructions of the others; eight
+            // accumulators in turn, reads DEPTH ahead.  us a call, all tiles at once, two ahead -> so: 4096 x 18944, b = 3 48.6 -> 47.2,
+            // 10000, b = 4 114.7 -> 111.2, 10000 x 14336 78.2 -> 75.2, 2048 x 24576 32.0 -> 31.4; 1024 x 18944 15.3 and 15.7, 28672 wide
+            // 0 - 2 percent less (two or four ahead, so: 4096 x 18944, b = 4 48.5 and 47.4 where three have 47.0).
+            constexpr int DEPTH = 3, ITEMS = 16 * STEPS;
+            auto step = [](int i) { return i % (8 * STEPS) / 8; };
+            auto tile = [](int i) { return i / (8 * STEPS) * 4 + i % 8 / 2; };
             auto read_item = [&](int i) {
-                const int k = i / 16, nt = i % 16 / 2, hh = i & 1;
+                const int k = step(i), nt = tile(i), hh = i & 1;
                 const uint8_t* p = ODD && k == STEPS - 1 ? last[hh] : rd0 + hh * HALF + k * 8192;
                 return *reinterpret_cast<const u32x4*>(p + nt * 512);
+            };
+            // additions j of 48, two operations each: the pairs of tiles 0 - 3, their first column stage, their second
+            auto addition = [&](int j) __attribute__((always_inline)) {
+                const int r = j % 4, q = j / 4 % 4, st = j / 16 - 1;
+                const int h0 = st < 0 ? 0 : q / 2, h1 = st < 0 ? 1 : q / 2;
+                const int t0 = st < 0 ? q : st == 0 ? 2 * (q % 2) : q % 2, t1 = st < 0 ? q : st == 0 ? t0 + 1 : t0 + 2;
+                const float u = acc[h0][t0][r], v = acc[h1][t1][r];
+                acc[h0][t0][r] = u + v;
+                acc[h1][t1][r] = u - v;
             };
             u32x4 minus = A[STEPS - 1];                  // the last step's tile for f
             if constexpr (DIAG) {
@@ -146,19 +162,29 @@ void k_wg_pair(RQ_WAVE_PARAMS) {
             u32x4 ring[DEPTH];
 #pragma unroll
             for (int i = 0; i < DEPTH; ++i) ring[i] = read_item(i);
-#pragma unroll
-            for (int i = 0; i < ITEMS; ++i) {
+            auto item = [&](int i) __attribute__((always_inline)) {
                 __builtin_amdgcn_sched_barrier(0);
-                const int k = i / 16, nt = i % 16 / 2, hh = i & 1;
+                const int k = step(i), nt = tile(i), hh = i & 1;
                 acc[hh][nt] = mfma_pm1<F16>(DIAG && hh && k == STEPS - 1 ? minus : A[k], ring[i % DEPTH], acc[hh][nt]);
                 if (i + DEPTH < ITEMS) ring[i % DEPTH] = read_item(i + DEPTH);
+            };
+#pragma unroll
+            for (int i = 0; i < ITEMS / 2; ++i) item(i);
+            item(ITEMS / 2);
+#pragma unroll
+            for (int i = 1; i < ITEMS / 2; ++i) {
+                constexpr int OF = ITEMS / 2 - 1;
+                item(ITEMS / 2 + i);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (48 * (i - 1) / OF + j < 48 * i / OF) addition(48 * (i - 1) / OF + j);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        // ---- phase 3: the pairs, the column stages, the row's maximum
+        // ---- phase 3: what is left of the pairs and column stages, the row's maximum
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int nt = 0; nt < 8; ++nt) {
+        for (int nt = 4; nt < 8; ++nt) {
             const f32x4 u = acc[0][nt], v = acc[1][nt];
             acc[0][nt] = u + v;
             acc[1][nt] = u - v;
@@ -175,7 +201,7 @@ void k_wg_pair(RQ_WAVE_PARAMS) {
             for (int s = 1; s < 8; s <<= 1)
 #pragma unroll
                 for (int nt = 0; nt < 8; ++nt)
-                    if (!(nt & s)) {
+                    if (!(nt & s) && (nt | s) >= 4) {
                         const f32x4 u = acc[hh][nt], v = acc[hh][nt | s];
                         acc[hh][nt] = u + v;
                         acc[hh][nt | s] = u - v;
