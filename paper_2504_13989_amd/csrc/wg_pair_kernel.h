@@ -95,6 +95,7 @@ void k_wg_pair(RQ_WAVE_PARAMS) {
     // 16 bytes that reader lane (g >> 1, c) of the group takes of each column tile.  Rows at or beyond pb lie beyond d and
     // read as zero.
     const int eoff = (32 * wave + 16 * (g >> 1) + (g & 1)) * 128 + c * 8;
+    static_assert((32 * (NW - 1) + 17) * 256 + 15 * 16 < 0x10000, "bytes of the first of them");
     uint8_t* const wr0 = ops + (g & 1) * HALF + wave * 4096 + ((g >> 1) * 16 + cphys) * 16;
     const uint8_t* const rd0 = ops + (g >> 1) * 4096 + ((g & 1) * 16 + cphys) * 16;
     const uint8_t* last[2];                              // the last step's operands, NW odd
@@ -112,9 +113,13 @@ void k_wg_pair(RQ_WAVE_PARAMS) {
     for (int64_t row = (int64_t)blockIdx.x + (int64_t)sub * gridDim.x; row < a.rows; row += (int64_t)gridDim.x * ROWS) {
         const RowView xv = row_view(a.X + row * a.ld, a.d);
         u32x4 R[8];
+        // (One address register for all: two block rows on, 512 bytes, as the instruction's own offset, which the range check counts
+        // with the register.  The masked register is known to stay below 2^16, so that the sum may be formed in the check.)
+        uint32_t off = (uint32_t)eoff * 2u;
+        asm volatile("" : "+v"(off));
+        off &= 0xffffu;
 #pragma unroll
-        for (int t = 0; t < 8; ++t)                      // (one address register for all: two block rows on, 512 bytes)
-            R[t] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xv.rs, eoff * 2, t * 512, 2));
+        for (int t = 0; t < 8; ++t) R[t] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xv.rs, off + t * 512u, 0, 2));
 #pragma unroll
         for (int ic = 0; ic < 8; ++ic) {
             const uint32_t sel = (ic & 1) ? 0x07060302u : 0x05040100u;

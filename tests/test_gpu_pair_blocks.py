@@ -47,3 +47,24 @@ def test_many_rows_against_few(n, dtype, bits):
     got = xs.view(torch.int16).cpu().numpy().view(np.uint16) if dtype == torch.bfloat16 else xs.cpu().numpy()
     if n <= 20480:                                       # (the dense matrix of the wider orders is too large here)
         parity.check_rotate_quantize(got, n, bits, 0.9, codes[some].cpu().numpy(), scales[some].cpu().numpy(), f"pairs n={n} b={bits}")
+
+
+@pytest.mark.parametrize("d", [8, 1000, 1784, 1792])
+@pytest.mark.parametrize("n", [148 * 128, 112 * 128, 224 * 128])
+def test_many_narrow_rows(n, d):
+    """Rows far narrower than the order, in a tensor whose other columns must not be seen: the rows' block rows from the first, the eighth
+    and the fourteenth on lie beyond the width."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rows = 3 * cus + 5
+    gen = torch.Generator(device="cuda").manual_seed(n + d)
+    wide = torch.full((rows, d + 4096), 3e4, device="cuda", dtype=torch.bfloat16)
+    wide[:, :d] = torch.randn((rows, d), generator=gen, device="cuda")
+    h = binding.hadamard_build(n)
+    codes, scales = binding.rotate_quantize(h, wide[:, :d], 4, 0.9)
+    few = [binding.rotate_quantize(h, wide[i:i + cus, :d], 4, 0.9) for i in range(0, rows, cus)]
+    want, wscales = (torch.cat([f[k] for f in few]) for k in (0, 1))
+    assert ((scales / wscales - 1).abs() < 16 * 2.0 ** -24).all()
+    assert (codes != want).float().mean().item() < 2e-5
+    xs = wide[[0, rows - 1], :d].contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
+    if n <= 20480:
+        parity.check_rotate_quantize(xs, n, 4, 0.9, codes[[0, rows - 1]].cpu().numpy(), scales[[0, rows - 1]].cpu().numpy(), f"narrow n={n} d={d}")
