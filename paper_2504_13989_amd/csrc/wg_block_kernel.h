@@ -156,10 +156,13 @@ void k_wg_block(RQ_WAVE_PARAMS, WgArgs<SINK> sa) {
     const uint32_t sg0 = (c & 1) ? 0x80000000u : 0u;
 
     // phase-1 geometry: lane (g, c) loads block rows 16 wave + 4 g + t, t = 0..3, at constant
-    // strides from one offset.  A group of four at or beyond pb (a multiple of 4) meets zero columns
-    // of B: any in-bounds data will do, and it reads the last four real rows.
+    // strides from one offset.  Block rows at or beyond pb meet zero columns of B, with which an infinity of a real row would
+    // make NaN: they lie beyond d and read as zero, or, where the loads do not check that (STANDIN), the last four real rows
+    // are read in their place and cleared.  (Registers spilled, bounds checked by the loads and so: full rows, KK = 5, b = 3 10
+    // and 0, b = 4 11 and 2; the search's passes of several rows, KK = 2 11 and 10; the other forms of several rows, KK = 5, 7 and 9.)
+    constexpr bool STANDIN = SINK != kWgRotate && (FULL || (SINK == kWgGrid && CB < 4));
     const int r0 = 16 * wave + 4 * g;
-    const int eoff0 = (r0 < pb ? r0 : pb - 4) * SEG + cl * 8;
+    const int eoff0 = (!STANDIN || r0 < pb ? r0 : pb - 4) * SEG + cl * 8;
     // phase-1 writes: the lane's block rows 16 wave + 4 g .. + 3 are one 8-byte half of the unit that
     // reader lane (2 (wave & 1) + g / 2, c) takes in contraction step wave / 2
     uint8_t* const wr0 = ops + ((((wave >> 1) * 4 + 2 * (wave & 1) + (g >> 1)) * 16 + cphys) * 16 + (g & 1) * 8);
@@ -255,6 +258,10 @@ void k_wg_block(RQ_WAVE_PARAMS, WgArgs<SINK> sa) {
             for (int kk = 0; kk < KK; ++kk) A[kk] = a.tiles[(wave * KK + kk) * 64 + l];
         }
         // ---- phase 1
+        if (STANDIN && 16 * wave + 16 > pb) {            // (the last wave)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) R[t] = 16 * wave + 4 * g < pb ? R[t] : u32x4{0u, 0u, 0u, 0u};
+        }
         // (4-bit codes of several rows a pass, or of blocks up to 64, are spread first and transposed like rows: us a call, so and
         // through code_operands, 3500 x 8960 23.0 and 25.3, 4000 x 8960 26.5 and 27.9, 3000 x 5120 10.4 and 10.8; the others 2000 x
         // 14336 18.0 and 17.2, 3000 x 11008 22.0 and 21.4, 2000 x 18944 26.4 and 25.9)
