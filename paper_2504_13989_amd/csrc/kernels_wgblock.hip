@@ -155,7 +155,6 @@ int wg_block_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float clip,
                              float* scales, hipStream_t s) {
     int pb, cb;
     if (!wg_shape(a, &pb, &cb)) return RQ_ERR_NO_ORDER;
-    if (cb == 4 && wg_pair_pays(h, a, pb)) return wg_pair_rotate_quantize(h, a, pb, clip, codes, scales, s);
     const bool f16 = a.dtype == RQ_F16;
     const double lvl = (double)((1 << a.bits) - 1);
     WaveArgs w{static_cast<const uint16_t*>(a.X), a.rows, a.d, a.ld,

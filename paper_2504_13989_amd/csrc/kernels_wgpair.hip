@@ -97,18 +97,20 @@ bool wg_pair_prepare(int pb) {
 // and 7.4, 18944 9.5 and 10.0, 20480 10.2 and 10.3; beyond (640 rows, b = 4): 14336 8.10 and 8.13, 16384 8.8 and 8.4, 18944
 // 12.3 and 11.7, 20480 12.7 and 12.3.  From six waves a row on, where the other kernel has one workgroup on a unit, the line is at
 // one row a unit: 28672 wide 8.3 and 8.6 there; beyond (384 rows) 24576 10.7 and 10.1, 28672 14.1 and 11.6, 32768 16.1 and 12.2.
-bool wg_pair_pays(const rq_hadamard* h, const RowArgs& a, int pb) {
+bool wg_pair_pays(const rq_hadamard* h, const RowArgs& a) {
+    int pb, cb;
     bool diag;
-    if (!in_pairs(h->f, &diag)) return false;
+    if (!wg_shape(a, &pb, &cb) || cb != 4 || !in_pairs(h->f, &diag)) return false;
     const PairForm f = pair_form(pb, diag, a.bits, a.dtype == RQ_F16);
     if (!f.kernel || f.lds + 256 > (size_t)h->max_lds) return false;
     return a.rows > (int64_t)h->num_cu * ((pb + 31) / 32 >= 6 ? 1 : 2);
 }
 
-int wg_pair_rotate_quantize(const rq_hadamard* h, const RowArgs& a, int pb, float clip, uint32_t* codes, float* scales, hipStream_t s) {
+int wg_pair_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float clip, uint32_t* codes, float* scales, hipStream_t s) {
     const bool f16 = a.dtype == RQ_F16;
+    int pb, cb;
     bool diag;
-    if (!in_pairs(h->f, &diag)) return RQ_ERR_NO_ORDER;
+    if (!wg_shape(a, &pb, &cb) || cb != 4 || !in_pairs(h->f, &diag)) return RQ_ERR_NO_ORDER;
     const PairForm f = pair_form(pb, diag, a.bits, f16);
     if (!f.kernel) return RQ_ERR_NO_ORDER;
     const double lvl = (double)((1 << a.bits) - 1);

@@ -367,6 +367,10 @@ int rq_rotate_quantize(const rq_hadamard_t* h, const void* X, int dtype, int64_t
         return rq::wave_block2_rotate_quantize(h, a, clip, static_cast<uint32_t*>(codes), scales, s);
     }
     if (h->variant == 0 && rq::wg_block_supports(h, a)) {
+        if (rq::wg_pair_pays(h, a)) {
+            note(h, "wg_block_pair");
+            return rq::wg_pair_rotate_quantize(h, a, clip, static_cast<uint32_t*>(codes), scales, s);
+        }
         note(h, "wg_block");
         return rq::wg_block_rotate_quantize(h, a, clip, static_cast<uint32_t*>(codes), scales, s);
     }

@@ -68,3 +68,26 @@ def test_many_narrow_rows(n, d):
     xs = wide[[0, rows - 1], :d].contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
     if n <= 20480:
         parity.check_rotate_quantize(xs, n, 4, 0.9, codes[[0, rows - 1]].cpu().numpy(), scales[[0, rows - 1]].cpu().numpy(), f"narrow n={n} d={d}")
+
+
+# (order, rows a compute unit up to which the workgroup block kernel takes it, 0: always)
+FORMS = [(148 * 128, 2), (160 * 128, 2), (192 * 128, 1), (112 * 128, 2), (128 * 128, 2), (196 * 128, 1), (224 * 128, 1), (256 * 128, 1),
+         (140 * 128, 0), (88 * 128, 0), (108 * 128, 0), (140 * 64, 0)]
+
+
+@pytest.mark.parametrize("n,line", FORMS)
+def test_which_form_runs(n, line):
+    """By the number of rows; without it the comparisons above could be of a kernel with itself."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    h = binding.hadamard_build(n)
+    x = torch.randn((3 * cus + 5, n), generator=torch.Generator(device="cuda").manual_seed(n), device="cuda").to(torch.bfloat16)
+    for rows in (1, cus, cus + 1, 2 * cus, 2 * cus + 1, 3 * cus + 5):
+        for bits in (3, 4):
+            binding.rotate_quantize(h, x[:rows], bits, 0.9)
+            assert h.last_kernel == ("wg_block_pair" if line and rows > line * cus else "wg_block"), rows
+    if n <= 148 * 128:                                   # (the general kernel holds no wider row)
+        binding.rotate_quantize(h, x[:, 1:n - 7], 4, 0.9)    # (rows off 16 bytes)
+        assert h.last_kernel == "generic_lds"
+        h.set_variant(1)
+        binding.rotate_quantize(h, x, 4, 0.9)
+        assert h.last_kernel == "generic_lds"
