@@ -21,8 +21,10 @@
 // 4096 rows, b = 3 82.4 -> 68.3; 2048 rows: 16384, b = 4 21.3 and 21.3, 20480, b = 3 28.2 -> 25.3, 24576, b = 4 34.2 -> 31.4, 25088, b = 4 39.7 ->
 // 34.5, 32768, b = 3 45.4 -> 36.6.
 // Scales against 64 bits, rms (largest), either form: 18944 wide 4.8 - 5.5e-8 (1.6e-7), 14336 4.6 - 5.4e-8 (1.8e-7).
-// (A row with infinities: 0 inf is NaN where an operand tile has zeros, so with a diagonal the 32 block rows of the infinity's wave are
-// NaN, which the maximum passes over; the scale is infinite as in the other form.)
+// A row with infinities: 0 inf is NaN where an operand tile has zeros, so with a diagonal all values of the 32 block rows of an
+// infinity's wave are NaN, which the maximum passes over.  Where every wave of a row has an infinity nothing else is left; the row is
+// then taken a second time for the answer of the other form (infinity_signs): an infinite scale if some value is the sum of
+// infinities of one sign, 0 if there is none or the row has a NaN.
 #pragma once
 #include "wave_common.h"
 
@@ -52,6 +54,25 @@ __device__ __forceinline__ void row_barrier(uint32_t* count, uint32_t& target, i
     asm volatile("" ::: "memory");
 }
 
+// Infinities among a lane's operands (eight column tiles of 16 bytes from `at`) to 1 with their sign, everything else to 0; how many
+// there were, more than a row holds for a NaN.  The sums of such rows are exact: one as large as the number of infinities has
+// added them all with one sign.  (In LDS, behind the row's phase 1, which stays as it is for it.)
+template <bool F16>
+__device__ __forceinline__ uint32_t infinity_signs(uint8_t* at) {
+    constexpr uint32_t INF = F16 ? 0x7c00u : 0x7f80u;
+    uint32_t count = 0, one = F16 ? 0x3c00u : 0x3f80u, nans = 1u << 20;
+    asm volatile("" : "+s"(one), "+s"(nans));            // (or both are held in vector registers for the whole launch)
+#pragma unroll 1
+    for (int i = 0; i < 32; ++i) {
+        uint32_t* const two = reinterpret_cast<uint32_t*>(at + (i >> 2) * 512) + (i & 3);
+        const uint32_t v = *two, lo = v & 0x7fffu, hi = (v >> 16) & 0x7fffu;
+        *two = (v & 0x80008000u) | (lo == INF ? one : 0u) | (hi == INF ? one << 16 : 0u);
+        count += (lo == INF) + (hi == INF);
+        if (lo > INF || hi > INF) count |= nans;
+    }
+    return count;
+}
+
 // NW = ceil(hb / 16) waves a row; DIAG: D is not zero (NW odd).
 template <int NW, bool DIAG, int BITS, bool F16>
 __global__ __launch_bounds__(64 * NW * pair_rows(NW)) __attribute__((amdgpu_waves_per_eu(4)))
@@ -73,6 +94,8 @@ void k_wg_pair(RQ_WAVE_PARAMS) {
     float* const wmax = wmax_all + sub * WM;
     __shared__ uint32_t counts[ROWS];
     uint32_t target = 0;
+    bool again = false;                                  // DIAG: the row is taken a second time
+    __shared__ uint32_t infinities[DIAG ? ROWS : 1];     // of such a row
     auto barrier = [&] {
         if constexpr (ROWS > 1) row_barrier<NW>(&counts[sub], target, lane);
         else __syncthreads();
@@ -107,10 +130,11 @@ void k_wg_pair(RQ_WAVE_PARAMS) {
     if (!DIAG && ODD)
         for (int i = tid; i < 256; i += 64 * NW) reinterpret_cast<u32x4*>(ops + 2 * HALF)[i] = u32x4{0u, 0u, 0u, 0u};
     if (tid < WM) wmax[tid] = 0.0f;
+    if (DIAG && tid == 0) infinities[sub] = 0;
 
     // (The next row's loads beside the quantizer, into the registers that it frees: no difference, 4096 x 28672, b = 3 64.6 and
     // 64.2, 2048 x 32768, b = 4 39.2 and 40.4, or slower, 4096 x 18944 44.9 and 46.1.)
-    for (int64_t row = (int64_t)blockIdx.x + (int64_t)sub * gridDim.x; row < a.rows; row += (int64_t)gridDim.x * ROWS) {
+    for (int64_t row = (int64_t)blockIdx.x + (int64_t)sub * gridDim.x; row < a.rows; row += again ? 0 : (int64_t)gridDim.x * ROWS) {
         const RowView xv = row_view(a.X + row * a.ld, a.d);
         u32x4 R[8];
         // (One address register for all: two block rows on, 512 bytes, as the instruction's own offset, which the range check counts
@@ -128,6 +152,7 @@ void k_wg_pair(RQ_WAVE_PARAMS) {
             for (int k = 0; k < 4; ++k) v[k] = __builtin_amdgcn_perm(R[2 * k + 1][ic >> 1], R[2 * k][ic >> 1], sel);
             *reinterpret_cast<u32x4*>(wr0 + ic * 512) = v;
         }
+        if (DIAG && __builtin_expect(again, 0)) atomicAdd(&infinities[sub], infinity_signs<F16>(wr0));
         barrier();
         // ---- phase 2: e in acc[0], f in acc[1].  (Waves in their vector phases go first, as in the workgroup block kernel.)
         __builtin_amdgcn_s_setprio(0);
@@ -220,8 +245,9 @@ void k_wg_pair(RQ_WAVE_PARAMS) {
             }
         }
         m = wave_absmax<4>(m);
-        if (lane == 0) wmax[wave] = m;
+        if (lane == 0) wmax[wave] = !DIAG || m > 0.0f ? m : acc[0][0][0];   // (0, or NaN of a wave that has nothing else)
         barrier();    // also: every wave is done reading this row's operands
+        [[maybe_unused]] float first;
         {
             f32x4 q[WM / 4];
 #pragma unroll
@@ -229,9 +255,14 @@ void k_wg_pair(RQ_WAVE_PARAMS) {
             m = 0.0f;
 #pragma unroll
             for (int i = 0; i < WM / 4; ++i) m = absmax4(m, q[i]);
+            first = q[0][0];
         }
         // ---- phase 4
-        const float s = m > 0.0f ? flip * div_pair(c1h, c1l, m) : 0.0f;
+        float s = 0.0f;
+        bool lost = false;                               // (the row's: all of its waves see the same maxima)
+        if (m > 0.0f) s = flip * div_pair(c1h, c1l, m);
+        else if (DIAG) lost = __builtin_amdgcn_readfirstlane(first != first);
+        if (DIAG && __builtin_expect(again, 0)) s = __builtin_nanf("");   // (the row's codes stay those of NaN)
         // the row's codes as a buffer resource: block rows at or beyond pb lie outside it and are not stored
         const auto out = __builtin_amdgcn_make_buffer_rsrc(a.codes + row * (int64_t)(4 * BITS) * pb, 0, 16 * BITS * pb, 0x00020000);
         const int r0 = 32 * wave + 2 * g;
@@ -255,7 +286,14 @@ void k_wg_pair(RQ_WAVE_PARAMS) {
             __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(stage + at), out, at, 0, 2);
             if (lane < 32) __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(stage + at + 1024), out, at + 1024, 0, 2);
         }
-        if (tid == 0) a.scales[row] = (float)(a.c2 * (double)m);
+        if (tid == 0) {
+            if (DIAG && __builtin_expect(again, 0)) {
+                m = m == (float)infinities[sub] ? __builtin_inff() : 0.0f;
+                infinities[sub] = 0;                     // (counted in again two barriers from here at the earliest)
+            }
+            a.scales[row] = (float)(a.c2 * (double)m);
+        }
+        if constexpr (DIAG) again = lost && !again;
     }
 }
 

@@ -91,3 +91,49 @@ def test_which_form_runs(n, line):
         h.set_variant(1)
         binding.rotate_quantize(h, x, 4, 0.9)
         assert h.last_kernel == "generic_lds"
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("n", [148 * 128, 196 * 128, 204 * 128, 160 * 128, 224 * 128])
+def test_rows_with_several_infinities(n, dtype):
+    """The scale is infinite where the infinities of some value agree in sign and 0 where none do or the row has a NaN, as in the
+    other form, also if every wave of the row has an infinity or all of the row is infinite."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rows, pb = 3 * cus + 5, n // 128
+    rng = np.random.default_rng(n)
+    signs = np.zeros((rows, n), dtype=np.float32)
+    for r in range(0, rows, 2):                          # (odd rows stay finite)
+        kind = (r // 2) % 4
+        if kind == 0:                                    # one in each wave's 32 block rows
+            at = [128 * rng.integers(32 * w, min(pb, 32 * w + 32)) + rng.integers(128) for w in range((pb + 31) // 32)]
+        else:
+            at = rng.choice(n, [rng.integers(5, 10), rng.integers(10, 15), rng.integers(15, 60)][kind - 1], replace=False)
+        signs[r, at] = rng.choice([-1.0, 1.0], len(at))
+    signs[8] = 1.0                                       # (the first block row and column are of one sign)
+    signs[10] = rng.choice([-1.0, 1.0], n)
+    # a value whose infinities all agree: the largest sum of their signs is their number
+    signs = torch.from_numpy(signs).cuda()
+    h = binding.hadamard_build(n)
+    sums = binding.rotate(h, signs.to(torch.bfloat16), out_dtype=torch.float32).abs().amax(1).double() * n ** 0.5
+    count = signs.abs().sum(1).double()
+    agree = (sums - count).abs() < 0.25
+    x = torch.randn((rows, n), generator=torch.Generator(device="cuda").manual_seed(n), device="cuda").to(dtype)
+    x[signs != 0] = signs[signs != 0].to(dtype) * float("inf")
+    x[12, 77] = float("nan")
+    x[14, torch.arange(60, n, 500, device="cuda")] = float("nan")
+    agree[[12, 14]] = False
+    nothing = count == 0
+    nothing[[12, 14]] = False
+    assert 20 < int((agree & ~nothing).sum()) and int((~agree).sum()) > 20
+    for bits in (3, 4):
+        codes, scales = binding.rotate_quantize(h, x, bits, 0.9)
+        assert h.last_kernel == "wg_block_pair"
+        few = [binding.rotate_quantize(h, x[i:i + cus], bits, 0.9) for i in range(0, rows, cus)]
+        assert h.last_kernel == "wg_block"
+        want, wscales = (torch.cat([f[k] for f in few]) for k in (0, 1))
+        odd = ~nothing
+        assert torch.equal(torch.isinf(wscales), agree & odd)
+        assert torch.equal(scales[odd].view(torch.int32), wscales[odd].view(torch.int32))
+        assert torch.equal(codes[odd], want[odd])
+        assert ((scales[nothing] / wscales[nothing] - 1).abs() < 16 * 2.0 ** -24).all()
+        assert (codes[nothing] != want[nothing]).float().mean().item() < 2e-5
