@@ -76,7 +76,8 @@ std::vector<uint32_t> wg_block_tiles(const std::vector<int8_t>& bm, int pb) {
 }
 
 bool wg_block_prepare(int pb) {
-    if (!wg_rotate_prepare(pb) || !wg_pair_prepare(pb)) return false;
+    if (!wg_rotate_prepare(pb)) return false;
+    wg_pair_prepare(pb);
     switch ((pb + 31) / 32) {
         case 1: return prepare_kk<1>();
         case 2: return prepare_kk<2>();

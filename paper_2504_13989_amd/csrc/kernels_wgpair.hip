@@ -82,14 +82,14 @@ std::vector<uint32_t> wg_pair_tiles(const std::vector<int8_t>& bm, int pb) {
 
 size_t wg_pair_tiles_at(int pb) { return (size_t)((pb + 15) / 16) * ((pb + 31) / 32) * 64; }
 
-bool wg_pair_prepare(int pb) {
+// (A form whose LDS a device does not have is not launched there, see wg_pair_pays; the workgroup block kernel serves its rows.)
+void wg_pair_prepare(int pb) {
     bool diag;
-    if (!in_pairs(pb, &diag)) return true;
+    if (!in_pairs(pb, &diag)) return;
     for (int k = 0; k < 4; ++k) {
         const PairForm f = pair_form(pb, diag, 3 + (k & 1), k & 2);
-        if (f.kernel && !allow_lds(f.kernel, f.lds)) return false;
+        if (f.kernel) (void)allow_lds(f.kernel, f.lds);
     }
-    return true;
 }
 
 // Few rows leave compute units with a row or two, whose latency the longer waves make longer: up to there the workgroup

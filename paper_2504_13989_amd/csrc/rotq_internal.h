@@ -228,7 +228,7 @@ bool wg_shape(const RowArgs& a, int* pb, int* cb);
 // Its operand tiles lie behind the others' (at wg_pair_tiles_at, in units of 16 bytes) where the block is large enough.
 std::vector<uint32_t> wg_pair_tiles(const std::vector<int8_t>& bm, int pb);
 size_t wg_pair_tiles_at(int pb);
-bool wg_pair_prepare(int pb);
+void wg_pair_prepare(int pb);
 bool wg_pair_pays(const rq_hadamard* h, const RowArgs& a);   // (of a call that wg_block_supports)
 int wg_pair_rotate_quantize(const rq_hadamard* h, const RowArgs& a, float clip, uint32_t* codes, float* scales, hipStream_t s);
 // Rotation alone on it, from rows or from packed per-token codes; with transpose the transposed block's tiles.
