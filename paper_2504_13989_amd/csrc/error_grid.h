@@ -47,6 +47,10 @@ struct ErrorGrid {
     static constexpr int WORDS = (FINE + COARSE + 1) / 2 * 2;        // (cleared by 16 bytes)
     static_assert(WORDS <= grid_words(BITS) + 2 * (SPREAD - 1) + SHARE_A + SHARE_B && SPREAD <= kGridSpread && (SPREAD & (SPREAD - 1)) == 0, "see search_rule.h");
     static constexpr size_t bytes() { return (size_t)WORDS * sizeof(uint64_t); }
+    // whether `rows` histograms and `arrays` bytes of static arrays keep to what grid_rows_beside allows for
+    static constexpr bool within_margin(int rows, size_t arrays) {
+        return rows * (bytes() - sizeof(uint64_t) * grid_words(BITS)) + arrays <= kGridMargin;
+    }
     static constexpr float kTiny = 1e-30f;                           // rows below it: their squares are zero in fp32
 
     // What scales a row: V = |y| s.  A row of zeros has s = 0.

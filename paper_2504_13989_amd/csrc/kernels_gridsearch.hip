@@ -29,6 +29,7 @@ __global__ __launch_bounds__(1024) void k_grid_rows(WaveArgs a, int pb, int conc
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     __shared__ float wmax[16];
     __shared__ uint64_t tot[2][8][3];
+    static_assert(Grid::within_margin(2, sizeof(wmax) + sizeof(tot)), "see grid_rows_beside");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rsub = wave >> 3, seg = wave % W, share = (wave & 7) / W, t = tid - rsub * NT;

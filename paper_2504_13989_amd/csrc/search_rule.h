@@ -37,10 +37,11 @@ constexpr int grid_cells(int bits) { return (2 * ((1 << (bits - 1)) - 1) - 1) * 
 constexpr int grid_words(int bits) { return grid_cells(bits) + kGridRatios; }
 constexpr int kGridSpread = 16;                              // words that share the last cell of either histogram
 // Rows whose histograms a workgroup can hold side by side: two, one, or none where not even one fits beside `other` bytes of
-// LDS and 1 KB for what the kernels keep in static arrays (448 bytes, 640 with several rows a pass) and the histograms' further words (up to 320
-// bytes a row, 288 with two rows).
+// LDS and a margin for what the kernels keep in static arrays (448 bytes, 640 with several rows a pass) and the histograms' further
+// words (up to 320 bytes a row, 288 with two rows); the kernels hold themselves to it.
+constexpr int kGridMargin = 1024;
 constexpr int grid_rows_beside(int bits, int64_t max_lds, int64_t other = 0) {
-    const int64_t row = 8 * (int64_t)grid_words(bits), left = max_lds - other - 1024;
+    const int64_t row = 8 * (int64_t)grid_words(bits), left = max_lds - other - kGridMargin;
     return left >= 2 * row ? 2 : left >= row ? 1 : 0;
 }
 

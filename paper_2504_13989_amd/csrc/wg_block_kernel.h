@@ -223,6 +223,7 @@ void k_wg_block(RQ_WAVE_PARAMS, WgArgs<SINK> sa) {
     constexpr int SUMS = SINK == kWgGrid ? (kGridRatios - 1 + 64 * (2 * KK - 1) - 1) / (64 * (2 * KK - 1)) : 1;   // ratios of a thread
     [[maybe_unused]] double sum[SUMS];
     __shared__ uint64_t tot[SINK == kWgGrid ? 16 : 1][3];
+    static_assert(SINK != kWgGrid || Grid::within_margin(1, sizeof(wmax) + sizeof(tot) + sizeof(esum)), "see grid_rows_beside");
     if constexpr (SINK == kWgGrid) {
 #pragma unroll
         for (int k = 0; k < SUMS; ++k) sum[k] = 0.0;
