@@ -35,8 +35,18 @@
  *
  * All functions return RQ_OK (0) or a negative error code; none throws or aborts.
  * Argument errors are detected on the host before any HIP call.  Data values are not
- * validated (NaN / Inf propagate).  The hot-path calls enqueue work on the caller's
- * stream and return without synchronising and without allocating.
+ * validated (NaN / Inf propagate: such a row has no useful codes and a scale that is
+ * infinite, NaN or 0; other rows are not affected).  The hot-path calls enqueue work on the
+ * caller's stream and return without synchronising and without allocating.
+ *
+ * The kernel is chosen by order, type and number of rows, and different kernels add in
+ * different orders.  The same row can therefore have other last bits in a call with another
+ * number of rows: scales up to 3e-7 apart (relative), and another code where a value lies that
+ * close to a rounding boundary (about one code byte in 10^7).  In rq_rotate_quantize this
+ * concerns 16-bit rows of the powers of two from 2048 to 8192, and of orders 128 pb with
+ * 97 <= pb <= 256 whose block is made of pairs of rows (14336, 18944 and 28672 among them): there the
+ * border is at two rows for each compute unit, from pb = 161 on at one.  Calls with
+ * the same number of rows give the same bits.
  */
 #ifndef ROTQ_H
 #define ROTQ_H
