@@ -173,9 +173,9 @@ struct ErrorGrid {
 
     // The same where at least THREADS threads, at most 64 more, share the row: a thread's words stay in registers between the two
     // passes over them, and their number needs no bounds in a loop.  The vector port bounds it (four waves a SIMD): about 200
-    // instructions a wave where the general form has 450; 512 x 4096 2.9 -> 1.7 us of a search's 23.  us a search: 512 x 4096 23.8
-    // -> 22.4, 1000 x 2048 (b = 4) 30.9 -> 27.9, 1000 x 3584 (b = 4) 34.4 -> 31.6, in the workgroup block kernel 512 x 18944 37.3 -> 34.6,
-    // 512 x 8960 36.7 -> 33.5, 200 x 4864 31.4 -> 28.3, 300 x 28672 (b = 4) 48.0 -> 44.0.
+    // instructions a wave where the general form has 450; 512 x 4096 2.9 -> 1.7 us of a search's 23.  us a search: 512 x 4096 23.1
+    // -> 22.4, 1000 x 2048 (b = 4) 30.6 -> 28.4, 1000 x 3584 (b = 4) 34.2 -> 32.0, in the workgroup block kernel 512 x 18944 37.0 -> 34.6,
+    // 512 x 8960 36.4 -> 33.5, 200 x 4864 31.0 -> 28.6, 300 x 28672 (b = 4) 47.6 -> 44.0.
     static __device__ __forceinline__ double finish_known(uint64_t* hist, double q2, int t, int nw, uint64_t (*tot)[3]) {
         static_assert(THREADS % 64 == 0 && THREADS * SHARE_A >= FINE && THREADS * SHARE_B >= COARSE, "every word is a thread's");
         const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);

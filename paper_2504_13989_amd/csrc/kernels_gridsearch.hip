@@ -9,7 +9,7 @@
 // in the second (1 MB of sums 1.5, the count of the workgroups 1, totals back 0.6, the walk 1.2, results over the bus 0.7).
 // The totals reduced inside the waves and both loads of the means at once: no difference (22.9 and 22.45 - 23.0).
 // A search, us a call, resident or batched form -> grid form, normal rows (heavy-tailed ones within 3 %): 512 x 4096 45 -> 22,
-// 512 x 8192 58 -> 25, 512 x 3584 44 -> 23, 512 x 5120 81 -> 28, 512 x 14336 121 -> 28, 512 x 18944 153 -> 32, 512 x 896 59 -> 46.
+// 512 x 8192 58 -> 25, 512 x 3584 44 -> 23, 512 x 5120 81 -> 28, 512 x 14336 121 -> 28, 512 x 18944 153 -> 33, 512 x 896 59 -> 46.
 #include "error_grid.h"
 #include "row_rotation.h"
 
@@ -117,8 +117,8 @@ __global__ __launch_bounds__(kWalkThreads) void k_grid_walk(GbsDev* dev, GbsOut*
         trace_clips[0] = (float)best * unit;
         trace_mse[0] = fm;
         // The probe to come and the two that may follow it, whose values are read while its own is compared: a step after the
-        // other, each waiting for a value out of LDS, is 1.7 us for 16 steps, this about 1.2 (512 x 3584 23.4 -> 22.9 us a search,
-        // 64 x 2048 20.1 -> 19.5).  Six steps at a time with a path a lane: 2.1, most of it instructions fetched for one use.
+        // other, each waiting for a value out of LDS, is 1.7 us for 16 steps, this about 1.2 (512 x 3584 23.4 -> 23.2 us a search,
+        // 64 x 2048 19.3 -> 19.1, 512 x 4096 22.3 -> 22.1).  Six steps at a time with a path a lane: 2.1, most of it instructions fetched for one use.
         int x = (left + best) >> 1;
         float fb = mean[x], fw = fb;
         bool better = true;                              // which of the two x is

@@ -93,10 +93,11 @@ void wg_pair_prepare(int pb) {
 }
 
 // Few rows leave compute units with a row or two, whose latency the longer waves make longer: up to there the workgroup
-// block kernel is the faster.  us a call there and here, two rows a unit (512 rows, b = 3): 14336 wide 6.6 and 7.2, 16384 7.1
-// and 7.4, 18944 9.5 and 10.0, 20480 10.2 and 10.3; beyond (640 rows, b = 4): 14336 8.10 and 8.13, 16384 8.8 and 8.4, 18944
-// 12.3 and 11.7, 20480 12.7 and 12.3.  From six waves a row on, where the other kernel has one workgroup on a unit, the line is at
-// one row a unit: 28672 wide 8.3 and 8.6 there; beyond (384 rows) 24576 10.7 and 10.1, 28672 14.1 and 11.6, 32768 16.1 and 12.2.
+// block kernel is the faster, or as fast.  us a call there and here, two rows a unit (512 rows, b = 3): 14336 wide 6.05 and 6.46, 16384
+// 6.47 and 6.83, 18944 8.79 and 8.84, 20480 9.15 and 9.00; beyond (520 rows, b = 4) 6.98 and 7.11, 7.67 and 7.44, 11.03 and 9.91, 11.55
+// and 10.07, 640 rows 7.59 and 7.35, 8.63 and 7.76, 11.54 and 10.69, 12.08 and 11.07.  From six waves a row on, where the other kernel
+// has one workgroup on a unit, the line is at one row a unit (b = 3): 256 rows 24576 wide 6.34 and 6.78, 28672 8.08 and 7.08; 264 rows
+// 24576 9.11 and 8.43, 28672 11.61 and 9.43, 32768 12.76 and 9.82.
 bool wg_pair_pays(const rq_hadamard* h, const RowArgs& a) {
     int pb, cb;
     bool diag;

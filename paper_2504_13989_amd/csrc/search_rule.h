@@ -58,10 +58,11 @@ struct GridCase {
 // Whether the grid form is the faster one for a search of up to `steps` steps: its time does not depend on them, that of the
 // forms it competes with (resident where the chip holds the tensor, else batches) grows with them.  Straight lines through
 // 4400 pairs of measured times, us (25 orders from 384 to 32768, 1 to 32768 rows, 0 to 16 steps, both code widths), of a grid form
-// up to 25 % slower than the present one.  Of 7488 pairs measured with one 5 to 11 % slower than the present (the same orders, 13 row counts, 12 numbers of steps, normal
-// rows) the form taken is within a tenth of the faster one but for 54, at worst 1.27 times it; on heavy-tailed rows but for 57.
-// 4096 x 2048 rows, b = 3: grid 44 at any number of steps; batches 26 for up to one, 33 for three, 54 for five, 135 for sixteen.
-// 1024 x 8192 rows: 103; 29, 33, 55, 134.  4096 x 64 rows: 20; resident 13, 13, 17, 33.  18944 x 512 rows: 35; 30, 36, 61, 153.
+// up to 25 % slower than the present one, so that the border leans to the other forms: of 8064 pairs measured with the present one (the same
+// orders, 14 row counts, 12 numbers of steps, normal rows) the form taken is within a tenth of the faster one but for 236, of
+// which 16 are grid; at worst it is 1.34 times it (32768 x 28672, b = 4, four steps, 2285 and 1710; 1536 x 256, b = 4, six, 25.2 and 19.3).
+// 4096 x 2048 rows, b = 3: grid 39 - 40 at any number of steps; batches 26 for up to two, 33 for three, 54 for five, 135 for sixteen.
+// 1024 x 8192 rows: 86 - 88; 28, 32, 53, 132.  4096 x 64 rows: 17 - 19; resident 13, 13, 17, 33.  18944 x 512 rows: 31 - 33; 29, 35, 59, 149.
 inline bool gbs_grid_pays(const GridCase& c, int steps) {
     if (c.beside < 1) return false;
     const double kilo = c.n / 1024.0, load = (double)c.rows * c.n / (4096.0 * c.cus);     // 4096 values a compute unit

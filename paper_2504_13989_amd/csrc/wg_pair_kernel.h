@@ -14,7 +14,7 @@
 // rows share a workgroup there (47), and two where a row takes six waves.  Each row's waves meet at a barrier of their own
 // (row_barrier), or the rows would load, contract and quantize in step.
 //
-// What bounds it: vector issue (905 instructions a wave and row, four fifths of the fullest SIMD's cycles at 16384 x 18944) at the
+// What bounds it: vector issue (910 instructions a wave and row, four fifths of the fullest SIMD's cycles at 16384 x 18944) at the
 // clock that the power limit leaves; the matrix cores are busy 16 percent of the time, 24 in the other form.  us a call, other form -> this:
 // 18944 wide, 1024 rows, b = 4 17.2 -> 15.7, 4096 rows, b = 3 52.8 -> 47.2, 10000 rows, b = 4 127.7 -> 111.2; 14336 wide, 700 rows, b = 4 9.8
 // -> 8.6, 3000 rows, b = 4 28.8 -> 27.6, 10000 rows, b = 3 81.6 -> 75.2; 28672 wide, 300 rows, b = 3 13.3 -> 10.7, 1000 rows, b = 4 26.4 -> 22.9,
