@@ -41,7 +41,7 @@
  *
  * The kernel is chosen by order, type and number of rows, and different kernels add in
  * different orders.  The same row can therefore have other last bits in a call with another
- * number of rows: scales up to 3e-7 apart (relative), and another code where a value lies that
+ * number of rows: scales a few parts in 10^7 apart, and another code where a value lies that
  * close to a rounding boundary (about one code byte in 10^7).  In rq_rotate_quantize this
  * concerns 16-bit rows of the powers of two from 2048 to 8192, and of orders 128 pb with
  * 97 <= pb <= 256 whose block is made of pairs of rows (14336, 18944 and 28672 among them): there the
